@@ -12,11 +12,14 @@
 namespace nsn {
 
 constexpr int kSumBlocks = 256;   // workgroups of the accumulation (and partial sums per cluster)
-constexpr int kSumThreads = 512;
-constexpr int kUpdateClusters = 8;  // clusters per workgroup of the update
+// four waves per SIMD (128 registers) for 4-dim codewords, three (170) for 8-dim ones, which spill at four: 26.5 against
+// 29.5 us and 38.0 against 39.8 us per K-Means iteration of 2^20 samples with two
+template <int SUB>
+constexpr int kSumThreads = SUB == 4 ? 1024 : 768;
+constexpr int kSumMost = 4096;  // samples added up in LDS at a time
 
 // workspace: centroids, error sum of every workgroup, cosine sum of every cluster, largest |sample| (bits), then
-// per workgroup of the accumulation 256 x SUB member sums and 256 member counts
+// per workgroup of the accumulation the member sums [256][SUB] and the member counts [256]
 template <int SUB>
 struct CodebookWs {
   double* centroids;
@@ -46,14 +49,26 @@ __global__ void cb_start_kernel(const T* __restrict__ from, double* __restrict__
   if (i == 0) *max_bits = 0u;
 }
 
-// largest |sample| of the set, as fp32 bits (their order is that of the values)
-__global__ __launch_bounds__(256) void cb_max_kernel(const float* __restrict__ samples, int64_t n_elems,
-                                                     uint32_t* __restrict__ max_bits) {
+// Largest |sample| of the set, as fp32 bits (their order is that of the values).  One atomic per workgroup: with one per
+// wave of a 4096-wave launch they took 45 of 56 us.
+constexpr int kMaxThreads = 1024;
+typedef float row4 __attribute__((ext_vector_type(4), aligned(4)));  // (the samples are aligned as floats are)
+__global__ __launch_bounds__(kMaxThreads) void cb_max_kernel(const float* __restrict__ samples, int64_t n_rows,
+                                                             uint32_t* __restrict__ max_bits) {
+  __shared__ float red[kMaxThreads / 64];
   float m = 0.f;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n_elems; i += (int64_t)gridDim.x * 256)
-    m = fmaxf(m, fabsf(samples[i]));
+#pragma unroll 4
+  for (int64_t i = (int64_t)blockIdx.x * kMaxThreads + threadIdx.x; i < n_rows; i += (int64_t)gridDim.x * kMaxThreads) {
+    const row4 v = reinterpret_cast<const row4*>(samples)[i];
+    m = fmaxf(fmaxf(m, fmaxf(fabsf(v.x), fabsf(v.y))), fmaxf(fabsf(v.z), fabsf(v.w)));
+  }
   m = wave_max(m);
-  if ((threadIdx.x & 63) == 0) atomicMax(max_bits, __float_as_uint(m));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    m = wave_max(red[threadIdx.x % (kMaxThreads / 64)]);
+    if (threadIdx.x == 0) atomicMax(max_bits, __float_as_uint(m));
+  }
 }
 
 __global__ void km_round_kernel(double* __restrict__ centroids, __half* __restrict__ out, int n_elems) {
@@ -81,7 +96,7 @@ __device__ __forceinline__ double exact_dist(const double* __restrict__ centroid
 //
 // The sums are formed in LDS by integer atomics on fixed-point values: integer addition is associative, so the result
 // does not depend on the order in which lanes and waves arrive.  A value enters with its last place at 2^-50 of the
-// power of two above the largest |sample| and at most 4096 values are added before the LDS sums move to fp64
+// power of two above the largest |sample| and at most kSumMost values are added before the LDS sums move to fp64
 // registers: no overflow of 63 bits, and a rounding error per value that is below that of the fp64 running sum
 // it stands for.  Adding 1.5 * 2^52 puts the fixed-point value into the low bits of the fp64 pattern;
 // the patterns are added as they are and the member count times the constant's pattern comes off at the end.
@@ -89,19 +104,29 @@ __device__ __forceinline__ double exact_dist(const double* __restrict__ centroid
 // 270 us per iteration of 2^20 4-dim samples, 1.05 ms with x / |x|.)
 enum { kSums, kUnitSums, kError };
 template <int SUB, int WHAT>
-__global__ __launch_bounds__(kSumThreads, 2) void cb_accumulate_kernel(const float* __restrict__ samples, int64_t n,
+__global__ __launch_bounds__(kSumThreads<SUB>) void cb_accumulate_kernel(const float* __restrict__ samples, int64_t n,
                                                                        CodebookWs<SUB> ws) {
-  constexpr int kOwn = kCodes * SUB / kSumThreads;  // sums a thread carries in registers
+  constexpr int NT = kSumThreads<SUB>;
+  constexpr int kOwn = (kCodes * SUB + NT - 1) / NT;  // sums a thread carries in registers
   constexpr double kMagic = 6755399441055744.0;      // 1.5 * 2^52
   __shared__ SearchTables<SUB> T;
   __shared__ double cx[kCodes][SUB];
   __shared__ unsigned long long acc[WHAT == kError ? 1 : SUB][kCodes];
   __shared__ uint32_t cnt[kCodes];
-  __shared__ double red[kSumThreads / 64];
+  __shared__ double red[NT / 64];
   const int tid = threadIdx.x;
+  const int64_t per = ((n + kSumBlocks - 1) / kSumBlocks + 63) & ~(int64_t)63;
+  const int64_t begin = (int64_t)blockIdx.x * per, end = min(n, begin + per);
+  row4 ahead[SUB / 4];
+  auto fetch = [&](int64_t idx) {  // (n >= 1)
+    const row4* row = reinterpret_cast<const row4*>(samples) + min(idx, n - 1) * (SUB / 4);
+#pragma unroll
+    for (int q = 0; q < SUB / 4; ++q) ahead[q] = row[q];
+  };
+  fetch(begin + tid);
   SearchRegs<SUB, false> R;
-  search_setup<SUB, false>(T, R, tid, [&](int c, int i) { return ws.centroids[c * SUB + i]; });
-  for (int i = tid; i < kCodes * SUB; i += kSumThreads) (&cx[0][0])[i] = ws.centroids[i];
+  search_setup<SUB, false>(T, R, tid, [&](int i) { return ws.centroids[tid * SUB + i]; });
+  for (int i = tid; i < kCodes * SUB; i += NT) (&cx[0][0])[i] = ws.centroids[i];
   double fixed = 0x1p50;  // values below 1
   if constexpr (WHAT == kSums) {
     int ex = 0;
@@ -111,7 +136,7 @@ __global__ __launch_bounds__(kSumThreads, 2) void cb_accumulate_kernel(const flo
   }
   auto clear = [&]() {
     if constexpr (WHAT != kError) {
-      for (int i = tid; i < kCodes * SUB; i += kSumThreads) (&acc[0][0])[i] = 0ull;
+      for (int i = tid; i < kCodes * SUB; i += NT) (&acc[0][0])[i] = 0ull;
       if (tid < kCodes) cnt[tid] = 0u;
     }
   };
@@ -120,22 +145,16 @@ __global__ __launch_bounds__(kSumThreads, 2) void cb_accumulate_kernel(const flo
 #pragma unroll
   for (int k = 0; k < kOwn; ++k) own[k] = 0.0;
   __syncthreads();
-  const int64_t per = ((n + kSumBlocks - 1) / kSumBlocks + kSumThreads - 1) / kSumThreads * kSumThreads;
-  const int64_t begin = (int64_t)blockIdx.x * per, end = min(n, begin + per);
-  for (int64_t base = begin; base < end; base += 8 * kSumThreads) {
-#pragma unroll 1
-    for (int u = 0; u < 8; ++u) {
-      const int64_t idx = base + u * kSumThreads + tid;
-      if (base + u * kSumThreads >= end) break;  // uniform
-      const bool valid = idx < end;
+  for (int64_t base = begin; base < end; base += kSumMost) {
+    const int64_t stop = min(end, base + kSumMost);
+    for (int64_t w0 = base + (tid & ~63); w0 < stop; w0 += NT) {  // 64 samples per wave
+      const bool valid = w0 + (tid & 63) < stop;
       float x[SUB];
-      typedef float row4 __attribute__((ext_vector_type(4), aligned(4)));  // (the samples are aligned as floats are)
-      const row4* row = reinterpret_cast<const row4*>(samples) + (valid ? idx : end - 1) * (SUB / 4);
 #pragma unroll
-      for (int q = 0; q < SUB / 4; ++q) {
-        const row4 v = row[q];
-        x[4 * q] = v.x, x[4 * q + 1] = v.y, x[4 * q + 2] = v.z, x[4 * q + 3] = v.w;
-      }
+      for (int i = 0; i < SUB; ++i) x[i] = ahead[i / 4][i % 4];
+      // the next 64 are on their way while these are searched (the last one of the block again where there are none)
+      const int64_t next = w0 + NT < stop ? w0 + NT : base + kSumMost + (tid & ~63);
+      fetch(next + (tid & 63));
       const int code = search_nearest<SUB, false>(T, R, x, [&](int c) { return exact_dist<SUB>(cx[c], x); });
       if constexpr (WHAT == kError) {
         if (valid) err += exact_dist<SUB>(cx[code], x);
@@ -159,10 +178,10 @@ __global__ __launch_bounds__(kSumThreads, 2) void cb_accumulate_kernel(const flo
     if constexpr (WHAT != kError) {
       __syncthreads();
 #pragma unroll
-      for (int k = 0; k < kOwn; ++k) {
-        const int e = tid + k * kSumThreads;
+      for (int k = 0; k < kOwn; ++k) {  // dimension e % SUB of cluster e / SUB
+        const int e = min(tid + k * NT, kCodes * SUB - 1);
         const unsigned long long s =
-            (&acc[0][0])[e] - (unsigned long long)cnt[e % kCodes] * (unsigned long long)__double_as_longlong(kMagic);
+            acc[e % SUB][e / SUB] - (unsigned long long)cnt[e / SUB] * (unsigned long long)__double_as_longlong(kMagic);
         own[k] += (double)(long long)s;
       }
       if (tid < kCodes) own_n += (double)cnt[tid];
@@ -177,67 +196,69 @@ __global__ __launch_bounds__(kSumThreads, 2) void cb_accumulate_kernel(const flo
     __syncthreads();
     if (tid == 0) {
       double t = 0.0;
-      for (int w = 0; w < kSumThreads / 64; ++w) t += red[w];
+      for (int w = 0; w < NT / 64; ++w) t += red[w];
       ws.block_err[blockIdx.x] = t;
     }
   } else {
-    double* out = ws.sums + (int64_t)blockIdx.x * kCodes * SUB;
     const double unit = 1.0 / fixed;  // a power of two
 #pragma unroll
     for (int k = 0; k < kOwn; ++k) {
-      const int e = tid + k * kSumThreads;  // dimension e / 256 of cluster e % 256
-      out[(e % kCodes) * SUB + e / kCodes] = own[k] * unit;
+      const int e = tid + k * NT;
+      if (e < kCodes * SUB) ws.sums[(int64_t)blockIdx.x * kCodes * SUB + e] = own[k] * unit;
     }
     if (tid < kCodes) ws.counts[(int64_t)blockIdx.x * kCodes + tid] = own_n;
   }
 }
 
-// Adds the partial sums of kUpdateClusters clusters: 1024 threads = 8 SUB sums x 1024 / (8 SUB) slices of the
-// workgroups, slices added in order.  Thread e < 8 SUB returns the sum of dimension e % SUB of cluster e / SUB of
-// the block's eight; cnt_s holds the eight member counts (a barrier has passed).
-constexpr int kUpdateThreads = 1024;
+// Adds the partial sums of kUpdateClusters neighbouring clusters (512 or 256 consecutive bytes of every row of partials)
+// in a fixed order (fp64): 1024 threads = 8 SUB sums x 1024 / (8 SUB) slices of the rows, 8 x 128 for the counts.
+// Threads 0..7 return with the sums and the member count of their cluster.  (Four clusters per workgroup and the sums
+// one dimension after the other, i.e. pieces of 32 bytes, took 10.7 us instead of 4.9.)
+constexpr int kUpdateClusters = 8, kUpdateThreads = 1024;
 template <int SUB>
-__device__ __forceinline__ double merge_partials(const CodebookWs<SUB>& ws, double (&sum_s)[kUpdateThreads],
-                                                 double (&cnt_s)[kUpdateClusters]) {
+__device__ __forceinline__ void merge_partials(const CodebookWs<SUB>& ws, double (&sum)[SUB], double& count) {
   constexpr int E = kUpdateClusters * SUB, SL = kUpdateThreads / E, PER = kSumBlocks / SL;
+  constexpr int CSL = kUpdateThreads / kUpdateClusters, CPER = kSumBlocks / CSL;
+  __shared__ double part[SL][E], cpart[kUpdateThreads / 64][kUpdateClusters];
   const int e = threadIdx.x % E, sl = threadIdx.x / E;
-  double v[PER], t = 0.0;
+  const int c = threadIdx.x % kUpdateClusters, cs = threadIdx.x / kUpdateClusters;
+  double v[PER], n[CPER], t = 0.0, m = 0.0;
 #pragma unroll
   for (int u = 0; u < PER; ++u) v[u] = ws.sums[((int64_t)(sl * PER + u) * kCodes + blockIdx.x * kUpdateClusters) * SUB + e];
 #pragma unroll
+  for (int u = 0; u < CPER; ++u) n[u] = ws.counts[(int64_t)(cs * CPER + u) * kCodes + blockIdx.x * kUpdateClusters + c];
+#pragma unroll
   for (int u = 0; u < PER; ++u) t += v[u];
-  sum_s[threadIdx.x] = t;
-  // counts: whole numbers, any order of addition gives the same
-  {
-    const int c = threadIdx.x % kUpdateClusters, s2 = threadIdx.x / kUpdateClusters;
-    double m = 0.0;
-    for (int w = s2; w < kSumBlocks; w += kUpdateThreads / kUpdateClusters)
-      m += ws.counts[(int64_t)w * kCodes + blockIdx.x * kUpdateClusters + c];
-    m += __shfl_xor(m, 8, 64), m += __shfl_xor(m, 16, 64), m += __shfl_xor(m, 32, 64);
-    __shared__ double cw[kUpdateThreads / 64][kUpdateClusters];
-    if ((threadIdx.x & 63) < kUpdateClusters) cw[threadIdx.x >> 6][c] = m;
-    __syncthreads();
-    if (threadIdx.x < kUpdateClusters) {
-      double tot = 0.0;
-      for (int w = 0; w < kUpdateThreads / 64; ++w) tot += cw[w][threadIdx.x];
-      cnt_s[threadIdx.x] = tot;
+#pragma unroll
+  for (int u = 0; u < CPER; ++u) m += n[u];
+  part[sl][e] = t;
+  m += xor_lane<8>(m);
+  m += xor_lane<16>(m);
+  m += xor_lane<32>(m);
+  if ((threadIdx.x & 63) < kUpdateClusters) cpart[threadIdx.x >> 6][threadIdx.x & 63] = m;
+  __syncthreads();
+  if (threadIdx.x < kUpdateClusters) {
+    count = 0.0;
+#pragma unroll
+    for (int w = 0; w < kUpdateThreads / 64; ++w) count += cpart[w][threadIdx.x];
+#pragma unroll
+    for (int i = 0; i < SUB; ++i) {
+      sum[i] = 0.0;
+#pragma unroll
+      for (int k = 0; k < SL; ++k) sum[i] += part[k][threadIdx.x * SUB + i];
     }
   }
-  __syncthreads();
-  double s = 0.0;
-  if (threadIdx.x < E)
-    for (int k = 0; k < SL; ++k) s += sum_s[k * E + threadIdx.x];
-  return s;
 }
 
 // an empty cluster keeps its centroid
 template <int SUB>
 __global__ __launch_bounds__(kUpdateThreads) void km_update_kernel(CodebookWs<SUB> ws) {
-  __shared__ double sum_s[kUpdateThreads], cnt_s[kUpdateClusters];
-  const double s = merge_partials<SUB>(ws, sum_s, cnt_s);
-  const int e = threadIdx.x;
-  if (e < kUpdateClusters * SUB && cnt_s[e / SUB] > 0.0)
-    ws.centroids[blockIdx.x * kUpdateClusters * SUB + e] = s / cnt_s[e / SUB];
+  double sum[SUB], count;
+  merge_partials<SUB>(ws, sum, count);
+  if (threadIdx.x < kUpdateClusters && count > 0.0) {
+#pragma unroll
+    for (int i = 0; i < SUB; ++i) ws.centroids[(blockIdx.x * kUpdateClusters + threadIdx.x) * SUB + i] = sum[i] / count;
+  }
 }
 
 // Fine-tuning for cosine distance (Sec. 3.4): S = sum of x / |x| over a codeword's samples (fp64), then the
@@ -246,17 +267,13 @@ __global__ __launch_bounds__(kUpdateThreads) void km_update_kernel(CodebookWs<SU
 // similarity BEFORE the move.
 template <int SUB>
 __global__ __launch_bounds__(kUpdateThreads) void ft_update_kernel(int64_t n, CodebookWs<SUB> ws, double lr) {
-  __shared__ double sum_s[kUpdateThreads], cnt_s[kUpdateClusters];
-  const double mine = merge_partials<SUB>(ws, sum_s, cnt_s);
-  __syncthreads();
-  if (threadIdx.x < kUpdateClusters * SUB) sum_s[threadIdx.x] = mine;
-  __syncthreads();
+  double S[SUB], count;
+  merge_partials<SUB>(ws, S, count);
   if (threadIdx.x < kUpdateClusters) {
     const int k = blockIdx.x * kUpdateClusters + threadIdx.x;
-    double S[SUB], c[SUB], cn2 = 0.0;
+    double c[SUB], cn2 = 0.0;
 #pragma unroll
     for (int i = 0; i < SUB; ++i) {
-      S[i] = sum_s[threadIdx.x * SUB + i];
       c[i] = ws.centroids[k * SUB + i];
       cn2 += c[i] * c[i];
     }
@@ -283,13 +300,13 @@ static int codebook_run_t(const float* samples, int64_t n, int iters, void* code
   const CodebookWs<SUB> ws(workspace);
   constexpr int n_elems = kCodes * SUB;
   cb_start_kernel<<<(n_elems + 255) / 256, 256, 0, stream>>>(samples, ws.centroids, n_elems, ws.max_bits);
-  cb_max_kernel<<<1024, 256, 0, stream>>>(samples, n * SUB, ws.max_bits);
+  cb_max_kernel<<<256, kMaxThreads, 0, stream>>>(samples, n * (SUB / 4), ws.max_bits);
   for (int it = 0; it < iters; ++it) {
-    cb_accumulate_kernel<SUB, kSums><<<kSumBlocks, kSumThreads, 0, stream>>>(samples, n, ws);
+    cb_accumulate_kernel<SUB, kSums><<<kSumBlocks, kSumThreads<SUB>, 0, stream>>>(samples, n, ws);
     km_update_kernel<SUB><<<kCodes / kUpdateClusters, kUpdateThreads, 0, stream>>>(ws);
   }
   km_round_kernel<<<(n_elems + 255) / 256, 256, 0, stream>>>(ws.centroids, static_cast<__half*>(codebook_out), n_elems);
-  cb_accumulate_kernel<SUB, kError><<<kSumBlocks, kSumThreads, 0, stream>>>(samples, n, ws);
+  cb_accumulate_kernel<SUB, kError><<<kSumBlocks, kSumThreads<SUB>, 0, stream>>>(samples, n, ws);
   if (hipGetLastError() != hipSuccess) return NSN_ERR_HIP;
   double host_err[kSumBlocks];
   if (hipMemcpyAsync(host_err, ws.block_err, sizeof(host_err), hipMemcpyDeviceToHost, stream) != hipSuccess)
@@ -310,7 +327,7 @@ static int finetune_run_t(const float* samples, int64_t n, int iters, double lr,
   constexpr int n_elems = kCodes * SUB;
   double host_cos[kCodes];
   auto step = [&](double rate) {
-    cb_accumulate_kernel<SUB, kUnitSums><<<kSumBlocks, kSumThreads, 0, stream>>>(samples, n, ws);
+    cb_accumulate_kernel<SUB, kUnitSums><<<kSumBlocks, kSumThreads<SUB>, 0, stream>>>(samples, n, ws);
     ft_update_kernel<SUB><<<kCodes / kUpdateClusters, kUpdateThreads, 0, stream>>>(n, ws, rate);
   };
   auto mean_cos = [&](double* out) -> int {  // assignment + cosine sums of the current centroids (no move: rate 0)

@@ -1,19 +1,19 @@
 // Nearest-codeword search (Eq. 1, squared Euclidean distance): one sub-vector per lane, 64 per call.
 //
-// Three steps, bound by vector instructions (about 300 per 64 searches of 256 codewords; keeping the best two
+// Three steps, bound by vector instructions (about 280 per 64 searches of 256 4-dim codewords; keeping the best two
 // indexed keys of every distance, the form this one replaced, took about 740):
 //   1. matrix cores: D = ||c||^2 - 2 c . y for 32 codewords (rows) x 32 sub-vectors (columns) at a time.  y, c and
-//      ||c||^2 enter as sums of fp16 parts, so D is good to about 2^-20 of (|c|^2 + 2 |c| |y|).  A lane
-//      then holds 16 distances of one sub-vector per tile and keeps only their minimum: half an instruction per
-//      distance (three-operand minima), no index bookkeeping.  16 groups of 16 codewords leave 16 minima per
-//      sub-vector, brought to the lane that owns it by half-wave swaps.
+//      ||c||^2 enter as sums of fp16 parts, so D is good to about 2^-19 of |c|^2 + 2 |c| |y|.  A lane
+//      then holds 16 distances of one sub-vector per tile and keeps only the minima of the two groups of eight: half
+//      an instruction per distance (three-operand minima), no index bookkeeping.  32 groups of 8 codewords leave 32
+//      minima per sub-vector, brought to the lane that owns it by half-wave swaps.
 //   2. every group whose minimum lies within twice the error bound of the smallest is listed (almost always one).
-//   3. the listed groups' codewords are gone through in fp32 on the vector ALUs (rows read from LDS, padded so
-//      that 16 different groups sit in 16 different bank quads: conflict-free for any choice of groups).  Again
-//      everything within the bound is listed: one candidate (all but about one sub-vector in a thousand) is the
+//   3. the listed groups' codewords are gone through in fp32 on the vector ALUs (rows read from LDS).  Again
+//      everything within the bound is listed: one candidate (all but about one sub-vector in two thousand) is the
 //      nearest codeword for certain; several are settled by fp64 distances, lowest index on ties, so the code equals
 //      an fp64 exhaustive search.
-// Groups of 16 balance the two sides: groups of 8 cost as much in step 2 as they save in step 3.
+// Groups of 8 against 16: twice the minima in step 2 (+56 instructions), half the rows in step 3 (-48 for 4-dim, -80 for
+// 8-dim codewords, and half the LDS reads).
 #pragma once
 
 #include <type_traits>
@@ -57,70 +57,74 @@ __device__ __forceinline__ float min3f(float a, float b, float c) {
   asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
   return r;
 }
-// Minimum of the sixteen results of a matrix instruction.  The first step is an instruction the compiler knows, so that
-// it waits for the matrix pipe; every other one takes its result as an operand and so comes after it.
-__device__ __forceinline__ float min16(const f16v& d) {
-  const float x = __builtin_amdgcn_fmed3f(d[0], d[1], -INFINITY);
-  float p = min3f(x, d[2], d[3]), q = min3f(x, d[8], d[9]);
-  p = min3f(p, d[4], d[5]), q = min3f(q, d[10], d[11]);
-  p = min3f(p, d[6], d[7]), q = min3f(q, d[12], d[13]);
-  return min3f(min3f(q, d[14], d[15]), p, p);
+// Minima of results 0..7 and 8..15 of a matrix instruction.  The first step is an instruction the compiler knows, so
+// that it waits for the matrix pipe; every other one takes its result as an operand and so comes after it.  `ninf` is
+// -inf in a register the compiler cannot look into (it would turn the median into a canonicalising minimum).
+__device__ __forceinline__ void min8x2(const f16v& d, float ninf, float& lo8, float& hi8) {
+  const float x = __builtin_amdgcn_fmed3f(d[0], d[1], ninf);
+  float q;
+  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(q) : "v"(d[8]), "v"(d[9]), "v"(d[10]), "v"(x));
+  float p = min3f(x, d[2], d[3]);
+  p = min3f(p, d[4], d[5]), q = min3f(q, d[11], d[12]);
+  lo8 = min3f(p, d[6], d[7]), q = min3f(q, d[13], d[14]);
+  asm("v_min_f32 %0, %1, %2" : "=v"(hi8) : "v"(q), "v"(d[15]));
 }
 
-// group g = 2 tile + half, row r of it <-> codeword (the rows a lane of that half holds of a 32 x 32 tile)
+// group g, row r of it <-> codeword: a lane of half hf holds rows 8 (k / 4) + 4 hf + k % 4, k = 0..15, of 32 x 32 tile m;
+// k < 8 is group 4 m + 2 hf, the others are group 4 m + 2 hf + 1
+constexpr int kGroups = 32, kGroupRows = 8;
 __host__ __device__ constexpr int group_codeword(int g, int r) {
-  return 32 * (g >> 1) + 8 * (r >> 2) + 4 * (g & 1) + (r & 3);
+  return 32 * (g >> 2) + 8 * (2 * (g & 1) + (r >> 2)) + 4 * ((g >> 1) & 1) + (r & 3);
 }
-__host__ __device__ constexpr int codeword_group(int c) { return 2 * (c >> 5) + ((c >> 2) & 1); }
-__host__ __device__ constexpr int codeword_row(int c) { return 4 * ((c >> 3) & 3) + (c & 3); }
+__host__ __device__ constexpr int codeword_group(int c) { return 4 * (c >> 5) + 2 * ((c >> 2) & 1) + ((c >> 4) & 1); }
+__host__ __device__ constexpr int codeword_row(int c) { return 4 * ((c >> 3) & 1) + (c & 3); }
 
-// LDS: -2 s c and ||s c||^2 in fp32, group by group; s = the power of two that brings the longest codeword to
-// norm [4, 8) (fp16 parts of any codebook then sit well inside the fp16 range).
+// LDS: -2 s c and ||s c||^2 in fp32, group by group (padded: neighbouring groups start in different banks); s = the
+// power of two that brings the longest codeword to norm [4, 8) (fp16 parts of any codebook then sit well inside the
+// fp16 range).  `image`: the codeword-side operands of the matrix instructions, 16 bytes per codeword and lane half.
 template <int SUB>
 struct SearchTables {
-  static constexpr int kRowStride = 17;   // 16-byte units per group of 16 rows
-  static constexpr int kNormStride = 20;  // floats per group
-  float4 n2c[SUB / 4][16 * kRowStride];
-  float cn[16 * kNormStride];
+  static constexpr int kRowStride = 9;    // 16-byte units per group
+  static constexpr int kNormStride = 12;  // floats per group
+  static constexpr int kImages = SUB == 4 ? 2 : 3;
+  float4 n2c[SUB / 4][kGroups * kRowStride];
+  float cn[kGroups * kNormStride];
+  float n2max[4];
+  h8 image[kImages][kCodes];
 };
 
 template <int SUB, bool EXACT16>
 struct SearchRegs {
   h8 A[8];
-  // SUB = 8: second operand; EXACT16 codewords (fp16 values) have no low part, ||c||^2 alone takes four slots
-  typename std::conditional<EXACT16, h4v, h8>::type A2[SUB == 8 ? 8 : 1];
+  // SUB = 8: second operand; EXACT16 codewords (fp16 values) have no low part, ||c||^2 alone takes four slots.  (The other
+  // form is read from LDS in every search: 32 registers that would halve the number of waves.)
+  h4v A2[SUB == 8 && EXACT16 ? 8 : 1];
   float cm;     // largest norm of a scaled codeword
   float scale;  // s
+  float ninf;   // see min8x2
 };
 
-// Fills the tables and the operands of every wave of the workgroup (256 threads or more).  get(c, i): element i of
-// codeword c.  No barrier inside: the caller puts one between this and the first search.
+// Fills the tables and the operands of every wave of the workgroup (256 threads or more, all of them call it).
+// get(i): element i of codeword `tid` (threads 0..255).
 template <int SUB, bool EXACT16, typename F>
 __device__ inline void search_setup(SearchTables<SUB>& T, SearchRegs<SUB, EXACT16>& R, int tid, F get) {
-  typedef decltype(get(0, 0)) real;
-  const int lane = tid & 63, row = lane & 31;
-  real e[8][SUB];
-#pragma unroll
-  for (int m = 0; m < 8; ++m)
-#pragma unroll
-    for (int i = 0; i < SUB; ++i) e[m][i] = get(32 * m + row, i);
+  typedef decltype(get(0)) real;
+  const int lane = tid & 63;
   real own[SUB];
-  if (tid < kCodes) {
-#pragma unroll
-    for (int i = 0; i < SUB; ++i) own[i] = get(tid, i);
-  }
-  float n2max = 0.f;
-#pragma unroll
-  for (int m = 0; m < 8; ++m) {
+  if (tid < kCodes) {  // (whole waves)
     float n2 = 0.f;
 #pragma unroll
-    for (int i = 0; i < SUB; ++i) n2 = fmaf((float)e[m][i], (float)e[m][i], n2);
-    n2max = fmaxf(n2max, n2);
+    for (int i = 0; i < SUB; ++i) {
+      own[i] = get(i);
+      n2 = fmaf((float)own[i], (float)own[i], n2);
+    }
+    n2 = wave_max(n2);
+    if (lane == 0) T.n2max[tid >> 6] = n2;
   }
-  n2max = wave_max(n2max);
+  __syncthreads();
   // s = 2^k with |c| s in [4, 8) for the longest codeword (1 for an empty or non-finite codebook)
+  const float nm = sqrtf(fmaxf(fmaxf(T.n2max[0], T.n2max[1]), fmaxf(T.n2max[2], T.n2max[3])));
   int ex = 0;
-  const float nm = sqrtf(n2max);
   if (nm > 0.f && nm < INFINITY) {
     (void)frexpf(nm, &ex);  // nm = f 2^ex, f in [1/2, 1)
     ex = min(max(3 - ex, -100), 100);
@@ -128,66 +132,62 @@ __device__ inline void search_setup(SearchTables<SUB>& T, SearchRegs<SUB, EXACT1
   const float s = ldexpf(1.f, ex);
   R.scale = s;
   R.cm = nm * s * 1.0001f;
-  auto parts = [](float cn, _Float16 (&p)[3]) {
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      p[k] = (_Float16)cn;
-      cn -= (float)p[k];
-    }
-  };
-#pragma unroll
-  for (int m = 0; m < 8; ++m) {
-    float cn = 0.f;
+  R.ninf = -INFINITY;
+  asm("" : "+v"(R.ninf));
+  if (tid < kCodes) {
+    float cn = 0.f, f[SUB];
+    h8 a0 = {}, a1 = {}, a2 = {};
     _Float16 hi[SUB], lo[SUB];
 #pragma unroll
     for (int i = 0; i < SUB; ++i) {
-      const real c = e[m][i] * (real)s;
-      cn = fmaf((float)c, (float)c, cn);
-      const real t = (real)-2 * c;
-      hi[i] = (_Float16)(float)t;
+      const real t = (real)-2 * (own[i] * (real)s);
+      f[i] = (float)t;
+      cn = fmaf(0.25f * f[i], f[i], cn);
+      hi[i] = (_Float16)f[i];
       lo[i] = EXACT16 ? (_Float16)0.f : (_Float16)(float)(t - (real)(float)hi[i]);
     }
     _Float16 p[3];
-    parts(cn, p);
-    const bool lower = lane < 32;
-    h8 a;
+    float rest = cn;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      p[k] = (_Float16)rest;
+      rest -= (float)p[k];
+    }
     if constexpr (SUB == 4) {  // k: -2c_hi (y_hi), -2c_hi (y_lo) | -2c_lo (y_hi), ||c||^2 in three parts, 0
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        a[i] = lower ? hi[i] : lo[i];
-        a[4 + i] = lower ? hi[i] : (i < 3 ? p[i < 3 ? i : 0] : (_Float16)0.f);
+        a0[i] = a0[4 + i] = hi[i];
+        a1[i] = lo[i];
+        a1[4 + i] = i < 3 ? p[i < 3 ? i : 0] : (_Float16)0.f;
       }
-      R.A[m] = a;
+      T.image[0][tid] = a0, T.image[1][tid] = a1;
     } else {  // -2c_hi (y_hi) | -2c_hi (y_lo); second operand: -2c_lo (y_hi) | parts of ||c||^2
 #pragma unroll
-      for (int i = 0; i < 8; ++i) a[i] = hi[i];
-      R.A[m] = a;
-      if constexpr (EXACT16) {
-        h4v b;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) b[i] = (lower && i < 3) ? p[i < 3 ? i : 0] : (_Float16)0.f;
-        R.A2[m] = b;
-      } else {
-        h8 b;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) b[i] = lower ? lo[i] : (i < 3 ? p[i < 3 ? i : 0] : (_Float16)0.f);
-        R.A2[m] = b;
+      for (int i = 0; i < 8; ++i) {
+        a0[i] = hi[i], a1[i] = lo[i];
+        a2[i] = i < 3 ? p[i < 3 ? i : 0] : (_Float16)0.f;
       }
+      T.image[0][tid] = a0, T.image[1][tid] = a1, T.image[2][tid] = a2;
     }
-  }
-  if (tid < kCodes) {
     const int g = codeword_group(tid), r = codeword_row(tid);
-    float cn = 0.f, f[SUB];
-#pragma unroll
-    for (int i = 0; i < SUB; ++i) {
-      const float c = (float)(own[i] * (real)s);
-      cn = fmaf(c, c, cn);
-      f[i] = -2.f * c;
-    }
 #pragma unroll
     for (int u = 0; u < SUB / 4; ++u)
       T.n2c[u][g * SearchTables<SUB>::kRowStride + r] = make_float4(f[4 * u], f[4 * u + 1], f[4 * u + 2], f[4 * u + 3]);
     T.cn[g * SearchTables<SUB>::kNormStride + r] = cn;
+  }
+  __syncthreads();
+  const int row = lane & 31, half = lane >> 5;
+#pragma unroll
+  for (int m = 0; m < 8; ++m) {
+    if constexpr (SUB == 4) {
+      R.A[m] = T.image[half][32 * m + row];
+    } else {
+      R.A[m] = T.image[0][32 * m + row];
+      if constexpr (EXACT16) {
+        const h8 q = T.image[2][32 * m + row];
+        R.A2[m] = half ? h4v{} : h4v{q[0], q[1], q[2], q[3]};
+      }
+    }
   }
 }
 
@@ -239,7 +239,9 @@ __device__ __forceinline__ int search_nearest(const SearchTables<SUB>& T, const 
       bb2 = words_h8(lower ? lo[0] : ONE1, lower ? lo[1] : ONE0, lower ? lo[2] : 0u, lower ? lo[3] : 0u);
     }
   }
-  float ta[8], tb[8];
+  float a0[8], a1[8], b0[8], b1[8];  // minima of the two groups of tile m held by this lane, sets a and b
+  int second = 256 * (1 + (int)((threadIdx.x >> 5) & 1)) + (int)(threadIdx.x & 31);
+  asm volatile("" : "+v"(second));  // (keeps the reads of the second operand inside the search)
   const f16v zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int m = 0; m < 8; ++m) {
@@ -252,25 +254,23 @@ __device__ __forceinline__ int search_nearest(const SearchTables<SUB>& T, const 
       da = __builtin_amdgcn_mfma_f32_32x32x16_f16(R.A[m], ba, d0, 0, 0, 0);
       db = __builtin_amdgcn_mfma_f32_32x32x16_f16(R.A[m], bb, d0, 0, 0, 0);
     } else {
-      da = __builtin_amdgcn_mfma_f32_32x32x16_f16(R.A2[m], ba2, zero, 0, 0, 0);
-      db = __builtin_amdgcn_mfma_f32_32x32x16_f16(R.A2[m], bb2, zero, 0, 0, 0);
+      const h8 a2 = (&T.image[0][0])[second + 32 * m];
+      da = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, ba2, zero, 0, 0, 0);
+      db = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, bb2, zero, 0, 0, 0);
       da = __builtin_amdgcn_mfma_f32_32x32x16_f16(R.A[m], ba, da, 0, 0, 0);
       db = __builtin_amdgcn_mfma_f32_32x32x16_f16(R.A[m], bb, db, 0, 0, 0);
     }
-    ta[m] = min16(da);
-    tb[m] = min16(db);
+    min8x2(da, R.ninf, a0[m], a1[m]);
+    min8x2(db, R.ninf, b0[m], b1[m]);
   }
-  // own sub-vector: ta[m] becomes the minimum of group 2m, tb[m] that of group 2m + 1
-  swap32x4(ta[0], tb[0], ta[1], tb[1], ta[2], tb[2], ta[3], tb[3]);
-  swap32x4(ta[4], tb[4], ta[5], tb[5], ta[6], tb[6], ta[7], tb[7]);
-  float best = min3f(ta[0], tb[0], ta[1]);
-  best = min3f(best, tb[1], ta[2]);
-  best = min3f(best, tb[2], ta[3]);
-  best = min3f(best, tb[3], ta[4]);
-  best = min3f(best, tb[4], ta[5]);
-  best = min3f(best, tb[5], ta[6]);
-  best = min3f(best, tb[6], ta[7]);
-  best = min3f(best, tb[7], tb[7]);
+  // own sub-vector: a0, a1, b0, b1 [m] become the minima of groups 4m, 4m + 1, 4m + 2, 4m + 3
+#pragma unroll
+  for (int m = 0; m < 8; m += 2) swap32x4(a0[m], b0[m], a1[m], b1[m], a0[m + 1], b0[m + 1], a1[m + 1], b1[m + 1]);
+  float best = min3f(a0[0], a1[0], b0[0]), best2 = min3f(b1[0], a0[1], a1[1]);
+  best = min3f(best, b0[1], b1[1]);
+#pragma unroll
+  for (int m = 2; m < 8; ++m) best = min3f(best, a0[m], a1[m]), best2 = min3f(best2, b0[m], b1[m]);
+  best = min3f(best, best2, best2);
   // Error bound of either form of a distance, relative to M >= ||c||^2 + 2 |c| |y|, in units of 2^-24: the fp16 splits of
   // y and c leave 4 each (two roundings of 2^-11), the dropped low x low product 4, low parts below the normal fp16
   // range 2 (M >= 16), fp32 rounding of the inputs 2, the sum of at most 32 terms 24 (matrix cores) or SUB + 3
@@ -280,8 +280,10 @@ __device__ __forceinline__ int search_nearest(const SearchTables<SUB>& T, const 
   uint32_t groups = 0u;
 #pragma unroll
   for (int m = 7; m >= 0; --m) {
-    groups = __builtin_amdgcn_alignbit(groups, __float_as_uint(tb[m] - thr), 31);
-    groups = __builtin_amdgcn_alignbit(groups, __float_as_uint(ta[m] - thr), 31);
+    groups = __builtin_amdgcn_alignbit(groups, __float_as_uint(b1[m] - thr), 31);
+    groups = __builtin_amdgcn_alignbit(groups, __float_as_uint(b0[m] - thr), 31);
+    groups = __builtin_amdgcn_alignbit(groups, __float_as_uint(a1[m] - thr), 31);
+    groups = __builtin_amdgcn_alignbit(groups, __float_as_uint(a0[m] - thr), 31);
   }
   if (!(yn < 1e9f)) groups = 0u;  // beyond the fp16 range (or not a number): fp64 search below
   // rows of group g within the bound, as a bit mask
@@ -291,7 +293,7 @@ __device__ __forceinline__ int search_nearest(const SearchTables<SUB>& T, const 
     const float4* n = reinterpret_cast<const float4*>(&T.cn[g * SearchTables<SUB>::kNormStride]);
     uint32_t mask = 0u;
 #pragma unroll
-    for (int u = 3; u >= 0; --u) {
+    for (int u = kGroupRows / 4 - 1; u >= 0; --u) {
       const float4 cn4 = n[u];
       const float cnv[4] = {cn4.x, cn4.y, cn4.z, cn4.w};
 #pragma unroll
