@@ -4,8 +4,8 @@
 // Lloyd iterations entirely on the device, deterministic, two launches each:
 //   cb_accumulate_kernel  nearest centroid per sample (nsn_search.h) and, in the same pass over the samples, the sums of
 //                         every cluster's members: one partial per workgroup
-//   km_update_kernel /    adds the partials in a fixed order (fp64) and moves the centroids
-//   ft_update_kernel
+//   km_update_kernel      adds the partials in a fixed order (fp64): the new centroids
+// (fine-tuning: ft_accumulate_kernel and ft_update_kernel)
 #include "nsn_host.h"
 #include "nsn_search.h"
 
@@ -91,8 +91,7 @@ __device__ __forceinline__ double exact_dist(const double* __restrict__ centroid
   return d;
 }
 
-// Assignment and member sums in one pass over the samples.  WHAT: kSums adds the samples, kUnitSums adds x / |x|
-// (zero samples add nothing), kError adds no members but the squared error.
+// Assignment and, in the same pass over the samples, member sums (ERR false) or the squared error (ERR true).
 //
 // The sums are formed in LDS by integer atomics on fixed-point values: integer addition is associative, so the result
 // does not depend on the order in which lanes and waves arrive.  A value enters with its last place at 2^-50 of the
@@ -101,9 +100,8 @@ __device__ __forceinline__ double exact_dist(const double* __restrict__ centroid
 // it stands for.  Adding 1.5 * 2^52 puts the fixed-point value into the low bits of the fp64 pattern;
 // the patterns are added as they are and the member count times the constant's pattern comes off at the end.
 // (The form this replaces wrote the assignments out and let one workgroup per cluster look through all of them:
-// 270 us per iteration of 2^20 4-dim samples, 1.05 ms with x / |x|.)
-enum { kSums, kUnitSums, kError };
-template <int SUB, int WHAT>
+// 270 us per iteration of 2^20 4-dim samples.)
+template <int SUB, bool ERR>
 __global__ __launch_bounds__(kSumThreads<SUB>) void cb_accumulate_kernel(const float* __restrict__ samples, int64_t n,
                                                                        CodebookWs<SUB> ws) {
   constexpr int NT = kSumThreads<SUB>;
@@ -111,7 +109,7 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_accumulate_kernel(const f
   constexpr double kMagic = 6755399441055744.0;      // 1.5 * 2^52
   __shared__ SearchTables<SUB> T;
   __shared__ double cx[kCodes][SUB];
-  __shared__ unsigned long long acc[WHAT == kError ? 1 : SUB][kCodes];
+  __shared__ unsigned long long acc[ERR ? 1 : SUB][kCodes];
   __shared__ uint32_t cnt[kCodes];
   __shared__ double red[NT / 64];
   const int tid = threadIdx.x;
@@ -127,15 +125,15 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_accumulate_kernel(const f
   SearchRegs<SUB, false> R;
   search_setup<SUB, false>(T, R, tid, [&](int i) { return ws.centroids[tid * SUB + i]; });
   for (int i = tid; i < kCodes * SUB; i += NT) (&cx[0][0])[i] = ws.centroids[i];
-  double fixed = 0x1p50;  // values below 1
-  if constexpr (WHAT == kSums) {
+  double fixed = 1.0;
+  if constexpr (!ERR) {
     int ex = 0;
     const float mx = __uint_as_float(*ws.max_bits);
     if (mx > 0.f && mx < INFINITY) (void)frexpf(mx, &ex);  // mx < 2^ex
     fixed = ldexp(1.0, 50 - ex);
   }
   auto clear = [&]() {
-    if constexpr (WHAT != kError) {
+    if constexpr (!ERR) {
       for (int i = tid; i < kCodes * SUB; i += NT) (&acc[0][0])[i] = 0ull;
       if (tid < kCodes) cnt[tid] = 0u;
     }
@@ -156,26 +154,16 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_accumulate_kernel(const f
       const int64_t next = w0 + NT < stop ? w0 + NT : base + kSumMost + (tid & ~63);
       fetch(next + (tid & 63));
       const int code = search_nearest<SUB, false>(T, R, x, [&](int c) { return exact_dist<SUB>(cx[c], x); });
-      if constexpr (WHAT == kError) {
+      if constexpr (ERR) {
         if (valid) err += exact_dist<SUB>(cx[code], x);
       } else if (valid) {
-        double v[SUB], n2 = 0.0;
-#pragma unroll
-        for (int i = 0; i < SUB; ++i) v[i] = (double)x[i];
-        if constexpr (WHAT == kUnitSums) {
-#pragma unroll
-          for (int i = 0; i < SUB; ++i) n2 += v[i] * v[i];
-          const double nx = sqrt(n2);
-#pragma unroll
-          for (int i = 0; i < SUB; ++i) v[i] = n2 > 0.0 ? v[i] / nx : 0.0;
-        }
 #pragma unroll
         for (int i = 0; i < SUB; ++i)
-          atomicAdd(&acc[i][code], (unsigned long long)__double_as_longlong(fma(v[i], fixed, kMagic)));
+          atomicAdd(&acc[i][code], (unsigned long long)__double_as_longlong(fma((double)x[i], fixed, kMagic)));
         atomicAdd(&cnt[code], 1u);
       }
     }
-    if constexpr (WHAT != kError) {
+    if constexpr (!ERR) {
       __syncthreads();
 #pragma unroll
       for (int k = 0; k < kOwn; ++k) {  // dimension e % SUB of cluster e / SUB
@@ -190,7 +178,7 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_accumulate_kernel(const f
       __syncthreads();
     }
   }
-  if constexpr (WHAT == kError) {
+  if constexpr (ERR) {
     err = xor_sum(err, 64);
     if ((tid & 63) == 0) red[tid >> 6] = err;
     __syncthreads();
@@ -207,6 +195,183 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_accumulate_kernel(const f
       if (e < kCodes * SUB) ws.sums[(int64_t)blockIdx.x * kCodes * SUB + e] = own[k] * unit;
     }
     if (tid < kCodes) ws.counts[(int64_t)blockIdx.x * kCodes + tid] = own_n;
+  }
+}
+
+// Fine-tuning: assignment and the sums of x / |x| over every codeword's samples (zero samples add nothing), in fp64 and in
+// ONE order: the steps are large (a rate of 2048 turns a small codeword by several times its error), so a
+// difference in the last place of a sum grows to a different codebook within twenty of them, and the order is part of
+// the result.  Runs of 16 samples are dealt out to 1024 chains, every chain adds the members of a codeword by
+// ascending index, chains are added in pairs up to 64 and the sixteen results one after the other.
+// A workgroup owns four neighbouring chains, i.e. 64 samples out of every 16384.  It searches 4096 of them at a time
+// and leaves (chain, codeword) lists of positions in LDS, in whatever order the lanes arrive; then a thread per
+// (chain, codeword) sorts its list (four entries on average) in registers and adds its samples.  A list that
+// overflows is rebuilt from the codes.  (One workgroup per codeword looking through all codes: 0.9 ms per step of 2^20
+// samples.)
+constexpr int kChains = 1024, kRun = 16;
+constexpr int kWgChains = kChains / kSumBlocks;             // 4
+constexpr int kBlockPos = kSumMost / kWgChains;             // positions of a chain per block: 1024
+constexpr int kPairs = kWgChains * kCodes, kListMost = 32;  // lists per workgroup, entries per list
+
+// the first N of e in ascending order: odd-even merge sort, all indices known to the compiler
+template <int N, int M>
+__device__ __forceinline__ void sort_ascending(uint32_t (&e)[M]) {
+#pragma unroll
+  for (int a = 1; a < N; a *= 2)
+#pragma unroll
+    for (int k = a; k >= 1; k /= 2)
+#pragma unroll
+      for (int j = k % a; j + k < N; j += 2 * k)
+#pragma unroll
+        for (int i = 0; i < k; ++i)
+          if (i + j + k < N && (i + j) / (2 * a) == (i + j + k) / (2 * a)) {
+            const uint32_t lo = min(e[i + j], e[i + j + k]), hi = max(e[i + j], e[i + j + k]);
+            e[i + j] = lo, e[i + j + k] = hi;
+          }
+}
+
+template <int SUB>
+__global__ __launch_bounds__(kSumThreads<SUB>) void ft_accumulate_kernel(const float* __restrict__ samples, int64_t n,
+                                                                         CodebookWs<SUB> ws) {
+  constexpr int NT = kSumThreads<SUB>, NWV = NT / 64, CPW = (kPairs / 64 + NWV - 1) / NWV;
+  __shared__ SearchTables<SUB> T;
+  __shared__ double cx[kCodes][SUB];
+  __shared__ __attribute__((aligned(16))) uint16_t list[kPairs][kListMost];
+  __shared__ uint32_t len[kPairs];
+  __shared__ __attribute__((aligned(16))) uint16_t codes[kWgChains][kBlockPos];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  SearchRegs<SUB, false> R;
+  search_setup<SUB, false>(T, R, tid, [&](int i) { return ws.centroids[tid * SUB + i]; });
+  for (int i = tid; i < kCodes * SUB; i += NT) (&cx[0][0])[i] = ws.centroids[i];
+  const int64_t n16 = n & ~(int64_t)(kRun - 1);
+  double acc[CPW][SUB];
+#pragma unroll
+  for (int c = 0; c < CPW; ++c)
+#pragma unroll
+    for (int i = 0; i < SUB; ++i) acc[c][i] = 0.0;
+  auto load = [&](int64_t idx, float (&x)[SUB]) {
+    const row4* row = reinterpret_cast<const row4*>(samples) + idx * (SUB / 4);
+#pragma unroll
+    for (int q = 0; q < SUB / 4; ++q) {
+      const row4 v = row[q];
+      x[4 * q] = v.x, x[4 * q + 1] = v.y, x[4 * q + 2] = v.z, x[4 * q + 3] = v.w;
+    }
+  };
+  auto add_unit = [&](const float (&x)[SUB], double (&a)[SUB]) {
+    double v[SUB], n2 = 0.0;
+#pragma unroll
+    for (int i = 0; i < SUB; ++i) {
+      v[i] = (double)x[i];
+      n2 += v[i] * v[i];
+    }
+    if (n2 > 0.0) {
+      // v / nx, correctly rounded, with one reciprocal for all elements (quotient, exact remainder, correction)
+      const double nx = sqrt(n2);
+      double r = __builtin_amdgcn_rcp(nx);
+      r = fma(fma(-nx, r, 1.0), r, r);
+      r = fma(fma(-nx, r, 1.0), r, r);
+#pragma unroll
+      for (int i = 0; i < SUB; ++i) {
+        const double q = v[i] * r;
+        a[i] += fma(fma(-q, nx, v[i]), r, q);
+      }
+    }
+  };
+  // block by block, the samples behind the last whole run (one per chain, the last of its order) as a block of their own
+  const int64_t blocks = (n16 + (int64_t)kSumMost * kSumBlocks - 1) / ((int64_t)kSumMost * kSumBlocks);
+  for (int64_t blk = 0; blk < blocks + (n > n16); ++blk) {
+    const bool tail = blk == blocks;
+    // sample of position p of chain `ch` (of the workgroup's four) in this block
+    auto sample_of = [&](int ch, int p) -> int64_t {
+      const int chain = blockIdx.x * kWgChains + ch;
+      return tail ? n16 + chain : ((blk * (kBlockPos / kRun) + (p >> 4)) * kChains + chain) * kRun + (p & 15);
+    };
+    const int64_t stop = tail ? n : n16;
+    for (int i = tid; i < kPairs; i += NT) len[i] = 0u;
+    __syncthreads();
+    for (int u = wave; u < (tail ? 1 : kBlockPos / kRun); u += NWV) {
+      const int ch = tail ? lane & 3 : lane >> 4, p = tail ? 0 : u * kRun + (lane & 15);
+      const int64_t idx = sample_of(ch, p);
+      const bool valid = idx < stop && !(tail && lane >= kWgChains);
+      if (!__any(valid)) break;
+      float x[SUB];
+      load(min(idx, n - 1), x);
+      const int code = search_nearest<SUB, false>(T, R, x, [&](int c) { return exact_dist<SUB>(cx[c], x); });
+      if (valid) {
+        const uint32_t at = atomicAdd(&len[code * kWgChains + ch], 1u);
+        if (at < kListMost) list[code * kWgChains + ch][at] = (uint16_t)p;
+      }
+      if (!tail) codes[ch][p] = valid ? (uint16_t)code : (uint16_t)0xffff;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < CPW; ++c) {
+      const int pair = (wave + c * NWV) * 64 + lane;  // codeword pair / 4, chain pair % 4
+      if (pair >= kPairs) break;  // (whole waves)
+      const uint32_t count = len[pair];
+      if (count > kListMost) {
+        for (int p0 = 0; p0 < kBlockPos; p0 += 8) {
+          const uint4 w4 = *reinterpret_cast<const uint4*>(&codes[pair & 3][p0]);
+          const uint32_t w[4] = {w4.x, w4.y, w4.z, w4.w};
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            const uint32_t code = (k & 1) ? w[k / 2] >> 16 : w[k / 2] & 0xffffu;
+            if (code == (uint32_t)(pair >> 2) && sample_of(pair & 3, p0 + k) < stop) {
+              float x[SUB];
+              load(sample_of(pair & 3, p0 + k), x);
+              add_unit(x, acc[c]);
+            }
+          }
+        }
+      }
+      const uint32_t here = count > kListMost ? 0u : count;
+      uint32_t e[kListMost];
+#pragma unroll
+      for (int q = 0; q < kListMost / 8; ++q) {
+        const uint4 w4 = reinterpret_cast<const uint4*>(list[pair])[q];
+        const uint32_t w[4] = {w4.x, w4.y, w4.z, w4.w};
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const uint32_t v = (k & 1) ? w[k / 2] >> 16 : w[k / 2] & 0xffffu;
+          e[8 * q + k] = 8 * q + k < (int)here ? v : 0xffffu;
+        }
+      }
+      if (__any(here > kListMost / 2))
+        sort_ascending<kListMost>(e);
+      else
+        sort_ascending<kListMost / 2>(e);
+      // (back to LDS: a loop over registers would be unrolled to a body of its own per entry)
+#pragma unroll
+      for (int q = 0; q < kListMost / 8; ++q)
+        reinterpret_cast<uint4*>(list[pair])[q] =
+            make_uint4(e[8 * q] | e[8 * q + 1] << 16, e[8 * q + 2] | e[8 * q + 3] << 16, e[8 * q + 4] | e[8 * q + 5] << 16,
+                       e[8 * q + 6] | e[8 * q + 7] << 16);
+      float ahead[SUB];
+      auto fetch = [&](uint32_t k) {  // (position 0 of the block exists for every chain that has entries)
+        const int64_t idx = sample_of(pair & 3, k < here ? list[pair][k] : 0);
+        load(min(idx, n - 1), ahead);
+      };
+      fetch(0);
+      for (uint32_t k = 0; __any(k < here); ++k) {
+        float x[SUB];
+#pragma unroll
+        for (int i = 0; i < SUB; ++i) x[i] = ahead[i];
+        fetch(k + 1);
+        if (k < here) add_unit(x, acc[c]);
+      }
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int c = 0; c < CPW; ++c) {
+    const int pair = (wave + c * NWV) * 64 + lane;
+    if (pair >= kPairs) break;
+#pragma unroll
+    for (int i = 0; i < SUB; ++i) {
+      acc[c][i] += xor_lane<1>(acc[c][i]);
+      acc[c][i] += xor_lane<2>(acc[c][i]);
+      if ((lane & 3) == 0) ws.sums[((int64_t)blockIdx.x * kCodes + pair / kWgChains) * SUB + i] = acc[c][i];
+    }
   }
 }
 
@@ -267,13 +432,29 @@ __global__ __launch_bounds__(kUpdateThreads) void km_update_kernel(CodebookWs<SU
 // similarity BEFORE the move.
 template <int SUB>
 __global__ __launch_bounds__(kUpdateThreads) void ft_update_kernel(int64_t n, CodebookWs<SUB> ws, double lr) {
-  double S[SUB], count;
-  merge_partials<SUB>(ws, S, count);
+  constexpr int E = kUpdateClusters * SUB, SL = kUpdateThreads / E;
+  constexpr int kTrees = kSumBlocks / 16;  // sixteen workgroups = 64 chains: added in pairs, then the trees in order
+  __shared__ double tree[kTrees][E];
+  for (int g = threadIdx.x / E; g < kTrees; g += SL) {
+    const int e = threadIdx.x % E;
+    double v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = ws.sums[((int64_t)(16 * g + u) * kCodes + blockIdx.x * kUpdateClusters) * SUB + e];
+#pragma unroll
+    for (int d = 1; d < 16; d *= 2)
+#pragma unroll
+      for (int u = 0; u < 16; u += 2 * d) v[u] += v[u + d];
+    tree[g][e] = v[0];
+  }
+  __syncthreads();
   if (threadIdx.x < kUpdateClusters) {
     const int k = blockIdx.x * kUpdateClusters + threadIdx.x;
-    double c[SUB], cn2 = 0.0;
+    double S[SUB], c[SUB], cn2 = 0.0;
 #pragma unroll
     for (int i = 0; i < SUB; ++i) {
+      S[i] = 0.0;
+#pragma unroll
+      for (int g = 0; g < kTrees; ++g) S[i] += tree[g][threadIdx.x * SUB + i];
       c[i] = ws.centroids[k * SUB + i];
       cn2 += c[i] * c[i];
     }
@@ -302,11 +483,11 @@ static int codebook_run_t(const float* samples, int64_t n, int iters, void* code
   cb_start_kernel<<<(n_elems + 255) / 256, 256, 0, stream>>>(samples, ws.centroids, n_elems, ws.max_bits);
   cb_max_kernel<<<256, kMaxThreads, 0, stream>>>(samples, n * (SUB / 4), ws.max_bits);
   for (int it = 0; it < iters; ++it) {
-    cb_accumulate_kernel<SUB, kSums><<<kSumBlocks, kSumThreads<SUB>, 0, stream>>>(samples, n, ws);
+    cb_accumulate_kernel<SUB, false><<<kSumBlocks, kSumThreads<SUB>, 0, stream>>>(samples, n, ws);
     km_update_kernel<SUB><<<kCodes / kUpdateClusters, kUpdateThreads, 0, stream>>>(ws);
   }
   km_round_kernel<<<(n_elems + 255) / 256, 256, 0, stream>>>(ws.centroids, static_cast<__half*>(codebook_out), n_elems);
-  cb_accumulate_kernel<SUB, kError><<<kSumBlocks, kSumThreads<SUB>, 0, stream>>>(samples, n, ws);
+  cb_accumulate_kernel<SUB, true><<<kSumBlocks, kSumThreads<SUB>, 0, stream>>>(samples, n, ws);
   if (hipGetLastError() != hipSuccess) return NSN_ERR_HIP;
   double host_err[kSumBlocks];
   if (hipMemcpyAsync(host_err, ws.block_err, sizeof(host_err), hipMemcpyDeviceToHost, stream) != hipSuccess)
@@ -327,7 +508,7 @@ static int finetune_run_t(const float* samples, int64_t n, int iters, double lr,
   constexpr int n_elems = kCodes * SUB;
   double host_cos[kCodes];
   auto step = [&](double rate) {
-    cb_accumulate_kernel<SUB, kUnitSums><<<kSumBlocks, kSumThreads<SUB>, 0, stream>>>(samples, n, ws);
+    ft_accumulate_kernel<SUB><<<kSumBlocks, kSumThreads<SUB>, 0, stream>>>(samples, n, ws);
     ft_update_kernel<SUB><<<kCodes / kUpdateClusters, kUpdateThreads, 0, stream>>>(n, ws, rate);
   };
   auto mean_cos = [&](double* out) -> int {  // assignment + cosine sums of the current centroids (no move: rate 0)

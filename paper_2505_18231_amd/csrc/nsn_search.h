@@ -146,6 +146,9 @@ __device__ inline void search_setup(SearchTables<SUB>& T, SearchRegs<SUB, EXACT1
       hi[i] = (_Float16)f[i];
       lo[i] = EXACT16 ? (_Float16)0.f : (_Float16)(float)(t - (real)(float)hi[i]);
     }
+    // (the sum is pinned: folded into the conversion, one use of its fp16 value would be rounded from the unrounded sum
+    // and the other from the fp32 one, and at a tie the parts would not add up)
+    asm("" : "+v"(cn));
     _Float16 p[3];
     float rest = cn;
 #pragma unroll
