@@ -13,7 +13,8 @@ namespace nsn {
 
 constexpr int kSumBlocks = 256;   // workgroups of the accumulation (and partial sums per cluster)
 // four waves per SIMD (128 registers) for 4-dim codewords, three (170) for 8-dim ones, which spill at four: 26.5 against
-// 29.5 us and 38.0 against 39.8 us per K-Means iteration of 2^20 samples with two
+// 29.5 us and 38.0 against 39.8 us per K-Means iteration of 2^20 samples with two (with the products requested a tile
+// ahead: 32 us, for want of registers, and 35.7 us)
 template <int SUB>
 constexpr int kSumThreads = SUB == 4 ? 1024 : 768;
 constexpr int kSumMost = 4096;  // samples added up in LDS at a time
@@ -153,7 +154,7 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_accumulate_kernel(const f
       // the next 64 are on their way while these are searched (the last one of the block again where there are none)
       const int64_t next = w0 + NT < stop ? w0 + NT : base + kSumMost + (tid & ~63);
       fetch(next + (tid & 63));
-      const int code = search_nearest<SUB, false>(T, R, x, [&](int c) { return exact_dist<SUB>(cx[c], x); });
+      const int code = search_nearest<SUB, false, SUB == 8>(T, R, x, [&](int c) { return exact_dist<SUB>(cx[c], x); }).code;
       if constexpr (ERR) {
         if (valid) err += exact_dist<SUB>(cx[code], x);
       } else if (valid) {
@@ -296,7 +297,7 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void ft_accumulate_kernel(const f
       if (!__any(valid)) break;
       float x[SUB];
       load(min(idx, n - 1), x);
-      const int code = search_nearest<SUB, false>(T, R, x, [&](int c) { return exact_dist<SUB>(cx[c], x); });
+      const int code = search_nearest<SUB, false, false>(T, R, x, [&](int c) { return exact_dist<SUB>(cx[c], x); }).code;
       if (valid) {
         const uint32_t at = atomicAdd(&len[code * kWgChains + ch], 1u);
         if (at < kListMost) list[code * kWgChains + ch][at] = (uint16_t)p;

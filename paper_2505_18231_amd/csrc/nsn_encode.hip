@@ -1,21 +1,20 @@
 // KV encoder kernels: Normalize - Shift - Normalize (Sec. 3.2), Hadamard rotation (Sec. 2),
 // nearest-codeword search (Eq. 1), scale adjustment (Sec. 3.3).
 //
-// Three launches per call:
-//   enc_stats_kernel  per token: b = fp16(||x|| / sqrt(d)); per chunk: fp64 partial sums of x / b
-//   enc_means_kernel  per group: o = fp16(sum of partials / count)           (skipped in append mode)
-//   enc_quant_kernel  per token: (x / b - o) -> s2 -> rotate -> codes, a = fp16(b * s2 * alpha)
-// Double quantization (Sec. 3.5, side_bits = 4): enc_stats_kernel leaves fp16(s1) in the workspace,
-// enc_brtn_kernel turns every 64-token block of them into 4-bit codes, enc_means_kernel stores the
-// means as 4-bit codes per 32 channels, and enc_quant_kernel shifts by the dequantised mean and
-// stores a' = fp16(s2 * alpha).
-// Normalisation, rotation and the dot products that feed fp16 roundings run in fp64 (same rate
-// as fp32 on this chip's vector units); only the 256-way distance scan runs in fp32.
+// enc_kernel does all of it for a call whose Shift means are known before a token is quantised: append mode (stored means)
+// and groups of 64 tokens (a workgroup holds a whole group).  Otherwise two launches form the means first:
+//   enc_stats_kernel  per chunk: fp64 partial sums of x / b, b = fp16(||x|| / sqrt(d))
+//   enc_means_kernel  per group: o = fp16(sum of partials / count)
+// Double quantization (Sec. 3.5, side_bits = 4): the means are stored as 4-bit codes per 32 channels and subtracted in
+// their dequantised form, s1 becomes 4-bit codes per 64-token block, and a' = fp16(s2 * alpha) is stored.
+// Normalisation, rotation and the dot products that feed fp16 roundings run in fp64 (same rate as fp32 on this chip's
+// vector units); the codeword search decides as an fp64 search would (nsn_search.h).
+// NSN_VARIANT_ALT (a cross-check) runs the stages as separate kernels with an fp32 scan of all 256 distances.
 #include "nsn_host.h"
-#include <cstdlib>
 #include <type_traits>
 
-#include "nsn_vq_mfma.h"
+#include "nsn_search.h"
+#include "nsn_vq.h"
 
 namespace nsn {
 
@@ -28,6 +27,29 @@ __device__ __forceinline__ void static_for_pow2(F&& f) {
   }
 }
 
+// Square root and reciprocals from the hardware estimates (about 2^-26) and Newton steps, within an fp64 unit or two.  The
+// arguments are sums of squares of moderate numbers or fp16 values: zero or far inside the fp64 range.
+__device__ __forceinline__ double sqrt_f64(double x) {
+  if (x == 0.0) return 0.0;
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+  const double r = fma(-h, g, 0.5);
+  g = fma(g, r, g), h = fma(h, r, h);
+  return fma(fma(-g, g, x), h, g);
+}
+__device__ __forceinline__ double rcp_f64(double x) {  // 0 for 0
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return x == 0.0 ? 0.0 : r;
+}
+__device__ __forceinline__ double rsqrt_f64(double x) {  // 0 for 0
+  double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);
+  y = fma(y * e, fma(0.375, e, 0.5), y);
+  return x == 0.0 ? 0.0 : y;
+}
+
 // ---------------------------------------------------------------------------------------
 // Stage A: first Normalize scale per token, partial channel sums of the normalised tokens.
 // grid (chunk, kv_head * 2 + tensor, sequence), block 256 = 4 waves; a wave takes four tokens at a
@@ -38,7 +60,8 @@ __global__ __launch_bounds__(256) void enc_stats_kernel(Geometry g, const __half
                                                         int max_len, const int32_t* __restrict__ seq_start,
                                                         const int32_t* __restrict__ n_new, CacheView kc,
                                                         CacheView vc, double* __restrict__ partial,
-                                                        int chunk_tokens, int n_chunks, __half* __restrict__ ws_b) {
+                                                        int chunk_tokens, int n_chunks, __half* __restrict__ ws_b,
+                                                        int write_b) {
   const int chunk = blockIdx.x, h = blockIdx.y >> 1, tensor = blockIdx.y & 1, b = blockIdx.z;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int row = lane >> 4, col = lane & 15;  // token of the wave's four, channels [8 col, 8 col + 8)
@@ -72,29 +95,11 @@ __global__ __launch_bounds__(256) void enc_stats_kernel(Geometry g, const __half
       ss = fma(x[i], x[i], ss);
     }
     ss = xor_sum_w<16>(ss);
-    // s1 = sqrt(ss / d) and 1 / fp16(s1) by the hardware estimates and Newton steps (ss is a sum of squares
-    // of fp16 values: zero or far inside the fp64 range, so no scaling is needed).  Both are within an fp64
-    // unit or two of the correctly rounded values; what is stored is rounded to fp16.
-    const double sd = ss * (1.0 / kHeadDim);
-    double s1 = 0.0;
-    if (sd != 0.0) {
-      const double y = __builtin_amdgcn_rsq(sd);
-      double gq = sd * y, hq = 0.5 * y;
-      const double r0 = fma(-hq, gq, 0.5);
-      gq = fma(gq, r0, gq), hq = fma(hq, r0, hq);
-      s1 = fma(fma(-gq, gq, sd), hq, gq);
-    }
-    const __half b16 = f64_to_f16(s1);
-    const double bb = (double)__half2float(b16);
-    double rb = 0.0;  // (tokens past the end add nothing)
-    if (bb != 0.0 && t < t_end) {
-      rb = __builtin_amdgcn_rcp(bb);
-      rb = fma(fma(-bb, rb, 1.0), rb, rb);
-      rb = fma(fma(-bb, rb, 1.0), rb, rb);
-    }
+    const __half b16 = f64_to_f16(sqrt_f64(ss * (1.0 / kHeadDim)));
+    const double rb = t < t_end ? rcp_f64((double)__half2float(b16)) : 0.0;  // (tokens past the end add nothing)
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] = fma(x[i], rb, acc[i]);
-    if (col == 0 && t < t_end) {
+    if (write_b && col == 0 && t < t_end) {
       if (linear) {
         b_out[(int64_t)t * b_stride] = b16;
       } else {
@@ -144,9 +149,45 @@ __device__ inline int rtn4_code(double x, double mn, double st) {
   return (int)fmin(fmax(lvl, 0.0), 15.0);
 }
 
+// 4-bit codes of fp16(s1) of a 64-token block into its norms record; a lane owns one token (the block has at least one:
+// lane 0 is valid)
+__device__ __forceinline__ void quantize_s1(float x, bool valid, int lane, unsigned char* rec) {
+  float lo = valid ? x : INFINITY, hi = valid ? x : -INFINITY;
+#pragma unroll
+  for (int m = 1; m < 64; m <<= 1) {
+    lo = fminf(lo, __shfl_xor(lo, m, 64));
+    hi = fmaxf(hi, __shfl_xor(hi, m, 64));
+  }
+  const __half mn16 = f64_to_f16((double)lo);  // exact: the minimum is one of the fp16 inputs
+  const __half st16 = f64_to_f16(((double)hi - (double)lo) / 15.0);
+  const int code = valid ? rtn4_code((double)x, (double)__half2float(mn16), (double)__half2float(st16)) : 0;
+  const int other = __shfl_xor(code, 1, 64);
+  if ((lane & 1) == 0 && valid) rec[kDqNormCodes + (lane >> 1)] = (unsigned char)(code | (other << 4));
+  if (lane == 0) *reinterpret_cast<__half2*>(rec + kDqNormPar) = __halves2half2(mn16, st16);
+}
+
+// 16 levels per 32 channels (half a wave) of a mean; channel c of the calling thread.  Returns the dequantised value,
+// stores the record where one is given.
+__device__ __forceinline__ double quantize_mean(double mean, int c, unsigned char* rec) {
+  double lo = mean, hi = mean;
+#pragma unroll
+  for (int m = 1; m < 32; m <<= 1) {
+    lo = fmin(lo, __shfl_xor(lo, m, 64));
+    hi = fmax(hi, __shfl_xor(hi, m, 64));
+  }
+  const __half mn16 = f64_to_f16(lo), st16 = f64_to_f16((hi - lo) / 15.0);
+  const double mn = (double)__half2float(mn16), st = (double)__half2float(st16);
+  const int code = rtn4_code(mean, mn, st);
+  const int other = __shfl_xor(code, 1, 64);
+  if (rec) {
+    if ((c & 1) == 0) rec[c >> 1] = (unsigned char)(code | (other << 4));
+    if ((c & 31) == 0) *reinterpret_cast<__half2*>(rec + kDqMeanPar + 4 * (c >> 5)) = __halves2half2(mn16, st16);
+  }
+  return mn + st * (double)code;
+}
+
 // ---------------------------------------------------------------------------------------
-// Stage A1 (side_bits = 4): 4-bit codes of fp16(s1) per 64-token block.  grid (64-token block of the
-// call, kv_head * 2 + tensor, sequence), block 64: a lane owns one token.
+// Stage A1 (side_bits = 4, NSN_VARIANT_ALT): grid (64-token block of the call, kv_head * 2 + tensor, sequence), block 64.
 // ---------------------------------------------------------------------------------------
 __global__ __launch_bounds__(64) void enc_brtn_kernel(Geometry g, int max_new, int max_len,
                                                       const int32_t* __restrict__ seq_start,
@@ -161,20 +202,8 @@ __global__ __launch_bounds__(64) void enc_brtn_kernel(Geometry g, int max_new, i
   const bool valid = t < count && pos < max_len;
   if (blockIdx.x * 64 >= count || start + blockIdx.x * 64 >= max_len) return;  // uniform: lane 0 is valid below
   const float x = valid ? __half2float(ws_b[((int64_t)(b * g.n_kv_heads + h) * 2 + tensor) * max_new + t]) : 0.f;
-  float lo = valid ? x : INFINITY, hi = valid ? x : -INFINITY;
-#pragma unroll
-  for (int m = 1; m < 64; m <<= 1) {
-    lo = fminf(lo, __shfl_xor(lo, m, 64));
-    hi = fmaxf(hi, __shfl_xor(hi, m, 64));
-  }
-  const __half mn16 = f64_to_f16((double)lo);  // exact: the minimum is one of the fp16 inputs
-  const __half st16 = f64_to_f16(((double)hi - (double)lo) / 15.0);
-  const int code = valid ? rtn4_code((double)x, (double)__half2float(mn16), (double)__half2float(st16)) : 0;
-  const int other = __shfl_xor(code, 1, 64);
   const int pos0 = start + blockIdx.x * 64;  // the block's first token (the record is chosen by it)
-  unsigned char* rec = dq_norm_rec(cv, unit_token_base(g, cv.block_table, b, h, pos0), token_in_unit(g, pos0));
-  if ((lane & 1) == 0 && valid) rec[kDqNormCodes + (lane >> 1)] = (unsigned char)(code | (other << 4));
-  if (lane == 0) *reinterpret_cast<__half2*>(rec + kDqNormPar) = __halves2half2(mn16, st16);
+  quantize_s1(x, valid, lane, dq_norm_rec(cv, unit_token_base(g, cv.block_table, b, h, pos0), token_in_unit(g, pos0)));
 }
 
 // ---------------------------------------------------------------------------------------
@@ -222,37 +251,388 @@ __global__ __launch_bounds__(128) void enc_means_kernel(Geometry g, int max_new,
     cv.means[mean_index * kHeadDim + c] = f64_to_f16(mean);
     return;
   }
-  // side_bits = 4: 16 levels per 32 channels (half a wave)
-  double lo = mean, hi = mean;
-#pragma unroll
-  for (int m = 1; m < 32; m <<= 1) {
-    lo = fmin(lo, __shfl_xor(lo, m, 64));
-    hi = fmax(hi, __shfl_xor(hi, m, 64));
-  }
-  const __half mn16 = f64_to_f16(lo), st16 = f64_to_f16((hi - lo) / 15.0);
-  const int code = rtn4_code(mean, (double)__half2float(mn16), (double)__half2float(st16));
-  const int other = __shfl_xor(code, 1, 64);
-  unsigned char* rec = dq_mean_rec(cv, mean_index);
-  if ((c & 1) == 0) rec[c >> 1] = (unsigned char)(code | (other << 4));
-  if ((c & 31) == 0) *reinterpret_cast<__half2*>(rec + kDqMeanPar + 4 * (c >> 5)) = __halves2half2(mn16, st16);
+  quantize_mean(mean, c, dq_mean_rec(cv, mean_index));
 }
 
 // ---------------------------------------------------------------------------------------
-// Stage B: shift, second Normalize, rotation, search, scale adjustment, stores.
+// The encoder.  grid (wg_tokens-token chunk of the call, kv_head * 2 + tensor, sequence), block 256.
+//
+// Bound by vector instructions.  A lane owns CPL channels of a token:
+//   CPL = 16 (large calls): eight lanes per token, eight tokens per wave step.  Everything done once per token (square
+//     roots, reciprocals, lane reductions) is shared by eight tokens, four of the seven butterfly stages stay
+//     inside the lane and two more swap register halves between lanes (one instruction per register).  The rotated
+//     token passes through LDS so that the search is a loop over the lane's sub-vectors (one copy of its code, its
+//     registers free).
+//   CPL = SUB (small calls): as many lanes as there are sub-vectors: the shortest chain of instructions per token.
+// (One sub-vector per lane for all sizes and a best-two search in one pass, the form this replaces, took 1147 vector
+// instructions per two 4-dim tokens.)
+// Lane layout for CPL = 16: bits 0, 4, 5 of the lane select channels 8 (l0 + 2 l4 + 4 l5) .. + 7 and the same plus 64,
+// bits 1..3 the token of the step; after the rotation the lane holds channels 8 (l0 + 2 r + 4 l4 + 8 l5) .. + 7 for register
+// halves r = 0, 1.  Channels i and i + 64, which the rotary embedding pairs, start out in one lane.
+// ---------------------------------------------------------------------------------------
+struct EncArgs {
+  Geometry g;
+  const __half *codebook, *k_in, *v_in;
+  int max_new, max_len;
+  const int32_t *seq_start, *n_new;
+  CacheView kc, vc;
+  int wg_tokens;  // tokens of a workgroup: 128 or 64 .. 8
+  int own_means;  // 1: groups of 64 tokens, their means are formed here
+};
+
+__device__ __forceinline__ double swap_sum16(double v) {  // v + value of lane ^ 16
+  uint2 a = __builtin_bit_cast(uint2, v), b = a;
+  asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\tv_permlane16_swap_b32 %2, %3"
+      : "+v"(a.x), "+v"(b.x), "+v"(a.y), "+v"(b.y));
+  return __builtin_bit_cast(double, a) + __builtin_bit_cast(double, b);
+}
+__device__ __forceinline__ double swap_sum32(double v) {  // v + value of lane ^ 32
+  uint2 a = __builtin_bit_cast(uint2, v), b = a;
+  asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\tv_permlane32_swap_b32 %2, %3"
+      : "+v"(a.x), "+v"(b.x), "+v"(a.y), "+v"(b.y));
+  return __builtin_bit_cast(double, a) + __builtin_bit_cast(double, b);
+}
+// sum over the lanes that share a token
+template <int CPL>
+__device__ __forceinline__ double token_sum(double v) {
+  if constexpr (CPL == 16) {
+    v += xor_lane<1>(v);
+    return swap_sum32(swap_sum16(v));
+  } else {
+    v = xor_sum_w<16>(v);
+    return CPL == 4 ? swap_sum16(v) : v;
+  }
+}
+// Walsh-Hadamard butterflies over the token's 128 channels (unnormalised), in the lane layouts above
+template <int CPL>
+__device__ __forceinline__ void rotate_token(double (&v)[CPL], int lane) {
+  auto inside = [&](int s) {
+#pragma unroll
+    for (int i = 0; i < CPL; ++i) {
+      if ((i & s) == 0) {
+        const double a0 = v[i], a1 = v[i | s];
+        v[i] = a0 + a1;
+        v[i | s] = a0 - a1;
+      }
+    }
+  };
+#pragma unroll
+  for (int s = 1; s < CPL; s <<= 1) inside(s);
+  auto across = [&](auto mc) {
+    constexpr int m = decltype(mc)::value;
+    const double sign = (lane & m) ? -1.0 : 1.0;
+#pragma unroll
+    for (int i = 0; i < CPL; ++i) v[i] = fma(v[i], sign, xor_lane<m>(v[i]));
+  };
+  if constexpr (CPL == 16) {
+    // lane bit 5 (then 4) changes places with register bit 3, whose butterfly is then inside the lane
+    uint2 w[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) w[i] = __builtin_bit_cast(uint2, v[i]);
+#pragma unroll
+    for (int i = 0; i < 8; i += 2)
+      swap32x4(w[i].x, w[i + 8].x, w[i].y, w[i + 8].y, w[i + 1].x, w[i + 9].x, w[i + 1].y, w[i + 9].y);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = __builtin_bit_cast(double, w[i]);
+    inside(8);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) w[i] = __builtin_bit_cast(uint2, v[i]);
+#pragma unroll
+    for (int i = 0; i < 8; i += 2)
+      swap16x4(w[i].x, w[i + 8].x, w[i].y, w[i + 8].y, w[i + 1].x, w[i + 9].x, w[i + 1].y, w[i + 9].y);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = __builtin_bit_cast(double, w[i]);
+    inside(8);
+    across(std::integral_constant<int, 1>{});
+  } else {
+    static_for_pow2<16>(across);
+    if constexpr (CPL == 4) across(std::integral_constant<int, 16>{});
+  }
+}
+
+template <int SUB, int CPL, bool SIGN, bool ROPE>
+__global__ __launch_bounds__(256, 2) void enc_kernel(EncArgs A) {
+  static_assert(CPL == 16 || CPL == SUB, "two lane layouts");
+  static_assert(!SIGN || SUB == 8, "the sign + index format is defined on 8-dim sub-vectors");
+  constexpr int J = kHeadDim / SUB, JB = SIGN ? 2 * J : J;  // sub-vectors, code bytes per token
+  constexpr int NQ = CPL / SUB;                             // sub-vectors per lane
+  constexpr int TPS = 64 * CPL / kHeadDim;                  // tokens per wave step
+  __shared__ SearchTables<SUB> T;
+  __shared__ double2 y_s[CPL == SUB ? 1 : 4][CPL == SUB ? 1 : CPL / 2][64];  // rotated tokens, per wave
+  __shared__ double red[4][kHeadDim], mean_s[kHeadDim];
+  __shared__ __half b_s[64];
+  const Geometry& g = A.g;
+  const int h = blockIdx.y >> 1, tensor = blockIdx.y & 1, b = blockIdx.z;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const CacheView& cv = tensor ? A.vc : A.kc;
+  const __half* in = (tensor ? A.v_in : A.k_in) + (int64_t)(b * g.n_kv_heads + h) * A.max_new * kHeadDim;
+  const int start = A.seq_start[b];
+  const int count = min(min(A.n_new[b], A.max_new), A.max_len - start);  // tokens that have a place in the cache
+  const int t_wg = blockIdx.x * A.wg_tokens, block0 = t_wg & ~63;
+  if (t_wg >= count) return;  // (the whole workgroup)
+  const int64_t mean_row = (int64_t)(b * g.n_kv_heads + h) * g.n_groups_max;
+
+  // ---- the lane's token and channels --------------------------------------------------------------
+  const int tok = CPL == 16 ? (lane >> 1) & 7 : lane / J;
+  const int l0 = lane & 1, l4 = (lane >> 4) & 1, l5 = lane >> 5;
+  const int jj = lane % J;
+  const int ch0 = CPL == 16 ? 8 * (l0 + 2 * l4 + 4 * l5) : jj * SUB;
+  const bool leader = CPL == 16 ? (lane & 0x31) == 0 : jj == 0;
+  const int j_first = CPL == 16 ? (SUB == 4 ? 16 * l5 + 8 * l4 + 2 * l0 : 8 * l5 + 4 * l4 + l0) : jj;
+  constexpr int kRaw = CPL == 4 ? 1 : CPL / 8;  // 16-byte (CPL = 4: 8-byte) pieces of the lane's inputs
+  typedef typename std::conditional<CPL == 4, uint2, uint4>::type raw_t;
+  const int wave_tokens = A.wg_tokens >> 2;
+  const int t_begin = t_wg + wave * wave_tokens, t_end = min(t_begin + wave_tokens, count);
+  raw_t xraw[kRaw];
+  auto fetch = [&](int t) {  // (count >= 1; rows past the end are read from the last valid one)
+    const __half* row = in + (int64_t)min(t, count - 1) * kHeadDim + ch0;
+#pragma unroll
+    for (int k = 0; k < kRaw; ++k) xraw[k] = *reinterpret_cast<const raw_t*>(row + 64 * k);
+  };
+  fetch(t_begin + tok);
+  // pass 1: a wave's sixteen tokens of the 64-token block, four at a time (lane: token lane / 16, channels 8 (lane % 16))
+  const bool pass1 = A.own_means || g.dq;
+  uint4 p1[4];
+  if (pass1) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      p1[u] = *reinterpret_cast<const uint4*>(
+          in + (int64_t)min(block0 + 16 * wave + 4 * u + (lane >> 4), count - 1) * kHeadDim + 8 * (lane & 15));
+  }
+  SearchRegs<SUB, true> R;
+  search_setup<SUB, true>(T, R, tid, [&](int i) { return __half2float(A.codebook[tid * SUB + i]); });
+
+  if (pass1) {
+    double acc[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] = 0.0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int tb = 16 * wave + 4 * u + (lane >> 4);  // token of the block
+      const __half* xh = reinterpret_cast<const __half*>(&p1[u]);
+      double x[8], ss = 0.0;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        x[i] = (double)__half2float(xh[i]);
+        ss = fma(x[i], x[i], ss);
+      }
+      const __half b16 = f64_to_f16(sqrt_f64(xor_sum_w<16>(ss) * (1.0 / kHeadDim)));
+      if ((lane & 15) == 0) b_s[tb] = b16;
+      const double rb = block0 + tb < count ? rcp_f64((double)__half2float(b16)) : 0.0;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[i] = fma(x[i], rb, acc[i]);
+    }
+    if (A.own_means) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[i] = swap_sum32(swap_sum16(acc[i]));
+      if (lane < 16) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) red[wave][8 * lane + i] = acc[i];
+      }
+    }
+    __syncthreads();
+    const bool stores = t_wg == block0;  // one of the block's workgroups writes what belongs to the block
+    if (A.own_means && tid < kHeadDim) {
+      const int64_t mean_index = mean_row + (start + block0) / g.group_size;
+      const double mean = (((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid]) / (double)min(64, count - block0);
+      if (!g.dq) {
+        const __half m16 = f64_to_f16(mean);
+        mean_s[tid] = (double)__half2float(m16);
+        if (stores) cv.means[mean_index * kHeadDim + tid] = m16;
+      } else {
+        mean_s[tid] = quantize_mean(mean, tid, stores ? dq_mean_rec(cv, mean_index) : nullptr);
+      }
+    }
+    if (g.dq && stores && wave == 3) {
+      const int pos0 = start + block0;
+      quantize_s1(__half2float(b_s[lane]), block0 + lane < count, lane,
+                  dq_norm_rec(cv, unit_token_base(g, cv.block_table, b, h, pos0), token_in_unit(g, pos0)));
+    }
+    __syncthreads();
+  }
+
+  // ---- pass 2 -----------------------------------------------------------------------------------
+  double o[CPL];
+  int grp = -1;  // Shift group whose mean is in o
+  if (A.own_means) {
+#pragma unroll
+    for (int i = 0; i < CPL; ++i) o[i] = mean_s[ch0 + (i & 7) + 64 * (i >> 3)];
+  }
+  auto load_mean = [&](int gi) {
+    if (g.dq) {
+      const unsigned char* rec = dq_mean_rec(cv, mean_row + gi);
+#pragma unroll
+      for (int k = 0; k < kRaw; ++k) {
+        const int c = ch0 + 64 * k;
+        const uint32_t codes = CPL == 4 ? *reinterpret_cast<const uint16_t*>(rec + (c >> 1))
+                                        : *reinterpret_cast<const uint32_t*>(rec + (c >> 1));
+        const __half2 par = *reinterpret_cast<const __half2*>(rec + kDqMeanPar + 4 * (c >> 5));
+        const double mn = (double)__low2float(par), st = (double)__high2float(par);
+#pragma unroll
+        for (int i = 0; i < (CPL == 4 ? 4 : 8); ++i) o[8 * k + i] = mn + st * (double)((codes >> (4 * i)) & 15u);
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < kRaw; ++k) {
+        const raw_t m = *reinterpret_cast<const raw_t*>(cv.means + (mean_row + gi) * kHeadDim + ch0 + 64 * k);
+        const __half* mh = reinterpret_cast<const __half*>(&m);
+#pragma unroll
+        for (int i = 0; i < (CPL == 4 ? 4 : 8); ++i) o[8 * k + i] = (double)__half2float(mh[i]);
+      }
+    }
+  };
+  const double cscale = -0.5 / (double)R.scale;  // codeword element = table entry * cscale (exact: powers of two)
+  // the lane's further codes lie at fixed distances from its first one (both layouts are linear in the bits of j)
+  const int64_t dq1 = NQ > 1 ? code_offset(g.tiled, tensor != 0, JB, 0, NQ == 4 ? 1 : 2) : 0;
+  const int64_t dq2 = NQ > 2 ? code_offset(g.tiled, tensor != 0, JB, 0, 4) : 0;
+  const int64_t dsign = SIGN ? code_offset(g.tiled, tensor != 0, JB, 0, J) : 0;
+
+  for (int t0 = t_begin; t0 < t_end; t0 += TPS) {  // (uniform over the wave)
+    const int t = t0 + tok, pos = start + t;
+    const bool valid = t < t_end;
+    double v[CPL];
+#pragma unroll
+    for (int k = 0; k < kRaw; ++k) {
+      const __half* xh = reinterpret_cast<const __half*>(&xraw[k]);
+#pragma unroll
+      for (int i = 0; i < (CPL == 4 ? 4 : 8); ++i) v[8 * k + i] = (double)__half2float(xh[i]);
+    }
+    if (t0 + TPS < t_end) fetch(t + TPS);
+    if (!A.own_means) {
+      const int want = min(group_of(g, min(pos, A.max_len - 1)), g.n_groups_max - 1);
+      if (__any(want != grp)) {
+        load_mean(want);
+        grp = want;
+      }
+    }
+    __half b16;
+    if (pass1) {
+      b16 = b_s[min(t - block0, 63)];
+    } else {
+      double ss = 0.0;
+#pragma unroll
+      for (int i = 0; i < CPL; ++i) ss = fma(v[i], v[i], ss);
+      b16 = f64_to_f16(sqrt_f64(token_sum<CPL>(ss) * (1.0 / kHeadDim)));
+    }
+    const double bb = (double)__half2float(b16), rb = rcp_f64(bb);
+    double ss = 0.0;
+#pragma unroll
+    for (int i = 0; i < CPL; ++i) {
+      v[i] = fma(v[i], rb, -o[i]);
+      ss = fma(v[i], v[i], ss);
+    }
+    ss = token_sum<CPL>(ss);
+    // second Normalize and the 1 / sqrt(d) of the rotation in one factor: v / s2 / sqrt(d) = v / ||v||
+    const double rs = rsqrt_f64(ss), s2 = ss * rs * kInvSqrtD;
+#pragma unroll
+    for (int i = 0; i < CPL; ++i) v[i] *= rs;
+    if constexpr (ROPE) {
+      if (tensor == 0) {  // keys only: channels c and c + 64 turn by position * inv_freq[c]
+        // cos / sin from the fp64 table: block part and in-block part combined by the addition theorems
+        const int pc = min(pos, A.max_len - 1), pair0 = ch0 & 63;
+        const double2* blk = reinterpret_cast<const double2*>(g.rope + kRopeBlkOff + (int64_t)(pc >> 6) * kRopeBlkStride +
+                                                              kRopeBlk64) + pair0;
+        const double2* inb = reinterpret_cast<const double2*>(g.rope + kRopeInOff) + (pc & 63) * 64 + pair0;
+        constexpr int NP = CPL == 4 ? 4 : 8;  // channel pairs of a lane
+        const double side = (ch0 & 64) ? 1.0 : -1.0;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+          const double2 c0 = blk[i], cj = inb[i];
+          const double c = c0.x * cj.x - c0.y * cj.y, sn = c0.y * cj.x + c0.x * cj.y;
+          if constexpr (CPL == 16) {
+            const double x0 = v[i], x1 = v[i + 8];
+            v[i] = x0 * c - x1 * sn;
+            v[i + 8] = x1 * c + x0 * sn;
+          } else {  // the partner channel lives in lane ^ (J / 2)
+            const double other = xor_lane<J / 2>(v[i]);
+            v[i] = v[i] * c + side * other * sn;
+          }
+        }
+      }
+    }
+    rotate_token<CPL>(v, lane);
+    if constexpr (NQ > 1) {
+#pragma unroll
+      for (int k = 0; k < CPL / 2; ++k) y_s[wave][k][lane] = make_double2(v[2 * k], v[2 * k + 1]);
+    }
+    const int64_t base = unit_token_base(g, cv.block_table, b, h, valid ? pos : start);
+    const int tin = token_in_unit(g, pos);
+    uint8_t* out = cv.codes + base * JB + code_offset(g.tiled, tensor != 0, JB, tin, j_first);
+    double dot = 0.0;  // |y| . C[code] (y . C[code] without signs) in table units
+#pragma unroll 1
+    for (int q = 0; q < NQ; ++q) {
+      double y[SUB];
+      if constexpr (NQ > 1) {  // (this lane's own entries)
+#pragma unroll
+        for (int k = 0; k < SUB / 2; ++k) {
+          const double2 p = y_s[wave][q * (SUB / 2) + k][lane];
+          y[2 * k] = p.x, y[2 * k + 1] = p.y;
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < SUB; ++i) y[i] = v[i];
+      }
+      // sign + index format: the nearest signed codeword has the signs of y and the magnitude codeword nearest to |y|
+      // (the magnitudes are non-negative), and y . y_Q = |y| . C[code]
+      uint32_t sign_byte = 0u;
+      if constexpr (SIGN) {
+#pragma unroll
+        for (int i = 0; i < SUB; ++i) {
+          if (y[i] < 0.0) sign_byte |= 1u << i;
+          y[i] = fabs(y[i]);
+        }
+      }
+      float yf[SUB];
+#pragma unroll
+      for (int i = 0; i < SUB; ++i) yf[i] = (float)y[i];
+      const Nearest best = search_nearest<SUB, true, true>(T, R, yf, [&](int c) {
+        double d = 0.0;
+#pragma unroll
+        for (int u = 0; u < SUB / 4; ++u) {
+          const float4 e = T.n2c[u][codeword_group(c) * SearchTables<SUB>::kRowStride + codeword_row(c)];
+          const float ev[4] = {e.x, e.y, e.z, e.w};
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const double dd = y[4 * u + i] - (double)ev[i] * cscale;
+            d = __dadd_rn(d, __dmul_rn(dd, dd));  // plain sum of squares
+          }
+        }
+        return d;
+      });
+#pragma unroll
+      for (int u = 0; u < SUB / 4; ++u) {
+        const float4 e = T.n2c[u][best.at];
+        dot = fma(y[4 * u], (double)e.x, dot), dot = fma(y[4 * u + 1], (double)e.y, dot);
+        dot = fma(y[4 * u + 2], (double)e.z, dot), dot = fma(y[4 * u + 3], (double)e.w, dot);
+      }
+      if (valid) {
+        const int64_t at = NQ == 4 ? (q & 1) * dq1 + (q >> 1) * dq2 : q * dq1;
+        out[at] = (uint8_t)best.code;
+        if constexpr (SIGN) out[at + dsign] = (uint8_t)sign_byte;
+      }
+    }
+    // scale adjustment: alpha = ||y||^2 / (y . y_Q), ||y||^2 = d
+    dot = token_sum<CPL>(dot) * cscale;
+    const double alpha = dot > 1e-12 * kHeadDim ? (double)kHeadDim * rcp_f64(dot) : 1.0;
+    if (valid && leader) {
+      if (g.dq)  // a' = fp16(s2 alpha); s1 is stored as a 4-bit code
+        reinterpret_cast<__half*>(dq_norm_rec(cv, base, tin))[tin & 63] = f64_to_f16(s2 * alpha);
+      else
+        cv.norms[base + tin] = __halves2half2(f64_to_f16(bb * s2 * alpha), b16);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------
+// NSN_VARIANT_ALT, last stage: shift, second Normalize, rotation, fp32 scan of the 256 distances, scale adjustment, stores.
 // grid (64- or 16-token chunk, kv_head * 2 + tensor, sequence), block 256.  A lane owns one
 // sub-vector (SUB channels) of one token; a wave covers 64 / J tokens at a time.
 // ---------------------------------------------------------------------------------------
-// MFMA:  distance contraction on the matrix cores (else the fp32 vector-ALU scan)
 // FUSED: append mode - the first-Normalize scale is computed here instead of by the stats kernel
-// The register budget is pinned to the main path's needs (4 waves per SIMD at sub-vector length 4,
-// 3 at length 8): without it the rarely taken re-listing path is scheduled for maximum
-// instruction-level parallelism and doubles the register count of the whole kernel.
 // SIGN:  the paper's 2-bit format (Sec. 3.4): the search runs on the absolute values against a
 //        codebook of magnitudes; byte row jj holds the index, byte row 16 + jj the eight sign bits
-// ROPE:  the K rows are keys before the rotary embedding (Sec. 3.2 "NSN applied to key and value"):
-//        v_nsn is turned by the token's position between the second Normalize and the Hadamard rotation
-template <int SUB, bool MFMA, bool FUSED, bool SIGN = false, bool ROPE = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SUB == 4 ? 4 : 3))) void enc_quant_kernel(Geometry g, const __half* __restrict__ codebook,
+template <int SUB, bool FUSED, bool SIGN = false>
+__global__ __launch_bounds__(256) void enc_quant_kernel(Geometry g, const __half* __restrict__ codebook,
                                                         const __half* __restrict__ k_in,
                                                         const __half* __restrict__ v_in, int max_new,
                                                         int max_len, const int32_t* __restrict__ seq_start,
@@ -323,8 +703,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SUB == 4 ? 
   Tok nxt = fetch(0);
 
   vq_tables_fill<SUB>(T, [&](int c, int i) { return (double)__half2float(codebook[c * SUB + i]); });
-  MfmaCodebook<SUB> MC;
-  if constexpr (MFMA) mfma_codebook_load<SUB>(MC, T, lane);
   if (blockIdx.x * (4 * wave_tokens) >= count) return;
 
   const int n_it = wave_tokens / TPW;
@@ -376,25 +754,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SUB == 4 ? 
     const double r2 = (s2 != 0.0) ? 1.0 / s2 : 0.0;
 #pragma unroll
     for (int i = 0; i < SUB; ++i) v[i] *= r2;
-    if constexpr (ROPE) {
-      if (tensor == 0) {  // keys only; the partner channel c ^ 64 lives in lane jj ^ (J / 2)
-        // cos / sin of position * inv_freq[pair] from the fp64 table: block part and in-block part
-        // combined by the addition theorems
-        const int pc = min(max(cur.pos, 0), max_len - 1);  // lanes without a token hold zeros; keep them in bounds
-        const int pair0 = (jj % (J / 2)) * SUB;
-        const double2* blk = reinterpret_cast<const double2*>(g.rope + kRopeBlkOff +
-                                                              (int64_t)(pc >> 6) * kRopeBlkStride + kRopeBlk64) + pair0;
-        const double2* inb = reinterpret_cast<const double2*>(g.rope + kRopeInOff) + (pc & 63) * 64 + pair0;
-        const bool upper = jj >= J / 2;
-#pragma unroll
-        for (int i = 0; i < SUB; ++i) {
-          const double other = xor_lane<J / 2>(v[i]);
-          const double2 c0 = blk[i], cj = inb[i];
-          const double c = c0.x * cj.x - c0.y * cj.y, sn = c0.y * cj.x + c0.x * cj.y;
-          v[i] = upper ? v[i] * c + other * sn : v[i] * c - other * sn;
-        }
-      }
-    }
     // Walsh-Hadamard butterflies: channel bits 0..log2(SUB)-1 in registers, the rest across lanes
 #pragma unroll
     for (int s = 1; s < SUB; s <<= 1) {
@@ -429,11 +788,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SUB == 4 ? 
       ys[i] = SIGN ? fabs(y[i]) : y[i];
       if (SIGN && y[i] < 0.0) sign_byte |= 1u << i;
     }
-    int code;
-    if constexpr (MFMA)
-      code = vq_search_mfma<SUB>(T, MC, ys, lane);
-    else
-      code = vq_search<SUB>(T, ys);
+    const int code = vq_search<SUB>(T, ys);
 
     // scale adjustment: alpha = ||y||^2 / (y . y_Q)
     double dot = 0.0, nrm2 = 0.0;
@@ -474,7 +829,7 @@ static size_t encode_partial_bytes(const nsn_shape& s, int batch, int64_t max_ne
 }
 
 size_t encode_workspace_bytes(const nsn_shape& s, int batch, int64_t max_new) {
-  // side_bits = 4: fp16(s1) of every new token passes through the workspace
+  // side_bits = 4 (NSN_VARIANT_ALT): fp16(s1) of every new token passes through the workspace
   const size_t b_bytes = s.side_bits == 4 ? (((size_t)batch * s.n_kv_heads * 2 * max_new * sizeof(__half)) + 255) & ~(size_t)255 : 0;
   return encode_partial_bytes(s, batch, max_new) + b_bytes;
 }
@@ -488,54 +843,72 @@ int encode_launch(const nsn_shape& s, const void* codebook, const void* k_in, co
   const int n_chunks = (max_new + ct - 1) / ct;
   double* partial = static_cast<double*>(workspace);
   __half* ws_b = reinterpret_cast<__half*>(static_cast<unsigned char*>(workspace) + encode_partial_bytes(s, batch, max_new));
-  const bool use_mfma = selected_variant(NSN_OP_ENCODE) != NSN_VARIANT_ALT;  // the alternative is the vector-ALU scan
-  if (!freeze_means || g.dq) {  // side_bits = 4: the s1 codes of a block need all its tokens first
+  // the alternative is the vector-ALU scan (keys before the rotary embedding have the default form only)
+  const bool alt = selected_variant(NSN_OP_ENCODE) == NSN_VARIANT_ALT && !g.rope;
+  const bool own_means = !alt && !freeze_means && s.group_size == 64;
+  if ((!freeze_means && !own_means) || (alt && g.dq)) {
     const dim3 grid_a(n_chunks, s.n_kv_heads * 2, batch);
     enc_stats_kernel<<<grid_a, 256, 0, stream>>>(g, (const __half*)k_in, (const __half*)v_in, max_new, s.max_len,
-                                                 seq_start, n_new, kv, vv, partial, ct, n_chunks, ws_b);
-    if (g.dq) {
+                                                 seq_start, n_new, kv, vv, partial, ct, n_chunks, ws_b, alt);
+    if (alt && g.dq) {
       const dim3 grid_r((max_new + 63) / 64, s.n_kv_heads * 2, batch);
       enc_brtn_kernel<<<grid_r, 64, 0, stream>>>(g, max_new, s.max_len, seq_start, n_new, kv, vv, ws_b);
     }
   }
-  if (!freeze_means) {
+  if (!freeze_means && !own_means) {
     const int n_groups_new = s.group_size > 0 ? n_chunks : 1;
     const dim3 grid_m(n_groups_new, s.n_kv_heads * 2, batch);
     enc_means_kernel<<<grid_m, 128, 0, stream>>>(g, max_new, s.max_len, seq_start, n_new, kv, vv, partial, ct,
                                                  n_chunks);
   }
-  const bool fused = freeze_means && !g.dq;  // the quantiser computes s1 itself (append mode)
-  // 64 tokens per workgroup; calls that would leave most compute units idle use 16 (4 per wave)
-  const int64_t blocks64 = (int64_t)((max_new + 63) / 64) * s.n_kv_heads * 2 * batch;
-  const int wave_tokens = blocks64 >= 1024 ? 16 : 4;
-  const dim3 grid_b((max_new + 4 * wave_tokens - 1) / (4 * wave_tokens), s.n_kv_heads * 2, batch);
-  auto launch = [&](auto kernel) {
-    kernel<<<grid_b, 256, 0, stream>>>(g, (const __half*)codebook, (const __half*)k_in, (const __half*)v_in, max_new,
-                                       s.max_len, seq_start, n_new, kv, vv, wave_tokens, ws_b);
-  };
-  if (g.rope) {  // keys before the rotary embedding: matrix-core search only
+  const int64_t tokens = (int64_t)max_new * s.n_kv_heads * 2 * batch;
+  if (alt) {
+    // 64 tokens per workgroup; calls that would leave most compute units idle use 16 (4 per wave)
+    const int wave_tokens = tokens >= 65536 ? 16 : 4;
+    const dim3 grid_b((max_new + 4 * wave_tokens - 1) / (4 * wave_tokens), s.n_kv_heads * 2, batch);
+    auto launch = [&](auto kernel) {
+      kernel<<<grid_b, 256, 0, stream>>>(g, (const __half*)codebook, (const __half*)k_in, (const __half*)v_in, max_new,
+                                         s.max_len, seq_start, n_new, kv, vv, wave_tokens, ws_b);
+    };
+    const bool fused = freeze_means && !g.dq;  // the quantiser computes s1 itself
     if (g.sign)
-      fused ? launch(enc_quant_kernel<8, true, true, true, true>) : launch(enc_quant_kernel<8, true, false, true, true>);
+      fused ? launch(enc_quant_kernel<8, true, true>) : launch(enc_quant_kernel<8, false, true>);
     else if (s.sub_dim == 8)
-      fused ? launch(enc_quant_kernel<8, true, true, false, true>) : launch(enc_quant_kernel<8, true, false, false, true>);
+      fused ? launch(enc_quant_kernel<8, true>) : launch(enc_quant_kernel<8, false>);
     else
-      fused ? launch(enc_quant_kernel<4, true, true, false, true>) : launch(enc_quant_kernel<4, true, false, false, true>);
-  } else if (g.sign) {
-    if (use_mfma)
-      fused ? launch(enc_quant_kernel<8, true, true, true>) : launch(enc_quant_kernel<8, true, false, true>);
-    else
-      fused ? launch(enc_quant_kernel<8, false, true, true>) : launch(enc_quant_kernel<8, false, false, true>);
-  } else if (s.sub_dim == 8) {
-    if (use_mfma)
-      fused ? launch(enc_quant_kernel<8, true, true>) : launch(enc_quant_kernel<8, true, false>);
-    else
-      fused ? launch(enc_quant_kernel<8, false, true>) : launch(enc_quant_kernel<8, false, false>);
-  } else {
-    if (use_mfma)
-      fused ? launch(enc_quant_kernel<4, true, true>) : launch(enc_quant_kernel<4, true, false>);
-    else
-      fused ? launch(enc_quant_kernel<4, false, true>) : launch(enc_quant_kernel<4, false, false>);
+      fused ? launch(enc_quant_kernel<4, true>) : launch(enc_quant_kernel<4, false>);
+    return hipGetLastError() == hipSuccess ? NSN_OK : NSN_ERR_HIP;
   }
+  // The sixteen-channel layout does the least work per token but takes at least eight tokens through one wave; below the
+  // line its waves are too few to fill the chip (8192 tokens: one wave per SIMD).  Measured, small / bulk layout:
+  // 4-dim 8192 tokens 13.5 / 11.2 us, 32768 tokens 41 / 25 us; 8-dim 8192 tokens 9.3 / 10.9 us, 32768 tokens 27 / 21 us.
+  const bool bulk = tokens >= (s.sub_dim == 4 ? 8192 : 16384);
+  EncArgs a = {g, (const __half*)codebook, (const __half*)k_in, (const __half*)v_in, max_new, s.max_len, seq_start, n_new,
+               kv, vv, 64, own_means};
+  // tokens per workgroup: one step per wave where that is what fills the chip, several where the workgroup's set-up
+  // (tables, operands: about a sixth of a step) is worth sharing; a 64-token block is the most that pass 1 holds
+  if (!bulk)
+    a.wg_tokens = s.sub_dim == 4 ? 8 : 16;
+  else if (tokens < 32768)
+    a.wg_tokens = 32;
+  else if (tokens >= 524288 && !own_means && !g.dq)
+    a.wg_tokens = 128;
+  const dim3 grid((max_new + a.wg_tokens - 1) / a.wg_tokens, s.n_kv_heads * 2, batch);
+  auto launch = [&](auto kernel) { kernel<<<grid, 256, 0, stream>>>(a); };
+  auto pick = [&](auto sub, auto sign, auto rope) {
+    constexpr int kSub = decltype(sub)::value;
+    constexpr bool kSign = decltype(sign)::value, kRope = decltype(rope)::value;
+    bulk ? launch(enc_kernel<kSub, 16, kSign, kRope>) : launch(enc_kernel<kSub, kSub, kSign, kRope>);
+  };
+  auto with_format = [&](auto rope) {
+    if (g.sign)
+      pick(std::integral_constant<int, 8>{}, std::true_type{}, rope);
+    else if (s.sub_dim == 8)
+      pick(std::integral_constant<int, 8>{}, std::false_type{}, rope);
+    else
+      pick(std::integral_constant<int, 4>{}, std::false_type{}, rope);
+  };
+  g.rope ? with_format(std::true_type{}) : with_format(std::false_type{});
   return hipGetLastError() == hipSuccess ? NSN_OK : NSN_ERR_HIP;
 }
 

@@ -2,9 +2,9 @@
 //
 // Three steps, bound by vector instructions (about 280 per 64 searches of 256 4-dim codewords; keeping the best two
 // indexed keys of every distance, the form this one replaced, took about 740):
-//   1. matrix cores: D = ||c||^2 - 2 c . y for 32 codewords (rows) x 32 sub-vectors (columns) at a time.  y, c and
-//      ||c||^2 enter as sums of fp16 parts, so D is good to about 2^-19 of |c|^2 + 2 |c| |y|.  A lane
-//      then holds 16 distances of one sub-vector per tile and keeps only the minima of the two groups of eight: half
+//   1. matrix cores: D = ||c||^2 - 2 c . y + n for 32 codewords (rows) x 32 sub-vectors (columns) at a time, n slightly
+//      above ||y||^2 (D > 0).  y, c and ||c||^2 enter as sums of fp16 parts, so D is good to about 2^-19 of
+//      (|c| + |y|)^2.  A lane then holds 16 distances of one sub-vector per tile and keeps only the minima of the two groups of eight: half
 //      an instruction per distance (three-operand minima), no index bookkeeping.  32 groups of 8 codewords leave 32
 //      minima per sub-vector, brought to the lane that owns it by half-wave swaps.
 //   2. every group whose minimum lies within twice the error bound of the smallest is listed (almost always one).
@@ -35,9 +35,6 @@ typedef float f16v __attribute__((ext_vector_type(16)));
 __device__ __forceinline__ void swap32(uint32_t& a, uint32_t& b) {
   asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
 }
-__device__ __forceinline__ void swap32(float& a, float& b) {
-  asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
-}
 // four pairs at a time: one wait for all of them
 #define NSN_SWAP4(NAME, INSN)                                                                                     \
   template <typename T>                                                                                           \
@@ -50,24 +47,13 @@ NSN_SWAP4(swap32x4, "v_permlane32_swap_b32")
 NSN_SWAP4(swap16x4, "v_permlane16_swap_b32")
 #undef NSN_SWAP4
 
-// The plain instruction: fminf() would add an operand canonicalisation per operand (no NaN can decide anything here:
-// a sub-vector without exactly one candidate goes through the fp64 path).
-__device__ __forceinline__ float min3f(float a, float b, float c) {
-  float r;
-  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
-// Minima of results 0..7 and 8..15 of a matrix instruction.  The first step is an instruction the compiler knows, so
-// that it waits for the matrix pipe; every other one takes its result as an operand and so comes after it.  `ninf` is
-// -inf in a register the compiler cannot look into (it would turn the median into a canonicalising minimum).
-__device__ __forceinline__ void min8x2(const f16v& d, float ninf, float& lo8, float& hi8) {
-  const float x = __builtin_amdgcn_fmed3f(d[0], d[1], ninf);
-  float q;
-  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(q) : "v"(d[8]), "v"(d[9]), "v"(d[10]), "v"(x));
-  float p = min3f(x, d[2], d[3]);
-  p = min3f(p, d[4], d[5]), q = min3f(q, d[11], d[12]);
-  lo8 = min3f(p, d[6], d[7]), q = min3f(q, d[13], d[14]);
-  asm("v_min_f32 %0, %1, %2" : "=v"(hi8) : "v"(q), "v"(d[15]));
+// Minima of results 0..7 and 8..15 of a matrix instruction.  All results are positive, so their bit patterns order like
+// integers: integer minima come without the operand canonicalisation that float minima have.
+__device__ __forceinline__ void min8x2(const f16v& d, uint32_t& lo8, uint32_t& hi8) {
+  auto u = [&](int i) { return __float_as_uint(d[i]); };
+  auto min3 = [](uint32_t a, uint32_t b, uint32_t c) { return min(min(a, b), c); };
+  lo8 = min(min3(min3(min3(u(0), u(1), u(2)), u(3), u(4)), u(5), u(6)), u(7));
+  hi8 = min(min3(min3(min3(u(8), u(9), u(10)), u(11), u(12)), u(13), u(14)), u(15));
 }
 
 // group g, row r of it <-> codeword: a lane of half hf holds rows 8 (k / 4) + 4 hf + k % 4, k = 0..15, of 32 x 32 tile m;
@@ -101,7 +87,6 @@ struct SearchRegs {
   h4v A2[SUB == 8 && EXACT16 ? 8 : 1];
   float cm;     // largest norm of a scaled codeword
   float scale;  // s
-  float ninf;   // see min8x2
 };
 
 // Fills the tables and the operands of every wave of the workgroup (256 threads or more, all of them call it).
@@ -132,8 +117,6 @@ __device__ inline void search_setup(SearchTables<SUB>& T, SearchRegs<SUB, EXACT1
   const float s = ldexpf(1.f, ex);
   R.scale = s;
   R.cm = nm * s * 1.0001f;
-  R.ninf = -INFINITY;
-  asm("" : "+v"(R.ninf));
   if (tid < kCodes) {
     float cn = 0.f, f[SUB];
     h8 a0 = {}, a1 = {}, a2 = {};
@@ -156,19 +139,19 @@ __device__ inline void search_setup(SearchTables<SUB>& T, SearchRegs<SUB, EXACT1
       p[k] = (_Float16)rest;
       rest -= (float)p[k];
     }
-    if constexpr (SUB == 4) {  // k: -2c_hi (y_hi), -2c_hi (y_lo) | -2c_lo (y_hi), ||c||^2 in three parts, 0
+    if constexpr (SUB == 4) {  // k: -2c_hi (y_hi), -2c_hi (y_lo) | -2c_lo (y_hi), ||c||^2 in three parts, 1 (n)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         a0[i] = a0[4 + i] = hi[i];
         a1[i] = lo[i];
-        a1[4 + i] = i < 3 ? p[i < 3 ? i : 0] : (_Float16)0.f;
+        a1[4 + i] = i < 3 ? p[i < 3 ? i : 0] : (_Float16)1.f;
       }
       T.image[0][tid] = a0, T.image[1][tid] = a1;
-    } else {  // -2c_hi (y_hi) | -2c_hi (y_lo); second operand: -2c_lo (y_hi) | parts of ||c||^2
+    } else {  // -2c_hi (y_hi) | -2c_hi (y_lo); second operand: -2c_lo (y_hi) | parts of ||c||^2, 1 (n)
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         a0[i] = hi[i], a1[i] = lo[i];
-        a2[i] = i < 3 ? p[i < 3 ? i : 0] : (_Float16)0.f;
+        a2[i] = i < 3 ? p[i < 3 ? i : 0] : (_Float16)(i == 3 ? 1.f : 0.f);
       }
       T.image[0][tid] = a0, T.image[1][tid] = a1, T.image[2][tid] = a2;
     }
@@ -202,10 +185,16 @@ __device__ __forceinline__ h8 words_h8(uint32_t a, uint32_t b, uint32_t c, uint3
   return __builtin_bit_cast(h8, u4v{a, b, c, d});
 }
 
-// Index of the codeword nearest to y (this lane's sub-vector); all 64 lanes take part.  exact(c): fp64 squared
+struct Nearest {
+  int code;  // the codeword
+  int at;    // its place in SearchTables::n2c[.]
+};
+
+// The codeword nearest to y (this lane's sub-vector); all 64 lanes take part.  exact(c): fp64 squared
 // distance of the lane's sub-vector to codeword c.
-template <int SUB, bool EXACT16, typename F>
-__device__ __forceinline__ int search_nearest(const SearchTables<SUB>& T, const SearchRegs<SUB, EXACT16>& R,
+// AHEAD: a tile's products are requested a whole tile before its minima are taken (32 more registers).
+template <int SUB, bool EXACT16, bool AHEAD, typename F>
+__device__ __forceinline__ Nearest search_nearest(const SearchTables<SUB>& T, const SearchRegs<SUB, EXACT16>& R,
                                               const float (&y_in)[SUB], F exact) {
   constexpr int NP = SUB / 2;
   float y[SUB], yn = 0.f;
@@ -222,73 +211,96 @@ __device__ __forceinline__ int search_nearest(const SearchTables<SUB>& T, const 
     lo[i] = pack_f16(y[2 * i] - (float)h[0], y[2 * i + 1] - (float)h[1]);
   }
   const bool lower = (threadIdx.x & 32) == 0;
-  constexpr uint32_t ONE1 = 0x3C003C00u, ONE0 = 0x00003C00u;  // (1, 1) and (1, 0)
+  // n: an fp16 value above ||y||^2 by more than any error of D (the same for all codewords: it decides nothing)
+  const float n = fmaf(yn, 1.0f + 0x1p-8f, 0x1p-5f);
+  constexpr uint32_t ONE1 = 0x3C003C00u;  // (1, 1)
+  uint32_t one_n = pack_f16(1.f, n);
+  // (by the instruction's own rounding: the value subtracted below is the one that was added)
+  const float n16 = (float)__builtin_bit_cast(h2v, one_n)[1];
   // operands of the two column sets: a = the sub-vectors of lanes 0..31, b = those of lanes 32..63
-  h8 ba, bb, ba2, bb2;
-  h4v ones4;
+  h8 ba, bb, ba2 = {}, bb2 = {};
+  h4v na = {}, nb = {};
   if constexpr (SUB == 4) {
-    uint32_t k0 = hi[0], k1 = hi[1], k2 = ONE1, k3 = ONE0;
-    swap32x4(hi[0], k0, hi[1], k1, lo[0], k2, lo[1], k3);
+    uint32_t k0 = hi[0], k1 = hi[1], k2 = ONE1;
+    swap32x4(hi[0], k0, hi[1], k1, lo[0], k2, lo[1], one_n);
     ba = words_h8(hi[0], hi[1], lo[0], lo[1]);
-    bb = words_h8(k0, k1, k2, k3);
+    bb = words_h8(k0, k1, k2, one_n);
   } else {
     swap32x4(hi[0], lo[0], hi[1], lo[1], hi[2], lo[2], hi[3], lo[3]);
     ba = words_h8(hi[0], hi[1], hi[2], hi[3]);
     bb = words_h8(lo[0], lo[1], lo[2], lo[3]);
+    uint32_t one_nb = one_n;
+    swap32(one_n, one_nb);  // n of the set's column in either half of the wave
     if constexpr (EXACT16) {
-      ones4 = h4v{(_Float16)1.f, (_Float16)1.f, (_Float16)1.f, (_Float16)0.f};
+      typedef uint32_t u2v __attribute__((ext_vector_type(2)));
+      na = __builtin_bit_cast(h4v, u2v{ONE1, one_n}), nb = __builtin_bit_cast(h4v, u2v{ONE1, one_nb});
     } else {
-      ba2 = words_h8(lower ? hi[0] : ONE1, lower ? hi[1] : ONE0, lower ? hi[2] : 0u, lower ? hi[3] : 0u);
-      bb2 = words_h8(lower ? lo[0] : ONE1, lower ? lo[1] : ONE0, lower ? lo[2] : 0u, lower ? lo[3] : 0u);
+      ba2 = words_h8(lower ? hi[0] : ONE1, lower ? hi[1] : one_n, lower ? hi[2] : 0u, lower ? hi[3] : 0u);
+      bb2 = words_h8(lower ? lo[0] : ONE1, lower ? lo[1] : one_nb, lower ? lo[2] : 0u, lower ? lo[3] : 0u);
     }
   }
-  float a0[8], a1[8], b0[8], b1[8];  // minima of the two groups of tile m held by this lane, sets a and b
+  uint32_t a0[8], a1[8], b0[8], b1[8];  // minima of the two groups of tile m held by this lane, sets a and b
   int second = 256 * (1 + (int)((threadIdx.x >> 5) & 1)) + (int)(threadIdx.x & 31);
   asm volatile("" : "+v"(second));  // (keeps the reads of the second operand inside the search)
   const f16v zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  auto tile = [&](int m, const h8& y1, const h8& y2, const h4v& nn) -> f16v {
+    f16v d = zero;
+    if constexpr (SUB == 8 && EXACT16)
+      d = __builtin_amdgcn_mfma_f32_32x32x8f16(R.A2[m], nn, d, 0, 0, 0);
+    else if constexpr (SUB == 8)
+      d = __builtin_amdgcn_mfma_f32_32x32x16_f16((&T.image[0][0])[second + 32 * m], y2, d, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(R.A[m], y1, d, 0, 0, 0);
+  };
+  // A result takes eleven issue slots, the minima of one set eight: left to itself the compiler puts them next to
+  // each other and waits.
+  if constexpr (AHEAD) {
+    f16v da = tile(0, ba, ba2, na), db = tile(0, bb, bb2, nb);
 #pragma unroll
-  for (int m = 0; m < 8; ++m) {
-    f16v da, db;
-    if constexpr (SUB == 4) {
-      da = __builtin_amdgcn_mfma_f32_32x32x16_f16(R.A[m], ba, zero, 0, 0, 0);
-      db = __builtin_amdgcn_mfma_f32_32x32x16_f16(R.A[m], bb, zero, 0, 0, 0);
-    } else if constexpr (EXACT16) {  // ||c||^2 is the same for every column: once for both sets
-      const f16v d0 = __builtin_amdgcn_mfma_f32_32x32x8f16(R.A2[m], ones4, zero, 0, 0, 0);
-      da = __builtin_amdgcn_mfma_f32_32x32x16_f16(R.A[m], ba, d0, 0, 0, 0);
-      db = __builtin_amdgcn_mfma_f32_32x32x16_f16(R.A[m], bb, d0, 0, 0, 0);
-    } else {
-      const h8 a2 = (&T.image[0][0])[second + 32 * m];
-      da = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, ba2, zero, 0, 0, 0);
-      db = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, bb2, zero, 0, 0, 0);
-      da = __builtin_amdgcn_mfma_f32_32x32x16_f16(R.A[m], ba, da, 0, 0, 0);
-      db = __builtin_amdgcn_mfma_f32_32x32x16_f16(R.A[m], bb, db, 0, 0, 0);
+    for (int m = 0; m < 8; ++m) {
+      f16v da_next, db_next;
+      __builtin_amdgcn_sched_barrier(0);
+      if (m < 7) da_next = tile(m + 1, ba, ba2, na);
+      __builtin_amdgcn_sched_barrier(0);
+      min8x2(da, a0[m], a1[m]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (m < 7) db_next = tile(m + 1, bb, bb2, nb);
+      __builtin_amdgcn_sched_barrier(0);
+      min8x2(db, b0[m], b1[m]);
+      if (m < 7) da = da_next, db = db_next;
     }
-    min8x2(da, R.ninf, a0[m], a1[m]);
-    min8x2(db, R.ninf, b0[m], b1[m]);
+    __builtin_amdgcn_sched_barrier(0);
+  } else {
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      min8x2(tile(m, ba, ba2, na), a0[m], a1[m]);
+      min8x2(tile(m, bb, bb2, nb), b0[m], b1[m]);
+    }
   }
   // own sub-vector: a0, a1, b0, b1 [m] become the minima of groups 4m, 4m + 1, 4m + 2, 4m + 3
 #pragma unroll
   for (int m = 0; m < 8; m += 2) swap32x4(a0[m], b0[m], a1[m], b1[m], a0[m + 1], b0[m + 1], a1[m + 1], b1[m + 1]);
-  float best = min3f(a0[0], a1[0], b0[0]), best2 = min3f(b1[0], a0[1], a1[1]);
-  best = min3f(best, b0[1], b1[1]);
+  uint32_t best_u = min(min(a0[0], a1[0]), b0[0]), best2 = min(min(b1[0], a0[1]), a1[1]);
+  best_u = min(min(best_u, b0[1]), b1[1]);
 #pragma unroll
-  for (int m = 2; m < 8; ++m) best = min3f(best, a0[m], a1[m]), best2 = min3f(best2, b0[m], b1[m]);
-  best = min3f(best, best2, best2);
-  // Error bound of either form of a distance, relative to M >= ||c||^2 + 2 |c| |y|, in units of 2^-24: the fp16 splits of
+  for (int m = 2; m < 8; ++m) best_u = min(min(best_u, a0[m]), a1[m]), best2 = min(min(best2, b0[m]), b1[m]);
+  const float best = __uint_as_float(min(best_u, best2));
+  // Error bound of either form of a distance, relative to M >= (|c| + |y|)^2, in units of 2^-24: the fp16 splits of
   // y and c leave 4 each (two roundings of 2^-11), the dropped low x low product 4, low parts below the normal fp16
-  // range 2 (M >= 16), fp32 rounding of the inputs 2, the sum of at most 32 terms 24 (matrix cores) or SUB + 3
-  // (fp32).  Anything that can be nearest lies within twice the bound of the computed minimum.
-  const float M = R.cm * (R.cm + 2.0002f * __builtin_amdgcn_sqrtf(yn));
-  const float thr = fmaf(2.f * 44.f * 5.9604645e-8f, M, best);
+  // range 2 (M >= 16), fp32 rounding of the inputs and of the threshold 3, the sum of at most 32 terms 24 (matrix cores)
+  // or SUB + 3 (fp32).  Anything that can be nearest lies within twice the bound of the computed minimum.
+  const float reach = R.cm + 1.0001f * __builtin_amdgcn_sqrtf(yn);
+  const float thr_n = fmaf(2.f * 44.f * 5.9604645e-8f * reach, reach, best);  // for D (with n in it)
+  const float thr = thr_n - n16;                                              // for the fp32 form
   uint32_t groups = 0u;
+  auto below = [&](uint32_t t) { return __float_as_uint(__uint_as_float(t) - thr_n); };  // sign bit set: listed
 #pragma unroll
   for (int m = 7; m >= 0; --m) {
-    groups = __builtin_amdgcn_alignbit(groups, __float_as_uint(b1[m] - thr), 31);
-    groups = __builtin_amdgcn_alignbit(groups, __float_as_uint(b0[m] - thr), 31);
-    groups = __builtin_amdgcn_alignbit(groups, __float_as_uint(a1[m] - thr), 31);
-    groups = __builtin_amdgcn_alignbit(groups, __float_as_uint(a0[m] - thr), 31);
+    groups = __builtin_amdgcn_alignbit(groups, below(b1[m]), 31);
+    groups = __builtin_amdgcn_alignbit(groups, below(b0[m]), 31);
+    groups = __builtin_amdgcn_alignbit(groups, below(a1[m]), 31);
+    groups = __builtin_amdgcn_alignbit(groups, below(a0[m]), 31);
   }
-  if (!(yn < 1e9f)) groups = 0u;  // beyond the fp16 range (or not a number): fp64 search below
+  if (!(yn < 60000.f)) groups = 0u;  // beyond the fp16 range (or not a number): fp64 search below
   // rows of group g within the bound, as a bit mask
   auto rows_of = [&](int g) -> uint32_t {
     const float4* r0 = &T.n2c[0][g * SearchTables<SUB>::kRowStride];
@@ -313,17 +325,21 @@ __device__ __forceinline__ int search_nearest(const SearchTables<SUB>& T, const 
     }
     return mask;
   };
-  int code = 0, found = 0;
+  constexpr int kStride = SearchTables<SUB>::kRowStride;
+  int at = 0, found = 0;
   {
     uint32_t left = groups;
     do {
       const int g = left ? __builtin_ctz(left) : 0;
       const uint32_t rows = left ? rows_of(g) : 0u;
-      if (rows) code = group_codeword(g, __builtin_ctz(rows));
+      if (rows) at = g * kStride + __builtin_ctz(rows);
       found += __builtin_popcount(rows);
       left &= left - 1u;
     } while (__any(left != 0u));
   }
+  Nearest res;
+  res.code = group_codeword(at / kStride, at % kStride);
+  res.at = at;
   if (__any(found != 1)) {  // (none at all: not a number somewhere, or out of range)
     double e1 = INFINITY;
     int k1 = 0;
@@ -347,9 +363,12 @@ __device__ __forceinline__ int search_nearest(const SearchTables<SUB>& T, const 
         if (d < e1) e1 = d, k1 = c;
       }
     }
-    if (found != 1) code = k1;
+    if (found != 1) {
+      res.code = k1;
+      res.at = codeword_group(k1) * kStride + codeword_row(k1);
+    }
   }
-  return code;
+  return res;
 }
 
 }  // namespace nsn
