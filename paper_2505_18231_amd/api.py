@@ -99,7 +99,9 @@ def _ptr(t) -> int | None:
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    """The current stream of the current device as a raw handle (torch.cuda.current_stream() builds two Python objects
+    on the way: 4 us of a call that takes 10)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 SIGN_CODES = 65536  # n_codes of the sign + index format: 256 magnitude codewords x 2^8 sign patterns
@@ -159,8 +161,12 @@ class CodedCache:
     block_table: torch.Tensor | None
 
     def c_struct(self) -> nsn_cache:
-        return nsn_cache(self.codes.data_ptr(), self.norms.data_ptr(), self.means.data_ptr(),
-                         _ptr(self.block_table))
+        """The C view of the buffers as they are now (the structure is made anew only when one of them has moved)."""
+        bt = self.block_table
+        now = (self.codes.data_ptr(), self.norms.data_ptr(), self.means.data_ptr(), None if bt is None else bt.data_ptr())
+        if getattr(self, "_c_ptrs", None) != now:
+            self._c_ptrs, self._c_struct = now, nsn_cache(*now)
+        return self._c_struct
 
 
 def alloc_cache(shape: nsn_shape, batch: int, device="cuda", block_table: torch.Tensor | None = None,
@@ -239,8 +245,8 @@ def nsn_encode(shape: nsn_shape, codebook: torch.Tensor, k: torch.Tensor, v: tor
     assert seq_start.dtype == torch.int32 and n_new.dtype == torch.int32
     batch, hkv, max_new, d = k.shape
     assert hkv == shape.n_kv_heads and d == HEAD_DIM
-    need = nsn_workspace_bytes(shape, NSN_OP_ENCODE, batch, max_new)
     if workspace is None:
+        need = nsn_workspace_bytes(shape, NSN_OP_ENCODE, batch, max_new)
         workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=k.device)
     kc, vc = k_cache.c_struct(), v_cache.c_struct()
     _check(lib().nsn_encode(C.byref(shape), codebook.data_ptr(), k.data_ptr(), v.data_ptr(), max_new,
@@ -259,8 +265,8 @@ def nsn_decode_attention(shape: nsn_shape, codebook: torch.Tensor, q: torch.Tens
     assert hq == shape.n_q_heads and d == HEAD_DIM
     if out is None:
         out = torch.empty((batch, hq, d), dtype=torch.float32, device=q.device)
-    need = nsn_workspace_bytes(shape, NSN_OP_DECODE, batch, 0, n_splits)
     if workspace is None:  # must start zero-filled (arrival counters); reusable afterwards
+        need = nsn_workspace_bytes(shape, NSN_OP_DECODE, batch, 0, n_splits)
         workspace = torch.zeros(max(need, 1), dtype=torch.uint8, device=q.device)
     kc, vc = k_cache.c_struct(), v_cache.c_struct()
     _check(lib().nsn_decode_attention(C.byref(shape), codebook.data_ptr(), q.data_ptr(), C.byref(kc),
@@ -288,8 +294,8 @@ def nsn_decode_attention_residual(shape: nsn_shape, codebook: torch.Tensor, q: t
     assert k_res.shape == v_res.shape and res_lens.numel() == batch
     if out is None:
         out = torch.empty((batch, hq, d), dtype=torch.float32, device=q.device)
-    need = nsn_workspace_bytes(shape, NSN_OP_DECODE, batch, 0, n_splits)
     if workspace is None:
+        need = nsn_workspace_bytes(shape, NSN_OP_DECODE, batch, 0, n_splits)
         workspace = torch.zeros(max(need, 1), dtype=torch.uint8, device=q.device)
     kc, vc = k_cache.c_struct(), v_cache.c_struct()
     res = nsn_residual(k_res.data_ptr(), v_res.data_ptr(), res_lens.data_ptr(), int(k_res.shape[2]))
