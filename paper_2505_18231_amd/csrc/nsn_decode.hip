@@ -261,7 +261,7 @@ bool decode_use_mfma(const nsn_shape& s) {
 }
 
 int decode_pick_splits(const nsn_shape& s, int batch, int max_seq_len, int requested) {
-  if (decode_use_mfma(s)) return decode_mfma_splits(s, batch, max_seq_len, requested);
+  if (decode_use_mfma(s)) return decode_tile_splits(s, batch, max_seq_len, requested);
   const int cap = max(1, min(64, (max_seq_len + 255) / 256));
   if (requested > 0) return min(requested, 64);
   const int rows = max(1, batch * s.n_q_heads);
@@ -269,7 +269,7 @@ int decode_pick_splits(const nsn_shape& s, int batch, int max_seq_len, int reque
 }
 
 size_t decode_workspace_bytes(const nsn_shape& s, int batch, int n_splits) {
-  if (decode_use_mfma(s)) return decode_mfma_workspace_bytes(s, batch, n_splits);
+  if (decode_use_mfma(s)) return decode_tile_workspace_bytes(s, batch, n_splits);
   return (size_t)batch * s.n_q_heads * n_splits * kPartialStride * sizeof(float);
 }
 
@@ -277,7 +277,7 @@ int decode_launch(const nsn_shape& s, const void* codebook, const void* q, const
                   const nsn_cache& vc, const int32_t* seq_lens, int batch, int max_seq_len, float scale,
                   int n_splits, const nsn_residual* residual, float* out, void* workspace, hipStream_t stream) {
   if (decode_use_mfma(s)) {
-    const int rc = decode_mfma_launch(s, codebook, q, kc, vc, seq_lens, batch, max_seq_len, scale, n_splits,
+    const int rc = decode_tile_launch(s, codebook, q, kc, vc, seq_lens, batch, max_seq_len, scale, n_splits,
                                       workspace, residual, out, stream);
     return rc != NSN_OK ? rc : hipGetLastError() == hipSuccess ? NSN_OK : NSN_ERR_HIP;
   }

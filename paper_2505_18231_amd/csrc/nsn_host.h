@@ -51,23 +51,18 @@ int encode_launch(const nsn_shape& s, const void* codebook, const void* k_in, co
                   const int32_t* seq_start, const int32_t* n_new, int batch, int freeze_means,
                   const nsn_cache& kc, const nsn_cache& vc, void* workspace, hipStream_t stream);
 
-// A resolved split count of kSplitsFlat selects the tiled-layout kernel's persistent instance: one workgroup
+// A resolved split count of kSplitsFlat selects the matrix-core kernel's persistent instance: one workgroup
 // per compute unit (at most kFlatRunsMax), each taking an equal run of the list of all 64-token groups.
 constexpr int kSplitsFlat = 0;
 constexpr int kFlatRunsMax = 256;
 int decode_pick_splits(const nsn_shape& s, int batch, int max_seq_len, int requested);
 bool decode_use_mfma(const nsn_shape& s);
-int decode_mfma_splits(const nsn_shape& s, int batch, int max_seq_len, int requested);
-size_t decode_mfma_workspace_bytes(const nsn_shape& s, int batch, int n_splits);
+int decode_tile_splits(const nsn_shape& s, int batch, int max_seq_len, int requested);
+size_t decode_tile_workspace_bytes(const nsn_shape& s, int batch, int n_splits);
 size_t decode_counter_bytes(const nsn_shape& s, int batch);  // arrival counters at the head of the decode workspace
 int decode_tile_launch(const nsn_shape& s, const void* codebook, const void* q, const nsn_cache& kc,
                        const nsn_cache& vc, const int32_t* seq_lens, int batch, int max_seq_len, float scale,
-                       int n_splits, void* workspace, size_t counter_bytes, const nsn_residual* residual, float* out,
-                       hipStream_t stream);
-int decode_mfma_launch(const nsn_shape& s, const void* codebook, const void* q, const nsn_cache& kc,
-                       const nsn_cache& vc, const int32_t* seq_lens, int batch, int max_seq_len, float scale,
-                       int n_splits, void* workspace, const nsn_residual* residual, float* out,
-                       hipStream_t stream);
+                       int n_splits, void* workspace, const nsn_residual* residual, float* out, hipStream_t stream);
 size_t decode_workspace_bytes(const nsn_shape& s, int batch, int n_splits);
 int decode_launch(const nsn_shape& s, const void* codebook, const void* q, const nsn_cache& kc,
                   const nsn_cache& vc, const int32_t* seq_lens, int batch, int max_seq_len, float scale,
