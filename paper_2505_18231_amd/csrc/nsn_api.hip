@@ -181,8 +181,11 @@ size_t nsn_workspace_bytes(const nsn_shape* shape, int op, int batch, int64_t n,
   }
   if (check_shape(shape) != NSN_OK || batch <= 0) return 0;
   if (op == NSN_OP_ENCODE) return n > 0 ? encode_workspace_bytes(*shape, batch, n) : 0;
-  if (op == NSN_OP_DECODE)
+  if (op == NSN_OP_DECODE) {
+    // automatic splitting in the matrix-core kernel: enough for either instance, whatever the sequences' lengths
+    if (n_splits <= 0 && decode_use_mfma(*shape)) return decode_workspace_bytes(*shape, batch, kSplitsFlat);
     return decode_workspace_bytes(*shape, batch, decode_pick_splits(*shape, batch, shape->max_len, n_splits));
+  }
   return 0;
 }
 
@@ -336,7 +339,10 @@ int nsn_decode_attention_noalloc(const nsn_shape* shape, const void* codebook_de
     set_error("decode (noalloc): negative size");
     return NSN_ERR_INVALID_ARG;
   }
-  const int splits = decode_pick_splits(*shape, batch, max_seq_len, n_splits);
+  int splits = decode_pick_splits(*shape, batch, max_seq_len, n_splits);
+  // (the persistent instance's partials of more than four query heads per kv head do not fit, the splits' do)
+  if (splits == kSplitsFlat && decode_workspace_bytes(*shape, batch, splits) > kScratchBytes)
+    splits = decode_tile_split_count(*shape, batch, max_seq_len);
   const size_t need = decode_workspace_bytes(*shape, batch, splits);
   if (need > kScratchBytes) {
     set_error("decode (noalloc): this call needs %zu scratch bytes, the built-in scratch holds %zu "
@@ -353,7 +359,7 @@ int nsn_decode_attention_noalloc(const nsn_shape* shape, const void* codebook_de
     return NSN_ERR_HIP;
   }
   return decode_common(shape, codebook_dev, q_fp16, k_cache, v_cache, seq_lens_dev, batch, max_seq_len, nullptr,
-                       softmax_scale, n_splits, out, ptr, kScratchBytes, stream);
+                       softmax_scale, splits, out, ptr, kScratchBytes, stream);
 }
 
 int nsn_decode_attention_residual(const nsn_shape* shape, const void* codebook_dev, const void* q_fp16,

@@ -57,6 +57,7 @@ constexpr int kSplitsFlat = 0;
 constexpr int kFlatRunsMax = 256;
 int decode_pick_splits(const nsn_shape& s, int batch, int max_seq_len, int requested);
 bool decode_use_mfma(const nsn_shape& s);
+int decode_tile_split_count(const nsn_shape& s, int batch, int max_seq_len);
 int decode_tile_splits(const nsn_shape& s, int batch, int max_seq_len, int requested);
 size_t decode_tile_workspace_bytes(const nsn_shape& s, int batch, int n_splits);
 size_t decode_counter_bytes(const nsn_shape& s, int batch);  // arrival counters at the head of the decode workspace
