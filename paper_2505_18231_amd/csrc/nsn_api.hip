@@ -340,7 +340,7 @@ int nsn_decode_attention_noalloc(const nsn_shape* shape, const void* codebook_de
     return NSN_ERR_INVALID_ARG;
   }
   int splits = decode_pick_splits(*shape, batch, max_seq_len, n_splits);
-  // (the persistent instance's partials of more than four query heads per kv head do not fit, the splits' do)
+  // (where the counters leave no room for the persistent instance's partials, the splits' may still fit)
   if (splits == kSplitsFlat && decode_workspace_bytes(*shape, batch, splits) > kScratchBytes)
     splits = decode_tile_split_count(*shape, batch, max_seq_len);
   const size_t need = decode_workspace_bytes(*shape, batch, splits);

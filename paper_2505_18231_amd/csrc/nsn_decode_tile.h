@@ -275,7 +275,7 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
                                                            const __half* __restrict__ q, CacheView kc, CacheView vc,
                                                            const int32_t* __restrict__ seq_lens, int batch,
                                                            float scale_log2e, int n_splits, int per, float* partial,
-                                                           int* counters, ResidualView res, int head_off, int r_pass,
+                                                           int* counters, ResidualView res, int n_rep,
                                                            float* __restrict__ out) {
   static_assert(NW == 8, "prologue work split: 512 threads fill the table, waves 0..3 rotate the query");
   constexpr int NSV = kHeadDim / SUB;  // sub-vectors per token
@@ -287,12 +287,14 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
   using Regs = GroupRegs<CW, SGN>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
 
-  const int r = r_pass;
+  // Five to eight query heads (n_rep) of a kv head are two units of up to four: unit head hu, kv head hu >> two
+  const int two = n_rep > 4 ? 1 : 0;
+  auto heads_of = [&](int hu) { return min(4, n_rep - 4 * (hu & two)); };
   const int tid = threadIdx.x, lane0 = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int cap_tokens = g.page_tokens * g.pages_per_seq;
   // the segment at hand (!FLAT: the launch's one (split, kv head, sequence))
-  int split = FLAT ? 0 : blockIdx.x, h = FLAT ? 0 : blockIdx.y, b = FLAT ? 0 : blockIdx.z;
+  int split = FLAT ? 0 : blockIdx.x, hu = FLAT ? 0 : blockIdx.y, h = hu >> two, b = FLAT ? 0 : blockIdx.z;
   int t0 = split * per;
   int64_t mean_base = (int64_t)(b * g.n_kv_heads + h) * g.n_groups_max;
 
@@ -302,7 +304,7 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
   const cw_t cw_reg = reinterpret_cast<const cw_t*>(codebook)[tid >> 1];  // two threads per code row
 
   // ---- FLAT: this workgroup's run of the group list (every wave computes the same numbers) --------
-  const int hkv = g.n_kv_heads;
+  const int hkv = g.n_kv_heads, n_units = hkv << two;  // kv heads, units per sequence
   int run_q = 0, run_pos = 0, run_end = 0, seg_g = 0;  // run length, list position, end of the run, slot inside the unit
   // codebook table: thread (code = tid / 2, half = tid % 2) fills eight 16-byte slots of its half row, starting
   // at a slot that depends on the code so that the 64 stores of a wave spread over all banks
@@ -338,7 +340,7 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
     // list positions taken by the sequences of one 64-sequence block: this lane's sequence, and the inclusive
     // prefix sums over the lanes
     auto block_sizes = [&](int b0, int& n, int& incl) {
-      n = (b0 + lane0 < batch) ? (groups_of(seq_lens[b0 + lane0]) + kSegCost) * hkv : 0;
+      n = (b0 + lane0 < batch) ? (groups_of(seq_lens[b0 + lane0]) + kSegCost) * n_units : 0;
       incl = n;
       static_for<6>([&](auto kc_) {
         constexpr int d = 1 << decltype(kc_)::value;
@@ -360,7 +362,7 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
     if (run_pos >= total) return;  // (all waves alike, before any barrier)
     run_end = min(total, run_pos + run_q);
     // the sequence that holds list position run_pos: sequences are laid out one after the other, each as
-    // n_kv_heads units of its group count
+    // n_units units of its group count
     int before = 0;  // list positions in front of the 64-sequence block at hand
     for (int b0 = 0; b0 < batch; b0 += 64) {
       int n = n0, incl = incl0;
@@ -370,10 +372,10 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
       if (n_before < n_here) {
         b = b0 + n_before;
         const int incl_b = __builtin_amdgcn_readlane(incl, n_before), n_b = __builtin_amdgcn_readlane(n, n_before);
-        const int off = run_pos - (before + incl_b - n_b);  // position inside the sequence's n_kv_heads units
-        const int slots = n_b / hkv;
-        h = off / slots;
-        seg_g = off - h * slots;  // (position among the unit's slots)
+        const int off = run_pos - (before + incl_b - n_b);  // position inside the sequence's units
+        const int slots = n_b / n_units;
+        hu = off / slots;
+        seg_g = off - hu * slots;  // (position among the unit's slots)
         break;
       }
       before += __builtin_amdgcn_readlane(incl, 63);
@@ -536,15 +538,18 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
     t0 = g0 << 6;
     t1 = min(len, g1 << 6);
     res_here = g1 == ng;
+    h = hu >> two;
     mean_base = (int64_t)(b * hkv + h) * g.n_groups_max;
     // advance to the next segment's start (used at the end of the pass)
     run_pos += take_slots;
     seg_g = 0;  // (a run that goes on goes on with the next unit)
   }
-  const int hq0 = h * (g.n_q_heads / hkv) + head_off;
+  const int r = heads_of(hu);
+  auto first_head = [&](int hv) { return (hv >> two) * n_rep + 4 * (hv & two); };
+  const int hq0 = first_head(hu);
   // waves 0..3 rotate one query head each (the others load a valid row that they do not use)
-  auto q_row = [&](int bb, int hh0) {
-    return *reinterpret_cast<const __half2*>(q + (int64_t)(bb * g.n_q_heads + hh0 + min(wave & 3, r - 1)) * kHeadDim +
+  auto q_row = [&](int bb, int hv) {
+    return *reinterpret_cast<const __half2*>(q + (int64_t)(bb * g.n_q_heads + first_head(hv) + min(wave & 3, heads_of(hv) - 1)) * kHeadDim +
                                              2 * lane);
   };
   auto mean_row_k = [&](int64_t base, int grp, uint32_t& w, uint32_t& par) {
@@ -563,19 +568,19 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
   __half2 q2_raw = q2_next;
   uint32_t ok_first = okf_next, okp_first = okfp_next;
   if (!FLAT || first_segment) {
-    q2_raw = q_row(b, hq0);
+    q2_raw = q_row(b, hu);
     if constexpr (!ROPE) mean_row_k(mean_base, grp_first, ok_first, okp_first);
   }
   if constexpr (FLAT) {
     // the unit after this one (if the run goes on, this segment ends its unit and the next begins one)
-    nb = b, nh = h;
-    if (run_pos < run_end && ++nh == hkv) {
+    nb = b, nh = hu;
+    if (run_pos < run_end && ++nh == n_units) {
       nh = 0;
       ++nb;
     }
     len_cur = seq_lens[nb];
-    q2_next = q_row(nb, nh * (g.n_q_heads / hkv) + head_off);
-    if constexpr (!ROPE) mean_row_k((int64_t)(nb * hkv + nh) * g.n_groups_max, 0, okf_next, okfp_next);
+    q2_next = q_row(nb, nh);
+    if constexpr (!ROPE) mean_row_k((int64_t)(nb * hkv + (nh >> two)) * g.n_groups_max, 0, okf_next, okfp_next);
   }
   // (the three small loads stay ahead of the bulk ones: the waits for them then leave every later load in flight)
   __builtin_amdgcn_sched_barrier(0);
@@ -1305,13 +1310,13 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
 
   // ---- d6: merge the splits; the last wave to arrive for this query head finishes it -------------
   if (n_live > 1) {
-    // !FLAT: partial [sequence][query head][split].  FLAT: [run][slot][query head of the kv head]: slot 0 for
+    // !FLAT: partial [sequence][query head][split].  FLAT: [run][slot][query head of the unit]: slot 0 for
     // the segment that continues a unit begun in an earlier run, slot 1 for the one that begins a unit and
     // leaves its end to the next run (a run has at most one of each); run c of the unit's runs
     // first_run .. first_run + n_live - 1 therefore wrote slot 1 if c == first_run, else slot 0.
     auto partial_of = [&](int s) -> float* {
       if constexpr (FLAT)
-        return partial + ((int64_t)((first_run + s) * 2 + (s == 0 ? 1 : 0)) * (g.n_q_heads / hkv) + head_off + hh) * kPartialStride;
+        return partial + ((int64_t)((first_run + s) * 2 + (s == 0 ? 1 : 0)) * min(n_rep, 4) + hh) * kPartialStride;
       else
         return partial + ((int64_t)(b * g.n_q_heads + hq0 + hh) * n_splits + s) * kPartialStride;
     };
@@ -1402,7 +1407,7 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
   }();
   if constexpr (!FLAT) break;
   if (run_pos >= run_end) break;
-  b = nb, h = nh;  // the next unit (its first row and length are on their way or here)
+  b = nb, hu = nh;  // the next unit (its first row and length are on their way or here)
   first_segment = false;
   if constexpr (PAGED) win0 = 0, win_k = nwin_k, win_v = nwin_v;
   }  // segments
@@ -1421,7 +1426,6 @@ struct Call {
   void* workspace;
   size_t counter_bytes;
   ResidualView res;
-  int head_off, r_pass;  // query heads [head_off, head_off + r_pass) of every kv head
   float* out;
   hipStream_t stream;
 };
@@ -1430,6 +1434,7 @@ template <int SUB, int NW, bool POW2, bool PAGED, bool FLAT, bool DQ, bool SGN =
 static int launch_one(const Call& c) {
   const Geometry& g = c.g;
   int n_splits = c.n_splits;
+  const int n_rep = g.n_q_heads / g.n_kv_heads, unit_heads = g.n_kv_heads * (n_rep > 4 ? 2 : 1);
   using SM = Smem<NW, ROPE>;
   const size_t smem = c.res.k != nullptr ? (size_t)SM::kBytesRes : (size_t)SM::kBytes;
   static const int attr_rc = [] {
@@ -1453,16 +1458,16 @@ static int launch_one(const Call& c) {
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
       return NSN_ERR_HIP;
-    const int64_t groups_max = (int64_t)c.batch * g.n_kv_heads * max(1, (c.max_seq_len + 63) / 64);
+    const int64_t groups_max = (int64_t)c.batch * unit_heads * max(1, (c.max_seq_len + 63) / 64);
     n_splits = (int)std::min<int64_t>(std::min(n_cu, kFlatRunsMax), groups_max);
     grid = dim3(n_splits, 1, 1);
   } else {
     per = (((c.max_seq_len + n_splits - 1) / n_splits) + 63) & ~63;
-    grid = dim3(n_splits, g.n_kv_heads, c.batch);
+    grid = dim3(n_splits, unit_heads, c.batch);
   }
   dec_tile_kernel<SUB, NW, POW2, PAGED, FLAT, DQ, SGN, ROPE><<<grid, NW * 64, smem, c.stream>>>(
       g, (const __half*)c.codebook, (const __half*)c.q, c.kc, c.vc, c.seq_lens, c.batch, c.scale * 1.44269504088896340736f,
-      n_splits, per, partial, counters, c.res, c.head_off, c.r_pass, c.out);
+      n_splits, per, partial, counters, c.res, n_rep, c.out);
   return hipGetLastError() == hipSuccess ? NSN_OK : NSN_ERR_HIP;
 }
 

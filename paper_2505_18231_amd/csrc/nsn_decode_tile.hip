@@ -10,7 +10,12 @@ size_t decode_counter_bytes(const nsn_shape& s, int batch) {
   return (size_t)batch * s.n_q_heads * kCounterStrideInts * sizeof(int);
 }
 
-// Splits per unit (sequence, kv head) of the one-workgroup-per-split instance.  A workgroup has a compute unit to itself
+// a unit is (sequence, kv head, up to four query heads of it)
+static int decode_units(const nsn_shape& s, int batch) {
+  return max(1, batch * s.n_kv_heads * (s.n_q_heads / s.n_kv_heads > 4 ? 2 : 1));
+}
+
+// Splits per unit of the one-workgroup-per-split instance.  A workgroup has a compute unit to itself
 // (its LDS holds the codebook table), so the count is rounded down: one workgroup too many costs a whole second round
 // (2-bit, 100 units x 8192 tokens: 17.3 us with two splits, 23.5 with three).  Eight groups or fewer are one per wave
 // and need no merge across workgroups (512 tokens: 6.2 us, 7.2 in four splits); beyond that a split gets eight groups,
@@ -18,7 +23,7 @@ size_t decode_counter_bytes(const nsn_shape& s, int batch) {
 // 8192 tokens in 16 / 32 splits 9.6 / 9.9 us).  More than 32 partials are read in two trips: only for very long contexts
 // (32768 tokens in 32 / 64 splits 12.0 / 13.7 us, 131072 tokens 19.4 / 17.9 us).
 int decode_tile_split_count(const nsn_shape& s, int batch, int max_seq_len) {
-  const int units = max(1, batch * s.n_kv_heads), groups = max(1, (max_seq_len + 63) / 64);
+  const int units = decode_units(s, batch), groups = max(1, (max_seq_len + 63) / 64);
   const int useful = groups <= 8 ? 1 : min(groups > 1024 ? 64 : 32, max(4, (groups + 7) / 8));
   return max(1, min(useful, 256 / units));
 }
@@ -34,17 +39,17 @@ int decode_tile_split_count(const nsn_shape& s, int batch, int max_seq_len) {
 int decode_tile_splits(const nsn_shape& s, int batch, int max_seq_len, int requested) {
   if (requested > 0) return min(requested, 64);
   const int splits = decode_tile_split_count(s, batch, max_seq_len);
-  const int units = max(1, batch * s.n_kv_heads), groups = max(1, (max_seq_len + 63) / 64);
+  const int units = decode_units(s, batch), groups = max(1, (max_seq_len + 63) / 64);
   const int per_wave = (groups + 8 * splits - 1) / (8 * splits), rounds = (units * splits + 255) / 256;
   const double split_cost = (double)rounds * (4 + per_wave);
   const double flat_cost = 3 + 5 * (1 + units / 256.0) + (batch > 1 ? 0.7 : 1.0) * units * groups / (256.0 * 8);
   return flat_cost < split_cost ? kSplitsFlat : splits;
 }
 
-// one split: no partial results.  kSplitsFlat: two partials per run and query head of a kv head, which is at least what
+// one split: no partial results.  kSplitsFlat: two partials per run and query head of a unit, which is at least what
 // an automatic split count takes (units x splits <= 256): the size for automatic splitting at any length
 size_t decode_tile_workspace_bytes(const nsn_shape& s, int batch, int n_splits) {
-  const size_t partials = n_splits == kSplitsFlat ? (size_t)kFlatRunsMax * 2 * (s.n_q_heads / s.n_kv_heads)
+  const size_t partials = n_splits == kSplitsFlat ? (size_t)kFlatRunsMax * 2 * min(4, s.n_q_heads / s.n_kv_heads)
                           : n_splits == 1         ? 0
                                                   : (size_t)batch * s.n_q_heads * n_splits;
   return decode_counter_bytes(s, batch) + partials * tile::kPartialStride * sizeof(float);
@@ -55,39 +60,28 @@ int decode_tile_launch(const nsn_shape& s, const void* codebook, const void* q, 
                        int n_splits, void* workspace, const nsn_residual* residual, float* out, hipStream_t stream) {
   const Geometry g = make_geometry(s);
   tile::Call c = {g, codebook, q, make_view(kc), make_view(vc), seq_lens, batch, max_seq_len, scale, n_splits, workspace,
-                  decode_counter_bytes(s, batch), {nullptr, nullptr, nullptr, 0}, 0, 0, out, stream};
+                  decode_counter_bytes(s, batch), {nullptr, nullptr, nullptr, 0}, out, stream};
   if (residual)
     c.res = {static_cast<const __half*>(residual->k_fp16), static_cast<const __half*>(residual->v_fp16),
              residual->lens, residual->capacity};
-  const int r_total = s.n_q_heads / s.n_kv_heads;
-  // up to four query heads per kv head in one launch; five to eight as two launches on the same stream
-  for (c.head_off = 0; c.head_off < r_total; c.head_off += 4) {
-    c.r_pass = min(4, r_total - c.head_off);
-    int rc;
-    if (!g.tiled) {
-      rc = decode_rows_launch(c, s.sub_dim);
-    } else {
-      const bool pow2 = (g.group_size <= 0 || g.group_shift >= 0) && (!g.paged || g.page_shift >= 0);
-      auto with_flags = [&](auto sub, auto flat, auto dq) {
-        constexpr int kSub = decltype(sub)::value;
-        constexpr bool kFlat = decltype(flat)::value, kDq = decltype(dq)::value;
-        if (g.paged)
-          return pow2 ? tile::launch_one<kSub, 8, true, true, kFlat, kDq>(c) : tile::launch_one<kSub, 8, false, true, kFlat, kDq>(c);
-        return pow2 ? tile::launch_one<kSub, 8, true, false, kFlat, kDq>(c) : tile::launch_one<kSub, 8, false, false, kFlat, kDq>(c);
-      };
-      auto with_sub = [&](auto flat) {
-        if (g.dq)
-          return s.sub_dim == 4 ? with_flags(std::integral_constant<int, 4>{}, flat, std::true_type{})
-                                : with_flags(std::integral_constant<int, 8>{}, flat, std::true_type{});
-        return s.sub_dim == 4 ? with_flags(std::integral_constant<int, 4>{}, flat, std::false_type{})
-                              : with_flags(std::integral_constant<int, 8>{}, flat, std::false_type{});
-      };
-      // n_splits == kSplitsFlat: the persistent instance that cuts the list of all groups into equal runs
-      rc = n_splits == kSplitsFlat ? with_sub(std::true_type{}) : with_sub(std::false_type{});
-    }
-    if (rc != NSN_OK) return rc;
-  }
-  return NSN_OK;
+  if (!g.tiled) return decode_rows_launch(c, s.sub_dim);
+  const bool pow2 = (g.group_size <= 0 || g.group_shift >= 0) && (!g.paged || g.page_shift >= 0);
+  auto with_flags = [&](auto sub, auto flat, auto dq) {
+    constexpr int kSub = decltype(sub)::value;
+    constexpr bool kFlat = decltype(flat)::value, kDq = decltype(dq)::value;
+    if (g.paged)
+      return pow2 ? tile::launch_one<kSub, 8, true, true, kFlat, kDq>(c) : tile::launch_one<kSub, 8, false, true, kFlat, kDq>(c);
+    return pow2 ? tile::launch_one<kSub, 8, true, false, kFlat, kDq>(c) : tile::launch_one<kSub, 8, false, false, kFlat, kDq>(c);
+  };
+  auto with_sub = [&](auto flat) {
+    if (g.dq)
+      return s.sub_dim == 4 ? with_flags(std::integral_constant<int, 4>{}, flat, std::true_type{})
+                            : with_flags(std::integral_constant<int, 8>{}, flat, std::true_type{});
+    return s.sub_dim == 4 ? with_flags(std::integral_constant<int, 4>{}, flat, std::false_type{})
+                          : with_flags(std::integral_constant<int, 8>{}, flat, std::false_type{});
+  };
+  // n_splits == kSplitsFlat: the persistent instance that cuts the list of all groups into equal runs
+  return n_splits == kSplitsFlat ? with_sub(std::true_type{}) : with_sub(std::false_type{});
 }
 
 }  // namespace nsn
