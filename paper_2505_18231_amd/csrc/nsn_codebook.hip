@@ -5,7 +5,11 @@
 //   cb_accumulate_kernel  nearest centroid per sample (nsn_search.h) and, in the same pass over the samples, the sums of
 //                         every cluster's members: one partial per workgroup
 //   km_update_kernel      adds the partials in a fixed order (fp64): the new centroids
-// (fine-tuning: ft_accumulate_kernel and ft_update_kernel)
+// (fine-tuning: cb_ordered_kernel and ft_update_kernel; K-Means of samples with a range that fixed-point sums do not
+// cover takes cb_ordered_kernel too)
+#include <cmath>
+#include <cstring>
+
 #include "nsn_host.h"
 #include "nsn_search.h"
 
@@ -19,8 +23,8 @@ template <int SUB>
 constexpr int kSumThreads = SUB == 4 ? 1024 : 768;
 constexpr int kSumMost = 4096;  // samples added up in LDS at a time
 
-// workspace: centroids, error sum of every workgroup, cosine sum of every cluster, largest |sample| (bits), then
-// per workgroup of the accumulation the member sums [256][SUB] and the member counts [256]
+// workspace: centroids, error sum of every workgroup, cosine sum of every cluster (K-Means: sum of |sample| of every
+// workgroup of cb_max_kernel), largest |sample| (bits), then per workgroup of the accumulation the member sums [256][SUB] and the member counts [256]
 template <int SUB>
 struct CodebookWs {
   double* centroids;
@@ -50,25 +54,34 @@ __global__ void cb_start_kernel(const T* __restrict__ from, double* __restrict__
   if (i == 0) *max_bits = 0u;
 }
 
-// Largest |sample| of the set, as fp32 bits (their order is that of the values).  One atomic per workgroup: with one per
-// wave of a 4096-wave launch they took 45 of 56 us.
-constexpr int kMaxThreads = 1024;
+// Largest |sample| of the set, as fp32 bits (their order is that of the values; infinities and NaN are above all of
+// them), and a quarter of the sum of |sample| per workgroup, in one order.  One atomic per workgroup: with one per wave of a
+// 4096-wave launch they took 45 of 56 us.
+constexpr int kMaxThreads = 1024, kMaxBlocks = 256;
+static_assert(kMaxBlocks == kCodes, "one sum per workgroup in cos_sum");
 typedef float row4 __attribute__((ext_vector_type(4), aligned(4)));  // (the samples are aligned as floats are)
 __global__ __launch_bounds__(kMaxThreads) void cb_max_kernel(const float* __restrict__ samples, int64_t n_rows,
-                                                             uint32_t* __restrict__ max_bits) {
-  __shared__ float red[kMaxThreads / 64];
-  float m = 0.f;
+                                                             uint32_t* __restrict__ max_bits,
+                                                             double* __restrict__ abs_sum) {
+  __shared__ uint32_t red[kMaxThreads / 64];
+  __shared__ double red_sum[kMaxThreads / 64];
+  uint32_t m = 0u;
+  double sum = 0.0;
 #pragma unroll 4
   for (int64_t i = (int64_t)blockIdx.x * kMaxThreads + threadIdx.x; i < n_rows; i += (int64_t)gridDim.x * kMaxThreads) {
     const row4 v = reinterpret_cast<const row4*>(samples)[i];
-    m = fmaxf(fmaxf(m, fmaxf(fabsf(v.x), fabsf(v.y))), fmaxf(fabsf(v.z), fabsf(v.w)));
+    m = max(m, max(max(__float_as_uint(fabsf(v.x)), __float_as_uint(fabsf(v.y))),
+                   max(__float_as_uint(fabsf(v.z)), __float_as_uint(fabsf(v.w)))));
+    sum += (double)((0.25f * fabsf(v.x) + 0.25f * fabsf(v.y)) + (0.25f * fabsf(v.z) + 0.25f * fabsf(v.w)));
   }
-  m = wave_max(m);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  for (int k = 1; k < 64; k <<= 1) m = max(m, (uint32_t)__shfl_xor((int)m, k, 64));
+  sum = xor_sum(sum, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m, red_sum[threadIdx.x >> 6] = sum;
   __syncthreads();
-  if (threadIdx.x < 64) {
-    m = wave_max(red[threadIdx.x % (kMaxThreads / 64)]);
-    if (threadIdx.x == 0) atomicMax(max_bits, __float_as_uint(m));
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kMaxThreads / 64; ++w) m = max(m, red[w]), sum += red_sum[w];
+    atomicMax(max_bits, m);
+    abs_sum[blockIdx.x] = sum;
   }
 }
 
@@ -98,7 +111,7 @@ __device__ __forceinline__ double exact_dist(const double* __restrict__ centroid
 // does not depend on the order in which lanes and waves arrive.  A value enters with its last place at 2^-50 of the
 // power of two above the largest |sample| and at most kSumMost values are added before the LDS sums move to fp64
 // registers: no overflow of 63 bits, and a rounding error per value that is below that of the fp64 running sum
-// it stands for.  Adding 1.5 * 2^52 puts the fixed-point value into the low bits of the fp64 pattern;
+// it stands for, where the samples are of one size (fixed_point_fits below; others go to cb_ordered_kernel).  Adding 1.5 * 2^52 puts the fixed-point value into the low bits of the fp64 pattern;
 // the patterns are added as they are and the member count times the constant's pattern comes off at the end.
 // (The form this replaces wrote the assignments out and let one workgroup per cluster look through all of them:
 // 270 us per iteration of 2^20 4-dim samples.)
@@ -199,8 +212,9 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_accumulate_kernel(const f
   }
 }
 
-// Fine-tuning: assignment and the sums of x / |x| over every codeword's samples (zero samples add nothing), in fp64 and in
-// ONE order: the steps are large (a rate of 2048 turns a small codeword by several times its error), so a
+// Assignment and sums over every codeword's samples in fp64 and in ONE order.  UNIT (fine-tuning): sums of x / |x| (zero
+// samples add nothing).  Otherwise (K-Means of samples that fixed-point sums do not fit): sums of x and member counts.
+// Fine-tuning needs the order: the steps are large (a rate of 2048 turns a small codeword by several times its error), so a
 // difference in the last place of a sum grows to a different codebook within twenty of them, and the order is part of
 // the result.  Runs of 16 samples are dealt out to 1024 chains, every chain adds the members of a codeword by
 // ascending index, chains are added in pairs up to 64 and the sixteen results one after the other.
@@ -231,9 +245,9 @@ __device__ __forceinline__ void sort_ascending(uint32_t (&e)[M]) {
           }
 }
 
-template <int SUB>
-__global__ __launch_bounds__(kSumThreads<SUB>) void ft_accumulate_kernel(const float* __restrict__ samples, int64_t n,
-                                                                         CodebookWs<SUB> ws) {
+template <int SUB, bool UNIT>
+__global__ __launch_bounds__(kSumThreads<SUB>) void cb_ordered_kernel(const float* __restrict__ samples, int64_t n,
+                                                                      CodebookWs<SUB> ws) {
   constexpr int NT = kSumThreads<SUB>, NWV = NT / 64, CPW = (kPairs / 64 + NWV - 1) / NWV;
   __shared__ SearchTables<SUB> T;
   __shared__ double cx[kCodes][SUB];
@@ -246,6 +260,7 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void ft_accumulate_kernel(const f
   for (int i = tid; i < kCodes * SUB; i += NT) (&cx[0][0])[i] = ws.centroids[i];
   const int64_t n16 = n & ~(int64_t)(kRun - 1);
   double acc[CPW][SUB];
+  uint32_t members[UNIT ? 1 : CPW] = {};
 #pragma unroll
   for (int c = 0; c < CPW; ++c)
 #pragma unroll
@@ -258,7 +273,12 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void ft_accumulate_kernel(const f
       x[4 * q] = v.x, x[4 * q + 1] = v.y, x[4 * q + 2] = v.z, x[4 * q + 3] = v.w;
     }
   };
-  auto add_unit = [&](const float (&x)[SUB], double (&a)[SUB]) {
+  auto add = [&](const float (&x)[SUB], double (&a)[SUB]) {
+    if constexpr (!UNIT) {
+#pragma unroll
+      for (int i = 0; i < SUB; ++i) a[i] += (double)x[i];
+      return;
+    }
     double v[SUB], n2 = 0.0;
 #pragma unroll
     for (int i = 0; i < SUB; ++i) {
@@ -310,6 +330,7 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void ft_accumulate_kernel(const f
       const int pair = (wave + c * NWV) * 64 + lane;  // codeword pair / 4, chain pair % 4
       if (pair >= kPairs) break;  // (whole waves)
       const uint32_t count = len[pair];
+      if constexpr (!UNIT) members[c] += count;
       if (count > kListMost) {
         for (int p0 = 0; p0 < kBlockPos; p0 += 8) {
           const uint4 w4 = *reinterpret_cast<const uint4*>(&codes[pair & 3][p0]);
@@ -320,7 +341,7 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void ft_accumulate_kernel(const f
             if (code == (uint32_t)(pair >> 2) && sample_of(pair & 3, p0 + k) < stop) {
               float x[SUB];
               load(sample_of(pair & 3, p0 + k), x);
-              add_unit(x, acc[c]);
+              add(x, acc[c]);
             }
           }
         }
@@ -358,7 +379,7 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void ft_accumulate_kernel(const f
 #pragma unroll
         for (int i = 0; i < SUB; ++i) x[i] = ahead[i];
         fetch(k + 1);
-        if (k < here) add_unit(x, acc[c]);
+        if (k < here) add(x, acc[c]);
       }
     }
     __syncthreads();
@@ -372,6 +393,12 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void ft_accumulate_kernel(const f
       acc[c][i] += xor_lane<1>(acc[c][i]);
       acc[c][i] += xor_lane<2>(acc[c][i]);
       if ((lane & 3) == 0) ws.sums[((int64_t)blockIdx.x * kCodes + pair / kWgChains) * SUB + i] = acc[c][i];
+    }
+    if constexpr (!UNIT) {
+      double m = (double)members[c];
+      m += xor_lane<1>(m);
+      m += xor_lane<2>(m);
+      if ((lane & 3) == 0) ws.counts[(int64_t)blockIdx.x * kCodes + pair / kWgChains] = m;
     }
   }
 }
@@ -476,27 +503,50 @@ size_t codebook_workspace_bytes(int sub_dim, int64_t) {
   return sub_dim == 8 ? CodebookWs<8>::bytes() : CodebookWs<4>::bytes();
 }
 
+// A value enters the fixed-point sums with an error of 2^-50 of the largest |sample|, which for samples far below it is
+// more than fp64 sums have.  Up to 2^10 times the mean |sample| (normal samples: about 6) it is 2^-40 of the mean;
+// sets with rarer, larger values, infinities or NaN are added in fp64 instead.
+static bool fixed_point_fits(uint32_t max_bits, const double* abs_sum, int64_t n_elems) {
+  float largest;
+  memcpy(&largest, &max_bits, sizeof(largest));
+  double sum = 0.0;
+  for (int i = 0; i < kMaxBlocks; ++i) sum += abs_sum[i];
+  return std::isfinite(largest) && (double)largest * (double)n_elems <= 1024.0 * 4.0 * sum;
+}
+
 template <int SUB>
 static int codebook_run_t(const float* samples, int64_t n, int iters, void* codebook_out, double* mse_host,
                           void* workspace, hipStream_t stream) {
   const CodebookWs<SUB> ws(workspace);
   constexpr int n_elems = kCodes * SUB;
-  cb_start_kernel<<<(n_elems + 255) / 256, 256, 0, stream>>>(samples, ws.centroids, n_elems, ws.max_bits);
-  cb_max_kernel<<<256, kMaxThreads, 0, stream>>>(samples, n * (SUB / 4), ws.max_bits);
-  for (int it = 0; it < iters; ++it) {
-    cb_accumulate_kernel<SUB, false><<<kSumBlocks, kSumThreads<SUB>, 0, stream>>>(samples, n, ws);
-    km_update_kernel<SUB><<<kCodes / kUpdateClusters, kUpdateThreads, 0, stream>>>(ws);
-  }
-  km_round_kernel<<<(n_elems + 255) / 256, 256, 0, stream>>>(ws.centroids, static_cast<__half*>(codebook_out), n_elems);
-  cb_accumulate_kernel<SUB, true><<<kSumBlocks, kSumThreads<SUB>, 0, stream>>>(samples, n, ws);
-  if (hipGetLastError() != hipSuccess) return NSN_ERR_HIP;
-  double host_err[kSumBlocks];
-  if (hipMemcpyAsync(host_err, ws.block_err, sizeof(host_err), hipMemcpyDeviceToHost, stream) != hipSuccess)
-    return NSN_ERR_HIP;
-  if (hipStreamSynchronize(stream) != hipSuccess) return NSN_ERR_HIP;
+  struct {
+    double err[kSumBlocks], abs_sum[kMaxBlocks];
+    uint32_t max_bits, unused;
+  } host;
+  auto run = [&](bool fixed) -> int {
+    cb_start_kernel<<<(n_elems + 255) / 256, 256, 0, stream>>>(samples, ws.centroids, n_elems, ws.max_bits);
+    cb_max_kernel<<<kMaxBlocks, kMaxThreads, 0, stream>>>(samples, n * (SUB / 4), ws.max_bits, ws.cos_sum);
+    for (int it = 0; it < iters; ++it) {
+      if (fixed)
+        cb_accumulate_kernel<SUB, false><<<kSumBlocks, kSumThreads<SUB>, 0, stream>>>(samples, n, ws);
+      else
+        cb_ordered_kernel<SUB, false><<<kSumBlocks, kSumThreads<SUB>, 0, stream>>>(samples, n, ws);
+      km_update_kernel<SUB><<<kCodes / kUpdateClusters, kUpdateThreads, 0, stream>>>(ws);
+    }
+    km_round_kernel<<<(n_elems + 255) / 256, 256, 0, stream>>>(ws.centroids, static_cast<__half*>(codebook_out), n_elems);
+    cb_accumulate_kernel<SUB, true><<<kSumBlocks, kSumThreads<SUB>, 0, stream>>>(samples, n, ws);
+    if (hipGetLastError() != hipSuccess) return NSN_ERR_HIP;
+    // error sums, sums of |sample| and the largest lie next to each other
+    if (hipMemcpyAsync(&host, ws.block_err, sizeof(host), hipMemcpyDeviceToHost, stream) != hipSuccess) return NSN_ERR_HIP;
+    return hipStreamSynchronize(stream) == hipSuccess ? NSN_OK : NSN_ERR_HIP;
+  };
+  // (the range comes back with the error sums, so that ordinary samples pay nothing for the question)
+  int rc = run(true);
+  if (rc == NSN_OK && iters > 0 && !fixed_point_fits(host.max_bits, host.abs_sum, n * SUB)) rc = run(false);
+  if (rc != NSN_OK) return rc;
   if (mse_host) {
     double tot = 0.0;
-    for (int i = 0; i < kSumBlocks; ++i) tot += host_err[i];
+    for (int i = 0; i < kSumBlocks; ++i) tot += host.err[i];
     *mse_host = tot / ((double)n * SUB);
   }
   return NSN_OK;
@@ -509,7 +559,7 @@ static int finetune_run_t(const float* samples, int64_t n, int iters, double lr,
   constexpr int n_elems = kCodes * SUB;
   double host_cos[kCodes];
   auto step = [&](double rate) {
-    ft_accumulate_kernel<SUB><<<kSumBlocks, kSumThreads<SUB>, 0, stream>>>(samples, n, ws);
+    cb_ordered_kernel<SUB, true><<<kSumBlocks, kSumThreads<SUB>, 0, stream>>>(samples, n, ws);
     ft_update_kernel<SUB><<<kCodes / kUpdateClusters, kUpdateThreads, 0, stream>>>(n, ws, rate);
   };
   auto mean_cos = [&](double* out) -> int {  // assignment + cosine sums of the current centroids (no move: rate 0)

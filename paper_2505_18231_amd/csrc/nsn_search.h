@@ -300,7 +300,8 @@ __device__ __forceinline__ Nearest search_nearest(const SearchTables<SUB>& T, co
     groups = __builtin_amdgcn_alignbit(groups, below(a1[m]), 31);
     groups = __builtin_amdgcn_alignbit(groups, below(a0[m]), 31);
   }
-  if (!(yn < 60000.f)) groups = 0u;  // beyond the fp16 range (or not a number): fp64 search below
+  // beyond the fp16 range (||y||^2 above 58000), a codebook that is not finite, or not a number: fp64 search below
+  if (!(reach < 245.f)) groups = 0u;
   // rows of group g within the bound, as a bit mask
   auto rows_of = [&](int g) -> uint32_t {
     const float4* r0 = &T.n2c[0][g * SearchTables<SUB>::kRowStride];

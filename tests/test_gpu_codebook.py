@@ -57,3 +57,40 @@ def test_codebook_on_16_levels_matches_oracle(gpu_api, codebooks, sub):
     assert np.array_equal(codes.cpu().numpy(), code)
     lv = levels.cpu().numpy()
     assert lv[0] == mn and lv[1] == st
+
+
+@pytest.mark.parametrize("sub", [4, 8])
+def test_codebook_of_samples_with_a_far_outlier(gpu_api, sub):
+    """Sums lose nothing to one sample 2^50 times the others (sums in units of the largest sample would)."""
+    import torch
+    print(f"case sub={sub}", flush=True)
+    samples = synth.codebook_samples(57, 4000, sub)
+    samples[2000, 1] = 2.0 ** 50
+    ref, _, _ = O.build_codebook(samples, 256, 3)
+    cb, _ = gpu_api.nsn_build_codebook(torch.from_numpy(samples).cuda(), 256, 3)
+    got, ref = cb.cpu().numpy(), ref.astype(np.float16)
+    rows = np.isfinite(ref).all(axis=1) & (np.abs(ref).max(axis=1) < 100)
+    assert rows.sum() >= 254
+    # both are single fp16 roundings of fp64 centroids that differ only by summation order
+    diff = np.abs(got[rows].view(np.int16).astype(np.int32) - ref[rows].view(np.int16).astype(np.int32))
+    assert diff.max() <= 1 and (diff == 0).mean() > 0.999
+
+
+@pytest.mark.parametrize("sub", [4, 8])
+def test_codebook_of_samples_that_are_not_finite(gpu_api, sub):
+    """Infinities and NaN go through the sums as they are: no distance to such a sample is a number below infinity, so it
+    belongs to the first codeword, and every other codeword is what the finite samples give."""
+    import torch
+    print(f"case sub={sub}", flush=True)
+    samples = synth.codebook_samples(58, 4000, sub)
+    finite = np.ones(len(samples), bool)
+    finite[[700, 900]] = False
+    x = samples[finite].astype(np.float64)
+    near = np.argmin(((x[:, None, :] - samples[None, :256].astype(np.float64)) ** 2).sum(axis=2), axis=1)
+    ref = np.stack([x[near == c].mean(axis=0) for c in range(256)]).astype(np.float16)
+    samples[700, 1], samples[900, 0] = np.nan, np.inf
+    cb, mse = gpu_api.nsn_build_codebook(torch.from_numpy(samples).cuda(), 256, 1)
+    got = cb.cpu().numpy()
+    assert np.isposinf(got[0, 0]) and np.isnan(got[0, 1]) and np.isfinite(got[0, 2:]).all() and not np.isfinite(mse)
+    diff = np.abs(got[1:].view(np.int16).astype(np.int32) - ref[1:].view(np.int16).astype(np.int32))
+    assert diff.max() <= 1 and (diff == 0).mean() > 0.999
