@@ -161,12 +161,8 @@ class CodedCache:
     block_table: torch.Tensor | None
 
     def c_struct(self) -> nsn_cache:
-        """The C view of the buffers as they are now (the structure is made anew only when one of them has moved)."""
-        bt = self.block_table
-        now = (self.codes.data_ptr(), self.norms.data_ptr(), self.means.data_ptr(), None if bt is None else bt.data_ptr())
-        if getattr(self, "_c_ptrs", None) != now:
-            self._c_ptrs, self._c_struct = now, nsn_cache(*now)
-        return self._c_struct
+        return nsn_cache(self.codes.data_ptr(), self.norms.data_ptr(), self.means.data_ptr(),
+                         _ptr(self.block_table))
 
 
 def alloc_cache(shape: nsn_shape, batch: int, device="cuda", block_table: torch.Tensor | None = None,
