@@ -433,10 +433,10 @@ def main() -> int:
                        and not args.pre_rope and args.side_bits == 16 and args.policy == "residual")
     traffic = MEASURED_TRAFFIC[args.workload] if default_options else None
     # encoder (prefill): bound by the vector ALUs.  Peak = 256 CUs x 64 lanes x 2.4 GHz lane-operations per
-    # second (packed fp32 is disabled in this build); the best-two selection over 256 distances alone needs
-    # 2.5 lane-operations per distance (index insertion, and min3 + med3 + min per pair), i.e. 2.5 x 8192 per token,
-    # kv head and tensor: counted as the algorithmic work
-    enc_lane_ops = encode_tokens_per_s * Hkv * 2 * (2.5 * (128 // sub) * 256)
+    # second (packed fp32 is disabled in this build); the nearest-codeword search alone takes about 280 of them per
+    # sub-vector (minima of groups of distances, then the listed groups in fp32): counted as the work
+    enc_lane_ops_per_token = Hkv * 2 * 280 * (128 // sub)
+    enc_lane_ops = encode_tokens_per_s * enc_lane_ops_per_token
     peak_lane_ops = 256 * 64 * 2.4e9
 
     result = {
@@ -483,10 +483,10 @@ def main() -> int:
                      "traffic": traffic["bytes"] if traffic else None,
                      "traffic_source": traffic["source"] if traffic else None,
                      "algorithmic_bytes": step_bytes},
-        "roofline_encode": {"bound": "alu", "kernel": "nsn::enc_quant_kernel (+ enc_stats_kernel, enc_means_kernel)",
+        "roofline_encode": {"bound": "alu", "kernel": "nsn::enc_kernel (+ enc_stats_kernel, enc_means_kernel)",
                             "achieved": round(enc_lane_ops / 1e12, 3), "peak": round(peak_lane_ops / 1e12, 2),
                             "unit": "Tlane-op/s", "frac": round(enc_lane_ops / peak_lane_ops, 4),
-                            "algorithmic_lane_ops_per_token": int(Hkv * 2 * 2.5 * (128 // sub) * 256),
+                            "algorithmic_lane_ops_per_token": enc_lane_ops_per_token,
                             "peak_derivation": "256 CUs x 64 lanes x 2.4 GHz, one fp32 operation per lane and clock"},
     }
     if flushes == 0 and args.policy == "residual":
