@@ -106,9 +106,9 @@ typedef struct nsn_shape {
   int32_t head_dim;   /* 128 */
   int32_t sub_dim;    /* 8 or 4 */
   int32_t n_codes;    /* 256, or 65536 with sub_dim 8: the sign + index format (see above) */
-  int32_t n_q_heads;  /* multiple of n_kv_heads; n_q_heads / n_kv_heads <= 8 (the decode kernel
-                         takes four query heads per kv head per launch: five to eight heads run
-                         as two launches, the second reading the cache again) */
+  int32_t n_q_heads;  /* multiple of n_kv_heads; n_q_heads / n_kv_heads <= 8 (a decode
+                         workgroup takes up to four query heads of a kv head: five to eight heads
+                         are two workgroups of one launch, each reading the cache) */
   int32_t n_kv_heads;
   int32_t group_size; /* G: tokens sharing one Shift mean; multiple of 64 (the paper uses 64),
                          or 0 = one group per sequence */

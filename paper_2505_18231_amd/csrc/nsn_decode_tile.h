@@ -23,7 +23,7 @@
 //     the accumulators are out_rot[head][channel] partial sums per 16-lane group.
 //   * the fp16 weights are p a^v / A with A a power of two >= every a^v seen so far (rescaled lazily like
 //     the running max), so the value contraction does not depend on the scale of V.
-// One workgroup per (split, kv head, sequence) - or, for batches of 128 units and more, one persistent
+// One workgroup per (split, unit) - or, where decode_tile_splits prices it lower, one persistent
 // workgroup per compute unit that takes an equal run of all groups (see the kernel's FLAT flag) - 8 waves,
 // one 64 KiB codebook table replicated per LDS bank group (conflict-free gathers: one v_perm_b32 forms the
 // address from a code byte).  Cache bytes are fetched two groups ahead into rotating register sets.  The fp16 residual (Sec. 3.2) is one more
