@@ -61,3 +61,27 @@ def test_noalloc_rejects_calls_beyond_its_scratch(gpu_api, codebooks):
     with pytest.raises(api.NsnError) as e:
         api.nsn_decode_attention_noalloc(shape, cb, q, kc, vc, lens, 8192, 0.1, 4, out=out)
     assert e.value.code == api.NSN_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("hq,hkv,sub", [(16, 8, 4), (40, 8, 8)])
+def test_noalloc_persistent_instance_by_a_loose_length_bound(gpu_api, hq, hkv, sub):
+    """17 sequences under a bound of 16384 tokens take the persistent instance (five query heads are two units each); the
+    same kernels in the same order of operations as with a caller's workspace: bit-identical."""
+    import torch
+    api = gpu_api
+    lens = [0, 1, 64, 65, 130, 300, 17, 256, 511, 77, 128, 5, 200, 333, 90, 400, 2049]
+    B, room = len(lens), 16384
+    print(f"case hq={hq} hkv={hkv} sub={sub}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(8)
+    shape = api.make_shape(sub, hq, hkv, room, 0)
+    cb = torch.randn((256, sub), generator=g, device="cuda").half()
+    kc, vc = api.alloc_cache(shape, B), api.alloc_cache(shape, B)
+    n = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    k, v = (torch.randn((B, hkv, max(lens), 128), generator=g, device="cuda").half() for _ in range(2))
+    api.nsn_encode(shape, cb, k, v, torch.zeros_like(n), n, kc, vc)
+    q = torch.randn((B, hq, 128), generator=g, device="cuda").half()
+    ref = api.nsn_decode_attention(shape, cb, q, kc, vc, n, room, 0.1, 0)
+    out = torch.full_like(ref, 7.0)
+    api.nsn_decode_attention_noalloc(shape, cb, q, kc, vc, n, room, 0.1, 0, out=out)
+    torch.cuda.synchronize()
+    assert torch.isfinite(ref).all() and torch.equal(out, ref)
