@@ -31,20 +31,22 @@ typedef float f16v __attribute__((ext_vector_type(16)));
 // v_permlane32_swap: the upper half of `a` changes places with the lower half of `b` (v_permlane16_swap: odd 16-lane
 // rows of `a` with even rows of `b`).  Written as instructions because the compiler's two-result builtins have
 // returned the first result twice; they read other lanes' registers, which needs two idle cycles after the
-// vector instruction that wrote them.
-__device__ __forceinline__ void swap32(uint32_t& a, uint32_t& b) {
-  asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+// vector instruction that wrote them.  So does a matrix instruction that reads a swapped register: the compiler keeps that
+// distance behind its own vector instructions but not behind asm, so the operand_ forms end with the two cycles.
+__device__ __forceinline__ void operand_swap32(uint32_t& a, uint32_t& b) {
+  asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
 }
 // four pairs at a time: one wait for all of them
-#define NSN_SWAP4(NAME, INSN)                                                                                     \
+#define NSN_SWAP4(NAME, INSN, AFTER)                                                                              \
   template <typename T>                                                                                           \
   __device__ __forceinline__ void NAME(T& a0, T& b0, T& a1, T& b1, T& a2, T& b2, T& a3, T& b3) {                  \
     static_assert(sizeof(T) == 4, "one register each");                                                           \
-    asm("s_nop 1\n\t" INSN " %0, %1\n\t" INSN " %2, %3\n\t" INSN " %4, %5\n\t" INSN " %6, %7"                     \
+    asm("s_nop 1\n\t" INSN " %0, %1\n\t" INSN " %2, %3\n\t" INSN " %4, %5\n\t" INSN " %6, %7" AFTER               \
         : "+v"(a0), "+v"(b0), "+v"(a1), "+v"(b1), "+v"(a2), "+v"(b2), "+v"(a3), "+v"(b3));                        \
   }
-NSN_SWAP4(swap32x4, "v_permlane32_swap_b32")
-NSN_SWAP4(swap16x4, "v_permlane16_swap_b32")
+NSN_SWAP4(swap32x4, "v_permlane32_swap_b32", "")
+NSN_SWAP4(swap16x4, "v_permlane16_swap_b32", "")
+NSN_SWAP4(operand_swap32x4, "v_permlane32_swap_b32", "\n\ts_nop 1")
 #undef NSN_SWAP4
 
 // Minima of results 0..7 and 8..15 of a matrix instruction.  All results are positive, so their bit patterns order like
@@ -222,15 +224,15 @@ __device__ __forceinline__ Nearest search_nearest(const SearchTables<SUB>& T, co
   h4v na = {}, nb = {};
   if constexpr (SUB == 4) {
     uint32_t k0 = hi[0], k1 = hi[1], k2 = ONE1;
-    swap32x4(hi[0], k0, hi[1], k1, lo[0], k2, lo[1], one_n);
+    operand_swap32x4(hi[0], k0, hi[1], k1, lo[0], k2, lo[1], one_n);
     ba = words_h8(hi[0], hi[1], lo[0], lo[1]);
     bb = words_h8(k0, k1, k2, one_n);
   } else {
-    swap32x4(hi[0], lo[0], hi[1], lo[1], hi[2], lo[2], hi[3], lo[3]);
+    operand_swap32x4(hi[0], lo[0], hi[1], lo[1], hi[2], lo[2], hi[3], lo[3]);
     ba = words_h8(hi[0], hi[1], hi[2], hi[3]);
     bb = words_h8(lo[0], lo[1], lo[2], lo[3]);
     uint32_t one_nb = one_n;
-    swap32(one_n, one_nb);  // n of the set's column in either half of the wave
+    operand_swap32(one_n, one_nb);  // n of the set's column in either half of the wave
     if constexpr (EXACT16) {
       typedef uint32_t u2v __attribute__((ext_vector_type(2)));
       na = __builtin_bit_cast(h4v, u2v{ONE1, one_n}), nb = __builtin_bit_cast(h4v, u2v{ONE1, one_nb});
