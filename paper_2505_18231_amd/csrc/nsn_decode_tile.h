@@ -1216,26 +1216,37 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
   if (wslot < n_grp) {
     int gi = wslot;
     arrange(S0);
-    if constexpr (LEGACY) {  // two register sets: the set that a group leaves takes the group after the next
+    // Legacy layout: two register sets; the set that a group leaves takes the group after the next.  (One plain loop per
+    // format: with the rotary batches as an outer loop of both, whose exit the inner one had taken already, the compiler
+    // made three nested loops of it and spilled 61 to 79 registers in the split instances of sign codes with 4-bit side
+    // information: 146.7 us for four launches of 8 x 8192 tokens, 82.2 so.)
+    if constexpr (ROPE) {
       while (true) {
-        if constexpr (ROPE) rope_compute();
+        rope_compute();
         k_gather(c0, S0, KA);
         k_gather(c1, S0, KB);
-        do {
-          process_group(c0, gi, S0, S1, S0);
-          gi += NW;
-          if (gi >= n_grp) break;
-          process_group(c1, gi, S1, S0, S1);
-          gi += NW;
-          if (gi >= n_grp) break;
-          if constexpr (ROPE) {
-            process_group(c2, gi, S0, S1, S0);
-            gi += NW;
-            if (gi >= n_grp) break;
-            process_group(c3, gi, S1, S0, S1);
-            gi += NW;
-          }
-        } while (!ROPE && gi < n_grp);
+        process_group(c0, gi, S0, S1, S0);
+        gi += NW;
+        if (gi >= n_grp) break;
+        process_group(c1, gi, S1, S0, S1);
+        gi += NW;
+        if (gi >= n_grp) break;
+        process_group(c2, gi, S0, S1, S0);
+        gi += NW;
+        if (gi >= n_grp) break;
+        process_group(c3, gi, S1, S0, S1);
+        gi += NW;
+        if (gi >= n_grp) break;
+      }
+    } else if constexpr (SGN) {
+      k_gather(c0, S0, KA);
+      k_gather(c1, S0, KB);
+      while (true) {
+        process_group(c0, gi, S0, S1, S0);
+        gi += NW;
+        if (gi >= n_grp) break;
+        process_group(c1, gi, S1, S0, S1);
+        gi += NW;
         if (gi >= n_grp) break;
       }
     } else {
