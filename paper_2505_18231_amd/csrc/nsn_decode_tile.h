@@ -893,8 +893,10 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
         valid[k] = tile_of_lane == wave && (16 * wave + 4 * rho + k) < rl;
         one[k] = valid[k] ? 1.f : 0.f;
       }
-#pragma unroll
-      for (auto& x : qo) x = 0.f;
+      // (by constant index: a loop by reference keeps the array in memory through the compiler's early passes, and the
+      // registers then came out so that the main loop waited for the loads of the groups ahead)
+      qo[0] = 0.f;
+      if constexpr (ROPE) qo[1] = qo[2] = qo[3] = 0.f;
       const h4 wop = softmax_step(sc, valid, false, one, zero, one, zero);
       // value rows: source lane (rho, k = n / 4, m = n % 4) reads token 4 rho + k of the tile, channels
       // [4 (4 X + m), +4); the transposing read hands lane (rho, m, e) four tokens of channel 16 X + 4 m + e

@@ -9,6 +9,7 @@ import pytest
 from paper_2505_18231_amd import build
 
 # sub_dim, waves, powers of two, paged, persistent, 4-bit side information, sign + index, rotary
+ONE_SPLIT = ["8,8,true,false,false,false", "4,8,true,false,false,false", "4,8,false,false,false,true"]
 SIGN_4BIT = ["8,8,false,false,false,true,true,false", "8,8,false,true,false,true,true,false"]
 
 
@@ -29,3 +30,31 @@ def test_sign_codes_with_4bit_side_information_spill_no_vector_registers(tmp_pat
     text = _listing(SIGN_4BIT, tmp_path)
     spilled = [int(n) for n in re.findall(r"\.vgpr_spill_count:\s+(\d+)", text)]
     assert spilled == [0] * len(SIGN_4BIT), spilled
+
+
+def _loop_loads(kernel):
+    """4-byte load targets of the main loop (Shift vectors, read only where the Shift group changes) with the number of vector
+    and LDS instructions of the loop that write the same register."""
+    code = [line.split(";")[0].strip() for line in kernel]
+    code = [line for line in code if line]
+    first = next(i for i, line in enumerate(code) if line.startswith("v_mfma_f32_16x16x32"))
+    last = max(i for i, line in enumerate(code) if line.startswith("v_mfma_f32_4x4x4"))
+    targets = {line.split()[1].rstrip(",") for line in code[first:last] if line.startswith("global_load_dword ")}
+    writes = dict.fromkeys(targets, 0)
+    for line in code[first:last]:
+        if line.startswith(("v_", "ds_read")):
+            args = [a.strip() for a in line.split(None, 1)[1].split(",")]
+            for reg in args[:2] if "swap" in line else args[:1]:
+                if reg in writes:
+                    writes[reg] += 1
+    return writes
+
+
+def test_load_targets_of_the_main_loop_hold_nothing_else(tmp_path):
+    """A load's target that is a temporary too makes the loop wait for that load, and with it for every load asked for ahead.
+    (Ten writes: the code where the Shift group changes takes the value from its register and may reuse it there.)"""
+    kernels = re.split(r"^_Z\S*dec_tile_kernel\S*:", _listing(ONE_SPLIT, tmp_path), flags=re.M)[1:]
+    assert len(kernels) == len(ONE_SPLIT)
+    for kernel in kernels:
+        writes = _loop_loads(kernel.split(".Lfunc_end")[0].splitlines())
+        assert len(writes) >= 6 and max(writes.values()) <= 10, writes
