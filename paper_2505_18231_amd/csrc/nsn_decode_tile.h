@@ -270,7 +270,11 @@ constexpr int kSegCost = 32;
 // 16 rho + 4 t + k (tiled layout: 16 t + 4 rho + k), a lane loads token 16 rho + 4 c + k's key bytes and sixteen tokens of
 // one value row, and arrange() exchanges words between 16-lane groups (four swaps) and bytes between lanes (twenty
 // instructions), once per group.
-template <int SUB, int NW, bool POW2, bool PAGED, bool FLAT, bool DQ, bool SGN = false, bool ROPE = false>
+// MANY: a kv head may have more than four query heads.  The others do without the unit arithmetic (with it at run time
+// for all, four launches of the ragged paged batch of 24 sequences took 92.4 instead of 91.5 us, of 131072 1-bit tokens 0.5
+// to 1 % more).
+template <int SUB, int NW, bool POW2, bool PAGED, bool FLAT, bool DQ, bool SGN = false, bool ROPE = false,
+          bool MANY = SGN || ROPE>
 __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __half* __restrict__ codebook,
                                                            const __half* __restrict__ q, CacheView kc, CacheView vc,
                                                            const int32_t* __restrict__ seq_lens, int batch,
@@ -288,8 +292,8 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
 
   // Five to eight query heads (n_rep) of a kv head are two units of up to four: unit head hu, kv head hu >> two
-  const int two = n_rep > 4 ? 1 : 0;
-  auto heads_of = [&](int hu) { return min(4, n_rep - 4 * (hu & two)); };
+  const int two = MANY && n_rep > 4 ? 1 : 0;
+  auto heads_of = [&](int hu) { return MANY ? min(4, n_rep - 4 * (hu & two)) : n_rep; };
   const int tid = threadIdx.x, lane0 = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int cap_tokens = g.page_tokens * g.pages_per_seq;
@@ -418,7 +422,7 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
     if constexpr (!PAGED) {
       kbase = vbase = (int64_t)(b * g.n_kv_heads + h) * g.page_tokens + tg;
     } else {
-      const bool shifts = POW2 || g.page_shift >= 0;
+      const bool shifts = POW2 || (LEGACY && g.page_shift >= 0);
       const int page = shifts ? tg >> g.page_shift : tg / g.page_tokens;
       const int tin = shifts ? tg & (g.page_tokens - 1) : tg - page * g.page_tokens;
       if ((unsigned)(page - win0) >= 64u) {  // wave-uniform
@@ -432,7 +436,7 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
   };
   auto shift_group = [&](int tg) -> int {
     if (g.group_size <= 0) return 0;
-    return POW2 || g.group_shift >= 0 ? tg >> g.group_shift : tg / g.group_size;
+    return POW2 || (LEGACY && g.group_shift >= 0) ? tg >> g.group_shift : tg / g.group_size;
   };
   // tg: first token of the group (a multiple of 64 inside the cache).  A group that does not exist (`real` false:
   // the wave's list of groups has ended) is loaded all the same, from the first bytes of every array (one cache line
@@ -1443,7 +1447,8 @@ struct Call {
   hipStream_t stream;
 };
 
-template <int SUB, int NW, bool POW2, bool PAGED, bool FLAT, bool DQ, bool SGN = false, bool ROPE = false>
+template <int SUB, int NW, bool POW2, bool PAGED, bool FLAT, bool DQ, bool SGN = false, bool ROPE = false,
+          bool MANY = SGN || ROPE>
 static int launch_one(const Call& c) {
   const Geometry& g = c.g;
   int n_splits = c.n_splits;
@@ -1454,7 +1459,7 @@ static int launch_one(const Call& c) {
     // the gathers address the codebook table by absolute LDS address: it must start at 0, i.e. the
     // kernel may not own any static LDS in front of its dynamic block
     hipFuncAttributes fa;
-    const void* fn = reinterpret_cast<const void*>(dec_tile_kernel<SUB, NW, POW2, PAGED, FLAT, DQ, SGN, ROPE>);
+    const void* fn = reinterpret_cast<const void*>(dec_tile_kernel<SUB, NW, POW2, PAGED, FLAT, DQ, SGN, ROPE, MANY>);
     if (hipFuncGetAttributes(&fa, fn) != hipSuccess || fa.sharedSizeBytes != 0) return (int)NSN_ERR_HIP;
     if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SM::kBytesRes) != hipSuccess)
       return (int)NSN_ERR_HIP;
@@ -1478,14 +1483,40 @@ static int launch_one(const Call& c) {
     per = (((c.max_seq_len + n_splits - 1) / n_splits) + 63) & ~63;
     grid = dim3(n_splits, unit_heads, c.batch);
   }
-  dec_tile_kernel<SUB, NW, POW2, PAGED, FLAT, DQ, SGN, ROPE><<<grid, NW * 64, smem, c.stream>>>(
+  dec_tile_kernel<SUB, NW, POW2, PAGED, FLAT, DQ, SGN, ROPE, MANY><<<grid, NW * 64, smem, c.stream>>>(
       g, (const __half*)c.codebook, (const __half*)c.q, c.kc, c.vc, c.seq_lens, c.batch, c.scale * 1.44269504088896340736f,
       n_splits, per, partial, counters, c.res, n_rep, c.out);
   return hipGetLastError() == hipSuccess ? NSN_OK : NSN_ERR_HIP;
 }
 
+// the instance of the tiled code layout that fits the call
+template <bool MANY>
+static int launch_tiled(const Call& c, int sub_dim) {
+  const Geometry& g = c.g;
+  const bool pow2 = (g.group_size <= 0 || g.group_shift >= 0) && (!g.paged || g.page_shift >= 0);
+  auto with_flags = [&](auto sub, auto flat, auto dq) {
+    constexpr int kSub = decltype(sub)::value;
+    constexpr bool kFlat = decltype(flat)::value, kDq = decltype(dq)::value;
+    if (g.paged)
+      return pow2 ? launch_one<kSub, 8, true, true, kFlat, kDq, false, false, MANY>(c)
+                  : launch_one<kSub, 8, false, true, kFlat, kDq, false, false, MANY>(c);
+    return pow2 ? launch_one<kSub, 8, true, false, kFlat, kDq, false, false, MANY>(c)
+                : launch_one<kSub, 8, false, false, kFlat, kDq, false, false, MANY>(c);
+  };
+  auto with_sub = [&](auto flat) {
+    if (g.dq)
+      return sub_dim == 4 ? with_flags(std::integral_constant<int, 4>{}, flat, std::true_type{})
+                          : with_flags(std::integral_constant<int, 8>{}, flat, std::true_type{});
+    return sub_dim == 4 ? with_flags(std::integral_constant<int, 4>{}, flat, std::false_type{})
+                        : with_flags(std::integral_constant<int, 8>{}, flat, std::false_type{});
+  };
+  // n_splits == kSplitsFlat: the persistent instance that cuts the list of all groups into equal runs
+  return c.n_splits == kSplitsFlat ? with_sub(std::true_type{}) : with_sub(std::false_type{});
+}
+
 }  // namespace tile
 
+int decode_many_heads_launch(const tile::Call& c, int sub_dim);  // tiled code layout, five to eight query heads per kv head
 int decode_rows_launch(const tile::Call& c, int sub_dim);  // the instances of the legacy code layout
 
 }  // namespace nsn

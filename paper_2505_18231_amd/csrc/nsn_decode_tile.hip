@@ -1,5 +1,5 @@
 // Host side of the matrix-core decode attention: workspace, split choice, and the kernel instances of the tiled code layout
-// (index-only codes, keys taken as given).
+// (index-only codes, keys taken as given) for up to four query heads per kv head.
 #include "nsn_decode_tile.h"
 
 namespace nsn {
@@ -65,23 +65,7 @@ int decode_tile_launch(const nsn_shape& s, const void* codebook, const void* q, 
     c.res = {static_cast<const __half*>(residual->k_fp16), static_cast<const __half*>(residual->v_fp16),
              residual->lens, residual->capacity};
   if (!g.tiled) return decode_rows_launch(c, s.sub_dim);
-  const bool pow2 = (g.group_size <= 0 || g.group_shift >= 0) && (!g.paged || g.page_shift >= 0);
-  auto with_flags = [&](auto sub, auto flat, auto dq) {
-    constexpr int kSub = decltype(sub)::value;
-    constexpr bool kFlat = decltype(flat)::value, kDq = decltype(dq)::value;
-    if (g.paged)
-      return pow2 ? tile::launch_one<kSub, 8, true, true, kFlat, kDq>(c) : tile::launch_one<kSub, 8, false, true, kFlat, kDq>(c);
-    return pow2 ? tile::launch_one<kSub, 8, true, false, kFlat, kDq>(c) : tile::launch_one<kSub, 8, false, false, kFlat, kDq>(c);
-  };
-  auto with_sub = [&](auto flat) {
-    if (g.dq)
-      return s.sub_dim == 4 ? with_flags(std::integral_constant<int, 4>{}, flat, std::true_type{})
-                            : with_flags(std::integral_constant<int, 8>{}, flat, std::true_type{});
-    return s.sub_dim == 4 ? with_flags(std::integral_constant<int, 4>{}, flat, std::false_type{})
-                          : with_flags(std::integral_constant<int, 8>{}, flat, std::false_type{});
-  };
-  // n_splits == kSplitsFlat: the persistent instance that cuts the list of all groups into equal runs
-  return n_splits == kSplitsFlat ? with_sub(std::true_type{}) : with_sub(std::false_type{});
+  return s.n_q_heads / s.n_kv_heads > 4 ? decode_many_heads_launch(c, s.sub_dim) : tile::launch_tiled<false>(c, s.sub_dim);
 }
 
 }  // namespace nsn

@@ -58,3 +58,13 @@ def test_load_targets_of_the_main_loop_hold_nothing_else(tmp_path):
     for kernel in kernels:
         writes = _loop_loads(kernel.split(".Lfunc_end")[0].splitlines())
         assert len(writes) >= 6 and max(writes.values()) <= 10, writes
+
+
+def test_up_to_four_query_heads_pay_nothing_for_two_units(tmp_path):
+    """The arithmetic of two units per kv head (five to eight query heads) is in the instances of such calls only."""
+    flags = "8,true,true,true,false,false,false"
+    for sub in (4, 8):
+        kernels = re.split(r"^_Z\S*dec_tile_kernel\S*:", _listing([f"{sub},{flags},false", f"{sub},{flags},true"], tmp_path),
+                           flags=re.M)[1:]
+        few, many = (len(re.findall(r"^\s+s_(?!nop|waitcnt|barrier|branch)", k.split(".Lfunc_end")[0], flags=re.M)) for k in kernels)
+        assert few < many, (few, many)
