@@ -23,21 +23,22 @@ template <int SUB>
 constexpr int kSumThreads = SUB == 4 ? 1024 : 768;
 constexpr int kSumMost = 4096;  // samples added up in LDS at a time
 
-// workspace: centroids, error sum of every workgroup, cosine sum of every cluster (K-Means: sum of |sample| of every
-// workgroup of cb_max_kernel), largest |sample| (bits), then per workgroup of the accumulation the member sums [256][SUB] and the member counts [256]
+// workspace: centroids, error sum of every workgroup, cosine sum of every cluster, the samples' range (largest |sample|,
+// smallest but zero less one, as fp32 bits), then per workgroup of the accumulation the member sums [256][SUB] and the
+// member counts [256]
 template <int SUB>
 struct CodebookWs {
   double* centroids;
   double* block_err;
   double* cos_sum;
-  uint32_t* max_bits;
+  uint32_t* range_bits;
   double* sums;
   double* counts;
   explicit CodebookWs(void* ws)
       : centroids(static_cast<double*>(ws)),
         block_err(centroids + kCodes * SUB),
         cos_sum(block_err + kSumBlocks),
-        max_bits(reinterpret_cast<uint32_t*>(cos_sum + kCodes)),
+        range_bits(reinterpret_cast<uint32_t*>(cos_sum + kCodes)),
         sums(cos_sum + kCodes + 2),
         counts(sums + (size_t)kSumBlocks * kCodes * SUB) {}
   static size_t bytes() {
@@ -45,43 +46,43 @@ struct CodebookWs {
   }
 };
 
-// start of a run: the centroids (the first samples, or the codebook at hand), no largest sample yet
+// start of a run: the centroids (the first samples, or the codebook at hand), no sample in the range yet
 template <typename T>
 __global__ void cb_start_kernel(const T* __restrict__ from, double* __restrict__ centroids, int n_elems,
-                                uint32_t* __restrict__ max_bits) {
+                                uint32_t* __restrict__ range_bits) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n_elems) centroids[i] = (double)(float)from[i];
-  if (i == 0) *max_bits = 0u;
+  if (i == 0) range_bits[0] = 0u, range_bits[1] = 0xffffffffu;
 }
 
-// Largest |sample| of the set, as fp32 bits (their order is that of the values; infinities and NaN are above all of
-// them), and a quarter of the sum of |sample| per workgroup, in one order.  One atomic per workgroup: with one per wave of a
-// 4096-wave launch they took 45 of 56 us.
-constexpr int kMaxThreads = 1024, kMaxBlocks = 256;
-static_assert(kMaxBlocks == kCodes, "one sum per workgroup in cos_sum");
+// Largest |sample| of the set and the smallest that is not zero, less one, as fp32 bits (their order is that of the values;
+// infinities and NaN are above all of them, and zeros less one as well).  Two atomics per workgroup: with one per wave of
+// a 4096-wave launch they took 45 of 56 us.
+constexpr int kRangeThreads = 1024, kRangeBlocks = 256;
 typedef float row4 __attribute__((ext_vector_type(4), aligned(4)));  // (the samples are aligned as floats are)
-__global__ __launch_bounds__(kMaxThreads) void cb_max_kernel(const float* __restrict__ samples, int64_t n_rows,
-                                                             uint32_t* __restrict__ max_bits,
-                                                             double* __restrict__ abs_sum) {
-  __shared__ uint32_t red[kMaxThreads / 64];
-  __shared__ double red_sum[kMaxThreads / 64];
-  uint32_t m = 0u;
-  double sum = 0.0;
+__global__ __launch_bounds__(kRangeThreads) void cb_range_kernel(const float* __restrict__ samples, int64_t n_rows,
+                                                                 uint32_t* __restrict__ range_bits) {
+  __shared__ uint32_t red[2][kRangeThreads / 64];
+  uint32_t most = 0u, least = 0xffffffffu;
 #pragma unroll 4
-  for (int64_t i = (int64_t)blockIdx.x * kMaxThreads + threadIdx.x; i < n_rows; i += (int64_t)gridDim.x * kMaxThreads) {
+  for (int64_t i = (int64_t)blockIdx.x * kRangeThreads + threadIdx.x; i < n_rows; i += (int64_t)gridDim.x * kRangeThreads) {
     const row4 v = reinterpret_cast<const row4*>(samples)[i];
-    m = max(m, max(max(__float_as_uint(fabsf(v.x)), __float_as_uint(fabsf(v.y))),
-                   max(__float_as_uint(fabsf(v.z)), __float_as_uint(fabsf(v.w)))));
-    sum += (double)((0.25f * fabsf(v.x) + 0.25f * fabsf(v.y)) + (0.25f * fabsf(v.z) + 0.25f * fabsf(v.w)));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t bits = __float_as_uint(fabsf(v[k]));
+      most = max(most, bits), least = min(least, bits - 1u);
+    }
   }
-  for (int k = 1; k < 64; k <<= 1) m = max(m, (uint32_t)__shfl_xor((int)m, k, 64));
-  sum = xor_sum(sum, 64);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m, red_sum[threadIdx.x >> 6] = sum;
+  for (int k = 1; k < 64; k <<= 1) {
+    most = max(most, (uint32_t)__shfl_xor((int)most, k, 64));
+    least = min(least, (uint32_t)__shfl_xor((int)least, k, 64));
+  }
+  if ((threadIdx.x & 63) == 0) red[0][threadIdx.x >> 6] = most, red[1][threadIdx.x >> 6] = least;
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < kMaxThreads / 64; ++w) m = max(m, red[w]), sum += red_sum[w];
-    atomicMax(max_bits, m);
-    abs_sum[blockIdx.x] = sum;
+    for (int w = 1; w < kRangeThreads / 64; ++w) most = max(most, red[0][w]), least = min(least, red[1][w]);
+    atomicMax(range_bits, most);
+    atomicMin(range_bits + 1, least);
   }
 }
 
@@ -108,11 +109,12 @@ __device__ __forceinline__ double exact_dist(const double* __restrict__ centroid
 // Assignment and, in the same pass over the samples, member sums (ERR false) or the squared error (ERR true).
 //
 // The sums are formed in LDS by integer atomics on fixed-point values: integer addition is associative, so the result
-// does not depend on the order in which lanes and waves arrive.  A value enters with its last place at 2^-50 of the
-// power of two above the largest |sample| and at most kSumMost values are added before the LDS sums move to fp64
-// registers: no overflow of 63 bits, and a rounding error per value that is below that of the fp64 running sum
-// it stands for, where the samples are of one size (fixed_point_fits below; others go to cb_ordered_kernel).  Adding 1.5 * 2^52 puts the fixed-point value into the low bits of the fp64 pattern;
-// the patterns are added as they are and the member count times the constant's pattern comes off at the end.
+// does not depend on the order in which lanes and waves arrive.  Every value enters exactly.  With 2^ex the power of two
+// above the largest |sample|, values from 2^(ex - 27) on are multiples of 2^(ex - 50); the smaller ones (one normal value in
+// twenty million) have sums of their own in units of 2^(ex - 77), which hold everything from 2^(ex - 54) on (sets with
+// smaller values go to cb_ordered_kernel: sums_fit below).  At most kSumMost values are added before the LDS sums move
+// to fp64 registers: no overflow of 63 bits.  Adding 1.5 * 2^52 puts the fixed-point value into the low bits of the fp64
+// pattern; the patterns are added as they are and the member count times the constant's pattern comes off at the end.
 // (The form this replaces wrote the assignments out and let one workgroup per cluster look through all of them:
 // 270 us per iteration of 2^20 4-dim samples.)
 template <int SUB, bool ERR>
@@ -123,7 +125,7 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_accumulate_kernel(const f
   constexpr double kMagic = 6755399441055744.0;      // 1.5 * 2^52
   __shared__ SearchTables<SUB> T;
   __shared__ double cx[kCodes][SUB];
-  __shared__ unsigned long long acc[ERR ? 1 : SUB][kCodes];
+  __shared__ unsigned long long acc[ERR ? 1 : SUB][kCodes], acc_small[ERR ? 1 : SUB][kCodes];
   __shared__ uint32_t cnt[kCodes];
   __shared__ double red[NT / 64];
   const int tid = threadIdx.x;
@@ -139,16 +141,23 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_accumulate_kernel(const f
   SearchRegs<SUB, false> R;
   search_setup<SUB, false>(T, R, tid, [&](int i) { return ws.centroids[tid * SUB + i]; });
   for (int i = tid; i < kCodes * SUB; i += NT) (&cx[0][0])[i] = ws.centroids[i];
-  double fixed = 1.0;
+  int ex = 0;
+  uint32_t small = 0u;  // twice the bits of 2^(ex - 27) where the set holds smaller values (but zero)
   if constexpr (!ERR) {
-    int ex = 0;
-    const float mx = __uint_as_float(*ws.max_bits);
+    const float mx = __uint_as_float(ws.range_bits[0]);
     if (mx > 0.f && mx < INFINITY) (void)frexpf(mx, &ex);  // mx < 2^ex
-    fixed = ldexp(1.0, 50 - ex);
+    ex = __builtin_amdgcn_readfirstlane(ex);
+    // (from ex = -100 down every fp32 value is a multiple of the unit)
+    const uint32_t from = ex > -100 ? (uint32_t)(ex - 27 + 127) << 23 : 0u;
+    if (ws.range_bits[1] + 1u < from && ws.range_bits[1] != 0xffffffffu) small = 2u * from;
+    small = __builtin_amdgcn_readfirstlane(small);
   }
+  const double fixed = ldexp(1.0, 50 - ex);
   auto clear = [&]() {
     if constexpr (!ERR) {
       for (int i = tid; i < kCodes * SUB; i += NT) (&acc[0][0])[i] = 0ull;
+      if (small)
+        for (int i = tid; i < kCodes * SUB; i += NT) (&acc_small[0][0])[i] = 0ull;
       if (tid < kCodes) cnt[tid] = 0u;
     }
   };
@@ -171,6 +180,20 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_accumulate_kernel(const f
       if constexpr (ERR) {
         if (valid) err += exact_dist<SUB>(cx[code], x);
       } else if (valid) {
+        if (small) {
+          uint32_t least = 0xffffffffu;
+#pragma unroll
+          for (int i = 0; i < SUB; ++i) least = min(least, __float_as_uint(x[i]) << 1);
+          if (least < small) {
+#pragma unroll
+            for (int i = 0; i < SUB; ++i) {
+              if ((__float_as_uint(x[i]) << 1) < small) {
+                atomicAdd(&acc_small[i][code], (unsigned long long)(long long)((double)x[i] * (fixed * 0x1p27)));
+                x[i] = 0.f;
+              }
+            }
+          }
+        }
 #pragma unroll
         for (int i = 0; i < SUB; ++i)
           atomicAdd(&acc[i][code], (unsigned long long)__double_as_longlong(fma((double)x[i], fixed, kMagic)));
@@ -184,7 +207,9 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_accumulate_kernel(const f
         const int e = min(tid + k * NT, kCodes * SUB - 1);
         const unsigned long long s =
             acc[e % SUB][e / SUB] - (unsigned long long)cnt[e / SUB] * (unsigned long long)__double_as_longlong(kMagic);
-        own[k] += (double)(long long)s;
+        double t = (double)(long long)s;
+        if (small) t += (double)(long long)acc_small[e % SUB][e / SUB] * 0x1p-27;
+        own[k] += t;
       }
       if (tid < kCodes) own_n += (double)cnt[tid];
       __syncthreads();
@@ -503,15 +528,17 @@ size_t codebook_workspace_bytes(int sub_dim, int64_t) {
   return sub_dim == 8 ? CodebookWs<8>::bytes() : CodebookWs<4>::bytes();
 }
 
-// A value enters the fixed-point sums with an error of 2^-50 of the largest |sample|, which for samples far below it is
-// more than fp64 sums have.  Up to 2^10 times the mean |sample| (normal samples: about 6) it is 2^-40 of the mean;
-// sets with rarer, larger values, infinities or NaN are added in fp64 instead.
-static bool fixed_point_fits(uint32_t max_bits, const double* abs_sum, int64_t n_elems) {
-  float largest;
-  memcpy(&largest, &max_bits, sizeof(largest));
-  double sum = 0.0;
-  for (int i = 0; i < kMaxBlocks; ++i) sum += abs_sum[i];
-  return std::isfinite(largest) && (double)largest * (double)n_elems <= 1024.0 * 4.0 * sum;
+// Every sample enters the fixed-point sums exactly from 2^-54 of the power of two above the largest on; sets with
+// smaller ones (but zero), infinities or NaN are added in fp64 instead.
+static bool sums_fit(const uint32_t (&range_bits)[2]) {
+  const uint32_t least_bits = range_bits[1] + 1u;  // (0: there are zeros only)
+  float largest, least;
+  memcpy(&largest, &range_bits[0], sizeof(largest));
+  memcpy(&least, &least_bits, sizeof(least));
+  if (!std::isfinite(largest)) return false;
+  int ex = 0;
+  (void)std::frexp(largest, &ex);
+  return least_bits == 0u || (double)least >= std::ldexp(1.0, ex - 54);
 }
 
 template <int SUB>
@@ -520,12 +547,12 @@ static int codebook_run_t(const float* samples, int64_t n, int iters, void* code
   const CodebookWs<SUB> ws(workspace);
   constexpr int n_elems = kCodes * SUB;
   struct {
-    double err[kSumBlocks], abs_sum[kMaxBlocks];
-    uint32_t max_bits, unused;
+    double err[kSumBlocks], unused[kCodes];
+    uint32_t range_bits[2];
   } host;
   auto run = [&](bool fixed) -> int {
-    cb_start_kernel<<<(n_elems + 255) / 256, 256, 0, stream>>>(samples, ws.centroids, n_elems, ws.max_bits);
-    cb_max_kernel<<<kMaxBlocks, kMaxThreads, 0, stream>>>(samples, n * (SUB / 4), ws.max_bits, ws.cos_sum);
+    cb_start_kernel<<<(n_elems + 255) / 256, 256, 0, stream>>>(samples, ws.centroids, n_elems, ws.range_bits);
+    cb_range_kernel<<<kRangeBlocks, kRangeThreads, 0, stream>>>(samples, n * (SUB / 4), ws.range_bits);
     for (int it = 0; it < iters; ++it) {
       if (fixed)
         cb_accumulate_kernel<SUB, false><<<kSumBlocks, kSumThreads<SUB>, 0, stream>>>(samples, n, ws);
@@ -536,13 +563,13 @@ static int codebook_run_t(const float* samples, int64_t n, int iters, void* code
     km_round_kernel<<<(n_elems + 255) / 256, 256, 0, stream>>>(ws.centroids, static_cast<__half*>(codebook_out), n_elems);
     cb_accumulate_kernel<SUB, true><<<kSumBlocks, kSumThreads<SUB>, 0, stream>>>(samples, n, ws);
     if (hipGetLastError() != hipSuccess) return NSN_ERR_HIP;
-    // error sums, sums of |sample| and the largest lie next to each other
+    // error sums, cosine sums (not used here) and the range lie next to each other
     if (hipMemcpyAsync(&host, ws.block_err, sizeof(host), hipMemcpyDeviceToHost, stream) != hipSuccess) return NSN_ERR_HIP;
     return hipStreamSynchronize(stream) == hipSuccess ? NSN_OK : NSN_ERR_HIP;
   };
   // (the range comes back with the error sums, so that ordinary samples pay nothing for the question)
   int rc = run(true);
-  if (rc == NSN_OK && iters > 0 && !fixed_point_fits(host.max_bits, host.abs_sum, n * SUB)) rc = run(false);
+  if (rc == NSN_OK && iters > 0 && !sums_fit(host.range_bits)) rc = run(false);
   if (rc != NSN_OK) return rc;
   if (mse_host) {
     double tot = 0.0;
@@ -574,7 +601,7 @@ static int finetune_run_t(const float* samples, int64_t n, int iters, double lr,
     return NSN_OK;
   };
   cb_start_kernel<<<(n_elems + 255) / 256, 256, 0, stream>>>(static_cast<const __half*>(codebook_io), ws.centroids, n_elems,
-                                                             ws.max_bits);
+                                                             ws.range_bits);
   int rc = NSN_OK;
   double before = 0.0, after = 0.0;
   if (cos_host && (rc = mean_cos(&before)) != NSN_OK) return rc;

@@ -94,3 +94,43 @@ def test_codebook_of_samples_that_are_not_finite(gpu_api, sub):
     assert np.isposinf(got[0, 0]) and np.isnan(got[0, 1]) and np.isfinite(got[0, 2:]).all() and not np.isfinite(mse)
     diff = np.abs(got[1:].view(np.int16).astype(np.int32) - ref[1:].view(np.int16).astype(np.int32))
     assert diff.max() <= 1 and (diff == 0).mean() > 0.999
+
+
+@pytest.mark.parametrize("sub", [4, 8])
+def test_member_sums_lose_nothing_to_larger_samples(gpu_api, sub):
+    """K-Means sums of samples whose sizes differ by up to 2^54 within one set: a dimension 10^13 times smaller than the
+    others, and samples 10^9 times smaller.  The sums of a workgroup's members are exact until they are rounded to fp64, twice
+    at most (two units of fixed point), so that a cluster's total over the workgroups is within 3 x 2^-53 of the
+    sum of their absolute values (adding in fp64 one by one would be within the number of members times that)."""
+    import math
+
+    import torch
+    print(f"case sub={sub}", flush=True)
+    samples = synth.codebook_samples(59, 4000, sub)
+    samples[:, sub - 1] *= np.float32(1e-13)
+    samples[1000:1500] *= np.float32(1e-9)
+    samples[2000, 0] = 7.0                                    # below 2^3
+    samples[2100:2110, sub - 1] = np.float32(2.0 ** -51)      # the smallest that the sums hold
+    samples[2200, 1] = 0.0
+    small = np.abs(samples[samples != 0])
+    samples[(samples != 0) & (np.abs(samples) < 2.0 ** -51)] = 0.0
+    assert small.max() < 8.0
+    c = samples[:256].astype(np.float64)
+    near = np.argmin(((samples[:, None, :].astype(np.float64) - c[None]) ** 2).sum(axis=2), axis=1)
+    x = torch.from_numpy(samples).cuda()
+    ws = torch.zeros(gpu_api.nsn_workspace_bytes(gpu_api.make_shape(sub, 1, 1, 64), gpu_api.NSN_OP_CODEBOOK, 1, len(samples)),
+                     dtype=torch.uint8, device="cuda")
+    gpu_api.nsn_build_codebook(x, 256, 1, workspace=ws)
+    # workspace: centroids, 256 + 256 + 2 doubles, then the sums [256 workgroups][256 codewords][sub]
+    doubles = ws.cpu().numpy().view(np.float64)
+    first = 256 * sub + 514
+    sums = doubles[first:first + 256 * 256 * sub].reshape(256, 256, sub)
+    worst = 0.0
+    for k in range(256):
+        for i in range(sub):
+            exact = math.fsum(samples[near == k, i].astype(np.float64))
+            bound = 3 * 2.0 ** -53 * float(np.abs(sums[:, k, i]).sum())
+            err = abs(math.fsum(sums[:, k, i].tolist() + [-exact]))
+            assert err <= bound, (k, i, exact, err, bound)
+            worst = max(worst, err / bound if bound else 0.0)
+    print(f"  largest share of the bound {worst:.3f}", flush=True)
