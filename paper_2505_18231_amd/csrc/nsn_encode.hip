@@ -400,7 +400,8 @@ __global__ __launch_bounds__(256, 2) void enc_kernel(EncArgs A) {
           in + (int64_t)min(block0 + 16 * wave + 4 * u + (lane >> 4), count - 1) * kHeadDim + 8 * (lane & 15));
   }
   SearchRegs<SUB, true> R;
-  search_setup<SUB, true>(T, R, tid, [&](int i) { return __half2float(A.codebook[tid * SUB + i]); });
+  // (a rotated token has norm sqrt(128): no sub-vector is longer than 11.4)
+  search_setup<SUB, true>(T, R, tid, [&](int i) { return __half2float(A.codebook[tid * SUB + i]); }, 4);
 
   if (pass1) {
     double acc[8];

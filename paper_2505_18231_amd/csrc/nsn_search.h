@@ -87,14 +87,18 @@ struct SearchRegs {
   // SUB = 8: second operand; EXACT16 codewords (fp16 values) have no low part, ||c||^2 alone takes four slots.  (The other
   // form is read from LDS in every search: 32 registers that would halve the number of waves.)
   h4v A2[SUB == 8 && EXACT16 ? 8 : 1];
-  float cm;     // largest norm of a scaled codeword
+  float cm;     // largest norm of a scaled codeword, at least 4
   float scale;  // s
 };
 
 // Fills the tables and the operands of every wave of the workgroup (256 threads or more, all of them call it).
-// get(i): element i of codeword `tid` (threads 0..255).
+// get(i): element i of codeword `tid` (threads 0..255).  s is 2^ex_most at most: a caller that knows the longest sub-vector
+// keeps it below 237 s this way.  Without that, sub-vectors 30 to 60 times as long as the longest codeword leave the fp16
+// range and take 256 fp64 distances per wave (encoder, 4096 tokens x 8 heads with codewords a hundredth of the usual: 495 us
+// instead of 54; K-Means of 2^20 samples whose first 256 are a fiftieth of the others: 100 to 270 us more in the first
+// iteration; there the samples have no bound that one far value would not spoil).
 template <int SUB, bool EXACT16, typename F>
-__device__ inline void search_setup(SearchTables<SUB>& T, SearchRegs<SUB, EXACT16>& R, int tid, F get) {
+__device__ inline void search_setup(SearchTables<SUB>& T, SearchRegs<SUB, EXACT16>& R, int tid, F get, int ex_most = 100) {
   typedef decltype(get(0)) real;
   const int lane = tid & 63;
   real own[SUB];
@@ -114,11 +118,12 @@ __device__ inline void search_setup(SearchTables<SUB>& T, SearchRegs<SUB, EXACT1
   int ex = 0;
   if (nm > 0.f && nm < INFINITY) {
     (void)frexpf(nm, &ex);  // nm = f 2^ex, f in [1/2, 1)
-    ex = min(max(3 - ex, -100), 100);
+    ex = min(max(3 - ex, -100), ex_most);
   }
   const float s = ldexpf(1.f, ex);
   R.scale = s;
   R.cm = nm * s * 1.0001f;
+  if (R.cm < 4.f) R.cm = 4.f;  // (the error bound counts on 16 at least for (|c| + |y|)^2)
   if (tid < kCodes) {
     float cn = 0.f, f[SUB];
     h8 a0 = {}, a1 = {}, a2 = {};

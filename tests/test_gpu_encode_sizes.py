@@ -69,3 +69,48 @@ def test_one_large_call_equals_sequence_by_sequence(gpu_api, codebooks, sub, sig
         for name in ("codes", "norms", "means"):
             assert torch.equal(getattr(x, name), getattr(y, name)), name
         assert int((x.codes != 0).sum()) > 0
+
+
+@pytest.mark.parametrize("sub,sign", [(4, False), (8, False), (8, True)])
+def test_codewords_of_any_length(gpu_api, codebooks, select_variant, sub, sign):
+    """Codewords a hundredth, down to a ten-thousandth, or a hundred times as long as the sub-vectors, and zero ones: the codes are those
+    of the fp32 scan with its fp64 decision; and short codewords take the same path as the usual ones (the fp64 search of whole
+    waves takes nine times as long; four is asked for)."""
+    import time
+
+    import torch
+    api = gpu_api
+    H, L = 8, 4096
+    g = torch.Generator(device="cuda").manual_seed(7)
+    k, v = (torch.randn((1, H, L, 128), generator=g, device="cuda").half() for _ in range(2))
+    k[0, 0, 5] = 0.0
+    k[0, 0, 6, 1:] = 0.0                                     # one channel: equal magnitudes after the rotation
+    base = torch.from_numpy(codebooks[sub].astype(np.float32)).cuda()
+    base = base.abs() if sign else base
+    shape = api.make_shape(sub, H, H, L, 64, sign_format=sign)
+    pos, n = torch.zeros(1, dtype=torch.int32, device="cuda"), torch.full((1,), L, dtype=torch.int32, device="cuda")
+    ws = torch.empty(max(1, api.nsn_workspace_bytes(shape, api.NSN_OP_ENCODE, 1, L)), dtype=torch.uint8, device="cuda")
+    took = {}
+    for factor in (1.0, 0.01, 0.001, 0.0001, 100.0, 0.0):
+        print(f"case sub={sub} sign={sign} factor={factor}", flush=True)
+        cb = (base * factor).half()
+        got = {}
+        for impl in ("mfma", "valu"):
+            select_variant("encode", impl)
+            caches = api.alloc_cache(shape, 1), api.alloc_cache(shape, 1)
+            api.nsn_encode(shape, cb, k, v, pos, n, *caches, workspace=ws)
+            torch.cuda.synchronize()
+            got[impl] = caches
+        for x, y in zip(got["mfma"], got["valu"]):
+            assert torch.equal(x.codes, y.codes) and torch.equal(x.norms, y.norms), factor
+        select_variant("encode", "mfma")
+        times = []
+        for _ in range(5):
+            start = time.perf_counter()
+            for _ in range(5):
+                api.nsn_encode(shape, cb, k, v, pos, n, *got["mfma"], workspace=ws)
+            torch.cuda.synchronize()
+            times.append(time.perf_counter() - start)
+        took[factor] = min(times)
+    print({f: f"{t / 5 * 1e6:.0f} us" for f, t in took.items()}, flush=True)
+    assert took[0.01] < 4 * took[1.0]
