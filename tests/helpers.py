@@ -3,6 +3,8 @@
 cache buffers."""
 from __future__ import annotations
 
+import ctypes as C
+
 import numpy as np
 
 D = 128
@@ -113,15 +115,52 @@ class HostCache:
 
     # device transfer -----------------------------------------------------------------------
     def to_device(self, api, shape, device="cuda"):
+        """On the device with room for shape.max_len tokens, which may be more than there are here: a sequence's tokens
+        come first in all arrays, whatever their length (further block-table entries: page 0)."""
         import torch
         bt = None if self.bt is None else torch.from_numpy(self.bt.astype(np.int32)).to(device)
-        return api.CodedCache(torch.from_numpy(self.codes).to(device), torch.from_numpy(self.norms).to(device),
-                              torch.from_numpy(self.means).to(device), bt)
+
+        def wide(t, dim, size):
+            out = torch.zeros((*t.shape[:dim], size, *t.shape[dim + 1:]), dtype=t.dtype, device=device)
+            out.narrow(dim, 0, t.shape[dim]).copy_(t)
+            return out
+        codes, norms, means = (torch.from_numpy(a).to(device) for a in (self.codes, self.norms, self.means))
+        if shape.max_len != self.max_len:
+            assert shape.max_len % self.max_len == 0 or shape.max_len % 768 == self.max_len % 768 == 0
+            means = wide(means, 2, n_groups(shape.max_len, self.G))
+            if bt is not None:
+                bt = wide(bt, 1, shape.max_len // self.page)
+            else:
+                codes, norms = (wide(t, 2, t.shape[2] * shape.max_len // self.max_len) for t in (codes, norms))
+        return api.CodedCache(codes, norms, means, bt)
 
     def from_device(self, dc):
         self.codes = dc.codes.cpu().numpy()
         self.norms = dc.norms.cpu().numpy()
         self.means = dc.means.cpu().numpy()
+
+
+def decode_splits(api, shape, batch: int, bound: int, n_splits: int = 0) -> int:
+    """The split count that a decode call of the matrix-core kernel resolves to (the library's own rule); 0: the persistent
+    instance."""
+    rule = api.lib()["_ZN3nsn18decode_tile_splitsERK9nsn_shapeiii"]  # nsn::decode_tile_splits(const nsn_shape&, int, int, int)
+    rule.restype, rule.argtypes = C.c_int, [C.c_void_p, C.c_int, C.c_int, C.c_int]
+    return rule(C.byref(shape), batch, bound, n_splits)
+
+
+def whole(lens) -> int:
+    """The longest length in whole pages and groups of 64, 128, 192 and 256 tokens."""
+    return max(768, (max(lens) + 767) // 768 * 768)
+
+
+def persistent_bound(api, batch: int, hq: int, hkv: int, at_least: int) -> int:
+    """The smallest length bound (multiples of 768 tokens) under which a
+    call of this many sequences and heads takes the persistent instance.  The bound sizes the launch only."""
+    bound = whole([at_least])
+    while decode_splits(api, api.make_shape(4, hq, hkv, 1 << 20, 0), batch, bound) != 0:
+        bound += 768
+        assert bound < 1 << 16, "no bound selects the persistent instance"
+    return bound
 
 
 def max_rel_err(out: np.ndarray, ref: np.ndarray) -> float:

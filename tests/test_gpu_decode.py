@@ -44,14 +44,14 @@ def oracle_out(kc, vc, q, lens, hq, hkv, cb, G, scale):
     return ref
 
 
-def gpu_out(api, kc, vc, q, lens, hq, hkv, sub, G, cb, max_len, scale, page=0, n_splits=0):
+def gpu_out(api, kc, vc, q, lens, hq, hkv, sub, G, cb, max_len, scale, page=0, n_splits=0, bound=None):
     import torch
-    shape = api.make_shape(sub, hq, hkv, max_len, G, page)
+    shape = api.make_shape(sub, hq, hkv, bound or max_len, G, page)
     dk, dv = kc.to_device(api, shape), vc.to_device(api, shape)
     cbd = torch.from_numpy(cb.astype(np.float16)).cuda()
     out = api.nsn_decode_attention(shape, cbd, torch.from_numpy(q).cuda(), dk, dv,
-                                   torch.tensor(lens, dtype=torch.int32).cuda(), max(max(lens), 0), scale,
-                                   n_splits)
+                                   torch.tensor(lens, dtype=torch.int32).cuda(),
+                                   max(max(lens), 0) if bound is None else bound, scale, n_splits)
     torch.cuda.synchronize()
     return out.cpu().numpy().astype(np.float64)
 
@@ -77,14 +77,17 @@ CASES = [
     ("long-2bit-eleven-waves", 2, 4, 1, [9000, 4100], 4, 64, 0, 2),   # splits of >= 4096 tokens: the 11-wave instance
     ("long-2bit-eleven-waves-mha", 1, 1, 1, [5000], 4, 0, 0, 1),
     ("long-1bit-eleven-waves", 2, 4, 1, [9000, 4100], 8, 64, 0, 2),   # the 8-dim form of the 11-wave instance
-    # 128 (sequence, kv head) units and automatic splitting: the persistent instance (equal runs of the list of
-    # all 64-token groups; short units share a run, long ones are cut by run boundaries; empty sequences)
+    # "flat": 128 (sequence, kv head) units and more under a length bound that selects the persistent instance (equal
+    # runs of the list of all 64-token groups; short units share a run, long ones are cut by run boundaries; empty sequences)
     ("flat-ragged-2bit", 16, 16, 8, FLAT_LENS, 4, 64, 0, 0),
     ("flat-paged-1bit", 16, 8, 8, FLAT_LENS[5:] + FLAT_LENS[:5], 8, 0, 256, 0),
     ("flat-gqa8-2bit-onegroup", 16, 64, 8, FLAT_LENS[::-1], 4, 0, 0, 0),
     ("flat-long-units-1bit", 16, 32, 8, [2100, 0, 70, 1500] + [40] * 12, 8, 128, 0, 0),
     # more than 64 sequences: the run boundaries are found across several 64-sequence blocks of lengths
     ("flat-paged64-long-1bit", 16, 8, 8, [4500, 0, 70, 5000] + [40] * 12, 8, 128, 64, 0),
+    ("flat-page192-2bit", 16, 8, 8, FLAT_LENS, 4, 0, 192, 0),     # no powers of two
+    ("flat-groups192-1bit", 16, 16, 8, FLAT_LENS, 8, 192, 0, 0),
+    ("all-empty", 16, 8, 8, [0] * 16, 4, 64, 0, 0),
     ("flat-all-empty", 16, 8, 8, [0] * 16, 4, 64, 0, 0),
     ("flat-130-sequences-1bit", 130, 2, 1, [(i * 37) % 200 for i in range(130)], 8, 0, 0, 0),
     ("flat-200-sequences-2bit-paged", 200, 4, 1, [(i * 53) % 300 for i in range(200)], 4, 64, 256, 0),
@@ -100,9 +103,11 @@ def test_decode_matches_oracle(gpu_api, codebooks, select_variant, impl, name, b
     print(f"case {name} impl={impl} lens={lens} sub={sub} G={G} page={page} splits={splits}", flush=True)
     cb = codebooks[sub]
     scale = 1.0 / math.sqrt(128)
-    kc, vc, q, max_len = build_case(100 + len(name), batch, hq, hkv, lens, sub, G, cb, page)
+    bound = helpers.persistent_bound(gpu_api, batch, hq, hkv, max(lens)) if name.startswith("flat") else None
+    kc, vc, q, max_len = build_case(100 + len(name), batch, hq, hkv, lens, sub, G, cb, page,
+                                max_len=helpers.whole(lens) if bound else None)
     ref = oracle_out(kc, vc, q, lens, hq, hkv, cb, G, scale)
-    out = gpu_out(gpu_api, kc, vc, q, lens, hq, hkv, sub, G, cb, max_len, scale, page, splits)
+    out = gpu_out(gpu_api, kc, vc, q, lens, hq, hkv, sub, G, cb, max_len, scale, page, splits, bound)
     for b in range(batch):
         if lens[b] == 0:
             assert np.all(out[b] == 0.0)
@@ -224,8 +229,8 @@ def test_one_dominant_token_among_many_low_score_tokens(gpu_api, codebooks, sele
 
 @pytest.mark.parametrize("seed", range(16))
 def test_persistent_instance_agrees_with_forced_splits_on_random_shapes(gpu_api, seed):
-    """The persistent instance (automatic split choice, 128 or more units) against the one-workgroup-per-split
-    instance (forced split count), which the oracle cases above cover, on random batch shapes: ragged lengths
+    """The persistent instance (automatic split choice under a length bound that selects it) against the
+    one-workgroup-per-split instance (forced split count), which the oracle cases above cover, on random batch shapes: ragged lengths
     with empty sequences, several kv-head counts, paged and contiguous caches, Shift groups, both code widths.
     Cache contents are random bytes (every byte is a valid code); the two launches differ in how the softmax
     partials are cut, so they agree to the rounding of the fp16 value weights, not bit for bit."""
@@ -244,8 +249,8 @@ def test_persistent_instance_agrees_with_forced_splits_on_random_shapes(gpu_api,
     lens[rng.integers(0, batch, size=3)] = 0
     lens[rng.integers(0, batch)] = top + 2000  # one long unit, cut by several run boundaries
     lens = [int(n) for n in lens]
-    max_len = ((max(lens) + 767) // 768) * 768
-    print(f"seed {seed}: batch={batch} hkv={hkv} r={r} sub={sub} page={page} G={G} top={top}", flush=True)
+    max_len = helpers.persistent_bound(api, batch, hkv * r, hkv, max(lens))
+    print(f"seed {seed}: batch={batch} hkv={hkv} r={r} sub={sub} page={page} G={G} top={top} bound={max_len}", flush=True)
     shape = api.make_shape(sub, hkv * r, hkv, max_len, G, page)
     dev = torch.device("cuda")
     g = torch.Generator(device=dev).manual_seed(seed)
@@ -262,8 +267,9 @@ def test_persistent_instance_agrees_with_forced_splits_on_random_shapes(gpu_api,
     lens_d = torch.tensor(lens, dtype=torch.int32, device=dev)
     scale = 1.0 / math.sqrt(128)
     outs = []
-    for n_splits in (0, 1, 3):
-        o = api.nsn_decode_attention(shape, cb, q, caches[0], caches[1], lens_d, max(lens), scale, n_splits)
+    for n_splits, bound in ((0, max_len), (1, max(lens)), (3, max(lens))):
+        assert helpers.decode_splits(api, shape, batch, bound, n_splits) == n_splits
+        o = api.nsn_decode_attention(shape, cb, q, caches[0], caches[1], lens_d, bound, scale, n_splits)
         torch.cuda.synchronize()
         outs.append(o.cpu().numpy().astype(np.float64))
     for b in range(batch):

@@ -138,21 +138,22 @@ DEC_CASES = [
     ("gqa2-1bit-paged", 4, 2, [900, 511], 8, 128, 256, 3, False, False),
     ("empty-and-short", 3, 1, [0, 65], 4, 64, 0, 2, False, False),
     ("gqa4-sign-groups", 4, 1, [600, 64], 8, 64, 0, 0, True, False),
-    ("gqa8-two-launches", 8, 1, [300, 129], 4, 64, 0, 2, False, False),
+    ("gqa8-as-two-units", 8, 1, [300, 129], 4, 64, 0, 2, False, False),
     ("long-six-iterations", 4, 1, [6000], 4, 64, 0, 2, False, False),
     ("gqa4-2bit-groups-prerope", 8, 2, [777, 130], 4, 64, 0, 4, False, True),
     ("gqa4-sign-groups-prerope", 4, 1, [3000], 8, 64, 0, 1, True, True),
     ("gqa2-1bit-onegroup-prerope", 2, 1, [1000, 64], 8, 0, 0, 3, False, True),
-    # 128 units, automatic splitting: the persistent instance of the tiled-layout kernel with 4-bit side information
+    # "flat": a length bound that selects the persistent instance
     ("flat-ragged-2bit", 16, 8, [0, 64, 65, 130, 300, 17, 256, 511, 77, 128, 5, 200, 333, 90, 400, 1], 4, 64, 0, 0, False, False),
+    ("flat-ragged-sign", 16, 8, [0, 64, 65, 130, 300, 17, 256, 511, 77, 128, 5, 200, 333, 90, 400, 1], 8, 64, 0, 0, True, False),
     ("flat-paged-1bit", 8, 8, [300, 17, 256, 511, 77, 128, 5, 200, 333, 90, 400, 0, 1, 64, 65, 130], 8, 128, 256, 0, False, False),
 ]
 
 
-def _build(seed, hkv, lens, sub, G, cb, page, sign, f):
+def _build(seed, hkv, lens, sub, G, cb, page, sign, f, max_len=None):
     batch = len(lens)
     J = (2 if sign else 1) * (128 // sub)
-    max_len = ((max(max(lens), 1) + 255) // 256) * 256
+    max_len = max_len or ((max(max(lens), 1) + 255) // 256) * 256
     bt = synth.shuffled_page_table(seed, batch, max_len // page) if page else None
     layout = "legacy" if (sign or f is not None) else "tiled"
     kc = helpers.HostCacheDQ("k", batch, hkv, J, max_len, G, page, bt, layout=layout)
@@ -178,13 +179,14 @@ def test_double_quant_decode_matches_oracle(gpu_api, codebooks, magnitude_codebo
     batch, r = len(lens), hq // hkv
     seed = 1150 + len(name)
     scale = 1.0 / math.sqrt(128)
-    kc, vc, max_len = _build(seed, hkv, lens, sub, G, cb, page, sign, f)
+    flat = helpers.persistent_bound(api, batch, hq, hkv, max(lens)) if name.startswith("flat") else None
+    kc, vc, max_len = _build(seed, hkv, lens, sub, G, cb, page, sign, f, helpers.whole(lens) if flat else None)
     q = synth.make_q(seed, batch, hq)
-    shape = api.make_shape(sub, hq, hkv, max_len, G, page, sign_format=sign, side_bits=4, rope_table=table)
+    shape = api.make_shape(sub, hq, hkv, flat or max_len, G, page, sign_format=sign, side_bits=4, rope_table=table)
     cbd = torch.from_numpy(cb.astype(np.float16)).cuda()
     out = api.nsn_decode_attention(shape, cbd, torch.from_numpy(q).cuda(), kc.to_device(api, shape),
                                    vc.to_device(api, shape), torch.tensor(lens, dtype=torch.int32).cuda(),
-                                   max(lens), scale, splits)
+                                   flat or max(lens), scale, splits)
     torch.cuda.synchronize()
     out = out.cpu().numpy().astype(np.float64)
     worst = 0.0

@@ -107,7 +107,7 @@ DEC_CASES = [
     ("gqa2-1bit-paged", 4, 2, [900, 511], 8, 128, 256, 3, False),
     ("empty-and-short", 3, 1, [0, 65], 4, 64, 0, 2, False),
     ("gqa4-sign-groups", 4, 1, [600, 64], 8, 64, 0, 0, True),
-    ("gqa8-two-launches", 8, 1, [300, 129], 4, 64, 0, 2, False),
+    ("gqa8-as-two-units", 8, 1, [300, 129], 4, 64, 0, 2, False),
     ("long-six-iterations-per-wave", 4, 1, [6000], 4, 64, 0, 2, False),   # more than one batch of four groups per wave
     ("long-onegroup-1bit", 2, 1, [5000], 8, 0, 0, 2, False),
 ]

@@ -26,10 +26,10 @@ CASES = [
     ("gqa3-2bit-onegroup", 3, 1, [500, 77], [20, 64], 4, 0, 0, 4),   # 3 heads run in the 4-head kernel
     ("residual-only", 4, 1, [0, 0], [64, 9], 4, 64, 0, 0),
     ("nothing-at-all", 4, 1, [0, 192], [0, 0], 8, 64, 0, 0),
-    ("gqa8-two-launches", 16, 2, [384, 64], [33, 64], 4, 64, 0, 0),   # 8 query heads per kv head
-    ("gqa5-two-launches", 5, 1, [130], [7], 8, 0, 0, 2),              # 4 + 1
+    ("gqa8-as-two-units", 16, 2, [384, 64], [33, 64], 4, 64, 0, 0),   # 8 query heads per kv head
+    ("gqa5-as-two-units", 5, 1, [130], [7], 8, 0, 0, 2),              # 4 + 1
     ("long-eleven-waves", 4, 1, [4608, 64], [64, 3], 4, 64, 0, 1),    # 4096+ token split: 11 main waves + the residual wave
-    # 128 units, automatic splitting: the persistent instance; the segment with a unit's last group takes the
+    # "flat": a length bound that selects the persistent instance; the segment with a unit's last group takes the
     # residual, also for units without coded tokens
     ("flat-ragged-2bit", 32, 8, [0, 1, 64, 65, 130, 300, 17, 256, 511, 77, 128, 5, 200, 333, 90, 400],
      [3, 64, 0, 17, 33, 64, 1, 0, 20, 5, 64, 63, 2, 48, 0, 9], 4, 64, 0, 0),
@@ -47,7 +47,8 @@ def test_residual_decode_matches_oracle(gpu_api, codebooks, name, hq, hkv, lens,
     batch, r, J = len(lens), hq // hkv, 128 // sub
     seed = 300 + len(name)
     scale = 1.0 / math.sqrt(128)
-    max_len = ((max(max(lens), 1) + 255) // 256) * 256
+    flat = helpers.persistent_bound(api, batch, hq, hkv, max(lens)) if name.startswith("flat") else None
+    max_len = helpers.whole(lens) if flat else ((max(max(lens), 1) + 255) // 256) * 256
     bt = synth.shuffled_page_table(seed, batch, max_len // page) if page else None
     kc = helpers.HostCache("k", batch, hkv, J, max_len, G, page, bt)
     vc = helpers.HostCache("v", batch, hkv, J, max_len, G, page, bt)
@@ -64,11 +65,11 @@ def test_residual_decode_matches_oracle(gpu_api, codebooks, name, hq, hkv, lens,
             k_res[b, h, :rlens[b]] = synth.make_k(seed, b, h, rlens[b], start=lens[b])
             v_res[b, h, :rlens[b]] = synth.make_v(seed, b, h, rlens[b], start=lens[b])
     q = synth.make_q(seed, batch, hq)
-    shape = api.make_shape(sub, hq, hkv, max_len, G, page)
+    shape = api.make_shape(sub, hq, hkv, flat or max_len, G, page)
     cbd = torch.from_numpy(cb.astype(np.float16)).cuda()
     out = api.nsn_decode_attention_residual(
         shape, cbd, torch.from_numpy(q).cuda(), kc.to_device(api, shape), vc.to_device(api, shape),
-        torch.tensor(lens, dtype=torch.int32).cuda(), max(lens), torch.from_numpy(k_res).cuda(),
+        torch.tensor(lens, dtype=torch.int32).cuda(), flat or max(lens), torch.from_numpy(k_res).cuda(),
         torch.from_numpy(v_res).cuda(), torch.tensor(rlens, dtype=torch.int32).cuda(), scale, splits)
     torch.cuda.synchronize()
     out = out.cpu().numpy().astype(np.float64)

@@ -31,8 +31,8 @@ CASES = [
     ("gqa2-paged", 4, 2, [900, 511], 128, 256, 3),
     ("empty-and-short", 3, 1, [0, 65], 64, 0, 2),
     ("long-many-splits", 4, 1, [5000], 0, 0, 16),
-    ("gqa8-two-launches", 8, 1, [300, 129], 64, 0, 2),   # 8 query heads per kv head: heads 0-3, then 4-7
-    ("gqa6-two-launches", 6, 1, [200], 0, 0, 0),         # 4 + 2
+    ("gqa8-as-two-units", 8, 1, [300, 129], 64, 0, 2),   # 8 query heads per kv head: heads 0-3, then 4-7
+    ("gqa6-as-two-units", 6, 1, [200], 0, 0, 0),         # 4 + 2
 ]
 
 

@@ -12,18 +12,18 @@ from tests.test_gpu_decode import build_case
 pytestmark = pytest.mark.gpu
 
 
-def _both(api, cb, seed, batch, hq, hkv, lens, sub, G, splits):
+def _both(api, cb, seed, batch, hq, hkv, lens, sub, G, splits, bound=None):
     import torch
     scale = 1.0 / math.sqrt(128)
-    kc, vc, q, max_len = build_case(seed, batch, hq, hkv, lens, sub, G, cb)
-    shape = api.make_shape(sub, hq, hkv, max_len, G)
+    kc, vc, q, max_len = build_case(seed, batch, hq, hkv, lens, sub, G, cb, max_len=helpers.whole(lens) if bound else None)
+    shape = api.make_shape(sub, hq, hkv, bound or max_len, G)
     dk, dv = kc.to_device(api, shape), vc.to_device(api, shape)
     cbd = torch.from_numpy(cb.astype(np.float16)).cuda()
     qd = torch.from_numpy(q).cuda()
     ld = torch.tensor(lens, dtype=torch.int32).cuda()
-    ref = api.nsn_decode_attention(shape, cbd, qd, dk, dv, ld, max(lens), scale, splits)
+    ref = api.nsn_decode_attention(shape, cbd, qd, dk, dv, ld, bound or max(lens), scale, splits)
     out = torch.full((batch, hq, 128), float("nan"), dtype=torch.float32, device="cuda")
-    api.nsn_decode_attention_noalloc(shape, cbd, qd, dk, dv, ld, max(lens), scale, splits, out=out)
+    api.nsn_decode_attention_noalloc(shape, cbd, qd, dk, dv, ld, bound or max(lens), scale, splits, out=out)
     torch.cuda.synchronize()
     return out.cpu().numpy(), ref.cpu().numpy()
 
@@ -39,9 +39,12 @@ def test_noalloc_matches_workspace_entry_point_twice(gpu_api, codebooks):
 
 
 def test_noalloc_persistent_instance_matches_workspace_entry_point(gpu_api, codebooks):
-    # 16 sequences x 8 kv heads = 128 units with automatic splitting: the persistent instance, whose partials
-    # (two per run) and counters live in the same scratch array
+    # 16 sequences x 8 kv heads = 128 units under a length bound that selects the persistent instance, whose partials
+    # (two per run) and counters live in the same scratch array; then the exact bound, which takes splits
     lens = [0, 1, 64, 65, 130, 300, 17, 256, 511, 77, 128, 5, 200, 333, 90, 400]
+    out, ref = _both(gpu_api, codebooks[4], 33, 16, 16, 8, lens, 4, 64, 0,
+                     helpers.persistent_bound(gpu_api, 16, 16, 8, max(lens)))
+    assert np.array_equal(out, ref)
     out, ref = _both(gpu_api, codebooks[4], 33, 16, 16, 8, lens, 4, 64, 0)
     assert np.array_equal(out, ref)
     out, ref = _both(gpu_api, codebooks[4], 34, 2, 8, 2, [700, 100], 4, 64, 3)   # then a small split call again
