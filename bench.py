@@ -432,12 +432,13 @@ def main() -> int:
     default_options = (args.workload in MEASURED_TRAFFIC and args.n_splits == 0 and not sign and G == 0
                        and not args.pre_rope and args.side_bits == 16 and args.policy == "residual")
     traffic = MEASURED_TRAFFIC[args.workload] if default_options else None
-    # encoder (prefill): bound by the vector ALUs.  Peak = 256 CUs x 64 lanes x 2.4 GHz lane-operations per
-    # second (packed fp32 is disabled in this build); the nearest-codeword search alone takes about 280 of them per
-    # sub-vector (minima of groups of distances, then the listed groups in fp32): counted as the work
-    enc_lane_ops_per_token = Hkv * 2 * 280 * (128 // sub)
-    enc_lane_ops = encode_tokens_per_s * enc_lane_ops_per_token
-    peak_lane_ops = 256 * 64 * 2.4e9
+    # encoder (prefill): what any implementation has to do per token, kv head and tensor - 256 codeword distances per
+    # sub-vector (2 operations per channel and codeword), seven rotation stages, two Normalize and a Shift - against the
+    # dense fp16 matrix rate.  The selection among the distances runs on the vector ALUs and bounds the kernel
+    # (counters under profiles/).
+    enc_flops_per_token = Hkv * 2 * 128 * (2 * 256 + 7 + 12)
+    enc_flops = encode_tokens_per_s * enc_flops_per_token
+    peak_flops = 2.5e15
 
     result = {
         "metric": "coded-KV decode attention: achieved HBM GB/s (coded bytes read per step / step time)",
@@ -484,10 +485,10 @@ def main() -> int:
                      "traffic_source": traffic["source"] if traffic else None,
                      "algorithmic_bytes": step_bytes},
         "roofline_encode": {"bound": "alu", "kernel": "nsn::enc_kernel (+ enc_stats_kernel, enc_means_kernel)",
-                            "achieved": round(enc_lane_ops / 1e12, 3), "peak": round(peak_lane_ops / 1e12, 2),
-                            "unit": "Tlane-op/s", "frac": round(enc_lane_ops / peak_lane_ops, 4),
-                            "algorithmic_lane_ops_per_token": enc_lane_ops_per_token,
-                            "peak_derivation": "256 CUs x 64 lanes x 2.4 GHz, one fp32 operation per lane and clock"},
+                            "achieved": round(enc_flops / 1e12, 3), "peak": round(peak_flops / 1e12, 2),
+                            "unit": "TFLOP/s", "frac": round(enc_flops / peak_flops, 4),
+                            "algorithmic_flops_per_token": enc_flops_per_token,
+                            "peak_derivation": "dense fp16 / bf16 matrix rate of the chip, 2.5 PFLOP/s"},
     }
     if flushes == 0 and args.policy == "residual":
         result["config"]["note"] = (f"the {K} timed steps contain no residual flush (one falls on every {RES}th "

@@ -16,9 +16,11 @@
 namespace nsn {
 
 constexpr int kSumBlocks = 256;   // workgroups of the accumulation (and partial sums per cluster)
-// four waves per SIMD (128 registers) for 4-dim codewords, three (170) for 8-dim ones, which spill at four: 26.5 against
-// 29.5 us and 38.0 against 39.8 us per K-Means iteration of 2^20 samples with two (with the products requested a tile
-// ahead: 32 us, for want of registers, and 35.7 us)
+// four waves per SIMD (128 registers) for 4-dim codewords, three (168) for 8-dim ones: 26.5 against 29.5 us and 38.0
+// against 39.8 us per K-Means iteration of 2^20 samples with two (with the products requested a tile ahead: 32 us, for
+// want of registers, and 35.7 us).  The 8-dim kernels spill 16 to 26 registers, the ordered 4-dim ones about 20: sums and
+// addresses, some forty scratch instructions per wave and 4096 samples.  Of a launch's time vector issue takes about half,
+// LDS 20 to 30 % (atomics with conflicts, second operands), the matrix cores 16 to 22 %.
 template <int SUB>
 constexpr int kSumThreads = SUB == 4 ? 1024 : 768;
 constexpr int kSumMost = 4096;  // samples added up in LDS at a time
@@ -311,7 +313,8 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_ordered_kernel(const floa
       n2 += v[i] * v[i];
     }
     if (n2 > 0.0) {
-      // v / nx, correctly rounded, with one reciprocal for all elements (quotient, exact remainder, correction)
+      // v / nx with one reciprocal for all elements: two Newton steps for it, then the quotient corrected by its exact
+      // remainder (Markstein's method), which rounds correctly
       const double nx = sqrt(n2);
       double r = __builtin_amdgcn_rcp(nx);
       r = fma(fma(-nx, r, 1.0), r, r);

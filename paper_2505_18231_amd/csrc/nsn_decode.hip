@@ -256,7 +256,7 @@ __global__ __launch_bounds__(128) void dec_merge_kernel(int n_q_heads, int n_spl
 // ---------------------------------------------------------------------------------------
 bool decode_use_mfma(const nsn_shape& s) {
   if (s.n_codes == kSignCodes) return true;   // the sign + index format exists in the matrix-core kernel only
-  // up to 8 query heads per kv head (checked with the shape): one launch per four heads
+  // up to 8 query heads per kv head (checked with the shape): units of four heads in one launch
   return selected_variant(NSN_OP_DECODE) != NSN_VARIANT_ALT;  // the alternative is the lookup-table kernel
 }
 

@@ -1,5 +1,7 @@
 // Kernel instances of the legacy code layout: the sign + index format, and every format with keys normalised before the rotary
 // embedding.  (Powers of two in group and page sizes are a run-time choice here: half as many instances.)
+// Sign codes without a rotary table fit in 256 registers; the rotary instances spill 2 to 17 of them (sign codes and 4-bit
+// side information most).
 #include "nsn_decode_tile.h"
 
 namespace nsn {

@@ -454,7 +454,7 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
     const uint32_t ln = real ? (uint32_t)lane : 0u;
     const unsigned char* kp = kc.codes + kbase * J + lco;
     const unsigned char* vp = vc.codes + vbase * J + lvo;
-    constexpr int VSTEP = LEGACY ? 16 * J / 16 : 1;  // legacy: the lane's second value row is sixteen rows on
+    constexpr int VSTEP = LEGACY ? J : 1;  // 16-byte pieces; legacy: the lane's second value row is sixteen rows on
 #pragma unroll
     for (int w4 = 0; w4 < CW / 4; ++w4) {
       const uint4 kv4 = reinterpret_cast<const uint4*>(kp)[w4];
@@ -638,12 +638,12 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
   } else {
     if (first_segment && wave == 4 && lane < 32) lds_write32(SM::kZero + lane * 4, 0u);
     if constexpr (!ROPE) {
-    const int hh = wave - 4;  // this wave loaded the query of head wave & 3 = hh
-    const float x0 = hh < r ? __low2float(q2_raw) : 0.f, x1 = hh < r ? __high2float(q2_raw) : 0.f;
-    float of0, of1;
-    mean_pair(ok_first, okp_first, of0, of1);
-    const float d = wave_sum_all(x0 * of0 + x1 * of1);
-    if (lane == 0) lds_write32(SM::kQoFirst + hh * 4, __float_as_uint(d * scale_log2e));
+      const int hh = wave - 4;  // this wave loaded the query of head wave & 3 = hh
+      const float x0 = hh < r ? __low2float(q2_raw) : 0.f, x1 = hh < r ? __high2float(q2_raw) : 0.f;
+      float of0, of1;
+      mean_pair(ok_first, okp_first, of0, of1);
+      const float d = wave_sum_all(x0 * of0 + x1 * of1);
+      if (lane == 0) lds_write32(SM::kQoFirst + hh * 4, __float_as_uint(d * scale_log2e));
     }
   }
   __builtin_amdgcn_sched_barrier(0);

@@ -16,8 +16,10 @@ static int decode_units(const nsn_shape& s, int batch) {
 }
 
 // Splits per unit of the one-workgroup-per-split instance.  A workgroup has a compute unit to itself
-// (its LDS holds the codebook table), so the count is rounded down: one workgroup too many costs a whole second round
-// (2-bit, 100 units x 8192 tokens: 17.3 us with two splits, 23.5 with three).  Eight groups or fewer are one per wave
+// (its LDS holds the codebook table) and the chip has 256 of them (the persistent launch, whose grid must not exceed
+// them, asks the device), so the count is rounded down: one workgroup too many costs a whole second round
+// (2-bit, 100 units x 8192 tokens: 17.3 us with two splits, 23.5 with three; with lengths of one kind and another, which the
+// host does not know, the second round is not whole: 96 units of 818 to 3934 tokens 11.2 and 11.0 us).  Eight groups or fewer are one per wave
 // and need no merge across workgroups (512 tokens: 6.2 us, 7.2 in four splits); beyond that a split gets eight groups,
 // one per wave, but a unit at least four splits (the merge is paid by then: 1024 tokens in 2 / 4 splits 7.6 / 7.3 us,
 // 8192 tokens in 16 / 32 splits 9.6 / 9.9 us).  More than 32 partials are read in two trips: only for very long contexts

@@ -72,7 +72,7 @@ __host__ __device__ inline int64_t v_code_offset(int J, int64_t t, int j) {
   return (t / J) * (int64_t)(J * J) + (int64_t)j * J + (t % J);
 }
 
-// Tiled layout (the formats read by dec_tile_kernel): 64-token blocks of 64 * NSV bytes (NSV = sub-vectors
+// Tiled layout (index-only codes, keys taken as given): 64-token blocks of 64 * NSV bytes (NSV = sub-vectors
 // per token), one run of NSV bytes per lane of the wave that reads the block (lane = 16 hi + lo):
 //   K: lane = 16 * (j / QS) + t % 16, byte (t % 64 / 16) * QS + j % QS           (QS = NSV / 4)
 //      - a lane holds one 32-channel quarter of tokens t % 16 of the block's four 16-token tiles

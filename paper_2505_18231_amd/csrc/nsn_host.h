@@ -5,7 +5,7 @@
 
 namespace nsn {
 
-// which formats keep their codes in the tiled layout (read by dec_tile_kernel)
+// which formats keep their codes in the tiled layout (dec_tile_kernel reads the legacy one too, see nsn_decode_rows.hip)
 inline bool shape_is_tiled(const nsn_shape& s) { return s.n_codes == kCodes && s.rope_table == nullptr; }
 
 inline Geometry make_geometry(const nsn_shape& s) {
