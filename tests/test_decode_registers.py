@@ -68,3 +68,13 @@ def test_up_to_four_query_heads_pay_nothing_for_two_units(tmp_path):
                            flags=re.M)[1:]
         few, many = (len(re.findall(r"^\s+s_(?!nop|waitcnt|barrier|branch)", k.split(".Lfunc_end")[0], flags=re.M)) for k in kernels)
         assert few < many, (few, many)
+
+
+def test_the_codebook_row_is_requested_ahead_of_the_other_loads(tmp_path):
+    """The table fill waits for the codebook row, so its load goes out first, and not just in front of the bulk loads that
+    fill the memory pipeline (one workgroup per split)."""
+    for kernel in re.split(r"^_Z\S*dec_tile_kernel\S*:", _listing(ONE_SPLIT[:2], tmp_path), flags=re.M)[1:]:
+        code = [line.split(";")[0].strip() for line in kernel.splitlines()]
+        code = [line for line in code if line and not line.startswith(".")]
+        first, second = [i for i, line in enumerate(code) if line.startswith("global_load")][:2]
+        assert second - first >= 20, (first, second)
