@@ -25,22 +25,23 @@ template <int SUB>
 constexpr int kSumThreads = SUB == 4 ? 1024 : 768;
 constexpr int kSumMost = 4096;  // samples added up in LDS at a time
 
-// workspace: centroids, error sum of every workgroup, cosine sum of every cluster, the samples' range (largest |sample|,
-// smallest but zero less one, as fp32 bits), then per workgroup of the accumulation the member sums [256][SUB] and the
-// member counts [256]
+// workspace: centroids, error sum of every workgroup, cosine sum of every cluster, the largest |sample| as fp32 bits, then
+// per workgroup of the accumulation the member sums [256][SUB] and the member counts [256].  K-Means keeps the smallest
+// |sample| but zero, less one, in the place of the cosine sums.
 template <int SUB>
 struct CodebookWs {
   double* centroids;
   double* block_err;
   double* cos_sum;
-  uint32_t* range_bits;
+  uint32_t *least_bits, *most_bits;
   double* sums;
   double* counts;
   explicit CodebookWs(void* ws)
       : centroids(static_cast<double*>(ws)),
         block_err(centroids + kCodes * SUB),
         cos_sum(block_err + kSumBlocks),
-        range_bits(reinterpret_cast<uint32_t*>(cos_sum + kCodes)),
+        least_bits(reinterpret_cast<uint32_t*>(cos_sum)),
+        most_bits(reinterpret_cast<uint32_t*>(cos_sum + kCodes)),
         sums(cos_sum + kCodes + 2),
         counts(sums + (size_t)kSumBlocks * kCodes * SUB) {}
   static size_t bytes() {
@@ -51,19 +52,20 @@ struct CodebookWs {
 // start of a run: the centroids (the first samples, or the codebook at hand), no sample in the range yet
 template <typename T>
 __global__ void cb_start_kernel(const T* __restrict__ from, double* __restrict__ centroids, int n_elems,
-                                uint32_t* __restrict__ range_bits) {
+                                uint32_t* __restrict__ least_bits, uint32_t* __restrict__ most_bits) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n_elems) centroids[i] = (double)(float)from[i];
-  if (i == 0) range_bits[0] = 0u, range_bits[1] = 0xffffffffu;
+  if (i == 0) *least_bits = 0xffffffffu, *most_bits = 0u;
 }
 
 // Largest |sample| of the set and the smallest that is not zero, less one, as fp32 bits (their order is that of the values;
-// infinities and NaN are above all of them, and zeros less one as well).  Two atomics per workgroup: with one per wave of
-// a 4096-wave launch they took 45 of 56 us.
+// infinities and NaN are above all of them, and zeros less one as well).  Two atomics per workgroup, on lines
+// of their own that are served side by side: with one per wave of a 4096-wave launch they took 45 of 56 us.
 constexpr int kRangeThreads = 1024, kRangeBlocks = 256;
 typedef float row4 __attribute__((ext_vector_type(4), aligned(4)));  // (the samples are aligned as floats are)
 __global__ __launch_bounds__(kRangeThreads) void cb_range_kernel(const float* __restrict__ samples, int64_t n_rows,
-                                                                 uint32_t* __restrict__ range_bits) {
+                                                                 uint32_t* __restrict__ least_bits,
+                                                                 uint32_t* __restrict__ most_bits) {
   __shared__ uint32_t red[2][kRangeThreads / 64];
   uint32_t most = 0u, least = 0xffffffffu;
 #pragma unroll 4
@@ -83,8 +85,8 @@ __global__ __launch_bounds__(kRangeThreads) void cb_range_kernel(const float* __
   __syncthreads();
   if (threadIdx.x == 0) {
     for (int w = 1; w < kRangeThreads / 64; ++w) most = max(most, red[0][w]), least = min(least, red[1][w]);
-    atomicMax(range_bits, most);
-    atomicMin(range_bits + 1, least);
+    atomicMax(most_bits, most);
+    atomicMin(least_bits, least);
   }
 }
 
@@ -140,18 +142,19 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_accumulate_kernel(const f
     for (int q = 0; q < SUB / 4; ++q) ahead[q] = row[q];
   };
   fetch(begin + tid);
+  const uint32_t most = ERR ? 0u : *ws.most_bits, least = ERR ? 0u : *ws.least_bits;  // (on their way during the set-up)
   SearchRegs<SUB, false> R;
   search_setup<SUB, false>(T, R, tid, [&](int i) { return ws.centroids[tid * SUB + i]; });
   for (int i = tid; i < kCodes * SUB; i += NT) (&cx[0][0])[i] = ws.centroids[i];
   int ex = 0;
   uint32_t small = 0u;  // twice the bits of 2^(ex - 27) where the set holds smaller values (but zero)
   if constexpr (!ERR) {
-    const float mx = __uint_as_float(ws.range_bits[0]);
+    const float mx = __uint_as_float(most);
     if (mx > 0.f && mx < INFINITY) (void)frexpf(mx, &ex);  // mx < 2^ex
     ex = __builtin_amdgcn_readfirstlane(ex);
     // (from ex = -100 down every fp32 value is a multiple of the unit)
     const uint32_t from = ex > -100 ? (uint32_t)(ex - 27 + 127) << 23 : 0u;
-    if (ws.range_bits[1] + 1u < from && ws.range_bits[1] != 0xffffffffu) small = 2u * from;
+    if (least + 1u < from && least != 0xffffffffu) small = 2u * from;
     small = __builtin_amdgcn_readfirstlane(small);
   }
   const double fixed = ldexp(1.0, 50 - ex);
@@ -183,10 +186,10 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_accumulate_kernel(const f
         if (valid) err += exact_dist<SUB>(cx[code], x);
       } else if (valid) {
         if (small) {
-          uint32_t least = 0xffffffffu;
+          uint32_t lowest = 0xffffffffu;
 #pragma unroll
-          for (int i = 0; i < SUB; ++i) least = min(least, __float_as_uint(x[i]) << 1);
-          if (least < small) {
+          for (int i = 0; i < SUB; ++i) lowest = min(lowest, __float_as_uint(x[i]) << 1);
+          if (lowest < small) {
 #pragma unroll
             for (int i = 0; i < SUB; ++i) {
               if ((__float_as_uint(x[i]) << 1) < small) {
@@ -533,10 +536,10 @@ size_t codebook_workspace_bytes(int sub_dim, int64_t) {
 
 // Every sample enters the fixed-point sums exactly from 2^-54 of the power of two above the largest on; sets with
 // smaller ones (but zero), infinities or NaN are added in fp64 instead.
-static bool sums_fit(const uint32_t (&range_bits)[2]) {
-  const uint32_t least_bits = range_bits[1] + 1u;  // (0: there are zeros only)
+static bool sums_fit(uint32_t least_less_one, uint32_t most_bits) {
+  const uint32_t least_bits = least_less_one + 1u;  // (0: there are zeros only)
   float largest, least;
-  memcpy(&largest, &range_bits[0], sizeof(largest));
+  memcpy(&largest, &most_bits, sizeof(largest));
   memcpy(&least, &least_bits, sizeof(least));
   if (!std::isfinite(largest)) return false;
   int ex = 0;
@@ -550,12 +553,13 @@ static int codebook_run_t(const float* samples, int64_t n, int iters, void* code
   const CodebookWs<SUB> ws(workspace);
   constexpr int n_elems = kCodes * SUB;
   struct {
-    double err[kSumBlocks], unused[kCodes];
-    uint32_t range_bits[2];
+    double err[kSumBlocks];
+    uint32_t least_bits, unused[2 * kCodes - 1], most_bits, unused2;
   } host;
   auto run = [&](bool fixed) -> int {
-    cb_start_kernel<<<(n_elems + 255) / 256, 256, 0, stream>>>(samples, ws.centroids, n_elems, ws.range_bits);
-    cb_range_kernel<<<kRangeBlocks, kRangeThreads, 0, stream>>>(samples, n * (SUB / 4), ws.range_bits);
+    cb_start_kernel<<<(n_elems + 255) / 256, 256, 0, stream>>>(samples, ws.centroids, n_elems, ws.least_bits,
+                                                               ws.most_bits);
+    cb_range_kernel<<<kRangeBlocks, kRangeThreads, 0, stream>>>(samples, n * (SUB / 4), ws.least_bits, ws.most_bits);
     for (int it = 0; it < iters; ++it) {
       if (fixed)
         cb_accumulate_kernel<SUB, false><<<kSumBlocks, kSumThreads<SUB>, 0, stream>>>(samples, n, ws);
@@ -566,13 +570,13 @@ static int codebook_run_t(const float* samples, int64_t n, int iters, void* code
     km_round_kernel<<<(n_elems + 255) / 256, 256, 0, stream>>>(ws.centroids, static_cast<__half*>(codebook_out), n_elems);
     cb_accumulate_kernel<SUB, true><<<kSumBlocks, kSumThreads<SUB>, 0, stream>>>(samples, n, ws);
     if (hipGetLastError() != hipSuccess) return NSN_ERR_HIP;
-    // error sums, cosine sums (not used here) and the range lie next to each other
+    // error sums and the range lie next to each other
     if (hipMemcpyAsync(&host, ws.block_err, sizeof(host), hipMemcpyDeviceToHost, stream) != hipSuccess) return NSN_ERR_HIP;
     return hipStreamSynchronize(stream) == hipSuccess ? NSN_OK : NSN_ERR_HIP;
   };
   // (the range comes back with the error sums, so that ordinary samples pay nothing for the question)
   int rc = run(true);
-  if (rc == NSN_OK && iters > 0 && !sums_fit(host.range_bits)) rc = run(false);
+  if (rc == NSN_OK && iters > 0 && !sums_fit(host.least_bits, host.most_bits)) rc = run(false);
   if (rc != NSN_OK) return rc;
   if (mse_host) {
     double tot = 0.0;
@@ -604,7 +608,7 @@ static int finetune_run_t(const float* samples, int64_t n, int iters, double lr,
     return NSN_OK;
   };
   cb_start_kernel<<<(n_elems + 255) / 256, 256, 0, stream>>>(static_cast<const __half*>(codebook_io), ws.centroids, n_elems,
-                                                             ws.range_bits);
+                                                             ws.least_bits, ws.most_bits);
   int rc = NSN_OK;
   double before = 0.0, after = 0.0;
   if (cos_host && (rc = mean_cos(&before)) != NSN_OK) return rc;
