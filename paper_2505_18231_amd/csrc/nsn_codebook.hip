@@ -9,6 +9,7 @@
 // cover takes cb_ordered_kernel too)
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 #include "nsn_host.h"
 #include "nsn_search.h"
@@ -16,13 +17,12 @@
 namespace nsn {
 
 constexpr int kSumBlocks = 256;   // workgroups of the accumulation (and partial sums per cluster)
-// four waves per SIMD (128 registers) for 4-dim codewords, three (168) for 8-dim ones: 26.5 against 29.5 us and 38.0
-// against 39.8 us per K-Means iteration of 2^20 samples with two (with the products requested a tile ahead: 32 us, for
-// want of registers, and 35.7 us).  The 8-dim kernels spill 16 to 26 registers, the ordered 4-dim ones about 20: sums and
-// addresses, some forty scratch instructions per wave and 4096 samples.  Of a launch's time vector issue takes about half,
-// LDS 20 to 30 % (atomics with conflicts, second operands), the matrix cores 16 to 22 %.
+// four waves per SIMD (128 registers) for 4-dim codewords, two (256) for 8-dim ones: with three (168 registers) those spilled 16
+// to 43 of them, and a kernel that needs scratch memory starts later: 2^20 8-dim samples 39 -> 36 us per K-Means iteration,
+// 2^14 samples 17 -> 15 us (the ordered 4-dim kernels spill about 20: in lists and addresses).  Of an accumulation of 2^20
+// 8-dim samples (27.5 us) set-up and the first samples take about 8, the merge of the waves' sums 3.
 template <int SUB>
-constexpr int kSumThreads = SUB == 4 ? 1024 : 768;
+constexpr int kSumThreads = SUB == 4 ? 1024 : 512;
 constexpr int kSumMost = 4096;  // samples added up in LDS at a time
 
 // workspace: centroids, error sum of every workgroup, cosine sum of every cluster, the largest |sample| as fp32 bits, then
@@ -77,10 +77,14 @@ __global__ __launch_bounds__(kRangeThreads) void cb_range_kernel(const float* __
       most = max(most, bits), least = min(least, bits - 1u);
     }
   }
-  for (int k = 1; k < 64; k <<= 1) {
-    most = max(most, (uint32_t)__shfl_xor((int)most, k, 64));
-    least = min(least, (uint32_t)__shfl_xor((int)least, k, 64));
-  }
+  auto with_lane = [&](auto mask) {
+    constexpr int M = decltype(mask)::value;
+    most = max(most, (uint32_t)xor_lane_i32<M>((int)most));
+    least = min(least, (uint32_t)xor_lane_i32<M>((int)least));
+  };
+  with_lane(std::integral_constant<int, 1>{}), with_lane(std::integral_constant<int, 2>{});
+  with_lane(std::integral_constant<int, 4>{}), with_lane(std::integral_constant<int, 8>{});
+  with_lane(std::integral_constant<int, 16>{}), with_lane(std::integral_constant<int, 32>{});
   if ((threadIdx.x & 63) == 0) red[0][threadIdx.x >> 6] = most, red[1][threadIdx.x >> 6] = least;
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -141,11 +145,26 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_accumulate_kernel(const f
 #pragma unroll
     for (int q = 0; q < SUB / 4; ++q) ahead[q] = row[q];
   };
+  double centroid[SUB] = {};  // of codeword `tid`
+  if (tid < kCodes) {
+#pragma unroll
+    for (int i = 0; i < SUB; ++i) centroid[i] = ws.centroids[tid * SUB + i];
+  }
   fetch(begin + tid);
   const uint32_t most = ERR ? 0u : *ws.most_bits, least = ERR ? 0u : *ws.least_bits;  // (on their way during the set-up)
+  auto clear = [&](auto& sums) {
+    for (int i = tid; i < kCodes * SUB; i += NT) (&sums[0][0])[i] = 0ull;
+  };
+  if constexpr (!ERR) {
+    clear(acc);
+    if (tid < kCodes) cnt[tid] = 0u;
+  }
+  if (tid < kCodes) {
+#pragma unroll
+    for (int i = 0; i < SUB; ++i) cx[tid][i] = centroid[i];
+  }
   SearchRegs<SUB, false> R;
-  search_setup<SUB, false>(T, R, tid, [&](int i) { return ws.centroids[tid * SUB + i]; });
-  for (int i = tid; i < kCodes * SUB; i += NT) (&cx[0][0])[i] = ws.centroids[i];
+  search_setup<SUB, false>(T, R, tid, [&](int i) { return centroid[i]; });
   int ex = 0;
   uint32_t small = 0u;  // twice the bits of 2^(ex - 27) where the set holds smaller values (but zero)
   if constexpr (!ERR) {
@@ -158,15 +177,8 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_accumulate_kernel(const f
     small = __builtin_amdgcn_readfirstlane(small);
   }
   const double fixed = ldexp(1.0, 50 - ex);
-  auto clear = [&]() {
-    if constexpr (!ERR) {
-      for (int i = tid; i < kCodes * SUB; i += NT) (&acc[0][0])[i] = 0ull;
-      if (small)
-        for (int i = tid; i < kCodes * SUB; i += NT) (&acc_small[0][0])[i] = 0ull;
-      if (tid < kCodes) cnt[tid] = 0u;
-    }
-  };
-  clear();
+  if constexpr (!ERR)
+    if (small) clear(acc_small);
   double own[kOwn], own_n = 0.0, err = 0.0;
 #pragma unroll
   for (int k = 0; k < kOwn; ++k) own[k] = 0.0;
@@ -217,9 +229,13 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_accumulate_kernel(const f
         own[k] += t;
       }
       if (tid < kCodes) own_n += (double)cnt[tid];
-      __syncthreads();
-      clear();
-      __syncthreads();
+      if (base + kSumMost < end) {
+        __syncthreads();
+        clear(acc);
+        if (small) clear(acc_small);
+        if (tid < kCodes) cnt[tid] = 0u;
+        __syncthreads();
+      }
     }
   }
   if constexpr (ERR) {
@@ -286,8 +302,16 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_ordered_kernel(const floa
   __shared__ __attribute__((aligned(16))) uint16_t codes[kWgChains][kBlockPos];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   SearchRegs<SUB, false> R;
-  search_setup<SUB, false>(T, R, tid, [&](int i) { return ws.centroids[tid * SUB + i]; });
-  for (int i = tid; i < kCodes * SUB; i += NT) (&cx[0][0])[i] = ws.centroids[i];
+  {
+    double centroid[SUB] = {};  // of codeword `tid`
+    if (tid < kCodes) {
+#pragma unroll
+      for (int i = 0; i < SUB; ++i) centroid[i] = ws.centroids[tid * SUB + i];
+#pragma unroll
+      for (int i = 0; i < SUB; ++i) cx[tid][i] = centroid[i];
+    }
+    search_setup<SUB, false>(T, R, tid, [&](int i) { return centroid[i]; });
+  }
   const int64_t n16 = n & ~(int64_t)(kRun - 1);
   double acc[CPW][SUB];
   uint32_t members[UNIT ? 1 : CPW] = {};
@@ -329,31 +353,31 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_ordered_kernel(const floa
       }
     }
   };
-  // block by block, the samples behind the last whole run (one per chain, the last of its order) as a block of their own
+  auto search = [&](const float (&x)[SUB]) {
+    return search_nearest<SUB, false, false>(T, R, x, [&](int c) { return exact_dist<SUB>(cx[c], x); }).code;
+  };
   const int64_t blocks = (n16 + (int64_t)kSumMost * kSumBlocks - 1) / ((int64_t)kSumMost * kSumBlocks);
-  for (int64_t blk = 0; blk < blocks + (n > n16); ++blk) {
-    const bool tail = blk == blocks;
+  for (int64_t blk = 0; blk < blocks; ++blk) {
     // sample of position p of chain `ch` (of the workgroup's four) in this block
     auto sample_of = [&](int ch, int p) -> int64_t {
       const int chain = blockIdx.x * kWgChains + ch;
-      return tail ? n16 + chain : ((blk * (kBlockPos / kRun) + (p >> 4)) * kChains + chain) * kRun + (p & 15);
+      return ((blk * (kBlockPos / kRun) + (p >> 4)) * kChains + chain) * kRun + (p & 15);
     };
-    const int64_t stop = tail ? n : n16;
     for (int i = tid; i < kPairs; i += NT) len[i] = 0u;
     __syncthreads();
-    for (int u = wave; u < (tail ? 1 : kBlockPos / kRun); u += NWV) {
-      const int ch = tail ? lane & 3 : lane >> 4, p = tail ? 0 : u * kRun + (lane & 15);
+    for (int u = wave; u < kBlockPos / kRun; u += NWV) {
+      const int ch = lane >> 4, p = u * kRun + (lane & 15);
       const int64_t idx = sample_of(ch, p);
-      const bool valid = idx < stop && !(tail && lane >= kWgChains);
+      const bool valid = idx < n16;
       if (!__any(valid)) break;
       float x[SUB];
       load(min(idx, n - 1), x);
-      const int code = search_nearest<SUB, false, false>(T, R, x, [&](int c) { return exact_dist<SUB>(cx[c], x); }).code;
+      const int code = search(x);
       if (valid) {
         const uint32_t at = atomicAdd(&len[code * kWgChains + ch], 1u);
         if (at < kListMost) list[code * kWgChains + ch][at] = (uint16_t)p;
       }
-      if (!tail) codes[ch][p] = valid ? (uint16_t)code : (uint16_t)0xffff;
+      codes[ch][p] = valid ? (uint16_t)code : (uint16_t)0xffff;
     }
     __syncthreads();
 #pragma unroll
@@ -369,7 +393,7 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_ordered_kernel(const floa
 #pragma unroll
           for (int k = 0; k < 8; ++k) {
             const uint32_t code = (k & 1) ? w[k / 2] >> 16 : w[k / 2] & 0xffffu;
-            if (code == (uint32_t)(pair >> 2) && sample_of(pair & 3, p0 + k) < stop) {
+            if (code == (uint32_t)(pair >> 2) && sample_of(pair & 3, p0 + k) < n16) {
               float x[SUB];
               load(sample_of(pair & 3, p0 + k), x);
               add(x, acc[c]);
@@ -399,21 +423,43 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_ordered_kernel(const floa
         reinterpret_cast<uint4*>(list[pair])[q] =
             make_uint4(e[8 * q] | e[8 * q + 1] << 16, e[8 * q + 2] | e[8 * q + 3] << 16, e[8 * q + 4] | e[8 * q + 5] << 16,
                        e[8 * q + 6] | e[8 * q + 7] << 16);
-      float ahead[SUB];
-      auto fetch = [&](uint32_t k) {  // (position 0 of the block exists for every chain that has entries)
-        const int64_t idx = sample_of(pair & 3, k < here ? list[pair][k] : 0);
-        load(min(idx, n - 1), ahead);
-      };
-      fetch(0);
-      for (uint32_t k = 0; __any(k < here); ++k) {
-        float x[SUB];
+      // (four samples are asked for at a time: a trip to memory takes as long as six additions.  One ahead: 49.4
+      // instead of 44.4 us per step of 2^20 8-dim samples)
+      for (uint32_t k = 0; __any(k < here); k += 4) {
+        float x[4][SUB];
 #pragma unroll
-        for (int i = 0; i < SUB; ++i) x[i] = ahead[i];
-        fetch(k + 1);
-        if (k < here) add(x, acc[c]);
+        for (uint32_t u = 0; u < 4; ++u) {  // (position 0 of the block exists for every chain that has entries)
+          const int64_t idx = sample_of(pair & 3, k + u < here ? list[pair][k + u] : 0);
+          load(min(idx, n - 1), x[u]);
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < 4; ++u)
+          if (k + u < here) add(x[u], acc[c]);
       }
     }
     __syncthreads();
+  }
+  // the samples behind the last whole run: one for each of the first chains, the last of its order.  (As a block of their
+  // own, with lists, they took 3 us a step.)
+  if (n > n16 && blockIdx.x < kRun / kWgChains) {
+    const int64_t tail0 = n16 + blockIdx.x * kWgChains;
+    if (wave == 0) {
+      float x[SUB];
+      load(min(tail0 + (lane & 3), n - 1), x);
+      const int code = search(x);
+      if (lane < kWgChains) codes[lane][0] = tail0 + lane < n ? (uint16_t)code : (uint16_t)0xffff;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < CPW; ++c) {
+      const int pair = (wave + c * NWV) * 64 + lane;
+      if (pair < kPairs && codes[pair & 3][0] == (uint32_t)(pair >> 2)) {
+        float x[SUB];
+        load(tail0 + (pair & 3), x);
+        add(x, acc[c]);
+        if constexpr (!UNIT) members[c] += 1u;
+      }
+    }
   }
 #pragma unroll
   for (int c = 0; c < CPW; ++c) {
@@ -434,34 +480,39 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_ordered_kernel(const floa
   }
 }
 
-// Adds the partial sums of kUpdateClusters neighbouring clusters (512 or 256 consecutive bytes of every row of partials)
-// in a fixed order (fp64): 1024 threads = 8 SUB sums x 1024 / (8 SUB) slices of the rows, 8 x 128 for the counts.
-// Threads 0..7 return with the sums and the member count of their cluster.  (Four clusters per workgroup and the sums
-// one dimension after the other, i.e. pieces of 32 bytes, took 10.7 us instead of 4.9.)
-constexpr int kUpdateClusters = 8, kUpdateThreads = 1024;
+// Adds the partial sums of kUpdateClusters<SUB> neighbouring clusters (128 consecutive bytes of every row of partials: one line)
+// in a fixed order (fp64): kUpdateThreads<SUB> = E sums x kUpdateThreads / E slices of the rows, clusters x 128 for the counts.
+// The first threads return with the sums and the member count of their cluster.  (Eight clusters per workgroup, i.e. 32
+// compute units at work: 5.3 us instead of 4.7; pieces of 32 bytes 10.7 us.)
+template <int SUB>
+constexpr int kUpdateClusters = 16 / SUB;
+constexpr int kUpdateThreads = 128;
 template <int SUB>
 __device__ __forceinline__ void merge_partials(const CodebookWs<SUB>& ws, double (&sum)[SUB], double& count) {
-  constexpr int E = kUpdateClusters * SUB, SL = kUpdateThreads / E, PER = kSumBlocks / SL;
-  constexpr int CSL = kUpdateThreads / kUpdateClusters, CPER = kSumBlocks / CSL;
-  __shared__ double part[SL][E], cpart[kUpdateThreads / 64][kUpdateClusters];
+  constexpr int UC = kUpdateClusters<SUB>, E = UC * SUB, SL = kUpdateThreads / E, PER = kSumBlocks / SL;
+  constexpr int CSL = kUpdateThreads / UC, CPER = kSumBlocks / CSL;
+  static_assert(PER * SL == kSumBlocks && CPER * CSL == kSumBlocks, "whole slices");
+  __shared__ double part[SL][E], cpart[kUpdateThreads / 64][UC];
   const int e = threadIdx.x % E, sl = threadIdx.x / E;
-  const int c = threadIdx.x % kUpdateClusters, cs = threadIdx.x / kUpdateClusters;
+  const int c = threadIdx.x % UC, cs = threadIdx.x / UC;
   double v[PER], n[CPER], t = 0.0, m = 0.0;
 #pragma unroll
-  for (int u = 0; u < PER; ++u) v[u] = ws.sums[((int64_t)(sl * PER + u) * kCodes + blockIdx.x * kUpdateClusters) * SUB + e];
+  for (int u = 0; u < PER; ++u) v[u] = ws.sums[((int64_t)(sl * PER + u) * kCodes + blockIdx.x * UC) * SUB + e];
 #pragma unroll
-  for (int u = 0; u < CPER; ++u) n[u] = ws.counts[(int64_t)(cs * CPER + u) * kCodes + blockIdx.x * kUpdateClusters + c];
+  for (int u = 0; u < CPER; ++u) n[u] = ws.counts[(int64_t)(cs * CPER + u) * kCodes + blockIdx.x * UC + c];
 #pragma unroll
   for (int u = 0; u < PER; ++u) t += v[u];
 #pragma unroll
   for (int u = 0; u < CPER; ++u) m += n[u];
   part[sl][e] = t;
+  if constexpr (UC < 4) m += xor_lane<2>(m);
+  m += xor_lane<4>(m);
   m += xor_lane<8>(m);
   m += xor_lane<16>(m);
   m += xor_lane<32>(m);
-  if ((threadIdx.x & 63) < kUpdateClusters) cpart[threadIdx.x >> 6][threadIdx.x & 63] = m;
+  if ((threadIdx.x & 63) < UC) cpart[threadIdx.x >> 6][threadIdx.x & 63] = m;
   __syncthreads();
-  if (threadIdx.x < kUpdateClusters) {
+  if (threadIdx.x < UC) {
     count = 0.0;
 #pragma unroll
     for (int w = 0; w < kUpdateThreads / 64; ++w) count += cpart[w][threadIdx.x];
@@ -479,9 +530,9 @@ template <int SUB>
 __global__ __launch_bounds__(kUpdateThreads) void km_update_kernel(CodebookWs<SUB> ws) {
   double sum[SUB], count;
   merge_partials<SUB>(ws, sum, count);
-  if (threadIdx.x < kUpdateClusters && count > 0.0) {
+  if (threadIdx.x < kUpdateClusters<SUB> && count > 0.0) {
 #pragma unroll
-    for (int i = 0; i < SUB; ++i) ws.centroids[(blockIdx.x * kUpdateClusters + threadIdx.x) * SUB + i] = sum[i] / count;
+    for (int i = 0; i < SUB; ++i) ws.centroids[(blockIdx.x * kUpdateClusters<SUB> + threadIdx.x) * SUB + i] = sum[i] / count;
   }
 }
 
@@ -491,14 +542,14 @@ __global__ __launch_bounds__(kUpdateThreads) void km_update_kernel(CodebookWs<SU
 // similarity BEFORE the move.
 template <int SUB>
 __global__ __launch_bounds__(kUpdateThreads) void ft_update_kernel(int64_t n, CodebookWs<SUB> ws, double lr) {
-  constexpr int E = kUpdateClusters * SUB, SL = kUpdateThreads / E;
+  constexpr int UC = kUpdateClusters<SUB>, E = UC * SUB, SL = kUpdateThreads / E;
   constexpr int kTrees = kSumBlocks / 16;  // sixteen workgroups = 64 chains: added in pairs, then the trees in order
   __shared__ double tree[kTrees][E];
   for (int g = threadIdx.x / E; g < kTrees; g += SL) {
     const int e = threadIdx.x % E;
     double v[16];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) v[u] = ws.sums[((int64_t)(16 * g + u) * kCodes + blockIdx.x * kUpdateClusters) * SUB + e];
+    for (int u = 0; u < 16; ++u) v[u] = ws.sums[((int64_t)(16 * g + u) * kCodes + blockIdx.x * UC) * SUB + e];
 #pragma unroll
     for (int d = 1; d < 16; d *= 2)
 #pragma unroll
@@ -506,8 +557,8 @@ __global__ __launch_bounds__(kUpdateThreads) void ft_update_kernel(int64_t n, Co
     tree[g][e] = v[0];
   }
   __syncthreads();
-  if (threadIdx.x < kUpdateClusters) {
-    const int k = blockIdx.x * kUpdateClusters + threadIdx.x;
+  if (threadIdx.x < UC) {
+    const int k = blockIdx.x * UC + threadIdx.x;
     double S[SUB], c[SUB], cn2 = 0.0;
 #pragma unroll
     for (int i = 0; i < SUB; ++i) {
@@ -565,7 +616,7 @@ static int codebook_run_t(const float* samples, int64_t n, int iters, void* code
         cb_accumulate_kernel<SUB, false><<<kSumBlocks, kSumThreads<SUB>, 0, stream>>>(samples, n, ws);
       else
         cb_ordered_kernel<SUB, false><<<kSumBlocks, kSumThreads<SUB>, 0, stream>>>(samples, n, ws);
-      km_update_kernel<SUB><<<kCodes / kUpdateClusters, kUpdateThreads, 0, stream>>>(ws);
+      km_update_kernel<SUB><<<kCodes / kUpdateClusters<SUB>, kUpdateThreads, 0, stream>>>(ws);
     }
     km_round_kernel<<<(n_elems + 255) / 256, 256, 0, stream>>>(ws.centroids, static_cast<__half*>(codebook_out), n_elems);
     cb_accumulate_kernel<SUB, true><<<kSumBlocks, kSumThreads<SUB>, 0, stream>>>(samples, n, ws);
@@ -594,7 +645,7 @@ static int finetune_run_t(const float* samples, int64_t n, int iters, double lr,
   double host_cos[kCodes];
   auto step = [&](double rate) {
     cb_ordered_kernel<SUB, true><<<kSumBlocks, kSumThreads<SUB>, 0, stream>>>(samples, n, ws);
-    ft_update_kernel<SUB><<<kCodes / kUpdateClusters, kUpdateThreads, 0, stream>>>(n, ws, rate);
+    ft_update_kernel<SUB><<<kCodes / kUpdateClusters<SUB>, kUpdateThreads, 0, stream>>>(n, ws, rate);
   };
   auto mean_cos = [&](double* out) -> int {  // assignment + cosine sums of the current centroids (no move: rate 0)
     step(0.0);

@@ -139,7 +139,9 @@ __device__ inline __half f64_to_f16(double x) {
   return __float2half_rn(f);
 }
 
-// Value of lane (lane ^ M): DPP moves inside a 16-lane row (no LDS traffic), a bpermute across rows.
+// Value of lane (lane ^ M): DPP moves inside a 16-lane row, swaps of two copies across rows (no LDS traffic; one-dimensional
+// workgroups).  v_permlane16_swap exchanges odd 16-lane rows of `a` with even rows of `b`, v_permlane32_swap the upper half of
+// `a` with the lower half of `b`; they read other lanes' registers, which takes two idle cycles after the write.
 template <int CTRL, int BANK>
 __device__ __forceinline__ int dpp_i32(int old, int v) {
   return __builtin_amdgcn_update_dpp(old, v, CTRL, 0xf, BANK, false);
@@ -162,7 +164,13 @@ __device__ __forceinline__ int xor_lane_i32(int v) {
   } else if constexpr (M == 8) {
     return dpp_mov_i32<0x128, 0xf>(v);  // row_ror:8
   } else {
-    return __shfl_xor(v, M, 64);
+    static_assert(M == 16 || M == 32, "a bit of the lane number");
+    int a = v, b = v;
+    if constexpr (M == 16)
+      asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+    else
+      asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+    return (threadIdx.x & M) ? a : b;
   }
 }
 template <int M>
