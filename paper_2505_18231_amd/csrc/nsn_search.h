@@ -1,17 +1,20 @@
 // Nearest-codeword search (Eq. 1, squared Euclidean distance): one sub-vector per lane, 64 per call.
 //
-// Three steps, bound by vector instructions (about 280 per 64 searches of 256 4-dim codewords; keeping the best two
-// indexed keys of every distance, the form this one replaced, took about 740):
+// Three steps, bound by vector instructions (about 270 per 64 searches of 256 4-dim codewords and 55 per group gone through;
+// keeping the best two indexed keys of every distance took about 740):
 //   1. matrix cores: D = ||c||^2 - 2 c . y + n for 32 codewords (rows) x 32 sub-vectors (columns) at a time, n slightly
 //      above ||y||^2 (D > 0).  y, c and ||c||^2 enter as sums of fp16 parts, so D is good to about 2^-19 of
-//      (|c| + |y|)^2.  A lane then holds 16 distances of one sub-vector per tile and keeps only the minima of the two groups of eight: half
-//      an instruction per distance (three-operand minima), no index bookkeeping.  32 groups of 8 codewords leave 32
-//      minima per sub-vector, brought to the lane that owns it by half-wave swaps.
+//      (|c| + |y|)^2.  A lane then holds 16 distances of one sub-vector per tile and keeps only the minima of the two groups
+//      of eight: half an instruction per distance (three-operand minima), no index bookkeeping.  32 groups of 8 codewords
+//      leave 32 minima per sub-vector, sixteen in either half of the wave.
 //   2. every group whose minimum lies within twice the error bound of the smallest is listed (almost always one).
 //   3. the listed groups' codewords are gone through in fp32 on the vector ALUs (rows read from LDS).  Again
 //      everything within the bound is listed: one candidate (all but about one sub-vector in two thousand) is the
 //      nearest codeword for certain; several are settled by fp64 distances, lowest index on ties, so the code equals
-//      an fp64 exhaustive search.
+//      an fp64 exhaustive search.  Where no sub-vector of the wave has more than two, they are noted on the way (one search in
+//      thirty; going through the lists again for them held up the workgroup, and the launch waits for its slowest one:
+//      64 tokens x 8 sequences x 8 heads 10.2 -> 8.9 us, 8 x 8192 tokens 580 -> 562 us, a K-Means iteration of 2^20
+//      8-dim samples 3 us less).
 // Groups of 8 against 16: twice the minima in step 2 (+56 instructions), half the rows in step 3 (-48 for 4-dim, -80 for
 // 8-dim codewords, and half the LDS reads).
 #pragma once
@@ -36,6 +39,20 @@ typedef float f16v __attribute__((ext_vector_type(16)));
 __device__ __forceinline__ void operand_swap32(uint32_t& a, uint32_t& b) {
   asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
 }
+template <typename T>
+__device__ __forceinline__ void swap32(T& a, T& b) {
+  static_assert(sizeof(T) == 4, "one register each");
+  asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+}
+// the largest of the wave's values, in every lane (no LDS traffic)
+__device__ __forceinline__ float wave_max_lanes(float v) {
+  v = fmaxf(v, xor_lane<1>(v)), v = fmaxf(v, xor_lane<2>(v)), v = fmaxf(v, xor_lane<4>(v)), v = fmaxf(v, xor_lane<8>(v));
+  float a = v, b = v;
+  asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+  float c = fmaxf(a, b), d = c;
+  swap32(c, d);
+  return fmaxf(c, d);
+}
 // four pairs at a time: one wait for all of them
 #define NSN_SWAP4(NAME, INSN, AFTER)                                                                              \
   template <typename T>                                                                                           \
@@ -59,12 +76,12 @@ __device__ __forceinline__ void min8x2(const f16v& d, uint32_t& lo8, uint32_t& h
 }
 
 // group g, row r of it <-> codeword: a lane of half hf holds rows 8 (k / 4) + 4 hf + k % 4, k = 0..15, of 32 x 32 tile m;
-// k < 8 is group 4 m + 2 hf, the others are group 4 m + 2 hf + 1
+// k < 8 is group 16 hf + 2 m, the others are group 16 hf + 2 m + 1
 constexpr int kGroups = 32, kGroupRows = 8;
 __host__ __device__ constexpr int group_codeword(int g, int r) {
-  return 32 * (g >> 2) + 8 * (2 * (g & 1) + (r >> 2)) + 4 * ((g >> 1) & 1) + (r & 3);
+  return 16 * (g & 15) + 4 * (g >> 4) + 8 * (r >> 2) + (r & 3);
 }
-__host__ __device__ constexpr int codeword_group(int c) { return 4 * (c >> 5) + 2 * ((c >> 2) & 1) + ((c >> 4) & 1); }
+__host__ __device__ constexpr int codeword_group(int c) { return 16 * ((c >> 2) & 1) + (c >> 4); }
 __host__ __device__ constexpr int codeword_row(int c) { return 4 * ((c >> 3) & 1) + (c & 3); }
 
 // LDS: -2 s c and ||s c||^2 in fp32, group by group (padded: neighbouring groups start in different banks); s = the
@@ -92,29 +109,22 @@ struct SearchRegs {
 };
 
 // Fills the tables and the operands of every wave of the workgroup (256 threads or more, all of them call it).
-// get(i): element i of codeword `tid` (threads 0..255).  s is 2^ex_most at most: a caller that knows the longest sub-vector
+// get(i): element i of codeword `tid` (threads 0..255); n2: the largest squared norm of a codeword, in every thread.  s is 2^ex_most at most: a caller that knows the longest sub-vector
 // keeps it below 237 s this way.  Without that, sub-vectors 30 to 60 times as long as the longest codeword leave the fp16
 // range and take 256 fp64 distances per wave (encoder, 4096 tokens x 8 heads with codewords a hundredth of the usual: 495 us
 // instead of 54; K-Means of 2^20 samples whose first 256 are a fiftieth of the others: 100 to 270 us more in the first
 // iteration; there the samples have no bound that one far value would not spoil).
 template <int SUB, bool EXACT16, typename F>
-__device__ inline void search_setup(SearchTables<SUB>& T, SearchRegs<SUB, EXACT16>& R, int tid, F get, int ex_most = 100) {
+__device__ inline void search_setup(SearchTables<SUB>& T, SearchRegs<SUB, EXACT16>& R, int tid, float n2, F get, int ex_most) {
   typedef decltype(get(0)) real;
   const int lane = tid & 63;
   real own[SUB];
-  if (tid < kCodes) {  // (whole waves)
-    float n2 = 0.f;
+  if (tid < kCodes) {
 #pragma unroll
-    for (int i = 0; i < SUB; ++i) {
-      own[i] = get(i);
-      n2 = fmaf((float)own[i], (float)own[i], n2);
-    }
-    n2 = wave_max(n2);
-    if (lane == 0) T.n2max[tid >> 6] = n2;
+    for (int i = 0; i < SUB; ++i) own[i] = get(i);
   }
-  __syncthreads();
   // s = 2^k with |c| s in [4, 8) for the longest codeword (1 for an empty or non-finite codebook)
-  const float nm = sqrtf(fmaxf(fmaxf(T.n2max[0], T.n2max[1]), fmaxf(T.n2max[2], T.n2max[3])));
+  const float nm = sqrtf(n2);
   int ex = 0;
   if (nm > 0.f && nm < INFINITY) {
     (void)frexpf(nm, &ex);  // nm = f 2^ex, f in [1/2, 1)
@@ -184,6 +194,20 @@ __device__ inline void search_setup(SearchTables<SUB>& T, SearchRegs<SUB, EXACT1
   }
 }
 
+// the same where a thread has only its own codeword at hand
+template <int SUB, bool EXACT16, typename F>
+__device__ inline void search_setup(SearchTables<SUB>& T, SearchRegs<SUB, EXACT16>& R, int tid, F get, int ex_most = 100) {
+  float n2 = 0.f;
+  if (tid < kCodes) {  // (whole waves)
+#pragma unroll
+    for (int i = 0; i < SUB; ++i) n2 = fmaf((float)get(i), (float)get(i), n2);
+    n2 = wave_max_lanes(n2);
+    if ((tid & 63) == 0) T.n2max[tid >> 6] = n2;
+  }
+  __syncthreads();
+  search_setup<SUB, EXACT16>(T, R, tid, fmaxf(fmaxf(T.n2max[0], T.n2max[1]), fmaxf(T.n2max[2], T.n2max[3])), get, ex_most);
+}
+
 __device__ __forceinline__ uint32_t pack_f16(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2v{a, b}, h2v));
 }
@@ -249,28 +273,37 @@ __device__ __forceinline__ Nearest search_nearest(const SearchTables<SUB>& T, co
   uint32_t a0[8], a1[8], b0[8], b1[8];  // minima of the two groups of tile m held by this lane, sets a and b
   int second = 256 * (1 + (int)((threadIdx.x >> 5) & 1)) + (int)(threadIdx.x & 31);
   asm volatile("" : "+v"(second));  // (keeps the reads of the second operand inside the search)
+  constexpr bool kFromLds = SUB == 8 && !EXACT16;
+  auto second_operand = [&](int m) -> h8 {
+    if constexpr (kFromLds) return (&T.image[0][0])[second + 32 * m];
+    return h8{};
+  };
   const f16v zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  auto tile = [&](int m, const h8& y1, const h8& y2, const h4v& nn) -> f16v {
+  auto tile = [&](int m, const h8& s2, const h8& y1, const h8& y2, const h4v& nn) -> f16v {
     f16v d = zero;
     if constexpr (SUB == 8 && EXACT16)
       d = __builtin_amdgcn_mfma_f32_32x32x8f16(R.A2[m], nn, d, 0, 0, 0);
     else if constexpr (SUB == 8)
-      d = __builtin_amdgcn_mfma_f32_32x32x16_f16((&T.image[0][0])[second + 32 * m], y2, d, 0, 0, 0);
+      d = __builtin_amdgcn_mfma_f32_32x32x16_f16(s2, y2, d, 0, 0, 0);
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(R.A[m], y1, d, 0, 0, 0);
   };
   // A result takes eleven issue slots, the minima of one set eight: left to itself the compiler puts them next to
-  // each other and waits.
+  // each other and waits.  The second operand of a tile is read a tile ahead of its products.
   if constexpr (AHEAD) {
-    f16v da = tile(0, ba, ba2, na), db = tile(0, bb, bb2, nb);
+    h8 s_now = second_operand(0), s_next = second_operand(1);
+    __builtin_amdgcn_sched_barrier(0);
+    f16v da = tile(0, s_now, ba, ba2, na), db = tile(0, s_now, bb, bb2, nb);
 #pragma unroll
     for (int m = 0; m < 8; ++m) {
       f16v da_next, db_next;
+      s_now = s_next;
       __builtin_amdgcn_sched_barrier(0);
-      if (m < 7) da_next = tile(m + 1, ba, ba2, na);
+      if (m < 7) da_next = tile(m + 1, s_now, ba, ba2, na);
       __builtin_amdgcn_sched_barrier(0);
+      if (m < 6) s_next = second_operand(m + 2);
       min8x2(da, a0[m], a1[m]);
       __builtin_amdgcn_sched_barrier(0);
-      if (m < 7) db_next = tile(m + 1, bb, bb2, nb);
+      if (m < 7) db_next = tile(m + 1, s_now, bb, bb2, nb);
       __builtin_amdgcn_sched_barrier(0);
       min8x2(db, b0[m], b1[m]);
       if (m < 7) da = da_next, db = db_next;
@@ -279,18 +312,18 @@ __device__ __forceinline__ Nearest search_nearest(const SearchTables<SUB>& T, co
   } else {
 #pragma unroll
     for (int m = 0; m < 8; ++m) {
-      min8x2(tile(m, ba, ba2, na), a0[m], a1[m]);
-      min8x2(tile(m, bb, bb2, nb), b0[m], b1[m]);
+      const h8 s2 = second_operand(m);
+      min8x2(tile(m, s2, ba, ba2, na), a0[m], a1[m]);
+      min8x2(tile(m, s2, bb, bb2, nb), b0[m], b1[m]);
     }
   }
-  // own sub-vector: a0, a1, b0, b1 [m] become the minima of groups 4m, 4m + 1, 4m + 2, 4m + 3
+  // The minima stay where they are: a lane holds those of its half's groups for one sub-vector of either column set.  What
+  // crosses the halves is the smallest of each set, the thresholds and the lists (a swap each, against sixteen for all minima).
+  uint32_t best_a = min(a0[0], a1[0]), best_b = min(b0[0], b1[0]);
 #pragma unroll
-  for (int m = 0; m < 8; m += 2) swap32x4(a0[m], b0[m], a1[m], b1[m], a0[m + 1], b0[m + 1], a1[m + 1], b1[m + 1]);
-  uint32_t best_u = min(min(a0[0], a1[0]), b0[0]), best2 = min(min(b1[0], a0[1]), a1[1]);
-  best_u = min(min(best_u, b0[1]), b1[1]);
-#pragma unroll
-  for (int m = 2; m < 8; ++m) best_u = min(min(best_u, a0[m]), a1[m]), best2 = min(min(best2, b0[m]), b1[m]);
-  const float best = __uint_as_float(min(best_u, best2));
+  for (int m = 1; m < 8; ++m) best_a = min(min(best_a, a0[m]), a1[m]), best_b = min(min(best_b, b0[m]), b1[m]);
+  swap32(best_a, best_b);
+  const float best = __uint_as_float(min(best_a, best_b));
   // Error bound of either form of a distance, relative to M >= (|c| + |y|)^2, in units of 2^-24: the fp16 splits of
   // y and c leave 4 each (two roundings of 2^-11), the dropped low x low product 4, low parts below the normal fp16
   // range 2 (M >= 16), fp32 rounding of the inputs and of the threshold 3, the sum of at most 32 terms 24 (matrix cores)
@@ -298,15 +331,19 @@ __device__ __forceinline__ Nearest search_nearest(const SearchTables<SUB>& T, co
   const float reach = R.cm + 1.0001f * __builtin_amdgcn_sqrtf(yn);
   const float thr_n = fmaf(2.f * 44.f * 5.9604645e-8f * reach, reach, best);  // for D (with n in it)
   const float thr = thr_n - n16;                                              // for the fp32 form
-  uint32_t groups = 0u;
-  auto below = [&](uint32_t t) { return __float_as_uint(__uint_as_float(t) - thr_n); };  // sign bit set: listed
+  float thr_a = thr_n, thr_b = thr_n;
+  swap32(thr_a, thr_b);  // of sets a and b, in both halves
+  uint32_t list_a = 0u, list_b = 0u;
+  auto below = [](uint32_t t, float thr) { return __float_as_uint(__uint_as_float(t) - thr); };  // sign bit set: listed
 #pragma unroll
   for (int m = 7; m >= 0; --m) {
-    groups = __builtin_amdgcn_alignbit(groups, below(b1[m]), 31);
-    groups = __builtin_amdgcn_alignbit(groups, below(b0[m]), 31);
-    groups = __builtin_amdgcn_alignbit(groups, below(a1[m]), 31);
-    groups = __builtin_amdgcn_alignbit(groups, below(a0[m]), 31);
+    list_a = __builtin_amdgcn_alignbit(list_a, below(a1[m], thr_a), 31);
+    list_b = __builtin_amdgcn_alignbit(list_b, below(b1[m], thr_b), 31);
+    list_a = __builtin_amdgcn_alignbit(list_a, below(a0[m], thr_a), 31);
+    list_b = __builtin_amdgcn_alignbit(list_b, below(b0[m], thr_b), 31);
   }
+  swap32(list_a, list_b);  // of the own sub-vector: lower, upper half of the groups
+  uint32_t groups = list_a | list_b << 16;
   // beyond the fp16 range (||y||^2 above 58000), a codebook that is not finite, or not a number: fp64 search below
   if (!(reach < 245.f)) groups = 0u;
   // rows of group g within the bound, as a bit mask
@@ -334,21 +371,33 @@ __device__ __forceinline__ Nearest search_nearest(const SearchTables<SUB>& T, co
     return mask;
   };
   constexpr int kStride = SearchTables<SUB>::kRowStride;
-  int at = 0, found = 0;
+  int at = 0, found = 0, at_before = 0;  // the first candidate of the last group that holds any, and of the one before it
+  uint32_t rows_at = 0u;                  // the candidates of the last such group
   {
     uint32_t left = groups;
     do {
       const int g = left ? __builtin_ctz(left) : 0;
       const uint32_t rows = left ? rows_of(g) : 0u;
-      if (rows) at = g * kStride + __builtin_ctz(rows);
+      if (rows) at_before = at, rows_at = rows, at = g * kStride + __builtin_ctz(rows);
       found += __builtin_popcount(rows);
       left &= left - 1u;
     } while (__any(left != 0u));
   }
   Nearest res;
-  res.code = group_codeword(at / kStride, at % kStride);
+  auto codeword_at = [](int place) { return group_codeword(place / kStride, place % kStride); };
+  res.code = codeword_at(at);
   res.at = at;
-  if (__any(found != 1)) {  // (none at all: not a number somewhere, or out of range)
+  if (!__any(found != 1)) return res;
+  if (!__any((unsigned)(found - 1) > 1u)) {
+    // two candidates (one search of a wave in thirty holds such a sub-vector, mostly one): they are at hand
+    if (found == 2) {
+      const uint32_t other = rows_at & (rows_at - 1u);
+      const int at2 = other ? at - __builtin_ctz(rows_at) + __builtin_ctz(other) : at_before;
+      const int code2 = codeword_at(at2);
+      const double d = exact(res.code), d2 = exact(code2);
+      if (d2 < d || (d2 == d && code2 < res.code)) res.code = code2, res.at = at2;
+    }
+  } else {  // (none at all: not a number somewhere, or out of range)
     double e1 = INFINITY;
     int k1 = 0;
     uint32_t left = found > 1 ? groups : 0u;
