@@ -350,7 +350,7 @@ __device__ __forceinline__ void rotate_token(double (&v)[CPL], int lane) {
   }
 }
 
-template <int SUB, int CPL, bool SIGN, bool ROPE>
+template <int SUB, int CPL, bool SIGN, bool ROPE, bool PASS1>
 __global__ __launch_bounds__(256, 2) void enc_kernel(EncArgs A) {
   static_assert(CPL == 16 || CPL == SUB, "two lane layouts");
   static_assert(!SIGN || SUB == 8, "the sign + index format is defined on 8-dim sub-vectors");
@@ -364,10 +364,27 @@ __global__ __launch_bounds__(256, 2) void enc_kernel(EncArgs A) {
   const Geometry& g = A.g;
   const int h = blockIdx.y >> 1, tensor = blockIdx.y & 1, b = blockIdx.z;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const CacheView& cv = tensor ? A.vc : A.kc;
+  // What a call of few tokens spends its time on is trips to memory one after the other, so everything goes out as early as it
+  // can: the arguments in one go (fetched where they are first needed they are three trips), the codebook beside the
+  // sequence's start, the first token's rows and Shift vector ahead of the set-up of the search.  One token: 5.7 -> 4.4 us; 64
+  // tokens x 8 sequences x 8 heads 11.1 -> 8.9 us, of that 10.7 with the new order alone (the rest: nsn_search.h).
+  asm volatile("" ::"s"(A.codebook), "s"(A.k_in), "s"(A.v_in), "s"(A.max_new), "s"(A.max_len), "s"(A.seq_start), "s"(A.n_new),
+               "s"(A.kc.codes), "s"(A.vc.codes), "s"(A.kc.means), "s"(A.vc.means), "s"(A.kc.norms), "s"(A.vc.norms),
+               "s"(A.wg_tokens), "s"(g.dq), "s"(g.n_kv_heads), "s"(g.n_groups_max), "s"(g.group_size));
+  const CacheView cv = {tensor ? A.vc.codes : A.kc.codes, tensor ? A.vc.norms : A.kc.norms, tensor ? A.vc.means : A.kc.means,
+                        tensor ? A.vc.block_table : A.kc.block_table};
   const __half* in = (tensor ? A.v_in : A.k_in) + (int64_t)(b * g.n_kv_heads + h) * A.max_new * kHeadDim;
-  const int start = A.seq_start[b];
-  const int count = min(min(A.n_new[b], A.max_new), A.max_len - start);  // tokens that have a place in the cache
+  const int start_v = A.seq_start[b], n_new_v = A.n_new[b];
+  // the whole codebook, four rows per lane (every wave finds the longest one), and the thread's own row
+  typedef uint32_t words2 __attribute__((ext_vector_type(2), aligned(4)));
+  typedef uint32_t words4 __attribute__((ext_vector_type(4), aligned(4)));
+  typedef typename std::conditional<SUB == 4, words2, words4>::type row_t;
+  row_t rows[kCodes / 64], own_row = reinterpret_cast<const row_t*>(A.codebook)[tid];
+#pragma unroll
+  for (int k = 0; k < kCodes / 64; ++k) rows[k] = reinterpret_cast<const row_t*>(A.codebook)[lane + 64 * k];
+  asm volatile("" ::: "memory");  // (or the compiler moves them behind the early return)
+  const int start = __builtin_amdgcn_readfirstlane(start_v), n_new = __builtin_amdgcn_readfirstlane(n_new_v);
+  const int count = min(min(n_new, A.max_new), A.max_len - start);  // tokens that have a place in the cache
   const int t_wg = blockIdx.x * A.wg_tokens, block0 = t_wg & ~63;
   if (t_wg >= count) return;  // (the whole workgroup)
   const int64_t mean_row = (int64_t)(b * g.n_kv_heads + h) * g.n_groups_max;
@@ -390,20 +407,52 @@ __global__ __launch_bounds__(256, 2) void enc_kernel(EncArgs A) {
     for (int k = 0; k < kRaw; ++k) xraw[k] = *reinterpret_cast<const raw_t*>(row + 64 * k);
   };
   fetch(t_begin + tok);
-  // pass 1: a wave's sixteen tokens of the 64-token block, four at a time (lane: token lane / 16, channels 8 (lane % 16))
-  const bool pass1 = A.own_means || g.dq;
+  // pass 1 (groups of 64 tokens whose means are formed here, 4-bit side information; an instance of its own, so that no load is
+  // under a condition): a wave's sixteen tokens of the 64-token block, four at a time (lane: token lane / 16, channels
+  // 8 (lane % 16))
+  const bool dq = PASS1 && g.dq, own_means = PASS1 && A.own_means;
   uint4 p1[4];
-  if (pass1) {
+  if constexpr (PASS1) {
 #pragma unroll
     for (int u = 0; u < 4; ++u)
       p1[u] = *reinterpret_cast<const uint4*>(
           in + (int64_t)min(block0 + 16 * wave + 4 * u + (lane >> 4), count - 1) * kHeadDim + 8 * (lane & 15));
   }
+  // Shift vectors as they are stored: the first token's is on its way during the set-up.  (One form of loads for fp16 and 4-bit
+  // means: with a branch the compiler waits for all earlier loads where the two meet.)
+  typedef typename std::conditional<CPL == 4, words2, words4>::type mean_t;
+  mean_t mraw[kRaw];    // fp16 channels, or their 4-bit codes from the first byte on (CPL = 4: from a multiple of four bytes)
+  uint32_t mpar[kRaw];  // 4-bit: (min, step)
+  auto fetch_mean = [&](int gi) {
+    const unsigned char* rec = reinterpret_cast<const unsigned char*>(cv.means) + (mean_row + gi) * (dq ? kDqMeanRec : 2 * kHeadDim);
+#pragma unroll
+    for (int k = 0; k < kRaw; ++k) {
+      const int c = ch0 + 64 * k, at = dq ? (c >> 1) & ~3 : 2 * c;
+      mraw[k] = *reinterpret_cast<const mean_t*>(rec + at);
+      mpar[k] = *reinterpret_cast<const uint32_t*>(rec + (dq ? kDqMeanPar + 4 * (c >> 5) : at));
+    }
+  };
+  auto group_at = [&](int pos) { return min(group_of(g, min(pos, A.max_len - 1)), g.n_groups_max - 1); };
+  int grp = -1;  // Shift group whose mean is in mraw
+  if (!own_means) grp = group_at(start + t_begin + tok);
+  fetch_mean(max(grp, 0));  // (where the means are formed here nothing of it is used)
   SearchRegs<SUB, true> R;
-  // (a rotated token has norm sqrt(128): no sub-vector is longer than 11.4)
-  search_setup<SUB, true>(T, R, tid, [&](int i) { return __half2float(A.codebook[tid * SUB + i]); }, 4);
+  {
+    float n2 = 0.f;
+#pragma unroll
+    for (int k = 0; k < kCodes / 64; ++k) {
+      const __half* c = reinterpret_cast<const __half*>(&rows[k]);
+      float t = 0.f;
+#pragma unroll
+      for (int i = 0; i < SUB; ++i) t = fmaf(__half2float(c[i]), __half2float(c[i]), t);
+      n2 = fmaxf(n2, t);
+    }
+    // (a rotated token has norm sqrt(128): no sub-vector is longer than 11.4)
+    search_setup<SUB, true>(T, R, tid, wave_max_lanes(n2),
+                            [&](int i) { return __half2float(reinterpret_cast<const __half*>(&own_row)[i]); }, 4);
+  }
 
-  if (pass1) {
+  if constexpr (PASS1) {
     double acc[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] = 0.0;
@@ -423,7 +472,7 @@ __global__ __launch_bounds__(256, 2) void enc_kernel(EncArgs A) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) acc[i] = fma(x[i], rb, acc[i]);
     }
-    if (A.own_means) {
+    if (own_means) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) acc[i] = swap_sum32(swap_sum16(acc[i]));
       if (lane < 16) {
@@ -433,10 +482,10 @@ __global__ __launch_bounds__(256, 2) void enc_kernel(EncArgs A) {
     }
     __syncthreads();
     const bool stores = t_wg == block0;  // one of the block's workgroups writes what belongs to the block
-    if (A.own_means && tid < kHeadDim) {
+    if (own_means && tid < kHeadDim) {
       const int64_t mean_index = mean_row + (start + block0) / g.group_size;
       const double mean = (((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid]) / (double)min(64, count - block0);
-      if (!g.dq) {
+      if (!dq) {
         const __half m16 = f64_to_f16(mean);
         mean_s[tid] = (double)__half2float(m16);
         if (stores) cv.means[mean_index * kHeadDim + tid] = m16;
@@ -444,7 +493,7 @@ __global__ __launch_bounds__(256, 2) void enc_kernel(EncArgs A) {
         mean_s[tid] = quantize_mean(mean, tid, stores ? dq_mean_rec(cv, mean_index) : nullptr);
       }
     }
-    if (g.dq && stores && wave == 3) {
+    if (dq && stores && wave == 3) {
       const int pos0 = start + block0;
       quantize_s1(__half2float(b_s[lane]), block0 + lane < count, lane,
                   dq_norm_rec(cv, unit_token_base(g, cv.block_table, b, h, pos0), token_in_unit(g, pos0)));
@@ -454,34 +503,28 @@ __global__ __launch_bounds__(256, 2) void enc_kernel(EncArgs A) {
 
   // ---- pass 2 -----------------------------------------------------------------------------------
   double o[CPL];
-  int grp = -1;  // Shift group whose mean is in o
-  if (A.own_means) {
+  if (own_means) {
 #pragma unroll
     for (int i = 0; i < CPL; ++i) o[i] = mean_s[ch0 + (i & 7) + 64 * (i >> 3)];
   }
-  auto load_mean = [&](int gi) {
-    if (g.dq) {
-      const unsigned char* rec = dq_mean_rec(cv, mean_row + gi);
+  auto unpack_mean = [&]() {
 #pragma unroll
-      for (int k = 0; k < kRaw; ++k) {
-        const int c = ch0 + 64 * k;
-        const uint32_t codes = CPL == 4 ? *reinterpret_cast<const uint16_t*>(rec + (c >> 1))
-                                        : *reinterpret_cast<const uint32_t*>(rec + (c >> 1));
-        const __half2 par = *reinterpret_cast<const __half2*>(rec + kDqMeanPar + 4 * (c >> 5));
+    for (int k = 0; k < kRaw; ++k) {
+      constexpr int N = CPL == 4 ? 4 : 8;
+      if (dq) {
+        const __half2 par = __builtin_bit_cast(__half2, mpar[k]);
         const double mn = (double)__low2float(par), st = (double)__high2float(par);
+        const uint32_t codes = CPL == 4 ? mraw[k].x >> (4 * (ch0 & 4)) : mraw[k].x;
 #pragma unroll
-        for (int i = 0; i < (CPL == 4 ? 4 : 8); ++i) o[8 * k + i] = mn + st * (double)((codes >> (4 * i)) & 15u);
-      }
-    } else {
+        for (int i = 0; i < N; ++i) o[8 * k + i] = mn + st * (double)((codes >> (4 * i)) & 15u);
+      } else {
+        const __half* mh = reinterpret_cast<const __half*>(&mraw[k]);
 #pragma unroll
-      for (int k = 0; k < kRaw; ++k) {
-        const raw_t m = *reinterpret_cast<const raw_t*>(cv.means + (mean_row + gi) * kHeadDim + ch0 + 64 * k);
-        const __half* mh = reinterpret_cast<const __half*>(&m);
-#pragma unroll
-        for (int i = 0; i < (CPL == 4 ? 4 : 8); ++i) o[8 * k + i] = (double)__half2float(mh[i]);
+        for (int i = 0; i < N; ++i) o[8 * k + i] = (double)__half2float(mh[i]);
       }
     }
   };
+  if (!own_means) unpack_mean();
   const double cscale = -0.5 / (double)R.scale;  // codeword element = table entry * cscale (exact: powers of two)
   // the lane's further codes lie at fixed distances from its first one (both layouts are linear in the bits of j)
   const int64_t dq1 = NQ > 1 ? code_offset(g.tiled, tensor != 0, JB, 0, NQ == 4 ? 1 : 2) : 0;
@@ -499,15 +542,16 @@ __global__ __launch_bounds__(256, 2) void enc_kernel(EncArgs A) {
       for (int i = 0; i < (CPL == 4 ? 4 : 8); ++i) v[8 * k + i] = (double)__half2float(xh[i]);
     }
     if (t0 + TPS < t_end) fetch(t + TPS);
-    if (!A.own_means) {
-      const int want = min(group_of(g, min(pos, A.max_len - 1)), g.n_groups_max - 1);
+    if (!own_means) {
+      const int want = group_at(pos);
       if (__any(want != grp)) {
-        load_mean(want);
         grp = want;
+        fetch_mean(grp);
+        unpack_mean();
       }
     }
     __half b16;
-    if (pass1) {
+    if constexpr (PASS1) {
       b16 = b_s[min(t - block0, 63)];
     } else {
       double ss = 0.0;
@@ -616,7 +660,7 @@ __global__ __launch_bounds__(256, 2) void enc_kernel(EncArgs A) {
     dot = token_sum<CPL>(dot) * cscale;
     const double alpha = dot > 1e-12 * kHeadDim ? (double)kHeadDim * rcp_f64(dot) : 1.0;
     if (valid && leader) {
-      if (g.dq)  // a' = fp16(s2 alpha); s1 is stored as a 4-bit code
+      if (dq)  // a' = fp16(s2 alpha); s1 is stored as a 4-bit code
         reinterpret_cast<__half*>(dq_norm_rec(cv, base, tin))[tin & 63] = f64_to_f16(s2 * alpha);
       else
         cv.norms[base + tin] = __halves2half2(f64_to_f16(bb * s2 * alpha), b16);
@@ -881,9 +925,12 @@ int encode_launch(const nsn_shape& s, const void* codebook, const void* k_in, co
     return hipGetLastError() == hipSuccess ? NSN_OK : NSN_ERR_HIP;
   }
   // The sixteen-channel layout does the least work per token but takes at least eight tokens through one wave; below the
-  // line its waves are too few to fill the chip (8192 tokens: one wave per SIMD).  Measured, small / bulk layout:
-  // 4-dim 8192 tokens 13.5 / 11.2 us, 32768 tokens 41 / 25 us; 8-dim 8192 tokens 9.3 / 10.9 us, 32768 tokens 27 / 21 us.
-  const bool bulk = tokens >= (s.sub_dim == 4 ? 8192 : 16384);
+  // line its waves are too few to fill the chip (8192 tokens: one wave per SIMD).  Measured, small / bulk layout, 4-dim: 4096
+  // tokens 6.4 / 8.5 us, 6144 tokens 8.8 / 8.6 us, 32768 tokens 34 / 21 us; 8-dim: 8192 tokens 7.4 / 8.2 us, 12288 tokens
+  // 10.5 / 10.4 us, 32768 tokens 21 / 17 us; with pass 1: 4-dim 4096 / 6144 tokens 8.7 / 10.3 and 13.7 / 11.5 us, everything of
+  // the paper 8192 / 12288 tokens 12.5 / 12.6 and 19.1 / 15.2 us.  (Sixteen lanes per token and eight channels of two 4-dim
+  // sub-vectors in each, a layout between the two: 8.2 us for 6144, 8.5 for 8192 (bulk 9.0), 14.8 for 16384 tokens (13.2).)
+  const bool bulk = tokens >= (s.sub_dim == 4 ? 6144 : 12288);
   EncArgs a = {g, (const __half*)codebook, (const __half*)k_in, (const __half*)v_in, max_new, s.max_len, seq_start, n_new,
                kv, vv, 64, own_means};
   // tokens per workgroup: one step per wave where that is what fills the chip, several where the workgroup's set-up
@@ -899,7 +946,10 @@ int encode_launch(const nsn_shape& s, const void* codebook, const void* k_in, co
   auto pick = [&](auto sub, auto sign, auto rope) {
     constexpr int kSub = decltype(sub)::value;
     constexpr bool kSign = decltype(sign)::value, kRope = decltype(rope)::value;
-    bulk ? launch(enc_kernel<kSub, 16, kSign, kRope>) : launch(enc_kernel<kSub, kSub, kSign, kRope>);
+    if (own_means || g.dq)
+      bulk ? launch(enc_kernel<kSub, 16, kSign, kRope, true>) : launch(enc_kernel<kSub, kSub, kSign, kRope, true>);
+    else
+      bulk ? launch(enc_kernel<kSub, 16, kSign, kRope, false>) : launch(enc_kernel<kSub, kSub, kSign, kRope, false>);
   };
   auto with_format = [&](auto rope) {
     if (g.sign)
