@@ -264,6 +264,7 @@ __global__ __launch_bounds__(128) void enc_means_kernel(Geometry g, int max_new,
 //     token passes through LDS so that the search is a loop over the lane's sub-vectors (one copy of its code, its
 //     registers free).
 //   CPL = SUB (small calls): as many lanes as there are sub-vectors: the shortest chain of instructions per token.
+//   CPL = 8 of 4-dim sub-vectors (calls between the two): sixteen lanes per token, two sub-vectors in each.
 // (One sub-vector per lane for all sizes and a best-two search in one pass, the form this replaces, took 1147 vector
 // instructions per two 4-dim tokens.)
 // Lane layout for CPL = 16: bits 0, 4, 5 of the lane select channels 8 (l0 + 2 l4 + 4 l5) .. + 7 and the same plus 64,
@@ -352,10 +353,10 @@ __device__ __forceinline__ void rotate_token(double (&v)[CPL], int lane) {
 
 template <int SUB, int CPL, bool SIGN, bool ROPE, bool PASS1>
 __global__ __launch_bounds__(256, 2) void enc_kernel(EncArgs A) {
-  static_assert(CPL == 16 || CPL == SUB, "two lane layouts");
+  static_assert(CPL == 16 || CPL == 8 || CPL == SUB, "lane layouts");
   static_assert(!SIGN || SUB == 8, "the sign + index format is defined on 8-dim sub-vectors");
   constexpr int J = kHeadDim / SUB, JB = SIGN ? 2 * J : J;  // sub-vectors, code bytes per token
-  constexpr int NQ = CPL / SUB;                             // sub-vectors per lane
+  constexpr int NQ = CPL / SUB, LPT = kHeadDim / CPL;       // sub-vectors per lane, lanes per token
   constexpr int TPS = 64 * CPL / kHeadDim;                  // tokens per wave step
   __shared__ SearchTables<SUB> T;
   __shared__ double2 y_s[CPL == SUB ? 1 : 4][CPL == SUB ? 1 : CPL / 2][64];  // rotated tokens, per wave
@@ -390,12 +391,12 @@ __global__ __launch_bounds__(256, 2) void enc_kernel(EncArgs A) {
   const int64_t mean_row = (int64_t)(b * g.n_kv_heads + h) * g.n_groups_max;
 
   // ---- the lane's token and channels --------------------------------------------------------------
-  const int tok = CPL == 16 ? (lane >> 1) & 7 : lane / J;
+  const int tok = CPL == 16 ? (lane >> 1) & 7 : lane / LPT;
   const int l0 = lane & 1, l4 = (lane >> 4) & 1, l5 = lane >> 5;
-  const int jj = lane % J;
-  const int ch0 = CPL == 16 ? 8 * (l0 + 2 * l4 + 4 * l5) : jj * SUB;
+  const int jj = lane % LPT;
+  const int ch0 = CPL == 16 ? 8 * (l0 + 2 * l4 + 4 * l5) : jj * CPL;
   const bool leader = CPL == 16 ? (lane & 0x31) == 0 : jj == 0;
-  const int j_first = CPL == 16 ? (SUB == 4 ? 16 * l5 + 8 * l4 + 2 * l0 : 8 * l5 + 4 * l4 + l0) : jj;
+  const int j_first = CPL == 16 ? (SUB == 4 ? 16 * l5 + 8 * l4 + 2 * l0 : 8 * l5 + 4 * l4 + l0) : jj * NQ;
   constexpr int kRaw = CPL == 4 ? 1 : CPL / 8;  // 16-byte (CPL = 4: 8-byte) pieces of the lane's inputs
   typedef typename std::conditional<CPL == 4, uint2, uint4>::type raw_t;
   const int wave_tokens = A.wg_tokens >> 2;
@@ -527,7 +528,7 @@ __global__ __launch_bounds__(256, 2) void enc_kernel(EncArgs A) {
   if (!own_means) unpack_mean();
   const double cscale = -0.5 / (double)R.scale;  // codeword element = table entry * cscale (exact: powers of two)
   // the lane's further codes lie at fixed distances from its first one (both layouts are linear in the bits of j)
-  const int64_t dq1 = NQ > 1 ? code_offset(g.tiled, tensor != 0, JB, 0, NQ == 4 ? 1 : 2) : 0;
+  const int64_t dq1 = NQ > 1 ? code_offset(g.tiled, tensor != 0, JB, 0, CPL == 16 && SUB == 8 ? 2 : 1) : 0;
   const int64_t dq2 = NQ > 2 ? code_offset(g.tiled, tensor != 0, JB, 0, 4) : 0;
   const int64_t dsign = SIGN ? code_offset(g.tiled, tensor != 0, JB, 0, J) : 0;
 
@@ -588,8 +589,8 @@ __global__ __launch_bounds__(256, 2) void enc_kernel(EncArgs A) {
             const double x0 = v[i], x1 = v[i + 8];
             v[i] = x0 * c - x1 * sn;
             v[i + 8] = x1 * c + x0 * sn;
-          } else {  // the partner channel lives in lane ^ (J / 2)
-            const double other = xor_lane<J / 2>(v[i]);
+          } else {  // the partner channel lives in lane ^ (LPT / 2)
+            const double other = xor_lane<LPT / 2>(v[i]);
             v[i] = v[i] * c + side * other * sn;
           }
         }
@@ -928,15 +929,18 @@ int encode_launch(const nsn_shape& s, const void* codebook, const void* k_in, co
   // line its waves are too few to fill the chip (8192 tokens: one wave per SIMD).  Measured, small / bulk layout, 4-dim: 4096
   // tokens 6.4 / 8.5 us, 6144 tokens 8.8 / 8.6 us, 32768 tokens 34 / 21 us; 8-dim: 8192 tokens 7.4 / 8.2 us, 12288 tokens
   // 10.5 / 10.4 us, 32768 tokens 21 / 17 us; with pass 1: 4-dim 4096 / 6144 tokens 8.7 / 10.3 and 13.7 / 11.5 us, everything of
-  // the paper 8192 / 12288 tokens 12.5 / 12.6 and 19.1 / 15.2 us.  (Sixteen lanes per token and eight channels of two 4-dim
-  // sub-vectors in each, a layout between the two: 8.2 us for 6144, 8.5 for 8192 (bulk 9.0), 14.8 for 16384 tokens (13.2).)
-  const bool bulk = tokens >= (s.sub_dim == 4 ? 6144 : 12288);
+  // the paper 8192 / 12288 tokens 12.5 / 12.6 and 19.1 / 15.2 us.  Around the 4-dim line eight channels per lane are faster
+  // than either (not with pass 1, which every workgroup goes through): small / eight / bulk 6.4 / 6.4 / 8.5 us for 4096 tokens,
+  // 8.8 / 8.2 / 8.6 for 6144, 10.6 / 8.5 / 9.0 for 8192, 14.7 / 11.6 / 12.3 for 12288, 18.9 / 14.8 / 13.2 for 16384.
+  const bool pass1 = own_means || g.dq;
+  const bool bulk = tokens >= (s.sub_dim == 8 ? 12288 : pass1 ? 6144 : 14336);
+  const bool eight = s.sub_dim == 4 && !pass1 && !bulk && tokens > 4096;
   EncArgs a = {g, (const __half*)codebook, (const __half*)k_in, (const __half*)v_in, max_new, s.max_len, seq_start, n_new,
                kv, vv, 64, own_means};
   // tokens per workgroup: one step per wave where that is what fills the chip, several where the workgroup's set-up
   // (tables, operands: about a sixth of a step) is worth sharing; a 64-token block is the most that pass 1 holds
   if (!bulk)
-    a.wg_tokens = s.sub_dim == 4 ? 8 : 16;
+    a.wg_tokens = s.sub_dim == 4 && !eight ? 8 : 16;
   else if (tokens < 32768)
     a.wg_tokens = 32;
   else if (tokens >= 524288 && !own_means && !g.dq)
@@ -946,8 +950,10 @@ int encode_launch(const nsn_shape& s, const void* codebook, const void* k_in, co
   auto pick = [&](auto sub, auto sign, auto rope) {
     constexpr int kSub = decltype(sub)::value;
     constexpr bool kSign = decltype(sign)::value, kRope = decltype(rope)::value;
-    if (own_means || g.dq)
+    if (pass1)
       bulk ? launch(enc_kernel<kSub, 16, kSign, kRope, true>) : launch(enc_kernel<kSub, kSub, kSign, kRope, true>);
+    else if (eight)
+      launch(enc_kernel<kSub, 8, kSign, kRope, false>);
     else
       bulk ? launch(enc_kernel<kSub, 16, kSign, kRope, false>) : launch(enc_kernel<kSub, kSub, kSign, kRope, false>);
   };

@@ -1,0 +1,56 @@
+"""The encoder's layout between the other two (4-dim sub-vectors, eight channels per lane, no pass for means of 64-token groups or
+4-bit side information) stores the same bytes as the layout of small calls: a ragged batch of 9240 token places against the same
+sequences one at a time (3080).  Lengths sit at the edges of its 4-token steps and 16-token workgroups."""
+import numpy as np
+import pytest
+
+from paper_2505_18231_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+LENS = [[1, 5, 385], [16, 17, 63], [300, 4, 128]]
+CASES = [(False, 0, 0, 0), (False, 128, 64, 128), (True, 0, 64, 0), (True, 256, 0, 61), (False, 64, 0, 30)]  # rope, group, page, start
+
+
+@pytest.mark.parametrize("lens", LENS)
+@pytest.mark.parametrize("rope,G,page,start", CASES)
+def test_middle_call_equals_sequence_by_sequence(gpu_api, codebooks, rope, G, page, start, lens):
+    import torch
+    api = gpu_api
+    B, H, cap, max_len = len(lens), 4, 385, 1024
+    print(f"case rope={rope} G={G} page={page} start={start} lens={lens}", flush=True)
+    assert 4096 >= 2 * H * cap and 4096 < 2 * B * H * cap < 14336
+    g = torch.Generator(device="cuda").manual_seed(15)
+    cb = torch.from_numpy(codebooks[4].astype(np.float16)).cuda()
+    table = api.nsn_build_rope_table(synth.rope_inv_freq(5e5), max_len) if rope else None
+    shape = api.make_shape(4, H, H, max_len, G, page, rope_table=table)
+    bt = torch.from_numpy(synth.shuffled_page_table(3, B, max_len // page)).cuda() if page else None
+    k, v = (torch.randn((B, H, cap, 128), generator=g, device="cuda").half() for _ in range(2))
+    k += 3.0
+    n = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    pos = torch.full((B,), start, dtype=torch.int32, device="cuda")
+    freeze = start > 0 and (G == 0 or start % G != 0)
+
+    def fresh():
+        caches = api.alloc_cache(shape, B, block_table=bt), api.alloc_cache(shape, B, block_table=bt)
+        for c in caches:
+            c.means.copy_((0.1 * torch.randn(c.means.shape, generator=torch.Generator().manual_seed(1))).half())
+        return caches
+
+    kc, vc = fresh()
+    api.nsn_encode(shape, cb, k, v, pos, n, kc, vc, freeze_means=freeze)
+    kr, vr = fresh()
+
+    def part(c, b):
+        if page:
+            return api.CodedCache(c.codes, c.norms, c.means[b:b + 1], c.block_table[b:b + 1])
+        return api.CodedCache(c.codes[b:b + 1], c.norms[b:b + 1], c.means[b:b + 1], None)
+
+    for b in range(B):
+        api.nsn_encode(shape, cb, k[b:b + 1].contiguous(), v[b:b + 1].contiguous(), pos[b:b + 1], n[b:b + 1], part(kr, b),
+                       part(vr, b), freeze_means=freeze)
+    torch.cuda.synchronize()
+    for x, y in ((kc, kr), (vc, vr)):
+        for name in ("codes", "norms", "means"):
+            assert torch.equal(getattr(x, name), getattr(y, name)), name
+        assert int((x.codes != 0).sum()) > 0
