@@ -279,31 +279,57 @@ __device__ __forceinline__ Nearest search_nearest(const SearchTables<SUB>& T, co
     return h8{};
   };
   const f16v zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  auto tile = [&](int m, const h8& s2, const h8& y1, const h8& y2, const h4v& nn) -> f16v {
-    f16v d = zero;
+  // a tile's product with 8-dim codewords is two matrix instructions, the second on the result of the first
+  auto first_half = [&](int m, const h8& s2, const h8& y2, const h4v& nn) -> f16v {
     if constexpr (SUB == 8 && EXACT16)
-      d = __builtin_amdgcn_mfma_f32_32x32x8f16(R.A2[m], nn, d, 0, 0, 0);
+      return __builtin_amdgcn_mfma_f32_32x32x8f16(R.A2[m], nn, zero, 0, 0, 0);
     else if constexpr (SUB == 8)
-      d = __builtin_amdgcn_mfma_f32_32x32x16_f16(s2, y2, d, 0, 0, 0);
+      return __builtin_amdgcn_mfma_f32_32x32x16_f16(s2, y2, zero, 0, 0, 0);
+    return zero;
+  };
+  auto second_half = [&](int m, const h8& y1, const f16v& d) -> f16v {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(R.A[m], y1, d, 0, 0, 0);
   };
+  auto tile = [&](int m, const h8& s2, const h8& y1, const h8& y2, const h4v& nn) -> f16v {
+    return second_half(m, y1, first_half(m, s2, y2, nn));
+  };
   // A result takes eleven issue slots, the minima of one set eight: left to itself the compiler puts them next to
-  // each other and waits.  The second operand of a tile is read a tile ahead of its products.
-  if constexpr (AHEAD) {
+  // each other and waits.
+  if constexpr (AHEAD && kFromLds) {
+    // The second operand of a tile is read a tile ahead of its products, and the first halves of both sets go out before
+    // either's second, which would wait for it: a K-Means iteration of 2^20 8-dim samples 32.7 -> 31.2 us.  (In the encoder,
+    // where the second operands are in registers, the longer lives cost as much as the waits.)
     h8 s_now = second_operand(0), s_next = second_operand(1);
     __builtin_amdgcn_sched_barrier(0);
-    f16v da = tile(0, s_now, ba, ba2, na), db = tile(0, s_now, bb, bb2, nb);
+    f16v ea = first_half(0, s_now, ba2, na), eb = first_half(0, s_now, bb2, nb);
+    f16v da = second_half(0, ba, ea), db = second_half(0, bb, eb);
 #pragma unroll
     for (int m = 0; m < 8; ++m) {
-      f16v da_next, db_next;
       s_now = s_next;
       __builtin_amdgcn_sched_barrier(0);
-      if (m < 7) da_next = tile(m + 1, s_now, ba, ba2, na);
+      if (m < 7) ea = first_half(m + 1, s_now, ba2, na), eb = first_half(m + 1, s_now, bb2, nb);
       __builtin_amdgcn_sched_barrier(0);
       if (m < 6) s_next = second_operand(m + 2);
       min8x2(da, a0[m], a1[m]);
       __builtin_amdgcn_sched_barrier(0);
-      if (m < 7) db_next = tile(m + 1, s_now, bb, bb2, nb);
+      if (m < 7) da = second_half(m + 1, ba, ea);
+      __builtin_amdgcn_sched_barrier(0);
+      min8x2(db, b0[m], b1[m]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (m < 7) db = second_half(m + 1, bb, eb);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  } else if constexpr (AHEAD) {
+    f16v da = tile(0, h8{}, ba, ba2, na), db = tile(0, h8{}, bb, bb2, nb);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      f16v da_next, db_next;
+      __builtin_amdgcn_sched_barrier(0);
+      if (m < 7) da_next = tile(m + 1, h8{}, ba, ba2, na);
+      __builtin_amdgcn_sched_barrier(0);
+      min8x2(da, a0[m], a1[m]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (m < 7) db_next = tile(m + 1, h8{}, bb, bb2, nb);
       __builtin_amdgcn_sched_barrier(0);
       min8x2(db, b0[m], b1[m]);
       if (m < 7) da = da_next, db = db_next;
