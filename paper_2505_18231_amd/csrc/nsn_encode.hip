@@ -153,15 +153,14 @@ __device__ inline int rtn4_code(double x, double mn, double st) {
 // lane 0 is valid)
 __device__ __forceinline__ void quantize_s1(float x, bool valid, int lane, unsigned char* rec) {
   float lo = valid ? x : INFINITY, hi = valid ? x : -INFINITY;
-#pragma unroll
-  for (int m = 1; m < 64; m <<= 1) {
-    lo = fminf(lo, __shfl_xor(lo, m, 64));
-    hi = fmaxf(hi, __shfl_xor(hi, m, 64));
-  }
+  static_for_pow2<64>([&](auto mask) {
+    constexpr int m = decltype(mask)::value;
+    lo = fminf(lo, xor_lane<m>(lo)), hi = fmaxf(hi, xor_lane<m>(hi));
+  });
   const __half mn16 = f64_to_f16((double)lo);  // exact: the minimum is one of the fp16 inputs
   const __half st16 = f64_to_f16(((double)hi - (double)lo) / 15.0);
   const int code = valid ? rtn4_code((double)x, (double)__half2float(mn16), (double)__half2float(st16)) : 0;
-  const int other = __shfl_xor(code, 1, 64);
+  const int other = xor_lane_i32<1>(code);
   if ((lane & 1) == 0 && valid) rec[kDqNormCodes + (lane >> 1)] = (unsigned char)(code | (other << 4));
   if (lane == 0) *reinterpret_cast<__half2*>(rec + kDqNormPar) = __halves2half2(mn16, st16);
 }
@@ -170,15 +169,14 @@ __device__ __forceinline__ void quantize_s1(float x, bool valid, int lane, unsig
 // stores the record where one is given.
 __device__ __forceinline__ double quantize_mean(double mean, int c, unsigned char* rec) {
   double lo = mean, hi = mean;
-#pragma unroll
-  for (int m = 1; m < 32; m <<= 1) {
-    lo = fmin(lo, __shfl_xor(lo, m, 64));
-    hi = fmax(hi, __shfl_xor(hi, m, 64));
-  }
+  static_for_pow2<32>([&](auto mask) {
+    constexpr int m = decltype(mask)::value;
+    lo = fmin(lo, xor_lane<m>(lo)), hi = fmax(hi, xor_lane<m>(hi));
+  });
   const __half mn16 = f64_to_f16(lo), st16 = f64_to_f16((hi - lo) / 15.0);
   const double mn = (double)__half2float(mn16), st = (double)__half2float(st16);
   const int code = rtn4_code(mean, mn, st);
-  const int other = __shfl_xor(code, 1, 64);
+  const int other = xor_lane_i32<1>(code);
   if (rec) {
     if ((c & 1) == 0) rec[c >> 1] = (unsigned char)(code | (other << 4));
     if ((c & 31) == 0) *reinterpret_cast<__half2*>(rec + kDqMeanPar + 4 * (c >> 5)) = __halves2half2(mn16, st16);
