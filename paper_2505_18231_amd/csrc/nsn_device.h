@@ -125,17 +125,13 @@ __device__ inline unsigned char* dq_mean_rec(const CacheView& cv, int64_t mean_i
 // ---- numeric helpers ------------------------------------------------------------------
 // fp64 -> fp16, round to nearest even in a single rounding: go through fp32 with
 // round-to-odd (sticky bit in the last place), then the hardware fp32 -> fp16 rounding.
+// (Selects and no branches: several conversions can then be under way at once.)
 __device__ inline __half f64_to_f16(double x) {
   float f = (float)x;
   const double r = x - (double)f;
-  if (r != 0.0 && f != 0.0f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 1u) == 0u) {
-      const bool grow = (r > 0.0) == (f > 0.0f);
-      u = grow ? u + 1u : u - 1u;
-      f = __uint_as_float(u);
-    }
-  }
+  const uint32_t u = __float_as_uint(f);
+  const bool sticky = (r != 0.0) & (f != 0.0f) & ((u & 1u) == 0u), grow = (r > 0.0) == (f > 0.0f);
+  f = __uint_as_float(sticky ? (grow ? u + 1u : u - 1u) : u);
   return __float2half_rn(f);
 }
 

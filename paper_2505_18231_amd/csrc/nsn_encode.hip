@@ -30,12 +30,11 @@ __device__ __forceinline__ void static_for_pow2(F&& f) {
 // Square root and reciprocals from the hardware estimates (about 2^-26) and Newton steps, within an fp64 unit or two.  The
 // arguments are sums of squares of moderate numbers or fp16 values: zero or far inside the fp64 range.
 __device__ __forceinline__ double sqrt_f64(double x) {
-  if (x == 0.0) return 0.0;
   const double y = __builtin_amdgcn_rsq(x);
   double g = x * y, h = 0.5 * y;
   const double r = fma(-h, g, 0.5);
   g = fma(g, r, g), h = fma(h, r, h);
-  return fma(fma(-g, g, x), h, g);
+  return x == 0.0 ? 0.0 : fma(fma(-g, g, x), h, g);
 }
 __device__ __forceinline__ double rcp_f64(double x) {  // 0 for 0
   double r = __builtin_amdgcn_rcp(x);
