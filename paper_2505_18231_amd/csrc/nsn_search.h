@@ -421,7 +421,8 @@ __device__ __forceinline__ Nearest search_nearest(const SearchTables<SUB>& T, co
       const int at2 = other ? at - __builtin_ctz(rows_at) + __builtin_ctz(other) : at_before;
       const int code2 = codeword_at(at2);
       const double d = exact(res.code), d2 = exact(code2);
-      if (d2 < d || (d2 == d && code2 < res.code)) res.code = code2, res.at = at2;
+      // (a codeword that holds a NaN is listed with its group where the sign bit is set: it is never the nearest)
+      if (d2 < d || d != d || (d2 == d && code2 < res.code)) res.code = code2, res.at = at2;
     }
   } else {  // (none at all: not a number somewhere, or out of range)
     double e1 = INFINITY;
