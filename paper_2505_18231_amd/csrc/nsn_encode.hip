@@ -909,6 +909,43 @@ size_t encode_workspace_bytes(const nsn_shape& s, int batch, int64_t max_new) {
   return encode_partial_bytes(s, batch, max_new) + b_bytes;
 }
 
+// What a call takes in one lane layout, in us: a fixed part and so much per round of the chip, a workgroup on each of its 256
+// compute units (two fit; the time grows by one step for every 256 of them all the same).  A round of workgroups with one wave
+// at work is shorter.  Fitted to 6639 calls of 1 to 450 tokens a sequence and 128 to 150000 token places, 15 formats, each timed in
+// every layout: the layout chosen is 0.3 % slower than the best one of a call in the geometric mean, where lines drawn at
+// numbers of token places (8-dim 12288; 4-dim 4096, 6144 and 14336) made it 7.4 %, and for few tokens of many
+// sequences up to twice as slow.  Small / eight / bulk, us: one token x 768 sequences x 8 kv heads, 8-dim 84 / - / 142; 4-dim, 8 kv
+// heads: 5 tokens x 75 sequences 12.0 / 15.2 / 16.7, 9 x 65 19.4 / 15.6 / 21.9, 64 x 4 6.4 / 6.5 / 8.6, 64 x 9 12.1 / 11.0 / 11.7,
+// 64 x 13 16.1 / 13.6 / 12.0, 64 x 30 31.7 / 24.7 / 21.4.
+struct LayoutTime {
+  float fixed, one_wave, round;
+};
+struct LayoutTimes {
+  LayoutTime small, eight, bulk;
+};
+constexpr LayoutTimes kLayoutTimes[2][2][2] = {  // 4-dim, 8-dim | pass 1 | keys before the rotary embedding
+    {{{{2.3f, 1.45f, 1.85f}, {2.4f, 1.5f, 2.6f}, {5.1f, 2.4f, 3.7f}}, {{2.6f, 1.4f, 2.2f}, {4.1f, 1.4f, 3.2f}, {5.4f, 2.8f, 3.85f}}},
+     {{{3.4f, 2.65f, 2.75f}, {}, {5.1f, 4.4f, 4.6f}}, {{3.4f, 2.65f, 2.75f}, {}, {5.1f, 4.4f, 4.6f}}}},
+    {{{{3.2f, 1.9f, 2.5f}, {}, {4.8f, 3.1f, 3.5f}}, {{3.6f, 1.7f, 3.1f}, {}, {4.2f, 3.5f, 4.3f}}},
+     {{{4.2f, 3.0f, 3.25f}, {}, {4.7f, 4.05f, 4.6f}}, {{5.1f, 3.8f, 4.0f}, {}, {4.5f, 4.8f, 5.0f}}}}};
+
+// The lane layout of a call: channels per lane (4, 8 or 16).  Tokens are counted by the workgroups that they take, not by their
+// number: a call of many sequences with a few tokens each fills neither the waves nor the workgroups of the sixteen-channel layout.
+int encode_layout(const nsn_shape& s, int batch, int max_new, bool pass1) {
+  const LayoutTimes& times = kLayoutTimes[s.sub_dim == 8][pass1][s.rope_table != nullptr];
+  auto workgroups = [&](int wg_tokens) {
+    return (int64_t)s.n_kv_heads * 2 * batch * ((max_new + wg_tokens - 1) / wg_tokens);
+  };
+  auto estimate = [&](const LayoutTime& t, int wg_tokens) {
+    return t.fixed + (float)((workgroups(wg_tokens) + 255) / 256) * (max_new <= wg_tokens / 4 ? t.one_wave : t.round);
+  };
+  const int small_tokens = s.sub_dim == 8 ? 16 : 8;
+  if (workgroups(small_tokens) <= 512) return s.sub_dim;  // all of them are under way at once: the shortest chain
+  const float small = estimate(times.small, small_tokens), bulk = estimate(times.bulk, 32);
+  const float eight = s.sub_dim == 4 && !pass1 ? estimate(times.eight, 16) : INFINITY;
+  return bulk < fminf(small, eight) ? 16 : eight < small ? 8 : s.sub_dim;
+}
+
 int encode_launch(const nsn_shape& s, const void* codebook, const void* k_in, const void* v_in, int max_new,
                   const int32_t* seq_start, const int32_t* n_new, int batch, int freeze_means,
                   const nsn_cache& kc, const nsn_cache& vc, void* workspace, hipStream_t stream) {
@@ -954,22 +991,15 @@ int encode_launch(const nsn_shape& s, const void* codebook, const void* k_in, co
       fused ? launch(enc_quant_kernel<4, true>) : launch(enc_quant_kernel<4, false>);
     return hipGetLastError() == hipSuccess ? NSN_OK : NSN_ERR_HIP;
   }
-  // The sixteen-channel layout does the least work per token but takes at least eight tokens through one wave; below the
-  // line its waves are too few to fill the chip (8192 tokens: one wave per SIMD).  Measured, small / bulk layout, 4-dim: 4096
-  // tokens 6.4 / 8.5 us, 6144 tokens 8.8 / 8.6 us, 32768 tokens 34 / 21 us; 8-dim: 8192 tokens 7.4 / 8.2 us, 12288 tokens
-  // 10.5 / 10.4 us, 32768 tokens 21 / 17 us; with pass 1: 4-dim 4096 / 6144 tokens 8.7 / 10.3 and 13.7 / 11.5 us, everything of
-  // the paper 8192 / 12288 tokens 12.5 / 12.6 and 19.1 / 15.2 us.  Around the 4-dim line eight channels per lane are faster
-  // than either (not with pass 1, which every workgroup goes through): small / eight / bulk 6.4 / 6.4 / 8.5 us for 4096 tokens,
-  // 8.8 / 8.2 / 8.6 for 6144, 10.6 / 8.5 / 9.0 for 8192, 14.7 / 11.6 / 12.3 for 12288, 18.9 / 14.8 / 13.2 for 16384.
   const bool pass1 = own_means || g.dq;
-  const bool bulk = tokens >= (s.sub_dim == 8 ? 12288 : pass1 ? 6144 : 14336);
-  const bool eight = s.sub_dim == 4 && !pass1 && !bulk && tokens > 4096;
+  const int layout = encode_layout(s, batch, max_new, pass1), small_tokens = s.sub_dim == 8 ? 16 : 8;
+  const bool bulk = layout == 16, eight = layout > s.sub_dim && !bulk;
   EncArgs a = {g, (const __half*)codebook, (const __half*)k_in, (const __half*)v_in, max_new, s.max_len, seq_start, n_new,
                kv, vv, 64, own_means};
   // tokens per workgroup: one step per wave where that is what fills the chip, several where the workgroup's set-up
   // (tables, operands: about a sixth of a step) is worth sharing; a 64-token block is the most that pass 1 holds
   if (!bulk)
-    a.wg_tokens = s.sub_dim == 4 && !eight ? 8 : 16;
+    a.wg_tokens = eight ? 16 : small_tokens;
   else if (tokens < 32768)
     a.wg_tokens = 32;
   else if (tokens >= 524288 && !own_means && !g.dq)

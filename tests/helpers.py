@@ -148,6 +148,13 @@ def decode_splits(api, shape, batch: int, bound: int, n_splits: int = 0) -> int:
     return rule(C.byref(shape), batch, bound, n_splits)
 
 
+def encode_layout(api, shape, batch: int, max_new: int, freeze_means: bool = False) -> int:
+    """Channels per lane (4, 8 or 16) of the layout that an encode call resolves to (the library's own rule)."""
+    rule = api.lib()["_ZN3nsn13encode_layoutERK9nsn_shapeiib"]  # nsn::encode_layout(const nsn_shape&, int, int, bool)
+    rule.restype, rule.argtypes = C.c_int, [C.c_void_p, C.c_int, C.c_int, C.c_bool]
+    return rule(C.byref(shape), batch, max_new, shape.side_bits == 4 or (shape.group_size == 64 and not freeze_means))
+
+
 def whole(lens) -> int:
     """The longest length in whole pages and groups of 64, 128, 192 and 256 tokens."""
     return max(768, (max(lens) + 767) // 768 * 768)

@@ -1,10 +1,12 @@
 """The encoder's layout between the other two (4-dim sub-vectors, eight channels per lane, no pass for means of 64-token groups or
-4-bit side information) stores the same bytes as the layout of small calls: a ragged batch of 9240 token places against the same
-sequences one at a time (3080).  Lengths sit at the edges of its 4-token steps and 16-token workgroups."""
+4-bit side information) stores the same bytes as the layout of small calls: a ragged batch of three sequences (of 60 with up to
+16 tokens each for keys before the rotary embedding, where longer ones take the other layouts) against the same sequences one
+at a time.  Lengths sit at the edges of its 4-token steps and 16-token workgroups."""
 import numpy as np
 import pytest
 
 from paper_2505_18231_amd import synth
+from tests import helpers
 
 pytestmark = pytest.mark.gpu
 
@@ -17,9 +19,10 @@ CASES = [(False, 0, 0, 0), (False, 128, 64, 128), (True, 0, 64, 0), (True, 256, 
 def test_middle_call_equals_sequence_by_sequence(gpu_api, codebooks, rope, G, page, start, lens):
     import torch
     api = gpu_api
-    B, H, cap, max_len = len(lens), 4, 385, 1024
+    if rope:
+        lens = [1 + (5 * i + lens[0]) % 16 for i in range(60)]
+    B, H, cap, max_len = len(lens), 4, 16 if rope else 385, 1024
     print(f"case rope={rope} G={G} page={page} start={start} lens={lens}", flush=True)
-    assert 4096 >= 2 * H * cap and 4096 < 2 * B * H * cap < 14336
     g = torch.Generator(device="cuda").manual_seed(15)
     cb = torch.from_numpy(codebooks[4].astype(np.float16)).cuda()
     table = api.nsn_build_rope_table(synth.rope_inv_freq(5e5), max_len) if rope else None
@@ -30,6 +33,7 @@ def test_middle_call_equals_sequence_by_sequence(gpu_api, codebooks, rope, G, pa
     n = torch.tensor(lens, dtype=torch.int32, device="cuda")
     pos = torch.full((B,), start, dtype=torch.int32, device="cuda")
     freeze = start > 0 and (G == 0 or start % G != 0)
+    assert [helpers.encode_layout(api, shape, n_seq, cap, freeze) for n_seq in (B, 1)] == [8, 4]
 
     def fresh():
         caches = api.alloc_cache(shape, B, block_table=bt), api.alloc_cache(shape, B, block_table=bt)

@@ -1,4 +1,4 @@
-"""The encoder's two lane layouts (one sub-vector per lane for small calls, sixteen channels per lane for large ones) store
+"""The encoder's lane layouts of small calls (one sub-vector per lane) and of large ones (sixteen channels per lane) store
 the same bytes: a ragged batch encoded in one call, large enough for the second layout, against the same sequences encoded
 one at a time with the first.  Lengths sit at the edges of the 8-token steps, 32- and 64-token workgroups.  The first layout is
 compared with the oracle by the other encoder tests.  Every stored value is an fp16 or a code decided in fp64 (relative
@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 
 from paper_2505_18231_amd import synth
+from tests import helpers
 
 pytestmark = pytest.mark.gpu
 
@@ -31,7 +32,6 @@ def test_one_large_call_equals_sequence_by_sequence(gpu_api, codebooks, sub, sig
     if G == 128:
         start = 128  # a group's start
     print(f"case sub={sub} sign={sign} rope={rope} side_bits={side_bits} G={G} page={page} start={start}", flush=True)
-    assert 2 * B * H * cap >= 16384 > 2 * H * cap      # the large layout / the small one
     max_len = 1024
     g = torch.Generator(device="cuda").manual_seed(5)
     cb = torch.from_numpy(codebooks[sub].astype(np.float16)).cuda()
@@ -44,6 +44,8 @@ def test_one_large_call_equals_sequence_by_sequence(gpu_api, codebooks, sub, sig
     n = torch.tensor(LENS, dtype=torch.int32, device="cuda")
     pos = torch.full((B,), start, dtype=torch.int32, device="cuda")
     freeze = start % 64 != 0 or (start > 0 and G == 0)
+    large, single = (helpers.encode_layout(api, shape, n_seq, cap, freeze) for n_seq in (B, 1))
+    assert large == 16 and single == sub               # the layout of large calls / the one of small calls
 
     def fresh():
         caches = api.alloc_cache(shape, B, block_table=bt), api.alloc_cache(shape, B, block_table=bt)
