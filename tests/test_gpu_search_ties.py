@@ -1,6 +1,7 @@
 """Codewords at equal distances: a codebook that holds rows twice or three times.  Every sub-vector nearest to such a row leaves
 two candidates (in one group of eight codewords of the search or in two) or three, which fp64 distances settle for the lowest
-index; codes are compared with an fp64 exhaustive search, and no later copy is ever taken."""
+index; codes are compared with an fp64 exhaustive search, and no later copy is ever taken.  In the encoder and in K-Means, whose
+instances of the search hold other operands (codewords with a low part)."""
 import numpy as np
 import pytest
 
@@ -50,3 +51,29 @@ def test_equal_distances_go_to_the_lowest_index(gpu_api, codebooks, sub, copies,
             assert np.all((codes == lowest[ref["codes"]]) | near_tie)
             taken += int(np.isin(codes, [lowest[row] for row, _ in copies]).sum())
     assert taken > 20, taken
+
+
+@pytest.mark.parametrize("sub,copies,n", [(4, PAIRS, 4000), (8, PAIRS, 4000), (4, PAIRS, 300), (8, PAIRS, 1 << 16), (4, MANY, 4000), (8, MANY, 4000),
+                                          (8, MANY, 1 << 16)])
+def test_kmeans_gives_all_members_to_the_lowest_copy(gpu_api, sub, copies, n):
+    """One iteration from first samples that hold rows twice or more: the later copies get no member and stay what they were, the
+    lowest one becomes the mean of all."""
+    import torch
+    print(f"case sub={sub} n={n} copies={len(copies)}", flush=True)
+    samples = synth.codebook_samples(63, n, sub)
+    later = []
+    for row, at in copies:
+        samples[at] = samples[row]
+        later += [k for k in (row, *at) if k != min(row, *at)]
+    c = samples[:256].astype(np.float64)
+    near = np.empty(n, np.int64)
+    for t in range(0, n, 4096):  # (equal rows have equal distances: the first one is taken)
+        near[t:t + 4096] = ((samples[t:t + 4096, None, :].astype(np.float64) - c[None]) ** 2).sum(axis=2).argmin(axis=1)
+    ref = np.stack([samples[near == k].astype(np.float64).mean(axis=0) if (near == k).any() else c[k] for k in range(256)])
+    cb, _ = gpu_api.nsn_build_codebook(torch.from_numpy(samples).cuda(), 256, 1)
+    got = cb.cpu().numpy()
+    assert np.array_equal(got[later], samples[later].astype(np.float16)), "a later copy got members"
+    diff = np.abs(got.view(np.int16).astype(np.int32) - ref.astype(np.float16).view(np.int16).astype(np.int32))
+    print(f"  {(diff != 0).sum()} of {diff.size} fp16 entries differ, max {diff.max()} ulp", flush=True)
+    # both are single fp16 roundings of fp64 centroids that differ only by summation order
+    assert diff.max() <= 1 and (diff == 0).mean() > 0.999
