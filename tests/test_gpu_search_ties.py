@@ -14,9 +14,12 @@ pytestmark = pytest.mark.gpu
 # copies (of row, at rows): two in one group of eight (rows 0..3 and 8..11 of a tile half), in neighbouring groups, in other tiles
 PAIRS = [(0, [1]), (2, [11]), (4, [17]), (5, [21]), (33, [250]), (64, [70]), (255, [100]), (130, [131])]
 MANY = [(0, [1, 2]), (8, [40, 200]), (77, [78, 79]), (99, [100])]
+# 32 and 33 equal rows: the most that the lists settle, and one more
+EDGE = [(3, list(range(60, 91))), (100, list(range(120, 152)))]
 
 
-@pytest.mark.parametrize("sub,copies,tokens", [(4, PAIRS, 9), (8, PAIRS, 9), (4, PAIRS, 500), (8, PAIRS, 500), (4, MANY, 300), (8, MANY, 300)])
+@pytest.mark.parametrize("sub,copies,tokens", [(4, PAIRS, 9), (8, PAIRS, 9), (4, PAIRS, 500), (8, PAIRS, 500), (4, MANY, 300), (8, MANY, 300),
+                                               (4, EDGE, 100), (8, EDGE, 100)])
 def test_equal_distances_go_to_the_lowest_index(gpu_api, codebooks, sub, copies, tokens):
     import torch
     api = gpu_api
@@ -54,7 +57,7 @@ def test_equal_distances_go_to_the_lowest_index(gpu_api, codebooks, sub, copies,
 
 
 @pytest.mark.parametrize("sub,copies,n", [(4, PAIRS, 4000), (8, PAIRS, 4000), (4, PAIRS, 300), (8, PAIRS, 1 << 16), (4, MANY, 4000), (8, MANY, 4000),
-                                          (8, MANY, 1 << 16)])
+                                          (8, MANY, 1 << 16), (4, EDGE, 4000), (8, EDGE, 4000)])
 def test_kmeans_gives_all_members_to_the_lowest_copy(gpu_api, sub, copies, n):
     """One iteration from first samples that hold rows twice or more: the later copies get no member and stay what they were, the
     lowest one becomes the mean of all."""
