@@ -481,9 +481,9 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_ordered_kernel(const floa
 }
 
 // Adds the partial sums of kUpdateClusters<SUB> neighbouring clusters (128 consecutive bytes of every row of partials: one line)
-// in a fixed order (fp64): kUpdateThreads = E sums x kUpdateThreads / E slices of the rows, clusters x 128 for the counts.
-// The first threads return with the sums and the member count of their cluster.  (Eight clusters per workgroup, i.e. 32
-// compute units at work: 5.3 us instead of 4.7; pieces of 32 bytes 10.7 us.)
+// in a fixed order (fp64): kUpdateThreads = E sums x kUpdateThreads / E slices of the rows; for the counts, clusters x
+// kUpdateThreads / clusters.  The first threads return with the sums and the member count of their cluster.  (Eight clusters per
+// workgroup, i.e. 32 compute units at work: 5.3 us instead of 4.7; pieces of 32 bytes 10.7 us.)
 template <int SUB>
 constexpr int kUpdateClusters = 16 / SUB;
 constexpr int kUpdateThreads = 128;

@@ -99,7 +99,9 @@ __global__ __launch_bounds__(256) void enc_stats_kernel(Geometry g, const __half
   // round's sixteen tokens and not once for every four: the sums over a token's sixteen lanes go apart as they are formed (five
   // additions in the order that sixteen had), lane `col` finishes step col & 3 and hands the reciprocal to the
   // other lanes.  8 x 8192 tokens x 8 heads: the whole call 553 -> 544 us with 4-dim codes, 443 -> 434 with 8-dim ones; 300
-  // tokens 16.8 -> 14.7 us.  A wave's only step is a round of its own (four cost a call of 16 tokens 0.2 us).
+  // tokens 16.8 -> 14.7 us.  A wave's only step is a round of its own (four cost a call of 16 tokens 0.2 us).  Two or three are not:
+  // their chains overlap in a round of four, and with it and the shorter search 17, 32 and 48 tokens of 8 sequences take 11.3, 11.7
+  // and 13.5 us where step by step they took 12.7, 13.1 and 17.3.
   const int tw = chunk * chunk_tokens + 4 * wave;  // the wave's first token of a step (uniform)
   uint4 buf[4] = {fetch(tw + row), fetch(tw + row + 16), fetch(tw + row + 32), fetch(tw + row + 48)};
   auto round = [&](auto steps, int t0) {
@@ -397,7 +399,9 @@ __global__ __launch_bounds__(256, 2) void enc_kernel(EncArgs A) {
   // What a call of few tokens spends its time on is trips to memory one after the other, so everything goes out as early as it
   // can: the arguments in one go (fetched where they are first needed they are three trips), the codebook beside the
   // sequence's start, the first token's rows and Shift vector ahead of the set-up of the search.  One token: 5.7 -> 4.4 us; 64
-  // tokens x 8 sequences x 8 heads 11.1 -> 8.9 us, of that 10.7 with the new order alone (the rest: nsn_search.h).
+  // tokens x 8 sequences x 8 heads 11.1 -> 8.9 us, of that 10.7 with the new order alone (the rest: nsn_search.h).  Workgroups without
+  // tokens fetch the codebook for nothing; calls that are mostly empty places gained all the same: 64 sequences of 8192 places with
+  // 64 tokens each 1579 -> 1485 us, 128 of 4096 with one token each 654 -> 588 us.
   asm volatile("" ::"s"(A.codebook), "s"(A.k_in), "s"(A.v_in), "s"(A.max_new), "s"(A.max_len), "s"(A.seq_start), "s"(A.n_new),
                "s"(A.kc.codes), "s"(A.vc.codes), "s"(A.kc.means), "s"(A.vc.means), "s"(A.kc.norms), "s"(A.vc.norms),
                "s"(A.wg_tokens), "s"(g.dq), "s"(g.n_kv_heads), "s"(g.n_groups_max), "s"(g.group_size));

@@ -1,7 +1,8 @@
 // Nearest-codeword search (Eq. 1, squared Euclidean distance): one sub-vector per lane, 64 per call.
 //
-// Three steps, bound by vector instructions (about 270 per 64 searches of 256 4-dim codewords and 55 per group gone through;
-// keeping the best two indexed keys of every distance took about 740):
+// Three steps, bound by vector instructions: per 64 searches of 256 4-dim codewords 265 of them (and 16 matrix instructions) up to
+// the lists, then 60 for every group of the longest list among the 64, which holds one at least; 8-dim codewords 295 (and 32) and
+// 95.  Settling two candidates takes 55 to 110 more.  (Keeping the best two indexed keys of every distance took about 740.)
 //   1. matrix cores: D = ||c||^2 - 2 c . y + n for 32 codewords (rows) x 32 sub-vectors (columns) at a time, n slightly
 //      above ||y||^2 (D > 0).  y, c and ||c||^2 enter as sums of fp16 parts, so D is good to about 2^-19 of
 //      (|c| + |y|)^2.  A lane then holds 16 distances of one sub-vector per tile and keeps only the minima of the two groups
@@ -102,14 +103,16 @@ template <int SUB, bool EXACT16>
 struct SearchRegs {
   h8 A[8];
   // SUB = 8: second operand; EXACT16 codewords (fp16 values) have no low part, ||c||^2 alone takes four slots.  (The other
-  // form is read from LDS in every search: 32 registers that would halve the number of waves.)
+  // form is read from LDS in every search: of the 256 registers at two waves per SIMD the ordered codebook kernels leave 18,
+  // and this would take 32.)
   h4v A2[SUB == 8 && EXACT16 ? 8 : 1];
   float cm;     // largest norm of a scaled codeword, at least 4
   float scale;  // s
 };
 
 // Fills the tables and the operands of every wave of the workgroup (256 threads or more, all of them call it).
-// get(i): element i of codeword `tid` (threads 0..255); n2: the largest squared norm of a codeword, in every thread.  s is 2^ex_most at most: a caller that knows the longest sub-vector
+// get(i): element i of codeword `tid` (threads 0..255); n2: the largest squared norm of a codeword, in every thread (codewords that
+// hold a NaN left out).  s is 2^ex_most at most: a caller that knows the longest sub-vector
 // keeps it below 237 s this way.  Without that, sub-vectors 30 to 60 times as long as the longest codeword leave the fp16
 // range and take 256 fp64 distances per wave (encoder, 4096 tokens x 8 heads with codewords a hundredth of the usual: 495 us
 // instead of 54; K-Means of 2^20 samples whose first 256 are a fiftieth of the others: 100 to 270 us more in the first
@@ -427,10 +430,10 @@ __device__ __forceinline__ Nearest search_nearest(const SearchTables<SUB>& T, co
     }
   } else {
     // None at all (not a number somewhere, or out of range): all codewords.  In the codebook's instances, whose samples have no
-    // bound, more than kListed too, and then for the whole wave, which reads the rows together and not through lists that differ from
-    // lane to lane.  (Samples a thousandth of the longest codeword list many groups: K-Means of 2^20 8-dim samples with an outlier
-    // of 1000, twelve iterations, 5.2 -> 4.0 ms, 2^16 4-dim ones 0.74 -> 0.51 ms; with 8 or 16 for kListed an outlier of 300 takes up to
-    // 1.5 times as long.  The encoder's sub-vectors have a bound; there the wider condition cost 0.5 % of a prefill.)
+    // bound, more than kListed too, and then for the whole wave, which reads the rows together and not through lists that differ
+    // from lane to lane.  (Samples a thousandth of the longest codeword list many groups: K-Means of 2^20 8-dim samples with an
+    // outlier of 1000, twelve iterations, 5.2 -> 4.0 ms, 2^16 4-dim ones 0.74 -> 0.51 ms; with 8 or 16 for kListed an outlier of 300
+    // takes up to 1.5 times as long.  The encoder's sub-vectors have a bound; there the wider condition cost 0.5 % of a prefill.)
     double e1 = INFINITY;
     int k1 = 0;
     const bool all = EXACT16 ? found < 1 : __any((unsigned)(found - 1) >= kListed);
