@@ -55,6 +55,7 @@ constexpr int kPartialStride = 2 * kHeadDim + 2;  // rotated acc, mean-term acc,
 constexpr float kLazyMaxLog2 = 5.0f;              // rescale only when a score beats the running max by 2^5
 constexpr float kWeightScale = 1024.0f;           // fp16 weights carry 2^10 / A: small weights stay normal numbers
 constexpr int kTableBytes = 65536;
+constexpr int kRebase = 1 << 25;                  // tokens: 2^30 bytes of codes at most
 
 template <int N, typename F>
 __device__ __forceinline__ void static_for(F&& f) {
@@ -93,6 +94,19 @@ __device__ __forceinline__ void lds_write128(uint32_t, u4v) {}
 __device__ __forceinline__ void lds_write64(uint32_t, u2v) {}
 __device__ __forceinline__ void lds_write32(uint32_t, uint32_t) {}
 #endif
+
+// Buffer descriptor: `bytes` bytes from p on; loads beyond them return zeros and do not access memory.
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+__device__ __forceinline__ rsrc_t make_rsrc(const void* p, uint32_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a), hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>((uint64_t)hi << 32 | lo), 0,
+                                           __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+}
+__device__ __forceinline__ u4v load128(rsrc_t r, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0); }
+__device__ __forceinline__ u2v load64(rsrc_t r, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0); }
+__device__ __forceinline__ uint32_t load32(rsrc_t r, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0); }
+__device__ __forceinline__ uint32_t load16(rsrc_t r, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b16(r, off, 0, 0); }
 
 template <int CTRL>
 __device__ __forceinline__ float dpp_mov(float v) {
@@ -193,8 +207,8 @@ __device__ __forceinline__ float half_hi_f(uint32_t u) { return (float)__builtin
 __device__ __forceinline__ void st_agent(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 // LDS plan (dynamic block, starts at LDS address 0 because the gathers form absolute addresses):
-//   [0, 64 KiB)   codebook table: entry (code c, copy p) at c * 256 + p * (2 * SUB): 32 copies of 8 bytes
-//                 (SUB = 4) or 16 copies of 16 bytes (SUB = 8)
+//   [0, 64 KiB)   codebook table: entry (code c, copy p) at c * 256 + p * 8: 32 copies of 8 bytes (SUB = 4), or 16 of the
+//                 first half of a codeword and, 128 bytes on, 16 of the second (SUB = 8: a lane's address serves both halves)
 //   query block   fp16 hi / lo of the rotated, pre-scaled query [4][128] each; the same of the unrotated
 //                 query (residual tiles); 128 zero bytes; q . o^k of the split's first Shift group (four
 //                 heads); the unrotated query in fp32 [4][128]
@@ -317,8 +331,10 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
     u4v v;
     if constexpr (SUB == 4)
       v = u4v{cw_reg.x, cw_reg.y, cw_reg.x, cw_reg.y};
-    else
+    else if constexpr (SGN)
       v = u4v{cw_reg.x, cw_reg.y, cw_reg.z, cw_reg.w};
+    else
+      v = half ? u4v{cw_reg.z, cw_reg.w, cw_reg.z, cw_reg.w} : u4v{cw_reg.x, cw_reg.y, cw_reg.x, cw_reg.y};
     const uint32_t row = code * 256 + half * 128;
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
@@ -434,17 +450,70 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
       vbase = ((int64_t)pv * g.n_kv_heads + h) * g.page_tokens + tin;
     }
   };
-  auto shift_group = [&](int tg) -> int {
-    if (g.group_size <= 0) return 0;
-    return POW2 || (LEGACY && g.group_shift >= 0) ? tg >> g.group_shift : tg / g.group_size;
+  const int gshift = g.group_size > 0 ? g.group_shift : 31;  // (no groups: index 0 for every token)
+  auto shift_group = [&](int tg) -> int { return POW2 || (LEGACY && gshift >= 0) ? tg >> gshift : gshift == 31 ? 0 : tg / g.group_size; };
+  // Contiguous caches are read through buffer descriptors (the Shift vectors, which every group has, through plain pointers):
+  // base and size in scalar registers, one vector addition per kind of array and group, and no address arithmetic on the scalar
+  // unit, whose instructions a wave waits for one by one (about eight cycles each; 64-bit addresses of six arrays were thirty
+  // of them per group).  Offsets count from token `base_tok` of the unit and have 32 bits: every kRebase tokens the
+  // descriptors move on (in the branch that masked tokens take).  With the masked tokens' selects in a branch of their own and
+  // one address for both halves of an 8-dim codeword (a group: 144 -> 103 vector instructions, 55 -> 15 scalar ones with 1-bit
+  // codes): 8 x 8192 tokens with residual, four launches 52.3 -> 50.9 us; 131072 1-bit tokens 77.4 -> 75.3; 64 x 32 heads x
+  // 32768 tokens 913 -> 870; all options of the paper 87.8 -> 83.2; paged caches, by the selects alone, 90.2 -> 87.6.
+  int base_tok = t0, base_group = 0, last_tok = t0;  // base_tok's Shift group, the last group's first token
+  rsrc_t kr_codes, vr_codes, kr_norms, vr_norms;
+  const unsigned char *kp_means, *vp_means;
+  constexpr uint32_t kMeanBytes = DQ ? kDqMeanRec : 2 * kHeadDim;
+  auto describe = [&](int end_tok) {  // groups from end_tok on read as zeros, without a memory access
+    const int64_t tok = (int64_t)(b * g.n_kv_heads + h) * g.page_tokens + base_tok;
+    const uint32_t n = (uint32_t)min(max(end_tok - base_tok, 0), 2 * kRebase);
+    kr_codes = make_rsrc(kc.codes + tok * J, n * J), vr_codes = make_rsrc(vc.codes + tok * J, n * J);
+    const int64_t norms_at = DQ ? (tok >> 6) * kDqNormRec : tok * 4;
+    const uint32_t norms_n = DQ ? (n >> 6) * kDqNormRec : n * 4;
+    kr_norms = make_rsrc(reinterpret_cast<const unsigned char*>(kc.norms) + norms_at, norms_n);
+    vr_norms = make_rsrc(reinterpret_cast<const unsigned char*>(vc.norms) + norms_at, norms_n);
+    last_tok = max(end_tok - 64, base_tok);
+    base_group = shift_group(base_tok);
+    const int64_t mean_at = (mean_base + (n ? base_group : 0)) * kMeanBytes;  // (a split beyond the cache: the unit's first)
+    kp_means = reinterpret_cast<const unsigned char*>(kc.means) + mean_at;
+    vp_means = reinterpret_cast<const unsigned char*>(vc.means) + mean_at;
   };
-  // tg: first token of the group (a multiple of 64 inside the cache).  A group that does not exist (`real` false:
-  // the wave's list of groups has ended) is loaded all the same, from the first bytes of every array (one cache line
-  // per instruction, nothing of it is used: any bytes are valid table indices).  With loads that are only issued
-  // under a condition, the number of loads behind a given one depends on the path, the compiler's wait counts
+  // tg: first token of the group (a multiple of 64).  A group that does not exist (`real` false: the wave's list of groups has
+  // ended) is loaded all the same: contiguous caches read zeros beyond the descriptors' ends, paged ones the first bytes of
+  // every array (one cache line per instruction); nothing of it is used and any bytes are valid table indices.  With loads that
+  // are only issued under a condition, the number of loads behind a given one depends on the path, the compiler's wait counts
   // take the smallest, and every wait for a group's bytes becomes a wait for all loads in flight, the groups
   // requested ahead included.
   auto load_group = [&](int tg, bool real, Regs& G) {
+    constexpr int VSTEP = LEGACY ? J : 1;  // 16-byte pieces; legacy: the lane's second value row is sixteen rows on
+    if constexpr (!PAGED) {
+      uint32_t rel = (uint32_t)(tg - base_tok);
+      asm("" : "+s"(rel));  // (or every offset gets a subtraction of its own)
+      const uint32_t ko = lane_code_off + rel * J, vo = lane_v_off + rel * J;
+#pragma unroll
+      for (int w4 = 0; w4 < CW / 4; ++w4) {
+        const u4v kv4 = load128(kr_codes, ko + 16 * w4), vv4 = load128(vr_codes, vo + 16 * w4 * VSTEP);
+        G.kc[4 * w4] = kv4.x, G.kc[4 * w4 + 1] = kv4.y, G.kc[4 * w4 + 2] = kv4.z, G.kc[4 * w4 + 3] = kv4.w;
+        G.vc[4 * w4] = vv4.x, G.vc[4 * w4 + 1] = vv4.y, G.vc[4 * w4 + 2] = vv4.z, G.vc[4 * w4 + 3] = vv4.w;
+      }
+      const uint32_t mrec = (uint32_t)(shift_group(min(tg, last_tok)) - base_group) * kMeanBytes;
+      if constexpr (DQ) {
+        const uint32_t rec = (rel >> 6) * kDqNormRec, tok0 = norm_off >> 2;
+        const u2v ka = load64(kr_norms, rec + 2 * tok0), va = load64(vr_norms, rec + 2 * tok0);
+        const uint32_t at_codes = rec + kDqNormCodes + (tok0 >> 1), at_par = rec + kDqNormPar;
+        G.nk = make_uint4(ka.x, ka.y, load16(kr_norms, at_codes), load32(kr_norms, at_par));
+        G.nv = make_uint4(va.x, va.y, load16(vr_norms, at_codes), load32(vr_norms, at_par));
+        const uint32_t at_mpar = mrec + kDqMeanPar + 4 * ((uint32_t)lane >> 4);
+        G.ok = kp_means[mrec + lane], G.ov = vp_means[mrec + lane];
+        G.okp = *reinterpret_cast<const uint32_t*>(kp_means + at_mpar), G.ovp = *reinterpret_cast<const uint32_t*>(vp_means + at_mpar);
+      } else {
+        const u4v nk = load128(kr_norms, norm_off + rel * 4), nv = load128(vr_norms, norm_off + rel * 4);
+        G.nk = make_uint4(nk.x, nk.y, nk.z, nk.w), G.nv = make_uint4(nv.x, nv.y, nv.z, nv.w);
+        G.ok = *reinterpret_cast<const uint32_t*>(kp_means + (mrec + lane_x4));
+        G.ov = *reinterpret_cast<const uint32_t*>(vp_means + (mrec + lane_x4));
+      }
+      return;
+    }
     int64_t kbase = 0, vbase = 0, mgrp = 0;  // wave-uniform
     if (real) {
       group_bases(tg, kbase, vbase);
@@ -454,7 +523,6 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
     const uint32_t ln = real ? (uint32_t)lane : 0u;
     const unsigned char* kp = kc.codes + kbase * J + lco;
     const unsigned char* vp = vc.codes + vbase * J + lvo;
-    constexpr int VSTEP = LEGACY ? J : 1;  // 16-byte pieces; legacy: the lane's second value row is sixteen rows on
 #pragma unroll
     for (int w4 = 0; w4 < CW / 4; ++w4) {
       const uint4 kv4 = reinterpret_cast<const uint4*>(kp)[w4];
@@ -596,7 +664,10 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
   if constexpr (!FLAT) {
     // contiguous caches: the wave's first group is in bounds whatever the sequence length is (clamped into
     // the cache when the split lies beyond it: then it is never processed)
-    if constexpr (!PAGED) load_group(min(t0 + (wave << 6), cap_tokens - 64), true, S0);  // (wslot == wave here)
+    if constexpr (!PAGED) {
+      describe(cap_tokens);
+      load_group(t0 + (wave << 6), true, S0);  // (wslot == wave here)
+    }
     len = seq_lens[b];
     // Splits that lie wholly beyond this sequence's end have nothing to do and leave at once (a ragged batch
     // is launched with the split count of its longest sequence); the others know how many of them there
@@ -607,6 +678,12 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
     res_here = split == n_live - 1;
   }
   n_grp = (t1 > t0) ? (t1 - t0 + 63) >> 6 : 0;  // 64-token groups of this segment
+  int t_whole = t1 - 64;                         // groups that begin later hold masked tokens (or are far from base_tok)
+  if constexpr (!PAGED) {
+    base_tok = t0;
+    describe(t0 + (n_grp << 6));
+    t_whole = min(t_whole, base_tok + kRebase);
+  }
   // FLAT: waves 4..7 take the segment's first groups: they are the ones that come out of the previous
   // segment early (waves 0..3 merge it), and a short segment then does not wait for the late ones
   const int wslot = FLAT ? (wave + 4) & 7 : wave;
@@ -755,8 +832,7 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
   for (int i = 0; i < 4; ++i) accm[i][0] = accm[i][1] = 0.f;
   int cur_group = -1;
   float ov0 = 0.f, ov1 = 0.f;
-  const uint32_t laneoff = (SUB == 4) ? (lane & 31) * 8 : (lane & 15) * 16;  // key-side gathers
-  const uint32_t laneoff_v0 = (lane & 31) * 8, laneoff_v1 = laneoff_v0 ^ 8;  // value-side 8-byte gathers
+  const uint32_t laneoff = SUB == 4 ? (lane & 31) * 8 : (lane & 15) * 8;  // the lane's copy of the table
   const uint32_t k8 = (rho & 1) * 8, v8 = (lane & 1) * 8;  // SGN: the half of a codeword that comes first
 
   auto half_lo = [](uint32_t u) -> float { return (float)__builtin_bit_cast(_Float16, (uint16_t)(u & 0xffffu)); };
@@ -776,19 +852,9 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
     cf = 1.f;
   };
 
-  // d3/d4 for the lane's four tokens; returns the fp16 weights p a^v 2^10 / A as the value-side A operand.
-  // Masked tokens (valid[k] false) must come in with finite sc and zero ak, bk, av, bv.
-  auto softmax_step = [&](const float (&sc)[4], const bool (&valid)[4], bool all_valid, const float (&ak)[4],
-                          const float (&bk)[4], const float (&av_in)[4], const float (&bv_in)[4]) -> h4 {
-    float s[4];
-    const float (&av)[4] = av_in;
-    const float (&bv)[4] = bv_in;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) s[k] = fmaf(ak[k], sc[k], bk[k] * qo[ROPE ? k : 0]);
-    if (!all_valid) {  // wave-uniform
-#pragma unroll
-      for (int k = 0; k < 4; ++k) s[k] = valid[k] ? s[k] : -INFINITY;
-    }
+  // d4 for the lane's four tokens (scores s in log2 units); returns the fp16 weights p a^v 2^10 / A as the value-side A
+  // operand.  Masked tokens come in with s = -inf and zero av, bv.
+  auto softmax_step = [&](const float (&s)[4], const float (&av)[4], const float (&bv)[4]) -> h4 {
     const float smax = max3f(s[0], s[1], max2f(s[2], s[3]));
     const float amax = max3f(av[0], av[1], max2f(av[2], av[3]));
     const bool need = (smax - m_run > kLazyMaxLog2) || (amax > a_run);
@@ -892,20 +958,16 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
       }
       // hi + lo columns; the lanes of tile `wave` (n / 4 == wave) hold its scores, all others are masked
       float sc[4];
-      bool valid[4];
       const float zero[4] = {0.f, 0.f, 0.f, 0.f};
       float one[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        sc[k] = D[k] + dpp_mov<0x128>(D[k]);
-        valid[k] = tile_of_lane == wave && (16 * wave + 4 * rho + k) < rl;
-        one[k] = valid[k] ? 1.f : 0.f;
+        const bool valid = tile_of_lane == wave && (16 * wave + 4 * rho + k) < rl;
+        const float x = D[k] + dpp_mov<0x128>(D[k]);
+        sc[k] = valid ? x : -INFINITY;
+        one[k] = valid ? 1.f : 0.f;
       }
-      // (by constant index: a loop by reference keeps the array in memory through the compiler's early passes, and the
-      // registers then came out so that the main loop waited for the loads of the groups ahead)
-      qo[0] = 0.f;
-      if constexpr (ROPE) qo[1] = qo[2] = qo[3] = 0.f;
-      const h4 wop = softmax_step(sc, valid, false, one, zero, one, zero);
+      const h4 wop = softmax_step(sc, one, zero);
       // value rows: source lane (rho, k = n / 4, m = n % 4) reads token 4 rho + k of the tile, channels
       // [4 (4 X + m), +4); the transposing read hands lane (rho, m, e) four tokens of channel 16 X + 4 m + e
       if constexpr (ROPE) {
@@ -981,7 +1043,9 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
         const u2v c1 = lds_read64(table_addr<2 * (S & 1) + 1>(w, laneoff));
         A[E] = __builtin_bit_cast(h8, u4v{c0.x, c0.y, c1.x, c1.y});
       } else {
-        A[E] = __builtin_bit_cast(h8, lds_read128(table_addr<S>(G.kc[T], laneoff)));
+        const uint32_t at = table_addr<S>(G.kc[T], laneoff);
+        const u2v c0 = lds_read64(at), c1 = lds_read64(at + 128);
+        A[E] = __builtin_bit_cast(h8, u4v{c0.x, c0.y, c1.x, c1.y});
       }
     });
   };
@@ -1004,9 +1068,9 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
         constexpr uint32_t sel = 0x0c0c0000u | ((4 + (X >> 1)) << 8) | (X >> 1);
         Bv[X] = lds_tr64((perm_b32(G.vc[T], (X & 1) ? G.vx[T] : G.vc[4 + T], sel) & 0xfff0u) | ((X & 1) ? v8 ^ 8u : v8));
       } else if constexpr (SUB == 4)
-        Bv[X] = lds_tr64(table_addr<X & 3>(G.vc[2 * T + (X >> 2)], laneoff_v0));
+        Bv[X] = lds_tr64(table_addr<X & 3>(G.vc[2 * T + (X >> 2)], laneoff));
       else
-        Bv[X] = lds_tr64(table_addr<(X >> 1)>(G.vc[T], (X & 1) ? laneoff_v1 : laneoff_v0));
+        Bv[X] = lds_tr64(table_addr<(X >> 1)>(G.vc[T], laneoff) + (X & 1) * 128);
     });
   };
   auto v_contract = [&](auto tc, const h4 (&Bv)[8], const h4& wop) {
@@ -1156,39 +1220,42 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
       const float y = D1[k] + dpp_mov<0x128>(D1[k]);
       sc[k] = (n16 < 8) ? x : y;
     }
-    const bool all_valid = (tg + 64 <= t1);
-    bool valid[4] = {true, true, true, true};
-    if (!all_valid) {  // wave-uniform: only a sequence's last group has masked tokens (their bytes may be anything)
-      const int tb0 = tg + tok_of_lane;  // the lane's first token
-#pragma unroll
-      for (int k = 0; k < 4; ++k) valid[k] = (tb0 + k) < t1;
-    }
     float ak[4], bk[4], av[4], bv[4];
     if constexpr (DQ) {  // b = min + step * code, a = b * a'
       const float apk[4] = {half_lo(G.nk.x), half_hi(G.nk.x), half_lo(G.nk.y), half_hi(G.nk.y)};
       const float apv[4] = {half_lo(G.nv.x), half_hi(G.nv.x), half_lo(G.nv.y), half_hi(G.nv.y)};
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const float b_k = dq_level(G.nk.w, (G.nk.z >> (4 * k)) & 15u), b_v = dq_level(G.nv.w, (G.nv.z >> (4 * k)) & 15u);
-        bk[k] = valid[k] ? b_k : 0.f, ak[k] = valid[k] ? b_k * apk[k] : 0.f;
-        bv[k] = valid[k] ? b_v : 0.f, av[k] = valid[k] ? b_v * apv[k] : 0.f;
+        bk[k] = dq_level(G.nk.w, (G.nk.z >> (4 * k)) & 15u), bv[k] = dq_level(G.nv.w, (G.nv.z >> (4 * k)) & 15u);
+        ak[k] = bk[k] * apk[k], av[k] = bv[k] * apv[k];
       }
     } else {
-      uint32_t nkw[4] = {G.nk.x, G.nk.y, G.nk.z, G.nk.w}, nvw[4] = {G.nv.x, G.nv.y, G.nv.z, G.nv.w};
-      if (!all_valid) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          nkw[k] = valid[k] ? nkw[k] : 0u;
-          nvw[k] = valid[k] ? nvw[k] : 0u;
-        }
-      }
+      const uint32_t nkw[4] = {G.nk.x, G.nk.y, G.nk.z, G.nk.w}, nvw[4] = {G.nv.x, G.nv.y, G.nv.z, G.nv.w};
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         ak[k] = half_lo(nkw[k]), bk[k] = half_hi(nkw[k]);
         av[k] = half_lo(nvw[k]), bv[k] = half_hi(nvw[k]);
       }
     }
-    const h4 wop = softmax_step(sc, valid, all_valid, ak, bk, av, bv);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) sc[k] = fmaf(ak[k], sc[k], bk[k] * qo[ROPE ? k : 0]);
+    if (tg > t_whole) {  // wave-uniform: only a sequence's last group has masked tokens (their bytes may be anything)
+      asm volatile("");  // (or the compiler makes twelve selects of it that every group goes through)
+      if constexpr (!PAGED) {
+        if (tg - base_tok > kRebase) {
+          base_tok += kRebase;
+          describe(t0 + (n_grp << 6));
+          t_whole = min(t1 - 64, base_tok + kRebase);
+        }
+      }
+      const int tb0 = tg + tok_of_lane;  // the lane's first token
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const bool valid = (tb0 + k) < t1;
+        sc[k] = valid ? sc[k] : -INFINITY, av[k] = valid ? av[k] : 0.f, bv[k] = valid ? bv[k] : 0.f;
+      }
+    }
+    const h4 wop = softmax_step(sc, av, bv);
 
     // d5: out_rot[head][channel] += sum over tokens of weight * codeword channel
     __builtin_amdgcn_sched_barrier(0);
@@ -1204,8 +1271,12 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
     // (this group's bytes have all been used by now)
     if constexpr (FLAT && !LEGACY)
       load_group(t0 + ((gi + 3 * NW) << 6), gi + 3 * NW < n_grp, G);
-    else
+    else {
+      // (the registers of the Shift vectors, which only a change of the Shift group reads, are nobody's temporaries: a write to
+      // one would wait for every load in flight)
+      if constexpr (!FLAT && !LEGACY) asm volatile("" ::"v"(Gnn.ok), "v"(Gnn.ov));
       load_group(t0 + ((gi + 2 * NW) << 6), gi + 2 * NW < n_grp, Gnn);
+    }
     if constexpr (ROPE && it == 3) rope_load(gi + NW);  // the next batch
     __builtin_amdgcn_sched_barrier(0);
     v_contract(c2, VC, wop);
@@ -1289,8 +1360,8 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
       int ch;
       if constexpr (SUB == 4)
         ch = 16 * X + 4 * m_res + e_res;
-      else  // X = 2 x + hf: sub-vector 4 x + m, half hf ^ (m & 1) (odd lanes gather the other half first)
-        ch = 8 * (4 * (X >> 1) + m_res) + 4 * ((X & 1) ^ (m_res & 1)) + e_res;
+      else  // X = 2 x + hf: sub-vector 4 x + m, half hf (sign codes: hf ^ (m & 1), odd lanes gather the other half first)
+        ch = 8 * (4 * (X >> 1) + m_res) + 4 * ((X & 1) ^ (SGN ? m_res & 1 : 0)) + e_res;
 #pragma unroll
       for (int i = 0; i < 4; ++i) lds_write32(mbase + (i * 128 + ch) * 4, __float_as_uint(red[j][i]));
     }
