@@ -433,22 +433,26 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
     const int64_t e = (int64_t)bb * g.pages_per_seq + min(w0 + lane, g.pages_per_seq - 1);
     wk = kc.block_table[e], wv = vc.block_table[e];
   };
-  // token index (counted over the whole buffer) of the first token of the group that starts at token tg
-  auto group_bases = [&](int tg, int64_t& kbase, int64_t& vbase) {
-    if constexpr (!PAGED) {
-      kbase = vbase = (int64_t)(b * g.n_kv_heads + h) * g.page_tokens + tg;
-    } else {
-      const bool shifts = POW2 || (LEGACY && g.page_shift >= 0);
-      const int page = shifts ? tg >> g.page_shift : tg / g.page_tokens;
-      const int tin = shifts ? tg & (g.page_tokens - 1) : tg - page * g.page_tokens;
-      if ((unsigned)(page - win0) >= 64u) {  // wave-uniform
-        win0 = page & ~63;
-        load_window(b, win0, win_k, win_v);
-      }
-      const int pk = __builtin_amdgcn_readlane(win_k, page - win0), pv = __builtin_amdgcn_readlane(win_v, page - win0);
-      kbase = ((int64_t)pk * g.n_kv_heads + h) * g.page_tokens + tin;
-      vbase = ((int64_t)pv * g.n_kv_heads + h) * g.page_tokens + tin;
+  // 64-token blocks of a page and of the whole buffer, whose number has 32 bits.  (With token indices in 64 bits, and the wait for
+  // the window's entries where the paths with and without a reload meet - a wait for every load in flight, in every group -,
+  // two launches of 32 ragged sequences took 87.4 instead of 86.4 us, 59 x 32 heads x 3232 tokens 113.1 instead of 111.1, four
+  // launches of 12 x 16 heads x 11644 tokens in pages of 64 with 4-bit side information 216.8 instead of 208.9)
+  const uint32_t page_blocks = (uint32_t)g.n_kv_heads * ((uint32_t)g.page_tokens >> 6);
+  auto group_blocks = [&](int tg, bool real, uint32_t& kblock, uint32_t& vblock) {
+    const bool shifts = POW2 || (LEGACY && g.page_shift >= 0);
+    const int page = shifts ? tg >> g.page_shift : tg / g.page_tokens;
+    const uint32_t tb = shifts ? ((uint32_t)tg & (g.page_tokens - 1)) >> 6 : (uint32_t)(tg - page * g.page_tokens) >> 6;
+    if (real && (unsigned)(page - win0) >= 64u) {  // wave-uniform
+      win0 = page & ~63;
+      load_window(b, win0, win_k, win_v);
+      // (waited for here: where the two paths meet, the wait would be every group's, and for every load in flight)
+      asm volatile("" : "+v"(win_k), "+v"(win_v));
     }
+    // (a group that does not exist: the buffers' first block, which every wave reads then)
+    const int at = (page - win0) & 63;
+    const uint32_t in_page = (uint32_t)h * ((uint32_t)g.page_tokens >> 6) + tb;
+    kblock = real ? (uint32_t)__builtin_amdgcn_readlane(win_k, at) * page_blocks + in_page : 0u;
+    vblock = real ? (uint32_t)__builtin_amdgcn_readlane(win_v, at) * page_blocks + in_page : 0u;
   };
   const int gshift = g.group_size > 0 ? g.group_shift : 31;  // (no groups: index 0 for every token)
   auto shift_group = [&](int tg) -> int { return POW2 || (LEGACY && gshift >= 0) ? tg >> gshift : gshift == 31 ? 0 : tg / g.group_size; };
@@ -465,16 +469,20 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
   const unsigned char *kp_means, *vp_means;
   constexpr uint32_t kMeanBytes = DQ ? kDqMeanRec : 2 * kHeadDim;
   auto describe = [&](int end_tok) {  // groups from end_tok on read as zeros, without a memory access
-    const int64_t tok = (int64_t)(b * g.n_kv_heads + h) * g.page_tokens + base_tok;
-    const uint32_t n = (uint32_t)min(max(end_tok - base_tok, 0), 2 * kRebase);
-    kr_codes = make_rsrc(kc.codes + tok * J, n * J), vr_codes = make_rsrc(vc.codes + tok * J, n * J);
-    const int64_t norms_at = DQ ? (tok >> 6) * kDqNormRec : tok * 4;
-    const uint32_t norms_n = DQ ? (n >> 6) * kDqNormRec : n * 4;
-    kr_norms = make_rsrc(reinterpret_cast<const unsigned char*>(kc.norms) + norms_at, norms_n);
-    vr_norms = make_rsrc(reinterpret_cast<const unsigned char*>(vc.norms) + norms_at, norms_n);
-    last_tok = max(end_tok - 64, base_tok);
     base_group = shift_group(base_tok);
-    const int64_t mean_at = (mean_base + (n ? base_group : 0)) * kMeanBytes;  // (a split beyond the cache: the unit's first)
+    int first_mean = base_group;
+    if constexpr (!PAGED) {
+      const uint32_t n = (uint32_t)min(max(end_tok - base_tok, 0), 2 * kRebase);
+      first_mean = n ? base_group : 0;  // (a split beyond the cache reads the unit's first one)
+      const int64_t tok = (int64_t)(b * g.n_kv_heads + h) * g.page_tokens + base_tok;
+      kr_codes = make_rsrc(kc.codes + tok * J, n * J), vr_codes = make_rsrc(vc.codes + tok * J, n * J);
+      const int64_t norms_at = DQ ? (tok >> 6) * kDqNormRec : tok * 4;
+      const uint32_t norms_n = DQ ? (n >> 6) * kDqNormRec : n * 4;
+      kr_norms = make_rsrc(reinterpret_cast<const unsigned char*>(kc.norms) + norms_at, norms_n);
+      vr_norms = make_rsrc(reinterpret_cast<const unsigned char*>(vc.norms) + norms_at, norms_n);
+    }
+    last_tok = max(end_tok - 64, base_tok);
+    const int64_t mean_at = (mean_base + first_mean) * kMeanBytes;
     kp_means = reinterpret_cast<const unsigned char*>(kc.means) + mean_at;
     vp_means = reinterpret_cast<const unsigned char*>(vc.means) + mean_at;
   };
@@ -486,72 +494,56 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
   // requested ahead included.
   auto load_group = [&](int tg, bool real, Regs& G) {
     constexpr int VSTEP = LEGACY ? J : 1;  // 16-byte pieces; legacy: the lane's second value row is sixteen rows on
+    auto set_codes = [&](int w4, u4v kv4, u4v vv4) {
+      G.kc[4 * w4] = kv4.x, G.kc[4 * w4 + 1] = kv4.y, G.kc[4 * w4 + 2] = kv4.z, G.kc[4 * w4 + 3] = kv4.w;
+      G.vc[4 * w4] = vv4.x, G.vc[4 * w4 + 1] = vv4.y, G.vc[4 * w4 + 2] = vv4.z, G.vc[4 * w4 + 3] = vv4.w;
+    };
     if constexpr (!PAGED) {
       uint32_t rel = (uint32_t)(tg - base_tok);
       asm("" : "+s"(rel));  // (or every offset gets a subtraction of its own)
       const uint32_t ko = lane_code_off + rel * J, vo = lane_v_off + rel * J;
 #pragma unroll
-      for (int w4 = 0; w4 < CW / 4; ++w4) {
-        const u4v kv4 = load128(kr_codes, ko + 16 * w4), vv4 = load128(vr_codes, vo + 16 * w4 * VSTEP);
-        G.kc[4 * w4] = kv4.x, G.kc[4 * w4 + 1] = kv4.y, G.kc[4 * w4 + 2] = kv4.z, G.kc[4 * w4 + 3] = kv4.w;
-        G.vc[4 * w4] = vv4.x, G.vc[4 * w4 + 1] = vv4.y, G.vc[4 * w4 + 2] = vv4.z, G.vc[4 * w4 + 3] = vv4.w;
-      }
-      const uint32_t mrec = (uint32_t)(shift_group(min(tg, last_tok)) - base_group) * kMeanBytes;
-      if constexpr (DQ) {
-        const uint32_t rec = (rel >> 6) * kDqNormRec, tok0 = norm_off >> 2;
+      for (int w4 = 0; w4 < CW / 4; ++w4) set_codes(w4, load128(kr_codes, ko + 16 * w4), load128(vr_codes, vo + 16 * w4 * VSTEP));
+      if constexpr (DQ) {  // one norm record per 64-token block
+        const uint32_t rec = (rel >> 6) * kDqNormRec, tok0 = norm_off >> 2;  // (the lane's first token: a multiple of 4)
         const u2v ka = load64(kr_norms, rec + 2 * tok0), va = load64(vr_norms, rec + 2 * tok0);
         const uint32_t at_codes = rec + kDqNormCodes + (tok0 >> 1), at_par = rec + kDqNormPar;
         G.nk = make_uint4(ka.x, ka.y, load16(kr_norms, at_codes), load32(kr_norms, at_par));
         G.nv = make_uint4(va.x, va.y, load16(vr_norms, at_codes), load32(vr_norms, at_par));
-        const uint32_t at_mpar = mrec + kDqMeanPar + 4 * ((uint32_t)lane >> 4);
-        G.ok = kp_means[mrec + lane], G.ov = vp_means[mrec + lane];
-        G.okp = *reinterpret_cast<const uint32_t*>(kp_means + at_mpar), G.ovp = *reinterpret_cast<const uint32_t*>(vp_means + at_mpar);
       } else {
         const u4v nk = load128(kr_norms, norm_off + rel * 4), nv = load128(vr_norms, norm_off + rel * 4);
         G.nk = make_uint4(nk.x, nk.y, nk.z, nk.w), G.nv = make_uint4(nv.x, nv.y, nv.z, nv.w);
-        G.ok = *reinterpret_cast<const uint32_t*>(kp_means + (mrec + lane_x4));
-        G.ov = *reinterpret_cast<const uint32_t*>(vp_means + (mrec + lane_x4));
       }
-      return;
-    }
-    int64_t kbase = 0, vbase = 0, mgrp = 0;  // wave-uniform
-    if (real) {
-      group_bases(tg, kbase, vbase);
-      mgrp = mean_base + shift_group(tg);
-    }
-    const uint32_t lco = real ? lane_code_off : 0u, lvo = real ? lane_v_off : 0u, noff = real ? norm_off : 0u, lx4 = real ? lane_x4 : 0u;
-    const uint32_t ln = real ? (uint32_t)lane : 0u;
-    const unsigned char* kp = kc.codes + kbase * J + lco;
-    const unsigned char* vp = vc.codes + vbase * J + lvo;
-#pragma unroll
-    for (int w4 = 0; w4 < CW / 4; ++w4) {
-      const uint4 kv4 = reinterpret_cast<const uint4*>(kp)[w4];
-      const uint4 vv4 = reinterpret_cast<const uint4*>(vp)[w4 * VSTEP];
-      G.kc[4 * w4] = kv4.x, G.kc[4 * w4 + 1] = kv4.y, G.kc[4 * w4 + 2] = kv4.z, G.kc[4 * w4 + 3] = kv4.w;
-      G.vc[4 * w4] = vv4.x, G.vc[4 * w4 + 1] = vv4.y, G.vc[4 * w4 + 2] = vv4.z, G.vc[4 * w4 + 3] = vv4.w;
-    }
-    if constexpr (DQ) {
-      // (kbase, vbase are multiples of 64: one norm record per 64-token block of the buffer)
-      const unsigned char* kr = reinterpret_cast<const unsigned char*>(kc.norms) + (kbase >> 6) * kDqNormRec;
-      const unsigned char* vr = reinterpret_cast<const unsigned char*>(vc.norms) + (vbase >> 6) * kDqNormRec;
-      const uint32_t tok0 = noff >> 2;  // the lane's first token of the group (a multiple of 4)
-      const uint2 ka = *reinterpret_cast<const uint2*>(kr + 2 * tok0), va = *reinterpret_cast<const uint2*>(vr + 2 * tok0);
-      G.nk = make_uint4(ka.x, ka.y, *reinterpret_cast<const uint16_t*>(kr + kDqNormCodes + (tok0 >> 1)),
-                        *reinterpret_cast<const uint32_t*>(kr + kDqNormPar));
-      G.nv = make_uint4(va.x, va.y, *reinterpret_cast<const uint16_t*>(vr + kDqNormCodes + (tok0 >> 1)),
-                        *reinterpret_cast<const uint32_t*>(vr + kDqNormPar));
-      const int64_t mo = mgrp * kDqMeanRec;
-      const unsigned char* km = reinterpret_cast<const unsigned char*>(kc.means) + mo;
-      const unsigned char* vm = reinterpret_cast<const unsigned char*>(vc.means) + mo;
-      G.ok = km[ln], G.ov = vm[ln];
-      G.okp = *reinterpret_cast<const uint32_t*>(km + kDqMeanPar + 4 * (ln >> 4));
-      G.ovp = *reinterpret_cast<const uint32_t*>(vm + kDqMeanPar + 4 * (ln >> 4));
     } else {
-      G.nk = *reinterpret_cast<const uint4*>(reinterpret_cast<const unsigned char*>(kc.norms + kbase) + noff);
-      G.nv = *reinterpret_cast<const uint4*>(reinterpret_cast<const unsigned char*>(vc.norms + vbase) + noff);
-      const int64_t mo = mgrp * kHeadDim;
-      G.ok = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const unsigned char*>(kc.means + mo) + lx4);
-      G.ov = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const unsigned char*>(vc.means + mo) + lx4);
+      uint32_t kblock, vblock;  // wave-uniform
+      group_blocks(tg, real, kblock, vblock);
+      const uint32_t lco = real ? lane_code_off : 0u, lvo = real ? lane_v_off : 0u, noff = real ? norm_off : 0u;
+      const unsigned char *kp = kc.codes + (uint64_t)kblock * (64 * J), *vp = vc.codes + (uint64_t)vblock * (64 * J);
+#pragma unroll
+      for (int w4 = 0; w4 < CW / 4; ++w4)
+        set_codes(w4, *reinterpret_cast<const u4v*>(kp + (lco + 16 * w4)), *reinterpret_cast<const u4v*>(vp + (lvo + 16 * w4 * VSTEP)));
+      constexpr int kBlockNorms = DQ ? kDqNormRec : 256;
+      const unsigned char* kn = reinterpret_cast<const unsigned char*>(kc.norms) + (uint64_t)kblock * kBlockNorms;
+      const unsigned char* vn = reinterpret_cast<const unsigned char*>(vc.norms) + (uint64_t)vblock * kBlockNorms;
+      if constexpr (DQ) {
+        const uint32_t tok0 = noff >> 2;
+        const uint2 ka = *reinterpret_cast<const uint2*>(kn + 2 * tok0), va = *reinterpret_cast<const uint2*>(vn + 2 * tok0);
+        G.nk = make_uint4(ka.x, ka.y, *reinterpret_cast<const uint16_t*>(kn + (kDqNormCodes + (tok0 >> 1))),
+                          *reinterpret_cast<const uint32_t*>(kn + kDqNormPar));
+        G.nv = make_uint4(va.x, va.y, *reinterpret_cast<const uint16_t*>(vn + (kDqNormCodes + (tok0 >> 1))),
+                          *reinterpret_cast<const uint32_t*>(vn + kDqNormPar));
+      } else {
+        G.nk = *reinterpret_cast<const uint4*>(kn + noff), G.nv = *reinterpret_cast<const uint4*>(vn + noff);
+      }
+    }
+    const uint32_t mrec = (uint32_t)(shift_group(min(tg, last_tok)) - base_group) * kMeanBytes;
+    if constexpr (DQ) {
+      const uint32_t at_par = mrec + kDqMeanPar + 4 * ((uint32_t)lane >> 4);
+      G.ok = kp_means[mrec + lane], G.ov = vp_means[mrec + lane];
+      G.okp = *reinterpret_cast<const uint32_t*>(kp_means + at_par), G.ovp = *reinterpret_cast<const uint32_t*>(vp_means + at_par);
+    } else {
+      G.ok = *reinterpret_cast<const uint32_t*>(kp_means + (mrec + lane_x4));
+      G.ov = *reinterpret_cast<const uint32_t*>(vp_means + (mrec + lane_x4));
     }
   };
   // legacy layout: a group's code bytes from the order they were loaded in to the order the gathers use
@@ -679,11 +671,9 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
   }
   n_grp = (t1 > t0) ? (t1 - t0 + 63) >> 6 : 0;  // 64-token groups of this segment
   int t_whole = t1 - 64;                         // groups that begin later hold masked tokens (or are far from base_tok)
-  if constexpr (!PAGED) {
-    base_tok = t0;
-    describe(t0 + (n_grp << 6));
-    t_whole = min(t_whole, base_tok + kRebase);
-  }
+  base_tok = t0;
+  describe(t0 + (n_grp << 6));
+  t_whole = min(t_whole, base_tok + kRebase);
   // FLAT: waves 4..7 take the segment's first groups: they are the ones that come out of the previous
   // segment early (waves 0..3 merge it), and a short segment then does not wait for the late ones
   const int wslot = FLAT ? (wave + 4) & 7 : wave;
@@ -1241,12 +1231,10 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
     for (int k = 0; k < 4; ++k) sc[k] = fmaf(ak[k], sc[k], bk[k] * qo[ROPE ? k : 0]);
     if (tg > t_whole) {  // wave-uniform: only a sequence's last group has masked tokens (their bytes may be anything)
       asm volatile("");  // (or the compiler makes twelve selects of it that every group goes through)
-      if constexpr (!PAGED) {
-        if (tg - base_tok > kRebase) {
-          base_tok += kRebase;
-          describe(t0 + (n_grp << 6));
-          t_whole = min(t1 - 64, base_tok + kRebase);
-        }
+      if (tg - base_tok > kRebase) {
+        base_tok += kRebase;
+        describe(t0 + (n_grp << 6));
+        t_whole = min(t1 - 64, base_tok + kRebase);
       }
       const int tb0 = tg + tok_of_lane;  // the lane's first token
 #pragma unroll
