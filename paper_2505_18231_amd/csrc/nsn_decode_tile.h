@@ -241,7 +241,7 @@ struct Smem {
 
 // one 64-token group's cache bytes as a lane needs them
 // CW dwords per tensor; the sign + index format (SGN): [0, 4) index bytes, [4, 8) sign bytes, brought by arrange() to the
-// byte order of the plain formats, the sign words shifted for the first and (kx, vx) the second half of a codeword
+// byte order of the plain formats, the sign words as low address bytes of the first and (kx, vx) the second half of a codeword
 template <int CW, bool SGN>
 struct GroupRegs {
   uint32_t kc[CW], vc[CW];  // the lane's code bytes of the group
@@ -259,7 +259,7 @@ __device__ __forceinline__ float dq_level(uint32_t par, uint32_t code) {
 }
 
 // POW2: group_size (if any) and, for paged caches, page_size are powers of two: group and page indices are
-// shifts (the other instance divides: about 35 scalar instructions per index)
+// shifts (the other instance multiplies by reciprocals)
 // PAGED: the caches are paged (block tables); the other instance never reads a block table and can
 // fetch its first group before the sequence length is known
 // FLAT: the launch is one persistent workgroup per compute unit.  All 64-token groups of all (sequence,
@@ -439,9 +439,8 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
   // launches of 12 x 16 heads x 11644 tokens in pages of 64 with 4-bit side information 216.8 instead of 208.9)
   const uint32_t page_blocks = (uint32_t)g.n_kv_heads * ((uint32_t)g.page_tokens >> 6);
   auto group_blocks = [&](int tg, bool real, uint32_t& kblock, uint32_t& vblock) {
-    const bool shifts = POW2 || (LEGACY && g.page_shift >= 0);
-    const int page = shifts ? tg >> g.page_shift : tg / g.page_tokens;
-    const uint32_t tb = shifts ? ((uint32_t)tg & (g.page_tokens - 1)) >> 6 : (uint32_t)(tg - page * g.page_tokens) >> 6;
+    const int page = POW2 ? tg >> g.page_shift : tokens_div(tg, g.page_div);
+    const uint32_t tb = (POW2 ? (uint32_t)tg & (g.page_tokens - 1) : (uint32_t)(tg - page * g.page_tokens)) >> 6;
     if (real && (unsigned)(page - win0) >= 64u) {  // wave-uniform
       win0 = page & ~63;
       load_window(b, win0, win_k, win_v);
@@ -455,7 +454,7 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
     vblock = real ? (uint32_t)__builtin_amdgcn_readlane(win_v, at) * page_blocks + in_page : 0u;
   };
   const int gshift = g.group_size > 0 ? g.group_shift : 31;  // (no groups: index 0 for every token)
-  auto shift_group = [&](int tg) -> int { return POW2 || (LEGACY && gshift >= 0) ? tg >> gshift : gshift == 31 ? 0 : tg / g.group_size; };
+  auto shift_group = [&](int tg) -> int { return POW2 ? tg >> gshift : tokens_div(tg, g.group_div); };
   // Contiguous caches are read through buffer descriptors (the Shift vectors, which every group has, through plain pointers):
   // base and size in scalar registers, one vector addition per kind of array and group, and no address arithmetic on the scalar
   // unit, whose instructions a wave waits for one by one (about eight cycles each; 64-bit addresses of six arrays were thirty
@@ -539,10 +538,10 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
     const uint32_t mrec = (uint32_t)(shift_group(min(tg, last_tok)) - base_group) * kMeanBytes;
     if constexpr (DQ) {
       const uint32_t at_par = mrec + kDqMeanPar + 4 * ((uint32_t)lane >> 4);
-      G.ok = kp_means[mrec + lane], G.ov = vp_means[mrec + lane];
-      G.okp = *reinterpret_cast<const uint32_t*>(kp_means + at_par), G.ovp = *reinterpret_cast<const uint32_t*>(vp_means + at_par);
+      if constexpr (!ROPE) G.ok = kp_means[mrec + lane], G.okp = *reinterpret_cast<const uint32_t*>(kp_means + at_par);
+      G.ov = vp_means[mrec + lane], G.ovp = *reinterpret_cast<const uint32_t*>(vp_means + at_par);
     } else {
-      G.ok = *reinterpret_cast<const uint32_t*>(kp_means + (mrec + lane_x4));
+      if constexpr (!ROPE) G.ok = *reinterpret_cast<const uint32_t*>(kp_means + (mrec + lane_x4));  // (ROPE: rope_load)
       G.ov = *reinterpret_cast<const uint32_t*>(vp_means + (mrec + lane_x4));
     }
   };
@@ -553,6 +552,7 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
       asm volatile("" : "+v"(ln));  // (the selectors are formed anew each time: no registers to spare for them)
       const uint32_t bsel_a = (ln & 4) ? 0x03070105u : 0x06020400u, bsel_b = (ln & 8) ? 0x03020706u : 0x05040100u;
       const uint32_t ksh = (ln & 16) ? 0u : 4u, vsh = (ln & 1) ? 0u : 4u;  // SGN: which half of a codeword comes first
+      const uint32_t k8 = (ln & 16) ? 0x08080808u : 0u, v8 = (ln & 1) ? 0x08080808u : 0u;
       if constexpr (SUB == 4) {
         group_transpose(G.kc[0], G.kc[2], G.kc[4], G.kc[6]);
         group_transpose(G.kc[1], G.kc[3], G.kc[5], G.kc[7]);
@@ -571,8 +571,11 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
 #pragma unroll
           for (int t = 0; t < 4; ++t) {
             const uint32_t ks = G.kc[4 + t], vs = byte_transpose(G.vc[4 + t], bsel_a, bsel_b);
-            G.kc[4 + t] = ks << ksh, G.kx[t] = ks << (4u - ksh);
-            G.vc[4 + t] = vs << vsh, G.vx[t] = vs << (4u - vsh);
+            // the low bytes of the gathers' addresses: sign pattern of a half << 4, offset of that half.  (Masked here, 32 words
+            // instead of 64 addresses; with indices by reciprocals and not by branches over shifts and divisions: 16 ragged
+            // sequences, two launches 54.7 -> 51.0 us, all options of the paper, four launches 82.8 -> 78.9)
+            G.kc[4 + t] = ((ks << ksh) & 0xf0f0f0f0u) | k8, G.kx[t] = ((ks << (4u - ksh)) & 0xf0f0f0f0u) | (k8 ^ 0x08080808u);
+            G.vc[4 + t] = ((vs << vsh) & 0xf0f0f0f0u) | v8, G.vx[t] = ((vs << (4u - vsh)) & 0xf0f0f0f0u) | (v8 ^ 0x08080808u);
           }
         }
       }
@@ -823,7 +826,6 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
   int cur_group = -1;
   float ov0 = 0.f, ov1 = 0.f;
   const uint32_t laneoff = SUB == 4 ? (lane & 31) * 8 : (lane & 15) * 8;  // the lane's copy of the table
-  const uint32_t k8 = (rho & 1) * 8, v8 = (lane & 1) * 8;  // SGN: the half of a codeword that comes first
 
   auto half_lo = [](uint32_t u) -> float { return (float)__builtin_bit_cast(_Float16, (uint16_t)(u & 0xffffu)); };
   auto half_hi = [](uint32_t u) -> float { return (float)__builtin_bit_cast(_Float16, (uint16_t)(u >> 16)); };
@@ -1024,8 +1026,7 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
       constexpr int T = 2 * (E & 1) + (B & 1), S = 2 * (B >> 1) + (E >> 1);
       if constexpr (SGN) {
         constexpr uint32_t sel = 0x0c0c0000u | ((4 + S) << 8) | S;  // code byte << 8 | sign byte
-        const u2v c0 = lds_read64((perm_b32(G.kc[T], G.kc[4 + T], sel) & 0xfff0u) | k8);
-        const u2v c1 = lds_read64((perm_b32(G.kc[T], G.kx[T], sel) & 0xfff0u) | (k8 ^ 8u));
+        const u2v c0 = lds_read64(perm_b32(G.kc[T], G.kc[4 + T], sel)), c1 = lds_read64(perm_b32(G.kc[T], G.kx[T], sel));
         A[E] = __builtin_bit_cast(h8, u4v{c0.x, c0.y, c1.x, c1.y});
       } else if constexpr (SUB == 4) {
         const uint32_t w = G.kc[2 * T + (S >> 1)];
@@ -1056,7 +1057,7 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
       constexpr int X = decltype(xc)::value;
       if constexpr (SGN) {
         constexpr uint32_t sel = 0x0c0c0000u | ((4 + (X >> 1)) << 8) | (X >> 1);
-        Bv[X] = lds_tr64((perm_b32(G.vc[T], (X & 1) ? G.vx[T] : G.vc[4 + T], sel) & 0xfff0u) | ((X & 1) ? v8 ^ 8u : v8));
+        Bv[X] = lds_tr64(perm_b32(G.vc[T], (X & 1) ? G.vx[T] : G.vc[4 + T], sel));
       } else if constexpr (SUB == 4)
         Bv[X] = lds_tr64(table_addr<X & 3>(G.vc[2 * T + (X >> 2)], laneoff));
       else

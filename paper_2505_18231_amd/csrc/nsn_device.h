@@ -61,7 +61,16 @@ struct Geometry {
   // kernels index groups and pages once or more per 64 tokens, and a division by a run-time value
   // costs about 35 scalar instructions
   int group_shift, page_shift;
+  // the same for any size, for tokens that are multiples of 64 (see tokens_div); groups: none is index 0
+  struct Div {
+    uint32_t factor;
+    int shift;
+  } group_div, page_div;
 };
+// floor(t / (64 d)) for multiples t of 64 below 2^31 and d < 2^25 blocks of 64 tokens, with k = ceil(log2 d) and
+// factor = ceil(2^(26 + k) / d): the factor is too large by less than one, which adds less than 2^31 / 2^(32 + k) <= 1 / (2 d) to a
+// quotient whose fraction is (d - 1) / d at most
+__host__ __device__ inline int tokens_div(int t, Geometry::Div v) { return (int)((uint32_t)(((uint64_t)(uint32_t)t * v.factor) >> 32) >> v.shift); }
 
 // Byte offset, inside one placement unit, of the code of (token t of the unit, sub-vector j).
 // K: token-major (a lane that owns a token reads its J bytes in one go).

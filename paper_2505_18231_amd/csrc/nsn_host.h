@@ -8,6 +8,13 @@ namespace nsn {
 // which formats keep their codes in the tiled layout (dec_tile_kernel reads the legacy one too, see nsn_decode_rows.hip)
 inline bool shape_is_tiled(const nsn_shape& s) { return s.n_codes == kCodes && s.rope_table == nullptr; }
 
+inline Geometry::Div tokens_divisor(int tokens) {  // a positive multiple of 64
+  const uint64_t d = (uint64_t)tokens >> 6;
+  int k = 0;
+  while (((uint64_t)1 << k) < d) ++k;
+  return {(uint32_t)((((uint64_t)1 << (26 + k)) + d - 1) / d), k};
+}
+
 inline Geometry make_geometry(const nsn_shape& s) {
   Geometry g;
   g.dq = s.side_bits == 4;
@@ -30,6 +37,8 @@ inline Geometry make_geometry(const nsn_shape& s) {
   };
   g.group_shift = log2_or_minus1(s.group_size);
   g.page_shift = log2_or_minus1(g.page_tokens);
+  g.group_div = s.group_size > 0 ? tokens_divisor(s.group_size) : Geometry::Div{0u, 0};
+  g.page_div = tokens_divisor(g.page_tokens);
   return g;
 }
 
