@@ -463,16 +463,15 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
   // one address for both halves of an 8-dim codeword (a group: 144 -> 103 vector instructions, 55 -> 15 scalar ones with 1-bit
   // codes): 8 x 8192 tokens with residual, four launches 52.3 -> 50.9 us; 131072 1-bit tokens 77.4 -> 75.3; 64 x 32 heads x
   // 32768 tokens 913 -> 870; all options of the paper 87.8 -> 83.2; paged caches, by the selects alone, 90.2 -> 87.6.
-  int base_tok = t0, base_group = 0, last_tok = t0;  // base_tok's Shift group, the last group's first token
+  // (a split beyond the cache, which leaves at once, begins at its last group)
+  int base_tok = min(t0, cap_tokens - 64), base_group = 0, last_tok = 0;  // base_tok's Shift group, the last group's first token
   rsrc_t kr_codes, vr_codes, kr_norms, vr_norms;
   const unsigned char *kp_means, *vp_means;
   constexpr uint32_t kMeanBytes = DQ ? kDqMeanRec : 2 * kHeadDim;
   auto describe = [&](int end_tok) {  // groups from end_tok on read as zeros, without a memory access
     base_group = shift_group(base_tok);
-    int first_mean = base_group;
     if constexpr (!PAGED) {
-      const uint32_t n = (uint32_t)min(max(end_tok - base_tok, 0), 2 * kRebase);
-      first_mean = n ? base_group : 0;  // (a split beyond the cache reads the unit's first one)
+      const uint32_t n = (uint32_t)min(end_tok - base_tok, 2 * kRebase);
       const int64_t tok = (int64_t)(b * g.n_kv_heads + h) * g.page_tokens + base_tok;
       kr_codes = make_rsrc(kc.codes + tok * J, n * J), vr_codes = make_rsrc(vc.codes + tok * J, n * J);
       const int64_t norms_at = DQ ? (tok >> 6) * kDqNormRec : tok * 4;
@@ -481,7 +480,7 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
       vr_norms = make_rsrc(reinterpret_cast<const unsigned char*>(vc.norms) + norms_at, norms_n);
     }
     last_tok = max(end_tok - 64, base_tok);
-    const int64_t mean_at = (mean_base + first_mean) * kMeanBytes;
+    const int64_t mean_at = (mean_base + base_group) * kMeanBytes;
     kp_means = reinterpret_cast<const unsigned char*>(kc.means) + mean_at;
     vp_means = reinterpret_cast<const unsigned char*>(vc.means) + mean_at;
   };
@@ -674,7 +673,7 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
   }
   n_grp = (t1 > t0) ? (t1 - t0 + 63) >> 6 : 0;  // 64-token groups of this segment
   int t_whole = t1 - 64;                         // groups that begin later hold masked tokens (or are far from base_tok)
-  base_tok = t0;
+  if constexpr (FLAT || PAGED) base_tok = t0;
   describe(t0 + (n_grp << 6));
   t_whole = min(t_whole, base_tok + kRebase);
   // FLAT: waves 4..7 take the segment's first groups: they are the ones that come out of the previous
