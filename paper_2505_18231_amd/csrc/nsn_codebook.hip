@@ -131,7 +131,7 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_accumulate_kernel(const f
   constexpr int NT = kSumThreads<SUB>;
   constexpr int kOwn = (kCodes * SUB + NT - 1) / NT;  // sums a thread carries in registers
   constexpr double kMagic = 6755399441055744.0;      // 1.5 * 2^52
-  __shared__ SearchTables<SUB> T;
+  __shared__ SearchTables<SUB, false> T;
   __shared__ double cx[kCodes][SUB];
   __shared__ unsigned long long acc[ERR ? 1 : SUB][kCodes], acc_small[ERR ? 1 : SUB][kCodes];
   __shared__ uint32_t cnt[kCodes];
@@ -164,7 +164,7 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_accumulate_kernel(const f
     for (int i = 0; i < SUB; ++i) cx[tid][i] = centroid[i];
   }
   SearchRegs<SUB, false> R;
-  search_setup<SUB, false>(T, R, tid, [&](int i) { return centroid[i]; });
+  search_setup<SUB, false, false>(T, R, tid, [&](int i) { return centroid[i]; });
   int ex = 0;
   uint32_t small = 0u;  // twice the bits of 2^(ex - 27) where the set holds smaller values (but zero)
   if constexpr (!ERR) {
@@ -193,7 +193,10 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_accumulate_kernel(const f
       // the next 64 are on their way while these are searched (the last one of the block again where there are none)
       const int64_t next = w0 + NT < stop ? w0 + NT : base + kSumMost + (tid & ~63);
       fetch(next + (tid & 63));
-      const int code = search_nearest<SUB, false, SUB == 8>(T, R, x, [&](int c) { return exact_dist<SUB>(cx[c], x); }).code;
+      float y[SUB];
+#pragma unroll
+      for (int i = 0; i < SUB; ++i) y[i] = x[i] * R.scale;
+      const int code = search_nearest<SUB, false, SUB == 8, false>(T, R, y, [&](int c) { return exact_dist<SUB>(cx[c], x); });
       if constexpr (ERR) {
         if (valid) err += exact_dist<SUB>(cx[code], x);
       } else if (valid) {
@@ -295,7 +298,7 @@ template <int SUB, bool UNIT>
 __global__ __launch_bounds__(kSumThreads<SUB>) void cb_ordered_kernel(const float* __restrict__ samples, int64_t n,
                                                                       CodebookWs<SUB> ws) {
   constexpr int NT = kSumThreads<SUB>, NWV = NT / 64, CPW = (kPairs / 64 + NWV - 1) / NWV;
-  __shared__ SearchTables<SUB> T;
+  __shared__ SearchTables<SUB, false> T;
   __shared__ double cx[kCodes][SUB];
   __shared__ __attribute__((aligned(16))) uint16_t list[kPairs][kListMost];
   __shared__ uint32_t len[kPairs];
@@ -310,7 +313,7 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_ordered_kernel(const floa
 #pragma unroll
       for (int i = 0; i < SUB; ++i) cx[tid][i] = centroid[i];
     }
-    search_setup<SUB, false>(T, R, tid, [&](int i) { return centroid[i]; });
+    search_setup<SUB, false, false>(T, R, tid, [&](int i) { return centroid[i]; });
   }
   const int64_t n16 = n & ~(int64_t)(kRun - 1);
   double acc[CPW][SUB];
@@ -354,7 +357,10 @@ __global__ __launch_bounds__(kSumThreads<SUB>) void cb_ordered_kernel(const floa
     }
   };
   auto search = [&](const float (&x)[SUB]) {
-    return search_nearest<SUB, false, false>(T, R, x, [&](int c) { return exact_dist<SUB>(cx[c], x); }).code;
+    float y[SUB];
+#pragma unroll
+    for (int i = 0; i < SUB; ++i) y[i] = x[i] * R.scale;
+    return search_nearest<SUB, false, false, false>(T, R, y, [&](int c) { return exact_dist<SUB>(cx[c], x); });
   };
   const int64_t blocks = (n16 + (int64_t)kSumMost * kSumBlocks - 1) / ((int64_t)kSumMost * kSumBlocks);
   for (int64_t blk = 0; blk < blocks; ++blk) {

@@ -382,16 +382,23 @@ __device__ __forceinline__ void rotate_token(double (&v)[CPL], int lane) {
   }
 }
 
-template <int SUB, int CPL, bool SIGN, bool ROPE, bool PASS1>
-__global__ __launch_bounds__(256, 2) void enc_kernel(EncArgs A) {
+// WAVES: workgroups on a compute unit, i.e. waves per SIMD.  Three (CPL = 16) leave 168 registers and 53 KB of LDS to each: the
+// search has its LEAN form, the Shift vector is unpacked in every step instead of held in 32 registers, and the sums of pass 1 lie
+// where the tokens come later.  8-dim instances spill 8 to 20 registers, none in the loop over the search's tiles.  8 x 8192
+// tokens, 8 kv heads, 4-dim: 542 -> 518 us; 4 ragged sequences of up to 4096 tokens, 8-dim signs with the rotary embedding:
+// 104.5 -> 92.6 us.
+template <int SUB, int CPL, bool SIGN, bool ROPE, bool PASS1, int WAVES = 2>
+__global__ __launch_bounds__(256, WAVES) void enc_kernel(EncArgs A) {
   static_assert(CPL == 16 || CPL == 8 || CPL == SUB, "lane layouts");
   static_assert(!SIGN || SUB == 8, "the sign + index format is defined on 8-dim sub-vectors");
   constexpr int J = kHeadDim / SUB, JB = SIGN ? 2 * J : J;  // sub-vectors, code bytes per token
   constexpr int NQ = CPL / SUB, LPT = kHeadDim / CPL;       // sub-vectors per lane, lanes per token
   constexpr int TPS = 64 * CPL / kHeadDim;                  // tokens per wave step
-  __shared__ SearchTables<SUB> T;
+  __shared__ SearchTables<SUB, true, (WAVES > 2)> T;
   __shared__ double2 y_s[CPL == SUB ? 1 : 4][CPL == SUB ? 1 : CPL / 2][64];  // rotated tokens, per wave
-  __shared__ double red[4][kHeadDim], mean_s[kHeadDim];
+  // the waves' sums of pass 1 (three workgroups to a compute unit: in the tokens' place, before there are any)
+  __shared__ double own_red[WAVES > 2 ? 1 : 4][kHeadDim], mean_s[kHeadDim];
+  double(*const red)[kHeadDim] = WAVES > 2 ? reinterpret_cast<double(*)[kHeadDim]>(y_s) : own_red;
   __shared__ __half b_s[64];
   const Geometry& g = A.g;
   const int h = blockIdx.y >> 1, tensor = blockIdx.y & 1, b = blockIdx.z;
@@ -482,7 +489,7 @@ __global__ __launch_bounds__(256, 2) void enc_kernel(EncArgs A) {
       n2 = fmaxf(n2, t);
     }
     // (a rotated token has norm sqrt(128): no sub-vector is longer than 11.4)
-    search_setup<SUB, true>(T, R, tid, wave_max_lanes(n2),
+    search_setup<SUB, true, (WAVES > 2)>(T, R, tid, wave_max_lanes(n2),
                             [&](int i) { return __half2float(reinterpret_cast<const __half*>(&own_row)[i]); }, 4);
   }
 
@@ -536,8 +543,9 @@ __global__ __launch_bounds__(256, 2) void enc_kernel(EncArgs A) {
   }
 
   // ---- pass 2 -----------------------------------------------------------------------------------
+  constexpr bool kLate = WAVES > 2;
   double o[CPL];
-  if (own_means) {
+  if (!kLate && own_means) {
 #pragma unroll
     for (int i = 0; i < CPL; ++i) o[i] = mean_s[ch0 + (i & 7) + 64 * (i >> 3)];
   }
@@ -558,8 +566,11 @@ __global__ __launch_bounds__(256, 2) void enc_kernel(EncArgs A) {
       }
     }
   };
-  if (!own_means) unpack_mean();
-  const double cscale = -0.5 / (double)R.scale;  // codeword element = table entry * cscale (exact: powers of two)
+  if (!kLate && !own_means) unpack_mean();
+  // (the rotated tokens are kept in the search's units; a table entry is -2 R.scale times the codeword's element.  All exact:
+  // powers of two)
+  const double y_scale = (double)R.scale;
+  const double dot_scale = __builtin_ldexp(-0.5, -2 * (__builtin_amdgcn_frexp_expf(R.scale) - 1));  // -0.5 / y_scale^2
   // the lane's further codes lie at fixed distances from its first one (both layouts are linear in the bits of j)
   const int64_t dq1 = NQ > 1 ? code_offset(g.tiled, tensor != 0, JB, 0, CPL == 16 && SUB == 8 ? 2 : 1) : 0;
   const int64_t dq2 = NQ > 2 ? code_offset(g.tiled, tensor != 0, JB, 0, 4) : 0;
@@ -581,7 +592,7 @@ __global__ __launch_bounds__(256, 2) void enc_kernel(EncArgs A) {
       if (__any(want != grp)) {
         grp = want;
         fetch_mean(grp);
-        unpack_mean();
+        if constexpr (!kLate) unpack_mean();
       }
     }
     __half b16;
@@ -595,6 +606,14 @@ __global__ __launch_bounds__(256, 2) void enc_kernel(EncArgs A) {
     }
     const double bb = (double)__half2float(b16), rb = rcp_f64(bb);
     double ss = 0.0;
+    if constexpr (kLate) {
+      if (own_means) {
+#pragma unroll
+        for (int i = 0; i < CPL; ++i) o[i] = mean_s[ch0 + (i & 7) + 64 * (i >> 3)];
+      } else {
+        unpack_mean();
+      }
+    }
 #pragma unroll
     for (int i = 0; i < CPL; ++i) {
       v[i] = fma(v[i], rb, -o[i]);
@@ -604,7 +623,7 @@ __global__ __launch_bounds__(256, 2) void enc_kernel(EncArgs A) {
     // second Normalize and the 1 / sqrt(d) of the rotation in one factor: v / s2 / sqrt(d) = v / ||v||
     const double rs = rsqrt_f64(ss), s2 = ss * rs * kInvSqrtD;
 #pragma unroll
-    for (int i = 0; i < CPL; ++i) v[i] *= rs;
+    for (int i = 0; i < CPL; ++i) v[i] *= rs * y_scale;
     if constexpr (ROPE) {
       if (tensor == 0) {  // keys only: channels c and c + 64 turn by position * inv_freq[c]
         // cos / sin from the fp64 table: block part and in-block part combined by the addition theorems
@@ -664,15 +683,15 @@ __global__ __launch_bounds__(256, 2) void enc_kernel(EncArgs A) {
       float yf[SUB];
 #pragma unroll
       for (int i = 0; i < SUB; ++i) yf[i] = (float)y[i];
-      const Nearest best = search_nearest<SUB, true, true>(T, R, yf, [&](int c) {
+      const int code = search_nearest<SUB, true, (WAVES == 2), (WAVES > 2)>(T, R, yf, [&](int c) {
         double d = 0.0;
 #pragma unroll
         for (int u = 0; u < SUB / 4; ++u) {
-          const float4 e = T.n2c[u][codeword_group(c) * SearchTables<SUB>::kRowStride + codeword_row(c)];
+          const float4 e = T.n2c[u][SearchTables<SUB, true, (WAVES > 2)>::row(c)];
           const float ev[4] = {e.x, e.y, e.z, e.w};
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const double dd = y[4 * u + i] - (double)ev[i] * cscale;
+            const double dd = y[4 * u + i] - (double)ev[i] * -0.5;
             d = __dadd_rn(d, __dmul_rn(dd, dd));  // plain sum of squares
           }
         }
@@ -680,18 +699,18 @@ __global__ __launch_bounds__(256, 2) void enc_kernel(EncArgs A) {
       });
 #pragma unroll
       for (int u = 0; u < SUB / 4; ++u) {
-        const float4 e = T.n2c[u][best.at];
+        const float4 e = T.n2c[u][SearchTables<SUB, true, (WAVES > 2)>::row(code)];
         dot = fma(y[4 * u], (double)e.x, dot), dot = fma(y[4 * u + 1], (double)e.y, dot);
         dot = fma(y[4 * u + 2], (double)e.z, dot), dot = fma(y[4 * u + 3], (double)e.w, dot);
       }
       if (valid) {
         const int64_t at = NQ == 4 ? (q & 1) * dq1 + (q >> 1) * dq2 : q * dq1;
-        out[at] = (uint8_t)best.code;
+        out[at] = (uint8_t)code;
         if constexpr (SIGN) out[at + dsign] = (uint8_t)sign_byte;
       }
     }
     // scale adjustment: alpha = ||y||^2 / (y . y_Q), ||y||^2 = d
-    dot = token_sum<CPL>(dot) * cscale;
+    dot = token_sum<CPL>(dot) * dot_scale;
     const double alpha = dot > 1e-12 * kHeadDim ? (double)kHeadDim * rcp_f64(dot) : 1.0;
     if (valid && leader) {
       if (dq)  // a' = fp16(s2 alpha); s1 is stored as a 4-bit code
@@ -950,6 +969,20 @@ int encode_layout(const nsn_shape& s, int batch, int max_new, bool pass1) {
   return bulk < fminf(small, eight) ? 16 : eight < small ? 8 : s.sub_dim;
 }
 
+// Three workgroups to a compute unit, of the 256, or two.  Three share their vector ALUs better, but their workgroups run without
+// the tile requested ahead and unpack the Shift vector in every step, so each takes longer: worth it where the chip goes through
+// fewer rounds, and always beyond four workgroups to a compute unit.  Two / three, us, batch 8 x 8 kv heads, formats 4-dim |
+// 8-dim | 4-dim with the rotary embedding | 8-dim signs with it and means formed here (same results in all):
+//    256 workgroups  17.2 / 18.3 | 15.9 / 16.6 | 18.7 / 19.3 | 13.9 / 15.7
+//    512             26.0 / 27.7 | 22.8 / 24.1 | 28.9 / 30.0 | 21.4 / 23.3
+//    640             34.8 / 34.4 | 30.2 / 29.1 | 37.5 / 36.4 | 30.4 / 28.3
+//    768             34.9 / 34.8 | 30.2 / 29.5 | 39.4 / 36.0 | 33.3 / 29.3
+//   1024             42.7 / 42.9 | 35.3 / 36.4 | 47.6 / 46.4 | 40.5 / 39.7
+//   1280             52.2 / 51.4 | 44.5 / 43.2 | 58.5 / 56.3 | 50.7 / 45.7
+//   2048             75.9 / 73.4 | 63.6 / 60.7 | 87.6 / 80.0 | 76.9 / 69.0
+//   4096             143.6 / 136.5 | 119.7 / 112.1 | 156.8 / 144.2 | 138.8 / 127.9
+bool three_to_a_unit(int64_t workgroups) { return workgroups > 1024 || (workgroups > 512 && workgroups <= 768); }
+
 int encode_launch(const nsn_shape& s, const void* codebook, const void* k_in, const void* v_in, int max_new,
                   const int32_t* seq_start, const int32_t* n_new, int batch, int freeze_means,
                   const nsn_cache& kc, const nsn_cache& vc, void* workspace, hipStream_t stream) {
@@ -1009,16 +1042,21 @@ int encode_launch(const nsn_shape& s, const void* codebook, const void* k_in, co
   else if (tokens >= 524288 && !own_means && !g.dq)
     a.wg_tokens = 128;
   const dim3 grid((max_new + a.wg_tokens - 1) / a.wg_tokens, s.n_kv_heads * 2, batch);
+  const bool three = bulk && three_to_a_unit((int64_t)grid.x * grid.y * grid.z);
   auto launch = [&](auto kernel) { kernel<<<grid, 256, 0, stream>>>(a); };
   auto pick = [&](auto sub, auto sign, auto rope) {
     constexpr int kSub = decltype(sub)::value;
     constexpr bool kSign = decltype(sign)::value, kRope = decltype(rope)::value;
     if (pass1)
-      bulk ? launch(enc_kernel<kSub, 16, kSign, kRope, true>) : launch(enc_kernel<kSub, kSub, kSign, kRope, true>);
+      three  ? launch(enc_kernel<kSub, 16, kSign, kRope, true, 3>)
+      : bulk ? launch(enc_kernel<kSub, 16, kSign, kRope, true>)
+             : launch(enc_kernel<kSub, kSub, kSign, kRope, true>);
     else if (eight)
       launch(enc_kernel<kSub, 8, kSign, kRope, false>);
     else
-      bulk ? launch(enc_kernel<kSub, 16, kSign, kRope, false>) : launch(enc_kernel<kSub, kSub, kSign, kRope, false>);
+      three  ? launch(enc_kernel<kSub, 16, kSign, kRope, false, 3>)
+      : bulk ? launch(enc_kernel<kSub, 16, kSign, kRope, false>)
+             : launch(enc_kernel<kSub, kSub, kSign, kRope, false>);
   };
   auto with_format = [&](auto rope) {
     if (g.sign)

@@ -1,12 +1,13 @@
 // Nearest-codeword search (Eq. 1, squared Euclidean distance): one sub-vector per lane, 64 per call.
 //
 // Three steps, bound by vector instructions: per 64 searches of 256 4-dim codewords 265 of them (and 16 matrix instructions) up to
-// the lists, then 60 for every group of the longest list among the 64, which holds one at least; 8-dim codewords 295 (and 32) and
-// 95.  Settling two candidates takes 55 to 110 more.  (Keeping the best two indexed keys of every distance took about 740.)
+// the lists, then 60 for every group of the longest list among the 64, which holds one at least (LEAN: sixteen fewer and six more);
+// 8-dim codewords 295 (and 32) and 95.  Settling two candidates takes 55 to 110 more.  (Keeping the best two indexed keys of every
+// distance took about 740.)
 //   1. matrix cores: D = ||c||^2 - 2 c . y + n for 32 codewords (rows) x 32 sub-vectors (columns) at a time, n slightly
 //      above ||y||^2 (D > 0).  y, c and ||c||^2 enter as sums of fp16 parts, so D is good to about 2^-19 of
-//      (|c| + |y|)^2.  A lane then holds 16 distances of one sub-vector per tile and keeps only the minima of the two groups
-//      of eight: half an instruction per distance (three-operand minima), no index bookkeeping.  32 groups of 8 codewords
+//      (|c| + |y|)^2.  A lane then holds 16 distances of one sub-vector per tile and keeps only the minima of two groups
+//      of about eight: half an instruction per distance (three-operand minima), no index bookkeeping.  32 groups of codewords
 //      leave 32 minima per sub-vector, sixteen in either half of the wave.
 //   2. every group whose minimum lies within twice the error bound of the smallest is listed (almost always one).
 //   3. the listed groups' codewords are gone through in fp32 on the vector ALUs (rows read from LDS).  Again
@@ -18,6 +19,9 @@
 //      8-dim samples 3 us less).
 // Groups of 8 against 16: twice the minima in step 2 (+56 instructions), half the rows in step 3 (-48 for 4-dim, -80 for
 // 8-dim codewords, and half the LDS reads).
+// LEAN is the form for three waves per SIMD (168 registers): no tile is requested ahead (the other waves fill the wait), the
+// 8-dim second operands are read from LDS, the 4-dim rows of step 3 are fp16 (half the reads) and the first listed group needs
+// no loop.
 #pragma once
 
 #include <type_traits>
@@ -67,36 +71,50 @@ NSN_SWAP4(swap16x4, "v_permlane16_swap_b32", "")
 NSN_SWAP4(operand_swap32x4, "v_permlane32_swap_b32", "\n\ts_nop 1")
 #undef NSN_SWAP4
 
-// Minima of results 0..7 and 8..15 of a matrix instruction.  All results are positive, so their bit patterns order like
-// integers: integer minima come without the operand canonicalisation that float minima have.
-__device__ __forceinline__ void min8x2(const f16v& d, uint32_t& lo8, uint32_t& hi8) {
+// Minima of the first N and of the other 16 - N results of a matrix instruction.  All results are positive, so their bit
+// patterns order like integers: integer minima come without the operand canonicalisation that float minima have.
+template <int N>
+__device__ __forceinline__ void two_minima(const f16v& d, uint32_t& first, uint32_t& second) {
   auto u = [&](int i) { return __float_as_uint(d[i]); };
   auto min3 = [](uint32_t a, uint32_t b, uint32_t c) { return min(min(a, b), c); };
-  lo8 = min(min3(min3(min3(u(0), u(1), u(2)), u(3), u(4)), u(5), u(6)), u(7));
-  hi8 = min(min3(min3(min3(u(8), u(9), u(10)), u(11), u(12)), u(13), u(14)), u(15));
+  first = u(0), second = u(N);
+#pragma unroll
+  for (int i = 1; i + 1 < N; i += 2) first = min3(first, u(i), u(i + 1));
+  if (N % 2 == 0) first = min(first, u(N - 1));
+#pragma unroll
+  for (int i = N + 1; i + 1 < 16; i += 2) second = min3(second, u(i), u(i + 1));
+  if (N % 2 == 0) second = min(second, u(15));
 }
 
-// group g, row r of it <-> codeword: a lane of half hf holds rows 8 (k / 4) + 4 hf + k % 4, k = 0..15, of 32 x 32 tile m;
-// k < 8 is group 16 hf + 2 m, the others are group 16 hf + 2 m + 1
-constexpr int kGroups = 32, kGroupRows = 8;
-__host__ __device__ constexpr int group_codeword(int g, int r) {
-  return 16 * (g & 15) + 4 * (g >> 4) + 8 * (r >> 2) + (r & 3);
-}
-__host__ __device__ constexpr int codeword_group(int c) { return 16 * ((c >> 2) & 1) + (c >> 4); }
-__host__ __device__ constexpr int codeword_row(int c) { return 4 * ((c >> 3) & 1) + (c & 3); }
+// A lane of half hf holds rows 8 (k / 4) + 4 hf + k % 4, k = 0..15, of 32 x 32 tile m: codewords 128 hf + 16 m + k.  Group
+// 16 hf + 2 m is the first of them, the next group the others.
+constexpr int kGroups = 32;
+__host__ __device__ constexpr int row_codeword(int row) { return 128 * ((row >> 2) & 1) + 4 * (row >> 3) + (row & 3); }  // of tile 0
 
-// LDS: -2 s c and ||s c||^2 in fp32, group by group (padded: neighbouring groups start in different banks); s = the
-// power of two that brings the longest codeword to norm [4, 8) (fp16 parts of any codebook then sit well inside the
-// fp16 range).  `image`: the codeword-side operands of the matrix instructions, 16 bytes per codeword and lane half.
-template <int SUB>
+// LDS: -2 s c in fp32 (and, for codewords that are fp16 values, in fp16: half the reads of step 3; sixteen codewords and a
+// gap, so that groups start in different banks) and ||s c||^2 group by group; s = the power of two that brings the longest
+// codeword to norm [4, 8) (fp16 parts of any codebook then sit well inside the fp16 range).  `image`: the codeword-side operands
+// of the matrix instructions, 16 bytes per codeword and lane half (without a gap between the halves' codewords: a 16-byte LDS
+// read serves lanes 0..3 and 12..15 together, then the next eight such, and a gap of four made those collide).
+template <int SUB, bool EXACT16, bool LEAN = false>
 struct SearchTables {
-  static constexpr int kRowStride = 9;    // 16-byte units per group
+  // 4-dim codewords: seven and nine to a group, which leaves no minimum with two operands (sixteen instructions fewer than
+  // eight and eight, and six more for the ninth codeword, which a group of seven has from its neighbour: a candidate like all
+  // others).  An 8-dim codeword takes ten.
+  static constexpr int kFirst = SUB == 4 && LEAN ? 7 : 8, kGroupRows = 16 - kFirst;
+  __host__ __device__ static constexpr int group_first(int g) { return 8 * g - (g & 1) * (8 - kFirst); }  // codeword
+  __host__ __device__ static constexpr int row(int c) { return c + (c >> 4); }
   static constexpr int kNormStride = 12;  // floats per group
-  static constexpr int kImages = SUB == 4 ? 2 : 3;
-  float4 n2c[SUB / 4][kGroups * kRowStride];
-  float cn[kGroups * kNormStride];
+  static constexpr bool kHalfRows = EXACT16 && SUB == 4 && LEAN;
+  static constexpr int kImages = SUB == 4 ? 2 : EXACT16 ? 1 : 3, kRows = kCodes + kCodes / 16;
+  alignas(16) float4 n2c[SUB / 4][kRows];
+  alignas(16) float cn[kGroups * kNormStride];  // (read sixteen bytes at a time: at eight-byte places 3 to 4 % of a small call)
   float n2max[4];
-  h8 image[kImages][kCodes];
+  alignas(16) _Float16 n2c16[kHalfRows ? kRows : 1][SUB];
+  // 8-dim fp16 codewords: ||c||^2 in three parts and 1, and zeros for the upper half of the wave
+  static constexpr int kZeros = kCodes;
+  alignas(16) h4v norm_parts[EXACT16 && SUB == 8 ? kZeros + 7 * 16 + 1 : 1];
+  alignas(16) h8 image[kImages][kCodes];
 };
 
 template <int SUB, bool EXACT16>
@@ -117,8 +135,9 @@ struct SearchRegs {
 // range and take 256 fp64 distances per wave (encoder, 4096 tokens x 8 heads with codewords a hundredth of the usual: 495 us
 // instead of 54; K-Means of 2^20 samples whose first 256 are a fiftieth of the others: 100 to 270 us more in the first
 // iteration; there the samples have no bound that one far value would not spoil).
-template <int SUB, bool EXACT16, typename F>
-__device__ inline void search_setup(SearchTables<SUB>& T, SearchRegs<SUB, EXACT16>& R, int tid, float n2, F get, int ex_most) {
+template <int SUB, bool EXACT16, bool LEAN, typename F>
+__device__ inline void search_setup(SearchTables<SUB, EXACT16, LEAN>& T, SearchRegs<SUB, EXACT16>& R, int tid, float n2, F get, int ex_most) {
+  using Tables = SearchTables<SUB, EXACT16, LEAN>;
   typedef decltype(get(0)) real;
   const int lane = tid & 63;
   real own[SUB];
@@ -173,33 +192,46 @@ __device__ inline void search_setup(SearchTables<SUB>& T, SearchRegs<SUB, EXACT1
         a0[i] = hi[i], a1[i] = lo[i];
         a2[i] = i < 3 ? p[i < 3 ? i : 0] : (_Float16)(i == 3 ? 1.f : 0.f);
       }
-      T.image[0][tid] = a0, T.image[1][tid] = a1, T.image[2][tid] = a2;
+      T.image[0][tid] = a0;
+      if constexpr (EXACT16) {
+        T.norm_parts[tid] = h4v{a2[0], a2[1], a2[2], a2[3]};
+        if (tid <= 7 * 16) T.norm_parts[Tables::kZeros + tid] = h4v{};
+      } else {
+        T.image[1][tid] = a1, T.image[2][tid] = a2;
+      }
     }
-    const int g = codeword_group(tid), r = codeword_row(tid);
 #pragma unroll
     for (int u = 0; u < SUB / 4; ++u)
-      T.n2c[u][g * SearchTables<SUB>::kRowStride + r] = make_float4(f[4 * u], f[4 * u + 1], f[4 * u + 2], f[4 * u + 3]);
-    T.cn[g * SearchTables<SUB>::kNormStride + r] = cn;
+      T.n2c[u][Tables::row(tid)] = make_float4(f[4 * u], f[4 * u + 1], f[4 * u + 2], f[4 * u + 3]);
+    if constexpr (Tables::kHalfRows) {  // (a0 begins with them)
+      typedef _Float16 row_t __attribute__((ext_vector_type(SUB)));
+      row_t r;
+#pragma unroll
+      for (int i = 0; i < SUB; ++i) r[i] = a0[i];
+      *reinterpret_cast<row_t*>(T.n2c16[Tables::row(tid)]) = r;
+    }
+    const int k = tid & 15;
+    float* const cn_of = &T.cn[(tid >> 4) * 2 * Tables::kNormStride];
+    const int in_first = k, in_second = Tables::kNormStride + k - Tables::kFirst;
+    cn_of[k < Tables::kGroupRows ? in_first : in_second] = cn;
+    if constexpr (Tables::kFirst == 7) cn_of[k >= 7 ? in_second : in_first] = cn;  // (7 and 8 are in both)
   }
   __syncthreads();
-  const int row = lane & 31, half = lane >> 5;
+  const int row = row_codeword(lane & 31), half = lane >> 5;
 #pragma unroll
   for (int m = 0; m < 8; ++m) {
     if constexpr (SUB == 4) {
-      R.A[m] = T.image[half][32 * m + row];
+      R.A[m] = T.image[half][16 * m + row];
     } else {
-      R.A[m] = T.image[0][32 * m + row];
-      if constexpr (EXACT16) {
-        const h8 q = T.image[2][32 * m + row];
-        R.A2[m] = half ? h4v{} : h4v{q[0], q[1], q[2], q[3]};
-      }
+      R.A[m] = T.image[0][16 * m + row];
+      if constexpr (EXACT16) R.A2[m] = T.norm_parts[16 * m + (half ? Tables::kZeros : row)];
     }
   }
 }
 
 // the same where a thread has only its own codeword at hand
-template <int SUB, bool EXACT16, typename F>
-__device__ inline void search_setup(SearchTables<SUB>& T, SearchRegs<SUB, EXACT16>& R, int tid, F get, int ex_most = 100) {
+template <int SUB, bool EXACT16, bool LEAN, typename F>
+__device__ inline void search_setup(SearchTables<SUB, EXACT16, LEAN>& T, SearchRegs<SUB, EXACT16>& R, int tid, F get, int ex_most = 100) {
   float n2 = 0.f;
   if (tid < kCodes) {  // (whole waves)
 #pragma unroll
@@ -208,7 +240,7 @@ __device__ inline void search_setup(SearchTables<SUB>& T, SearchRegs<SUB, EXACT1
     if ((tid & 63) == 0) T.n2max[tid >> 6] = n2;
   }
   __syncthreads();
-  search_setup<SUB, EXACT16>(T, R, tid, fmaxf(fmaxf(T.n2max[0], T.n2max[1]), fmaxf(T.n2max[2], T.n2max[3])), get, ex_most);
+  search_setup<SUB, EXACT16, LEAN>(T, R, tid, fmaxf(fmaxf(T.n2max[0], T.n2max[1]), fmaxf(T.n2max[2], T.n2max[3])), get, ex_most);
 }
 
 __device__ __forceinline__ uint32_t pack_f16(float a, float b) {
@@ -219,24 +251,17 @@ __device__ __forceinline__ h8 words_h8(uint32_t a, uint32_t b, uint32_t c, uint3
   return __builtin_bit_cast(h8, u4v{a, b, c, d});
 }
 
-struct Nearest {
-  int code;  // the codeword
-  int at;    // its place in SearchTables::n2c[.]
-};
-
-// The codeword nearest to y (this lane's sub-vector); all 64 lanes take part.  exact(c): fp64 squared
-// distance of the lane's sub-vector to codeword c.
+// The codeword nearest to y / R.scale (this lane's sub-vector); all 64 lanes take part.  exact(c): fp64 squared
+// distance of the lane's sub-vector to codeword c, in any unit.
 // AHEAD: a tile's products are requested a whole tile before its minima are taken (32 more registers).
-template <int SUB, bool EXACT16, bool AHEAD, typename F>
-__device__ __forceinline__ Nearest search_nearest(const SearchTables<SUB>& T, const SearchRegs<SUB, EXACT16>& R,
-                                              const float (&y_in)[SUB], F exact) {
+template <int SUB, bool EXACT16, bool AHEAD, bool LEAN, typename F>
+__device__ __forceinline__ int search_nearest(const SearchTables<SUB, EXACT16, LEAN>& T, const SearchRegs<SUB, EXACT16>& R,
+                                              const float (&y)[SUB], F exact) {
+  using Tables = SearchTables<SUB, EXACT16, LEAN>;
   constexpr int NP = SUB / 2;
-  float y[SUB], yn = 0.f;
+  float yn = 0.f;
 #pragma unroll
-  for (int i = 0; i < SUB; ++i) {
-    y[i] = y_in[i] * R.scale;
-    yn = fmaf(y[i], y[i], yn);
-  }
+  for (int i = 0; i < SUB; ++i) yn = fmaf(y[i], y[i], yn);
   uint32_t hi[NP], lo[NP];
 #pragma unroll
   for (int i = 0; i < NP; ++i) {
@@ -274,18 +299,22 @@ __device__ __forceinline__ Nearest search_nearest(const SearchTables<SUB>& T, co
     }
   }
   uint32_t a0[8], a1[8], b0[8], b1[8];  // minima of the two groups of tile m held by this lane, sets a and b
-  int second = 256 * (1 + (int)((threadIdx.x >> 5) & 1)) + (int)(threadIdx.x & 31);
-  asm volatile("" : "+v"(second));  // (keeps the reads of the second operand inside the search)
-  constexpr bool kFromLds = SUB == 8 && !EXACT16;
+  constexpr bool kFromLds = SUB == 8 && !EXACT16, kPartsFromLds = SUB == 8 && EXACT16 && LEAN;
+  int second = row_codeword((int)(threadIdx.x & 31));
+  if constexpr (EXACT16)
+    second = lower ? second : Tables::kZeros;
+  else
+    second += kCodes * (1 + (int)((threadIdx.x >> 5) & 1));
+  if constexpr (SUB == 8) asm volatile("" : "+v"(second));  // (keeps the reads of the second operand inside the search)
   auto second_operand = [&](int m) -> h8 {
-    if constexpr (kFromLds) return (&T.image[0][0])[second + 32 * m];
+    if constexpr (kFromLds) return (&T.image[0][0])[second + 16 * m];
     return h8{};
   };
   const f16v zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   // a tile's product with 8-dim codewords is two matrix instructions, the second on the result of the first
   auto first_half = [&](int m, const h8& s2, const h8& y2, const h4v& nn) -> f16v {
     if constexpr (SUB == 8 && EXACT16)
-      return __builtin_amdgcn_mfma_f32_32x32x8f16(R.A2[m], nn, zero, 0, 0, 0);
+      return __builtin_amdgcn_mfma_f32_32x32x8f16(kPartsFromLds ? T.norm_parts[second + 16 * m] : R.A2[m], nn, zero, 0, 0, 0);
     else if constexpr (SUB == 8)
       return __builtin_amdgcn_mfma_f32_32x32x16_f16(s2, y2, zero, 0, 0, 0);
     return zero;
@@ -313,11 +342,11 @@ __device__ __forceinline__ Nearest search_nearest(const SearchTables<SUB>& T, co
       if (m < 7) ea = first_half(m + 1, s_now, ba2, na), eb = first_half(m + 1, s_now, bb2, nb);
       __builtin_amdgcn_sched_barrier(0);
       if (m < 6) s_next = second_operand(m + 2);
-      min8x2(da, a0[m], a1[m]);
+      two_minima<Tables::kFirst>(da, a0[m], a1[m]);
       __builtin_amdgcn_sched_barrier(0);
       if (m < 7) da = second_half(m + 1, ba, ea);
       __builtin_amdgcn_sched_barrier(0);
-      min8x2(db, b0[m], b1[m]);
+      two_minima<Tables::kFirst>(db, b0[m], b1[m]);
       __builtin_amdgcn_sched_barrier(0);
       if (m < 7) db = second_half(m + 1, bb, eb);
     }
@@ -330,11 +359,11 @@ __device__ __forceinline__ Nearest search_nearest(const SearchTables<SUB>& T, co
       __builtin_amdgcn_sched_barrier(0);
       if (m < 7) da_next = tile(m + 1, h8{}, ba, ba2, na);
       __builtin_amdgcn_sched_barrier(0);
-      min8x2(da, a0[m], a1[m]);
+      two_minima<Tables::kFirst>(da, a0[m], a1[m]);
       __builtin_amdgcn_sched_barrier(0);
       if (m < 7) db_next = tile(m + 1, h8{}, bb, bb2, nb);
       __builtin_amdgcn_sched_barrier(0);
-      min8x2(db, b0[m], b1[m]);
+      two_minima<Tables::kFirst>(db, b0[m], b1[m]);
       if (m < 7) da = da_next, db = db_next;
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -342,8 +371,8 @@ __device__ __forceinline__ Nearest search_nearest(const SearchTables<SUB>& T, co
 #pragma unroll
     for (int m = 0; m < 8; ++m) {
       const h8 s2 = second_operand(m);
-      min8x2(tile(m, s2, ba, ba2, na), a0[m], a1[m]);
-      min8x2(tile(m, s2, bb, bb2, nb), b0[m], b1[m]);
+      two_minima<Tables::kFirst>(tile(m, s2, ba, ba2, na), a0[m], a1[m]);
+      two_minima<Tables::kFirst>(tile(m, s2, bb, bb2, nb), b0[m], b1[m]);
     }
   }
   // The minima stay where they are: a lane holds those of its half's groups for one sub-vector of either column set.  What
@@ -358,8 +387,10 @@ __device__ __forceinline__ Nearest search_nearest(const SearchTables<SUB>& T, co
   // range 2 (M >= 16), fp32 rounding of the inputs and of the threshold 3, the sum of at most 32 terms 24 (matrix cores)
   // or SUB + 3 (fp32).  Anything that can be nearest lies within twice the bound of the computed minimum.
   const float reach = R.cm + 1.0001f * __builtin_amdgcn_sqrtf(yn);
-  const float thr_n = fmaf(2.f * 44.f * 5.9604645e-8f * reach, reach, best);  // for D (with n in it)
-  const float thr = thr_n - n16;                                              // for the fp32 form
+  // (beyond the fp16 range - ||y||^2 above 58000 -, a codebook that is not finite, or not a number: nothing is listed)
+  const bool in_range = reach < 245.f;
+  const float thr_n = in_range ? fmaf(2.f * 44.f * 5.9604645e-8f * reach, reach, best) : -INFINITY;  // for D (with n in it)
+  const float thr = thr_n - n16;                                                                     // for the fp32 form
   float thr_a = thr_n, thr_b = thr_n;
   swap32(thr_a, thr_b);  // of sets a and b, in both halves
   uint32_t list_a = 0u, list_b = 0u;
@@ -372,61 +403,71 @@ __device__ __forceinline__ Nearest search_nearest(const SearchTables<SUB>& T, co
     list_b = __builtin_amdgcn_alignbit(list_b, below(b0[m], thr_b), 31);
   }
   swap32(list_a, list_b);  // of the own sub-vector: lower, upper half of the groups
-  uint32_t groups = list_a | list_b << 16;
-  // beyond the fp16 range (||y||^2 above 58000), a codebook that is not finite, or not a number: fp64 search below
-  if (!(reach < 245.f)) groups = 0u;
+  const uint32_t groups = in_range ? list_a | list_b << 16 : 0u;
   // rows of group g within the bound, as a bit mask
   auto rows_of = [&](int g) -> uint32_t {
-    const float4* r0 = &T.n2c[0][g * SearchTables<SUB>::kRowStride];
-    const float4* r1 = &T.n2c[SUB / 4 - 1][g * SearchTables<SUB>::kRowStride];
-    const float4* n = reinterpret_cast<const float4*>(&T.cn[g * SearchTables<SUB>::kNormStride]);
+    const int first = Tables::row(Tables::group_first(g));
+    const float* n = &T.cn[g * Tables::kNormStride];
+    const float4 n0 = reinterpret_cast<const float4*>(n)[0], n1 = reinterpret_cast<const float4*>(n)[1];
+    float cnv[9] = {n0.x, n0.y, n0.z, n0.w, n1.x, n1.y, n1.z, n1.w};
+    if constexpr (Tables::kGroupRows == 9) cnv[8] = n[8];
     uint32_t mask = 0u;
 #pragma unroll
-    for (int u = kGroupRows / 4 - 1; u >= 0; --u) {
-      const float4 cn4 = n[u];
-      const float cnv[4] = {cn4.x, cn4.y, cn4.z, cn4.w};
+    for (int k = Tables::kGroupRows - 1; k >= 0; --k) {
+      float c[SUB];
+      if constexpr (Tables::kHalfRows) {
+        typedef _Float16 row_t __attribute__((ext_vector_type(SUB)));
+        const row_t r = *reinterpret_cast<const row_t*>(T.n2c16[first + k]);
 #pragma unroll
-      for (int k = 3; k >= 0; --k) {
-        const float4 c = r0[4 * u + k];
-        float d = cnv[k] - thr;
-        d = fmaf(c.x, y[0], d), d = fmaf(c.y, y[1], d), d = fmaf(c.z, y[2], d), d = fmaf(c.w, y[3], d);
-        if constexpr (SUB == 8) {
-          const float4 e = r1[4 * u + k];
-          d = fmaf(e.x, y[4], d), d = fmaf(e.y, y[5], d), d = fmaf(e.z, y[6], d), d = fmaf(e.w, y[7], d);
+        for (int i = 0; i < SUB; ++i) c[i] = (float)r[i];
+      } else {
+#pragma unroll
+        for (int u = 0; u < SUB / 4; ++u) {
+          const float4 r = T.n2c[u][first + k];
+          c[4 * u] = r.x, c[4 * u + 1] = r.y, c[4 * u + 2] = r.z, c[4 * u + 3] = r.w;
         }
-        mask = __builtin_amdgcn_alignbit(mask, __float_as_uint(d), 31);
       }
+      float d = cnv[k] - thr;
+#pragma unroll
+      for (int i = 0; i < SUB; ++i) d = fmaf(c[i], y[i], d);
+      mask = __builtin_amdgcn_alignbit(mask, __float_as_uint(d), 31);
     }
     return mask;
   };
-  constexpr int kStride = SearchTables<SUB>::kRowStride;
   constexpr unsigned kListed = 32;  // candidates of a sub-vector that are settled by its lists
-  int at = 0, found = 0, at_before = 0;  // the first candidate of the last group that holds any, and of the one before it
-  uint32_t rows_at = 0u;                  // the candidates of the last such group
-  {
-    uint32_t left = groups;
+  int code = 0, code_before = 0, found = 0;  // the first candidate of the last group that holds any, and of the one before it
+  uint32_t rows_at = 0u;                      // the candidates of the last such group
+  auto take_group = [&](int g, uint32_t rows) {
+    if (rows) code_before = code, rows_at = rows, code = Tables::group_first(g) + __builtin_ctz(rows);
+    found += __builtin_popcount(rows);
+  };
+  uint32_t left = groups;
+  if constexpr (LEAN) {  // every list holds a group, but for lanes out of range, where the last group stands in and nothing is taken
+    const int g = __builtin_ctz(left | 0x80000000u);
+    rows_at = rows_of(g);
+    code = code_before = Tables::group_first(g) + __builtin_ctz(rows_at | 0x80000000u);
+    found = left ? __builtin_popcount(rows_at) : 0;
+    left &= left - 1u;
+    for (; __any(left != 0u); left &= left - 1u) {
+      const int gn = left ? __builtin_ctz(left) : 0;
+      take_group(gn, left ? rows_of(gn) : 0u);
+    }
+  } else {
     do {
       const int g = left ? __builtin_ctz(left) : 0;
-      const uint32_t rows = left ? rows_of(g) : 0u;
-      if (rows) at_before = at, rows_at = rows, at = g * kStride + __builtin_ctz(rows);
-      found += __builtin_popcount(rows);
+      take_group(g, left ? rows_of(g) : 0u);
       left &= left - 1u;
     } while (__any(left != 0u));
   }
-  Nearest res;
-  auto codeword_at = [](int place) { return group_codeword(place / kStride, place % kStride); };
-  res.code = codeword_at(at);
-  res.at = at;
-  if (!__any(found != 1)) return res;
+  if (!__any(found != 1)) return code;
   if (!__any((unsigned)(found - 1) > 1u)) {
     // two candidates (one search of a wave in thirty holds such a sub-vector, mostly one): they are at hand
     if (found == 2) {
       const uint32_t other = rows_at & (rows_at - 1u);
-      const int at2 = other ? at - __builtin_ctz(rows_at) + __builtin_ctz(other) : at_before;
-      const int code2 = codeword_at(at2);
-      const double d = exact(res.code), d2 = exact(code2);
+      const int code2 = other ? code - __builtin_ctz(rows_at) + __builtin_ctz(other) : code_before;
+      const double d = exact(code), d2 = exact(code2);
       // (a codeword that holds a NaN is listed with its group where the sign bit is set: it is never the nearest)
-      if (d2 < d || d != d || (d2 == d && code2 < res.code)) res.code = code2, res.at = at2;
+      if (d2 < d || d != d || (d2 == d && code2 < code)) code = code2;
     }
   } else {
     // None at all (not a number somewhere, or out of range): all codewords.  In the codebook's instances, whose samples have no
@@ -437,13 +478,13 @@ __device__ __forceinline__ Nearest search_nearest(const SearchTables<SUB>& T, co
     double e1 = INFINITY;
     int k1 = 0;
     const bool all = EXACT16 ? found < 1 : __any((unsigned)(found - 1) >= kListed);
-    uint32_t left = found > 1 && !all ? groups : 0u;
+    left = found > 1 && !all ? groups : 0u;
     while (__any(left != 0u)) {
       const int g = left ? __builtin_ctz(left) : 0;
       uint32_t rows = left ? rows_of(g) : 0u;
       while (__any(rows != 0u)) {
         if (rows) {
-          const int c = group_codeword(g, __builtin_ctz(rows));
+          const int c = Tables::group_first(g) + __builtin_ctz(rows);
           const double d = exact(c);
           if (d < e1 || (d == e1 && c < k1)) e1 = d, k1 = c;
         }
@@ -463,12 +504,9 @@ __device__ __forceinline__ Nearest search_nearest(const SearchTables<SUB>& T, co
         for (int c = 0; c < kCodes; ++c) take(c);
       }
     }
-    if (found != 1) {
-      res.code = k1;
-      res.at = codeword_group(k1) * kStride + codeword_row(k1);
-    }
+    if (found != 1) code = k1;
   }
-  return res;
+  return code;
 }
 
 }  // namespace nsn
