@@ -438,9 +438,9 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
   // two launches of 32 ragged sequences took 87.4 instead of 86.4 us, 59 x 32 heads x 3232 tokens 113.1 instead of 111.1, four
   // launches of 12 x 16 heads x 11644 tokens in pages of 64 with 4-bit side information 216.8 instead of 208.9)
   const uint32_t page_blocks = (uint32_t)g.n_kv_heads * ((uint32_t)g.page_tokens >> 6);
-  auto group_blocks = [&](int tg, bool real, uint32_t& kblock, uint32_t& vblock) {
-    const int page = POW2 ? tg >> g.page_shift : tokens_div(tg, g.page_div);
-    const uint32_t tb = (POW2 ? (uint32_t)tg & (g.page_tokens - 1) : (uint32_t)(tg - page * g.page_tokens)) >> 6;
+  auto group_blocks = [&](uint32_t tg, bool real, uint32_t& kblock, uint32_t& vblock) {
+    const int page = POW2 ? (int)(tg >> g.page_shift) : tokens_div((int)tg, g.page_div);
+    const uint32_t tb = (POW2 ? tg & (g.page_tokens - 1) : tg - (uint32_t)page * g.page_tokens) >> 6;
     if (real && (unsigned)(page - win0) >= 64u) {  // wave-uniform
       win0 = page & ~63;
       load_window(b, win0, win_k, win_v);
@@ -484,20 +484,20 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
     kp_means = reinterpret_cast<const unsigned char*>(kc.means) + mean_at;
     vp_means = reinterpret_cast<const unsigned char*>(vc.means) + mean_at;
   };
-  // tg: first token of the group (a multiple of 64).  A group that does not exist (`real` false: the wave's list of groups has
-  // ended) is loaded all the same: contiguous caches read zeros beyond the descriptors' ends, paged ones the first bytes of
-  // every array (one cache line per instruction); nothing of it is used and any bytes are valid table indices.  With loads that
-  // are only issued under a condition, the number of loads behind a given one depends on the path, the compiler's wait counts
-  // take the smallest, and every wait for a group's bytes becomes a wait for all loads in flight, the groups
-  // requested ahead included.
-  auto load_group = [&](int tg, bool real, Regs& G) {
+  // n: the group, counted from token t0.  One that does not exist (`real` false: the wave's list of groups has ended) is
+  // loaded all the same: contiguous caches read zeros beyond the descriptors' ends, paged ones the first bytes of every array
+  // (one cache line per instruction); nothing of it is used and any bytes are valid table indices.  With loads that are only
+  // issued under a condition, the number of loads behind a given one depends on the path, the compiler's wait counts take the
+  // smallest, and every wait for a group's bytes becomes a wait for all loads in flight, the groups requested ahead included.
+  auto load_group = [&](int n, bool real, Regs& G) {
+    const uint32_t tg = token_of_group(t0, n);
     constexpr int VSTEP = LEGACY ? J : 1;  // 16-byte pieces; legacy: the lane's second value row is sixteen rows on
     auto set_codes = [&](int w4, u4v kv4, u4v vv4) {
       G.kc[4 * w4] = kv4.x, G.kc[4 * w4 + 1] = kv4.y, G.kc[4 * w4 + 2] = kv4.z, G.kc[4 * w4 + 3] = kv4.w;
       G.vc[4 * w4] = vv4.x, G.vc[4 * w4 + 1] = vv4.y, G.vc[4 * w4 + 2] = vv4.z, G.vc[4 * w4 + 3] = vv4.w;
     };
     if constexpr (!PAGED) {
-      uint32_t rel = (uint32_t)(tg - base_tok);
+      uint32_t rel = tg - (uint32_t)base_tok;
       asm("" : "+s"(rel));  // (or every offset gets a subtraction of its own)
       const uint32_t ko = lane_code_off + rel * J, vo = lane_v_off + rel * J;
 #pragma unroll
@@ -534,7 +534,7 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
         G.nk = *reinterpret_cast<const uint4*>(kn + noff), G.nv = *reinterpret_cast<const uint4*>(vn + noff);
       }
     }
-    const uint32_t mrec = (uint32_t)(shift_group(min(tg, last_tok)) - base_group) * kMeanBytes;
+    const uint32_t mrec = (uint32_t)(shift_group(token_up_to(tg, last_tok)) - base_group) * kMeanBytes;
     if constexpr (DQ) {
       const uint32_t at_par = mrec + kDqMeanPar + 4 * ((uint32_t)lane >> 4);
       if constexpr (!ROPE) G.ok = kp_means[mrec + lane], G.okp = *reinterpret_cast<const uint32_t*>(kp_means + at_par);
@@ -660,7 +660,7 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
     // the cache when the split lies beyond it: then it is never processed)
     if constexpr (!PAGED) {
       describe(cap_tokens);
-      load_group(t0 + (wave << 6), true, S0);  // (wslot == wave here)
+      load_group(wave, true, S0);  // (wslot == wave here)
     }
     len = seq_lens[b];
     // Splits that lie wholly beyond this sequence's end have nothing to do and leave at once (a ragged batch
@@ -679,7 +679,7 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
   // FLAT: waves 4..7 take the segment's first groups: they are the ones that come out of the previous
   // segment early (waves 0..3 merge it), and a short segment then does not wait for the late ones
   const int wslot = FLAT ? (wave + 4) & 7 : wave;
-  if constexpr (PAGED || FLAT) load_group(t0 + (wslot << 6), wslot < n_grp, S0);
+  if constexpr (PAGED || FLAT) load_group(wslot, wslot < n_grp, S0);
   // ---- prologue: codebook table, query operands --------------------------------------------------
   if constexpr (!FLAT) fill_table();
   if (wave < 4) {  // d1: wave w rotates head w (zeros for a head that this launch does not have)
@@ -761,7 +761,7 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
   auto rope_load = [&](int gi0) {
     const int bi = n16 >> 2, c = n16 & 3;
     // groups past the end are clamped into the tables (their results are never read)
-    const int tg = min(t0 + ((gi0 + NW * bi) << 6), cap_tokens - 64);
+    const int tg = token_up_to(token_of_group(t0, gi0 + NW * bi), cap_tokens - 64);
     const unsigned char* rec = g.rope + kRopeBlkOff + (int64_t)(tg >> 6) * kRopeBlkStride;
     const int i0 = 32 * (c >> 1) + 8 * rho + 4 * (c & 1);
     const int64_t row = mean_base + shift_group(tg);
@@ -780,12 +780,12 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
     rin.c23 = reinterpret_cast<const float4*>(rec)[(i0 >> 1) + 1];
   };
   if constexpr (ROPE) rope_load(wslot);
-  if constexpr (FLAT) load_group(t0 + ((wslot + NW) << 6), wslot + NW < n_grp, S1);
+  if constexpr (FLAT) load_group(wslot + NW, wslot + NW < n_grp, S1);
   __syncthreads();
   if constexpr (FLAT && !LEGACY) {
     // segments are short and start cold: three groups per wave go out before the first is used, and the set
     // that a group leaves takes the group three rounds on (see process_group)
-    load_group(t0 + ((wslot + 2 * NW) << 6), wslot + 2 * NW < n_grp, S2);
+    load_group(wslot + 2 * NW, wslot + 2 * NW < n_grp, S2);
   }
 
   // B operands of the score contraction (see the header): for tile parity p and k-step s the lane's eight
@@ -1012,7 +1012,7 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
   }
   // (per-split instance: the wave's second group, see above; behind the residual tile, which needs no loads, so
   // that a wave with a tile asks out of the way of the other waves' load issue)
-  if constexpr (!FLAT) load_group(t0 + ((wslot + NW) << 6), wslot + NW < n_grp, S1);
+  if constexpr (!FLAT) load_group(wslot + NW, wslot + NW < n_grp, S1);
 
   // Gathers and contractions of one group, in batches.  Key side: sixteen matrix instructions in four
   // batches of four (tiles (0, 2) or (1, 3) x two k-steps, so that consecutive instructions alternate
@@ -1258,12 +1258,12 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
     // the group after the next one: requested just before the next one's bytes are first needed (below)
     // (this group's bytes have all been used by now)
     if constexpr (FLAT && !LEGACY)
-      load_group(t0 + ((gi + 3 * NW) << 6), gi + 3 * NW < n_grp, G);
+      load_group(gi + 3 * NW, gi + 3 * NW < n_grp, G);
     else {
       // (the registers of the Shift vectors, which only a change of the Shift group reads, are nobody's temporaries: a write to
       // one would wait for every load in flight)
       if constexpr (!FLAT && !LEGACY) asm volatile("" ::"v"(Gnn.ok), "v"(Gnn.ov));
-      load_group(t0 + ((gi + 2 * NW) << 6), gi + 2 * NW < n_grp, Gnn);
+      load_group(gi + 2 * NW, gi + 2 * NW < n_grp, Gnn);
     }
     if constexpr (ROPE && it == 3) rope_load(gi + NW);  // the next batch
     __builtin_amdgcn_sched_barrier(0);

@@ -72,6 +72,11 @@ struct Geometry {
 // quotient whose fraction is (d - 1) / d at most
 __host__ __device__ inline int tokens_div(int t, Geometry::Div v) { return (int)((uint32_t)(((uint64_t)(uint32_t)t * v.factor) >> 32) >> v.shift); }
 
+// First token of the n-th 64-token group from token t0 on, and the same but not beyond token `last`.  Unsigned: groups are asked
+// for ahead of their use, whether they exist or not, and a cache may end 64 tokens below 2^31.
+__host__ __device__ inline uint32_t token_of_group(int t0, int n) { return (uint32_t)t0 + ((uint32_t)n << 6); }
+__host__ __device__ inline int token_up_to(uint32_t t, int last) { return (int)(t < (uint32_t)last ? t : (uint32_t)last); }
+
 // Byte offset, inside one placement unit, of the code of (token t of the unit, sub-vector j).
 // K: token-major (a lane that owns a token reads its J bytes in one go).
 // V: blocks of J tokens, sub-vector-major inside a block (a lane that owns a sub-vector reads
