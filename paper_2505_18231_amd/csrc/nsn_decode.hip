@@ -66,7 +66,7 @@ __global__ __launch_bounds__(256) void dec_lut_kernel(Geometry g, const __half* 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int len = seq_lens[b];
   const int per = (((len + n_splits - 1) / n_splits) + 63) & ~63;
-  const int t0 = split * per, t1 = min(len, t0 + per);
+  const int t0 = split * per, t1 = split_end(t0, per, len);
   float* P = partial + ((int64_t)(b * g.n_q_heads + hq) * n_splits + split) * kPartialStride;
   if (t0 >= t1) {  // empty split (uniform for the block)
     if (tid < kHeadDim) {
@@ -110,9 +110,10 @@ __global__ __launch_bounds__(256) void dec_lut_kernel(Geometry g, const __half* 
 #pragma unroll
   for (int i = 0; i < SUB; ++i) acc[i] = 0.f;
 
-  for (int c0 = t0; c0 < t1; c0 += 256) {
+  for (uint32_t c = t0; c < (uint32_t)t1; c += 256) {  // (the last sum may be 2^31 and more)
+    const int c0 = (int)c, here = min(256, t1 - c0);    // tokens of this chunk
     const int g_first = group_of(g, c0);
-    const int n_g = group_of(g, min(c0 + 255, t1 - 1)) - g_first + 1;  // <= 4
+    const int n_g = group_of(g, c0 + here - 1) - g_first + 1;  // <= 4
     if (wave < n_g) {  // q . o^k of the groups this chunk touches
       const __half2 o2 =
           *reinterpret_cast<const __half2*>(kc.means + (mean_base + g_first + wave) * kHeadDim + 2 * lane);
@@ -123,8 +124,8 @@ __global__ __launch_bounds__(256) void dec_lut_kernel(Geometry g, const __half* 
     __syncthreads();
 
     // d3: score of this thread's token
-    const int t = c0 + tid;
-    const bool valid = t < t1;
+    const bool valid = tid < here;
+    const int t = c0 + min(tid, here - 1);
     float score = -INFINITY, av = 0.f, bv = 0.f;
     if (valid) {
       const int64_t base = unit_token_base(g, kc.block_table, b, h, t);
@@ -176,9 +177,8 @@ __global__ __launch_bounds__(256) void dec_lut_kernel(Geometry g, const __half* 
     // d5: value accumulation in the rotated domain: lane owns sub-vector jv of tokens ts, ts+TS, ..
 #pragma unroll
     for (int i = 0; i < SUB; ++i) acc[i] *= corr;
-    for (int tt = ts; tt < 256; tt += TS) {
+    for (int tt = ts; tt < here; tt += TS) {
       const int tv = c0 + tt;
-      if (tv >= t1) break;
       const int64_t vbase = unit_token_base(g, vc.block_table, b, h, tv);
       const int tin = token_in_unit(g, tv);
       const int code = vc.codes[vbase * J + code_offset(g.tiled, true, J, tin, jv)];
@@ -189,10 +189,8 @@ __global__ __launch_bounds__(256) void dec_lut_kernel(Geometry g, const __half* 
     // mean-vector term: beta_g = sum_{t in g} p_t b^v_t, then += beta_g * o^v_g
     if (wave < n_g) {
       float s = 0.f;
-      for (int tt = lane; tt < 256; tt += 64) {
-        const int tv = c0 + tt;
-        if (tv < t1 && group_of(g, tv) == g_first + wave) s += pb[tt];
-      }
+      for (int tt = lane; tt < here; tt += 64)
+        if (group_of(g, c0 + tt) == g_first + wave) s += pb[tt];
       s = xor_sum(s, 64);
       if (lane == 0) beta_s[wave] = s;
     }
@@ -262,7 +260,7 @@ bool decode_use_mfma(const nsn_shape& s) {
 
 int decode_pick_splits(const nsn_shape& s, int batch, int max_seq_len, int requested) {
   if (decode_use_mfma(s)) return decode_tile_splits(s, batch, max_seq_len, requested);
-  const int cap = max(1, min(64, (max_seq_len + 255) / 256));
+  const int cap = max(1, min(64, max_seq_len / 256 + (max_seq_len % 256 != 0)));
   if (requested > 0) return min(requested, 64);
   const int rows = max(1, batch * s.n_q_heads);
   return max(1, min(cap, (1024 + rows - 1) / rows));

@@ -668,14 +668,14 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
     // are.  A sequence without coded tokens keeps split 0 (it may still have residual rows).
     n_live = len > 0 ? (len - 1) / per + 1 : 1;
     if (split >= n_live) return;
-    t1 = min(len, t0 + per);
+    t1 = split_end(t0, per, len);
     res_here = split == n_live - 1;
   }
   n_grp = (t1 > t0) ? (t1 - t0 + 63) >> 6 : 0;  // 64-token groups of this segment
   int t_whole = t1 - 64;                         // groups that begin later hold masked tokens (or are far from base_tok)
   if constexpr (FLAT || PAGED) base_tok = t0;
   describe(t0 + (n_grp << 6));
-  t_whole = min(t_whole, base_tok + kRebase);
+  t_whole = base_tok + min(t_whole - base_tok, kRebase);
   // FLAT: waves 4..7 take the segment's first groups: they are the ones that come out of the previous
   // segment early (waves 0..3 merge it), and a short segment then does not wait for the late ones
   const int wslot = FLAT ? (wave + 4) & 7 : wave;
@@ -1234,7 +1234,7 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
       if (tg - base_tok > kRebase) {
         base_tok += kRebase;
         describe(t0 + (n_grp << 6));
-        t_whole = min(t1 - 64, base_tok + kRebase);
+        t_whole = base_tok + min(t1 - 64 - base_tok, kRebase);
       }
       const int tb0 = tg + tok_of_lane;  // the lane's first token
 #pragma unroll

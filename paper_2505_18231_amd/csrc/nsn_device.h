@@ -76,6 +76,8 @@ __host__ __device__ inline int tokens_div(int t, Geometry::Div v) { return (int)
 // for ahead of their use, whether they exist or not, and a cache may end 64 tokens below 2^31.
 __host__ __device__ inline uint32_t token_of_group(int t0, int n) { return (uint32_t)t0 + ((uint32_t)n << 6); }
 __host__ __device__ inline int token_up_to(uint32_t t, int last) { return (int)(t < (uint32_t)last ? t : (uint32_t)last); }
+// End of the split of `per` tokens from t0 on of a sequence of len tokens (t0 + per may be 2^31 and more)
+__host__ __device__ inline int split_end(int t0, int per, int len) { return t0 < len ? len - t0 < per ? len : t0 + per : len; }
 
 // Byte offset, inside one placement unit, of the code of (token t of the unit, sub-vector j).
 // K: token-major (a lane that owns a token reads its J bytes in one go).
