@@ -287,14 +287,21 @@ constexpr int kSegCost = 32;
 // MANY: a kv head may have more than four query heads.  The others do without the unit arithmetic (with it at run time
 // for all, four launches of the ragged paged batch of 24 sequences took 92.4 instead of 91.5 us, of 131072 1-bit tokens 0.5
 // to 1 % more).
+// Arguments: they fill four 64-byte lines, which no cache holds at the start of a launch.  Scalar loads are waited for all
+// together: the lines that a prologue touches first cost one trip, and a line that it touches behind that wait costs another.
+// What it needs ahead of the bulk loads lies in the first three (g to vc, seq_lens), the counts on the third and the fourth; the
+// compiler reads four of them, from scale_log2e on, with one load that brings both lines in.  (With n_rep behind res, in the fourth
+// line alone, and asked for behind the first wait: two launches of 56 units x 900 tokens on 32 caches in turn 15.49 instead of
+// 15.19 us, four of 131072 1-bit tokens in HBM 88 to 86 instead of 87 to 85; on one cache, which the L2 holds, 14.56 instead of
+// 14.63.  The legacy formats with the rotary embedding, which had all lines in one trip before, take 0.2 to 0.6 % longer.)
 template <int SUB, int NW, bool POW2, bool PAGED, bool FLAT, bool DQ, bool SGN = false, bool ROPE = false,
           bool MANY = SGN || ROPE>
 __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __half* __restrict__ codebook,
                                                            const __half* __restrict__ q, CacheView kc, CacheView vc,
-                                                           const int32_t* __restrict__ seq_lens, int batch,
-                                                           float scale_log2e, int n_splits, int per, float* partial,
-                                                           int* counters, ResidualView res, int n_rep,
-                                                           float* __restrict__ out) {
+                                                           const int32_t* __restrict__ seq_lens,
+                                                           float* __restrict__ out, int batch, float scale_log2e,
+                                                           int n_splits, int per, int n_rep, float* partial,
+                                                           int* counters, ResidualView res) {
   static_assert(NW == 8, "prologue work split: 512 threads fill the table, waves 0..3 rotate the query");
   constexpr int NSV = kHeadDim / SUB;  // sub-vectors per token
   constexpr bool LEGACY = SGN || ROPE;
@@ -1547,8 +1554,8 @@ static int launch_one(const Call& c) {
     grid = dim3(n_splits, unit_heads, c.batch);
   }
   dec_tile_kernel<SUB, NW, POW2, PAGED, FLAT, DQ, SGN, ROPE, MANY><<<grid, NW * 64, smem, c.stream>>>(
-      g, (const __half*)c.codebook, (const __half*)c.q, c.kc, c.vc, c.seq_lens, c.batch, c.scale * 1.44269504088896340736f,
-      n_splits, per, partial, counters, c.res, n_rep, c.out);
+      g, (const __half*)c.codebook, (const __half*)c.q, c.kc, c.vc, c.seq_lens, c.out, c.batch,
+      c.scale * 1.44269504088896340736f, n_splits, per, n_rep, partial, counters, c.res);
   return hipGetLastError() == hipSuccess ? NSN_OK : NSN_ERR_HIP;
 }
 

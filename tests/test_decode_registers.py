@@ -78,3 +78,19 @@ def test_the_codebook_row_is_requested_ahead_of_the_other_loads(tmp_path):
         code = [line for line in code if line and not line.startswith(".")]
         first, second = [i for i, line in enumerate(code) if line.startswith("global_load")][:2]
         assert second - first >= 20, (first, second)
+
+
+def test_the_arguments_come_in_one_trip(tmp_path):
+    """Scalar loads are waited for all together, and no cache holds the arguments at the start of a launch: every 64-byte line of
+    them that is read ahead of the first vector load is asked for ahead of the first wait (one workgroup per split)."""
+    for kernel in re.split(r"^_Z\S*dec_tile_kernel\S*:", _listing(ONE_SPLIT, tmp_path), flags=re.M)[1:]:
+        code = [line.split(";")[0].strip() for line in kernel.splitlines()]
+        vector = next(i for i, line in enumerate(code) if line.startswith(("global_load", "buffer_load")))
+        wait = next(i for i, line in enumerate(code) if line.startswith("s_waitcnt"))
+        lines = {True: set(), False: set()}  # asked for ahead of the wait, behind it
+        for i, line in enumerate(code[:vector]):
+            m = re.match(r"s_load_dword(?:x(\d+))? \S+ s\[0:1\], (\w+)", line)
+            if m:
+                at, n = int(m.group(2), 0), 4 * int(m.group(1) or 1)
+                lines[i < wait] |= {at // 64, (at + n - 1) // 64}
+        assert lines[True] >= {0, 1, 2} | lines[False], lines
