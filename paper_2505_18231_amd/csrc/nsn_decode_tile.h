@@ -467,9 +467,16 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
   // unit, whose instructions a wave waits for one by one (about eight cycles each; 64-bit addresses of six arrays were thirty
   // of them per group).  Offsets count from token `base_tok` of the unit and have 32 bits: every kRebase tokens the
   // descriptors move on (in the branch that masked tokens take).  With the masked tokens' selects in a branch of their own and
-  // one address for both halves of an 8-dim codeword (a group: 144 -> 103 vector instructions, 55 -> 15 scalar ones with 1-bit
-  // codes): 8 x 8192 tokens with residual, four launches 52.3 -> 50.9 us; 131072 1-bit tokens 77.4 -> 75.3; 64 x 32 heads x
-  // 32768 tokens 913 -> 870; all options of the paper 87.8 -> 83.2; paged caches, by the selects alone, 90.2 -> 87.6.
+  // one address for both halves of an 8-dim codeword a group with 1-bit codes takes 103 vector instructions instead of 144, 15
+  // scalar ones instead of 55.  Persistent: 64 x 32 heads x 32768 tokens 916 -> 869 us; legacy formats: all options of the paper
+  // 87.6 -> 77.9.  One workgroup per split, by machine: 131072 1-bit tokens, four launches 78 to 80 -> 75 to 77 on caches that
+  // stay in the last-level cache, 80 to 88 -> 77 to 86 in HBM; 8 x 8192 tokens with residual 52.0 to 53.5 -> 50.0 to 52.1, and in
+  // HBM 57.6 -> 56.4 on fast machines, 61 -> 61 to 62 on slow ones.  Its 4-bit instances go by block numbers as paged caches do:
+  // setting up two sorts of descriptors ahead of the first load costs calls of a few groups per wave more than it saves (56
+  // units x 900 4-dim tokens, two launches 15.6 against 15.45; 8-dim ones of 600 to 1300 tokens are 0.5 to 1 % above 64-bit
+  // addresses either way).
+  constexpr bool DESC = !PAGED && (FLAT || LEGACY || !DQ);
+  const uint32_t unit_block = (uint32_t)(b * g.n_kv_heads + h) * ((uint32_t)g.page_tokens >> 6);  // (!DESC, contiguous)
   // (a split beyond the cache, which leaves at once, begins at its last group)
   int base_tok = min(t0, cap_tokens - 64), base_group = 0, last_tok = 0;  // base_tok's Shift group, the last group's first token
   rsrc_t kr_codes, vr_codes, kr_norms, vr_norms;
@@ -477,7 +484,7 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
   constexpr uint32_t kMeanBytes = DQ ? kDqMeanRec : 2 * kHeadDim;
   auto describe = [&](int end_tok) {  // groups from end_tok on read as zeros, without a memory access
     base_group = shift_group(base_tok);
-    if constexpr (!PAGED) {
+    if constexpr (DESC) {
       const uint32_t n = (uint32_t)min(end_tok - base_tok, 2 * kRebase);
       const int64_t tok = (int64_t)(b * g.n_kv_heads + h) * g.page_tokens + base_tok;
       kr_codes = make_rsrc(kc.codes + tok * J, n * J), vr_codes = make_rsrc(vc.codes + tok * J, n * J);
@@ -492,63 +499,95 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
     vp_means = reinterpret_cast<const unsigned char*>(vc.means) + mean_at;
   };
   // n: the group, counted from token t0.  One that does not exist (`real` false: the wave's list of groups has ended) is
-  // loaded all the same: contiguous caches read zeros beyond the descriptors' ends, paged ones the first bytes of every array
+  // loaded all the same: descriptors read zeros beyond their ends, the other form reads the first bytes of every array
   // (one cache line per instruction); nothing of it is used and any bytes are valid table indices.  With loads that are only
   // issued under a condition, the number of loads behind a given one depends on the path, the compiler's wait counts take the
   // smallest, and every wait for a group's bytes becomes a wait for all loads in flight, the groups requested ahead included.
+  // Side information ahead of the codes: where the loop's first group meets its Shift vectors' and norms' first use, the wait is the
+  // one that holds for every way there, also for one behind a group whose loads were the last ones (the compiler cannot know
+  // that it is never taken), and counts only the loads that follow within a group.  Behind the codes, they made a wave with
+  // one group wait for all of the second one's loads.  4-bit side information, eight loads of the fourteen: 56 units x 256
+  // tokens, two launches 11.95 -> 11.45 us (4-dim), x 900 tokens 16.0 -> 15.5; all options of the paper, 8 x 8192 tokens, four
+  // launches 69.6 -> 67.9.  Codes first: 8-dim fp16 calls on pages (1 % less) and the persistent fp16 instance on contiguous
+  // caches (64 x 32 heads x 32768 tokens 869 instead of 876).  8-dim tiled instances are left to the scheduler within the order,
+  // which gives them 0.5 %.
   auto load_group = [&](int n, bool real, Regs& G) {
+    constexpr bool kCodesFirst = !LEGACY && !DQ && (PAGED ? SUB == 8 : FLAT), kOrdered = SUB == 4 || LEGACY;
     const uint32_t tg = token_of_group(t0, n);
-    constexpr int VSTEP = LEGACY ? J : 1;  // 16-byte pieces; legacy: the lane's second value row is sixteen rows on
-    auto set_codes = [&](int w4, u4v kv4, u4v vv4) {
-      G.kc[4 * w4] = kv4.x, G.kc[4 * w4 + 1] = kv4.y, G.kc[4 * w4 + 2] = kv4.z, G.kc[4 * w4 + 3] = kv4.w;
-      G.vc[4 * w4] = vv4.x, G.vc[4 * w4 + 1] = vv4.y, G.vc[4 * w4 + 2] = vv4.z, G.vc[4 * w4 + 3] = vv4.w;
-    };
-    if constexpr (!PAGED) {
-      uint32_t rel = tg - (uint32_t)base_tok;
-      asm("" : "+s"(rel));  // (or every offset gets a subtraction of its own)
-      const uint32_t ko = lane_code_off + rel * J, vo = lane_v_off + rel * J;
-#pragma unroll
-      for (int w4 = 0; w4 < CW / 4; ++w4) set_codes(w4, load128(kr_codes, ko + 16 * w4), load128(vr_codes, vo + 16 * w4 * VSTEP));
-      if constexpr (DQ) {  // one norm record per 64-token block
-        const uint32_t rec = (rel >> 6) * kDqNormRec, tok0 = norm_off >> 2;  // (the lane's first token: a multiple of 4)
-        const u2v ka = load64(kr_norms, rec + 2 * tok0), va = load64(vr_norms, rec + 2 * tok0);
-        const uint32_t at_codes = rec + kDqNormCodes + (tok0 >> 1), at_par = rec + kDqNormPar;
-        G.nk = make_uint4(ka.x, ka.y, load16(kr_norms, at_codes), load32(kr_norms, at_par));
-        G.nv = make_uint4(va.x, va.y, load16(vr_norms, at_codes), load32(vr_norms, at_par));
+    auto load_means = [&]() {
+      const uint32_t mrec = (uint32_t)(shift_group(token_up_to(tg, last_tok)) - base_group) * kMeanBytes;
+      if constexpr (DQ) {
+        const uint32_t at_par = mrec + kDqMeanPar + 4 * ((uint32_t)lane >> 4);
+        if constexpr (!ROPE) G.ok = kp_means[mrec + lane], G.okp = *reinterpret_cast<const uint32_t*>(kp_means + at_par);
+        G.ov = vp_means[mrec + lane], G.ovp = *reinterpret_cast<const uint32_t*>(vp_means + at_par);
       } else {
-        const u4v nk = load128(kr_norms, norm_off + rel * 4), nv = load128(vr_norms, norm_off + rel * 4);
-        G.nk = make_uint4(nk.x, nk.y, nk.z, nk.w), G.nv = make_uint4(nv.x, nv.y, nv.z, nv.w);
+        if constexpr (!ROPE) G.ok = *reinterpret_cast<const uint32_t*>(kp_means + (mrec + lane_x4));  // (ROPE: rope_load)
+        G.ov = *reinterpret_cast<const uint32_t*>(vp_means + (mrec + lane_x4));
       }
-    } else {
-      uint32_t kblock, vblock;  // wave-uniform
-      group_blocks(tg, real, kblock, vblock);
-      const uint32_t lco = real ? lane_code_off : 0u, lvo = real ? lane_v_off : 0u, noff = real ? norm_off : 0u;
+    };
+    uint32_t rel = 0u, kblock = 0u, vblock = 0u;  // DESC: the group's distance from base_tok; its 64-token blocks
+    if constexpr (DESC) {
+      rel = tg - (uint32_t)base_tok;
+      asm("" : "+s"(rel));  // (or every offset gets a subtraction of its own)
+    }
+    auto load_norms = [&]() {
+      if constexpr (DESC) {
+        if constexpr (DQ) {  // one norm record per 64-token block
+          const uint32_t rec = (rel >> 6) * kDqNormRec, tok0 = norm_off >> 2;  // (the lane's first token: a multiple of 4)
+          const u2v ka = load64(kr_norms, rec + 2 * tok0), va = load64(vr_norms, rec + 2 * tok0);
+          const uint32_t at_codes = rec + kDqNormCodes + (tok0 >> 1), at_par = rec + kDqNormPar;
+          G.nk = make_uint4(ka.x, ka.y, load16(kr_norms, at_codes), load32(kr_norms, at_par));
+          G.nv = make_uint4(va.x, va.y, load16(vr_norms, at_codes), load32(vr_norms, at_par));
+        } else {
+          const u4v nk = load128(kr_norms, norm_off + rel * 4), nv = load128(vr_norms, norm_off + rel * 4);
+          G.nk = make_uint4(nk.x, nk.y, nk.z, nk.w), G.nv = make_uint4(nv.x, nv.y, nv.z, nv.w);
+        }
+      } else {
+        constexpr int kBlockNorms = DQ ? kDqNormRec : 256;
+        const uint32_t noff = real ? norm_off : 0u;
+        const unsigned char* kn = reinterpret_cast<const unsigned char*>(kc.norms) + (uint64_t)kblock * kBlockNorms;
+        const unsigned char* vn = reinterpret_cast<const unsigned char*>(vc.norms) + (uint64_t)vblock * kBlockNorms;
+        if constexpr (DQ) {
+          const uint32_t tok0 = noff >> 2;
+          const uint2 ka = *reinterpret_cast<const uint2*>(kn + 2 * tok0), va = *reinterpret_cast<const uint2*>(vn + 2 * tok0);
+          G.nk = make_uint4(ka.x, ka.y, *reinterpret_cast<const uint16_t*>(kn + (kDqNormCodes + (tok0 >> 1))),
+                            *reinterpret_cast<const uint32_t*>(kn + kDqNormPar));
+          G.nv = make_uint4(va.x, va.y, *reinterpret_cast<const uint16_t*>(vn + (kDqNormCodes + (tok0 >> 1))),
+                            *reinterpret_cast<const uint32_t*>(vn + kDqNormPar));
+        } else {
+          G.nk = *reinterpret_cast<const uint4*>(kn + noff), G.nv = *reinterpret_cast<const uint4*>(vn + noff);
+        }
+      }
+    };
+    auto load_codes = [&]() {
+      constexpr int VSTEP = LEGACY ? J : 1;  // 16-byte pieces; legacy: the lane's second value row is sixteen rows on
+      const uint32_t lco = DESC ? lane_code_off + rel * J : real ? lane_code_off : 0u;
+      const uint32_t lvo = DESC ? lane_v_off + rel * J : real ? lane_v_off : 0u;
       const unsigned char *kp = kc.codes + (uint64_t)kblock * (64 * J), *vp = vc.codes + (uint64_t)vblock * (64 * J);
 #pragma unroll
-      for (int w4 = 0; w4 < CW / 4; ++w4)
-        set_codes(w4, *reinterpret_cast<const u4v*>(kp + (lco + 16 * w4)), *reinterpret_cast<const u4v*>(vp + (lvo + 16 * w4 * VSTEP)));
-      constexpr int kBlockNorms = DQ ? kDqNormRec : 256;
-      const unsigned char* kn = reinterpret_cast<const unsigned char*>(kc.norms) + (uint64_t)kblock * kBlockNorms;
-      const unsigned char* vn = reinterpret_cast<const unsigned char*>(vc.norms) + (uint64_t)vblock * kBlockNorms;
-      if constexpr (DQ) {
-        const uint32_t tok0 = noff >> 2;
-        const uint2 ka = *reinterpret_cast<const uint2*>(kn + 2 * tok0), va = *reinterpret_cast<const uint2*>(vn + 2 * tok0);
-        G.nk = make_uint4(ka.x, ka.y, *reinterpret_cast<const uint16_t*>(kn + (kDqNormCodes + (tok0 >> 1))),
-                          *reinterpret_cast<const uint32_t*>(kn + kDqNormPar));
-        G.nv = make_uint4(va.x, va.y, *reinterpret_cast<const uint16_t*>(vn + (kDqNormCodes + (tok0 >> 1))),
-                          *reinterpret_cast<const uint32_t*>(vn + kDqNormPar));
-      } else {
-        G.nk = *reinterpret_cast<const uint4*>(kn + noff), G.nv = *reinterpret_cast<const uint4*>(vn + noff);
+      for (int w4 = 0; w4 < CW / 4; ++w4) {
+        u4v kv4, vv4;
+        if constexpr (DESC)
+          kv4 = load128(kr_codes, lco + 16 * w4), vv4 = load128(vr_codes, lvo + 16 * w4 * VSTEP);
+        else
+          kv4 = *reinterpret_cast<const u4v*>(kp + (lco + 16 * w4)), vv4 = *reinterpret_cast<const u4v*>(vp + (lvo + 16 * w4 * VSTEP));
+        G.kc[4 * w4] = kv4.x, G.kc[4 * w4 + 1] = kv4.y, G.kc[4 * w4 + 2] = kv4.z, G.kc[4 * w4 + 3] = kv4.w;
+        G.vc[4 * w4] = vv4.x, G.vc[4 * w4 + 1] = vv4.y, G.vc[4 * w4 + 2] = vv4.z, G.vc[4 * w4 + 3] = vv4.w;
       }
-    }
-    const uint32_t mrec = (uint32_t)(shift_group(token_up_to(tg, last_tok)) - base_group) * kMeanBytes;
-    if constexpr (DQ) {
-      const uint32_t at_par = mrec + kDqMeanPar + 4 * ((uint32_t)lane >> 4);
-      if constexpr (!ROPE) G.ok = kp_means[mrec + lane], G.okp = *reinterpret_cast<const uint32_t*>(kp_means + at_par);
-      G.ov = vp_means[mrec + lane], G.ovp = *reinterpret_cast<const uint32_t*>(vp_means + at_par);
+    };
+    if constexpr (kCodesFirst) {
+      if constexpr (PAGED) group_blocks(tg, real, kblock, vblock);
+      load_codes(), load_norms(), load_means();
     } else {
-      if constexpr (!ROPE) G.ok = *reinterpret_cast<const uint32_t*>(kp_means + (mrec + lane_x4));  // (ROPE: rope_load)
-      G.ov = *reinterpret_cast<const uint32_t*>(vp_means + (mrec + lane_x4));
+      load_means();
+      if constexpr (kOrdered) __builtin_amdgcn_sched_barrier(0);
+      if constexpr (PAGED)
+        group_blocks(tg, real, kblock, vblock);
+      else if constexpr (!DESC)
+        kblock = vblock = real ? unit_block + (tg >> 6) : 0u;
+      load_norms();
+      if constexpr (kOrdered) __builtin_amdgcn_sched_barrier(0);
+      load_codes();
     }
   };
   // legacy layout: a group's code bytes from the order they were loaded in to the order the gathers use
@@ -667,7 +706,7 @@ __global__ __launch_bounds__(NW * 64) void dec_tile_kernel(Geometry g, const __h
     // the cache when the split lies beyond it: then it is never processed)
     if constexpr (!PAGED) {
       describe(cap_tokens);
-      load_group(wave, true, S0);  // (wslot == wave here)
+      load_group(wave, DESC || token_of_group(t0, wave) < (uint32_t)cap_tokens, S0);  // (wslot == wave here)
     }
     len = seq_lens[b];
     // Splits that lie wholly beyond this sequence's end have nothing to do and leave at once (a ragged batch
