@@ -969,6 +969,14 @@ int encode_layout(const nsn_shape& s, int batch, int max_new, bool pass1) {
   return bulk < fminf(small, eight) ? 16 : eight < small ? 8 : s.sub_dim;
 }
 
+// Tokens per workgroup: one step per wave where that is what fills the chip, several where the workgroup's set-up (tables, operands:
+// about a sixth of a step) is worth sharing; a 64-token block is the most that pass 1 holds.
+int encode_wg_tokens(const nsn_shape& s, int batch, int max_new, bool pass1, int layout) {
+  if (layout != 16) return layout > s.sub_dim ? 16 : s.sub_dim == 8 ? 16 : 8;
+  const int64_t tokens = (int64_t)max_new * s.n_kv_heads * 2 * batch;
+  return tokens < 32768 ? 32 : tokens >= 524288 && !pass1 ? 128 : 64;
+}
+
 // Three workgroups to a compute unit, of the 256, or two.  Three share their vector ALUs better, but their workgroups run without
 // the tile requested ahead and unpack the Shift vector in every step, so each takes longer: worth it where the chip goes through
 // fewer rounds, and always beyond four workgroups to a compute unit.  Two / three, us, batch 8 x 8 kv heads, formats 4-dim |
@@ -981,7 +989,18 @@ int encode_layout(const nsn_shape& s, int batch, int max_new, bool pass1) {
 //   1280             52.2 / 51.4 | 44.5 / 43.2 | 58.5 / 56.3 | 50.7 / 45.7
 //   2048             75.9 / 73.4 | 63.6 / 60.7 | 87.6 / 80.0 | 76.9 / 69.0
 //   4096             143.6 / 136.5 | 119.7 / 112.1 | 156.8 / 144.2 | 138.8 / 127.9
-bool three_to_a_unit(int64_t workgroups) { return workgroups > 1024 || (workgroups > 512 && workgroups <= 768); }
+// Those are sequences of one length.  Of a batch the host knows only the places, and workgroups without tokens leave holes: three
+// that have some then lie on one compute unit and none on the next, where two to a unit leave the rest waiting for whichever is
+// free.  16 sequences of 0.4 to 1 times 1088 tokens, one kv head, 544 places: 27.5 / 34.2, 24.0 / 28.6, 29.3 / 35.5, 21.1 / 28.4;
+// 1280 to 1664 places with one long sequence among eight 0.75 to 0.87 times as fast.  Over 708 calls of 2 to 64 sequences, lengths from
+// 0.03, 0.4 or 0.8 times the longest up, no one beyond 1900 places was slower with three (geometric mean 1.07 times as fast), and
+// from 2048 on none of 480 more in which one sequence or half of them are long and the others a tenth of that.
+int encode_per_unit(const nsn_shape& s, int batch, int max_new, int layout, int wg_tokens) {
+  if (layout != 16) return 2;
+  const int64_t places = (int64_t)s.n_kv_heads * 2 * batch * ((max_new + wg_tokens - 1) / wg_tokens);
+  const bool three = batch > 1 ? places >= 2048 : places > 1024 || (places > 512 && places <= 768);
+  return three ? 3 : 2;
+}
 
 int encode_launch(const nsn_shape& s, const void* codebook, const void* k_in, const void* v_in, int max_new,
                   const int32_t* seq_start, const int32_t* n_new, int batch, int freeze_means,
@@ -1029,20 +1048,12 @@ int encode_launch(const nsn_shape& s, const void* codebook, const void* k_in, co
     return hipGetLastError() == hipSuccess ? NSN_OK : NSN_ERR_HIP;
   }
   const bool pass1 = own_means || g.dq;
-  const int layout = encode_layout(s, batch, max_new, pass1), small_tokens = s.sub_dim == 8 ? 16 : 8;
+  const int layout = encode_layout(s, batch, max_new, pass1), wg_tokens = encode_wg_tokens(s, batch, max_new, pass1, layout);
   const bool bulk = layout == 16, eight = layout > s.sub_dim && !bulk;
-  EncArgs a = {g, (const __half*)codebook, (const __half*)k_in, (const __half*)v_in, max_new, s.max_len, seq_start, n_new,
-               kv, vv, 64, own_means};
-  // tokens per workgroup: one step per wave where that is what fills the chip, several where the workgroup's set-up
-  // (tables, operands: about a sixth of a step) is worth sharing; a 64-token block is the most that pass 1 holds
-  if (!bulk)
-    a.wg_tokens = eight ? 16 : small_tokens;
-  else if (tokens < 32768)
-    a.wg_tokens = 32;
-  else if (tokens >= 524288 && !own_means && !g.dq)
-    a.wg_tokens = 128;
-  const dim3 grid((max_new + a.wg_tokens - 1) / a.wg_tokens, s.n_kv_heads * 2, batch);
-  const bool three = bulk && three_to_a_unit((int64_t)grid.x * grid.y * grid.z);
+  const bool three = encode_per_unit(s, batch, max_new, layout, wg_tokens) == 3;
+  const EncArgs a = {g, (const __half*)codebook, (const __half*)k_in, (const __half*)v_in, max_new, s.max_len, seq_start, n_new,
+                     kv, vv, wg_tokens, own_means};
+  const dim3 grid((max_new + wg_tokens - 1) / wg_tokens, s.n_kv_heads * 2, batch);
   auto launch = [&](auto kernel) { kernel<<<grid, 256, 0, stream>>>(a); };
   auto pick = [&](auto sub, auto sign, auto rope) {
     constexpr int kSub = decltype(sub)::value;

@@ -58,6 +58,8 @@ int selected_variant(int op);  // NSN_VARIANT_* of NSN_OP_ENCODE / NSN_OP_DECODE
 size_t encode_workspace_bytes(const nsn_shape& s, int batch, int64_t max_new);
 // pass1: groups of 64 tokens whose means the call forms, or 4-bit side information
 int encode_layout(const nsn_shape& s, int batch, int max_new, bool pass1);
+int encode_wg_tokens(const nsn_shape& s, int batch, int max_new, bool pass1, int layout);
+int encode_per_unit(const nsn_shape& s, int batch, int max_new, int layout, int wg_tokens);  // workgroups on a compute unit: 2 or 3
 int encode_launch(const nsn_shape& s, const void* codebook, const void* k_in, const void* v_in, int max_new,
                   const int32_t* seq_start, const int32_t* n_new, int batch, int freeze_means,
                   const nsn_cache& kc, const nsn_cache& vc, void* workspace, hipStream_t stream);

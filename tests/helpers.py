@@ -155,6 +155,17 @@ def encode_layout(api, shape, batch: int, max_new: int, freeze_means: bool = Fal
     return rule(C.byref(shape), batch, max_new, shape.side_bits == 4 or (shape.group_size == 64 and not freeze_means))
 
 
+def encode_launch_form(api, shape, batch: int, max_new: int, freeze_means: bool = False):
+    """(layout, tokens per workgroup, workgroups per compute unit) that an encode call resolves to (the library's own rules)."""
+    layout = encode_layout(api, shape, batch, max_new, freeze_means)
+    lib, pass1 = api.lib(), shape.side_bits == 4 or (shape.group_size == 64 and not freeze_means)
+    tokens, units = lib["_ZN3nsn16encode_wg_tokensERK9nsn_shapeiibi"], lib["_ZN3nsn15encode_per_unitERK9nsn_shapeiiii"]
+    tokens.restype, tokens.argtypes = C.c_int, [C.c_void_p, C.c_int, C.c_int, C.c_bool, C.c_int]
+    units.restype, units.argtypes = C.c_int, [C.c_void_p] + [C.c_int] * 4
+    wg_tokens = tokens(C.byref(shape), batch, max_new, pass1, layout)
+    return layout, wg_tokens, units(C.byref(shape), batch, max_new, layout, wg_tokens)
+
+
 def whole(lens) -> int:
     """The longest length in whole pages and groups of 64, 128, 192 and 256 tokens."""
     return max(768, (max(lens) + 767) // 768 * 768)

@@ -50,3 +50,28 @@ def test_eight_channels_lie_between_them():
     for fmt in FORMATS[2:]:  # (an instance of the plain 4-dim formats)
         for batch in range(1, 200):
             assert _layout(fmt, batch, 8, 64) in (fmt[0], 16)
+
+
+def _form(fmt, batch, kv_heads, max_new):
+    sub, sign, rope, side_bits, group = fmt
+    shape = api.make_shape(sub, kv_heads, kv_heads, 1 << 17, group, 0, sign_format=sign, side_bits=side_bits)
+    shape.rope_table = 4096 if rope else None
+    return helpers.encode_launch_form(api, shape, batch, max_new)
+
+
+@pytest.mark.parametrize("fmt", FORMATS)
+def test_ragged_batches_take_three_workgroups_to_a_unit_only_where_they_are_many(fmt):
+    """A batch's places need not hold tokens: with few of them, three workgroups with tokens would share one compute unit while others
+    have none.  One sequence fills its places: there the rounds of the chip decide."""
+    for batch, kv_heads, max_new in ((16, 1, 1088), (8, 4, 640), (8, 4, 1664), (31, 1, 1056), (2, 8, 4032)):
+        layout, tokens, units = _form(fmt, batch, kv_heads, max_new)
+        assert 512 < 2 * kv_heads * batch * -(-max_new // tokens) < 2048
+        assert layout == 16 and units == 2, (batch, kv_heads, max_new, layout, units)
+    for batch, kv_heads, max_new in ((2, 8, 4096), (16, 2, 2048), (32, 1, 2048), (8, 8, 8192)):
+        layout, tokens, units = _form(fmt, batch, kv_heads, max_new)
+        assert layout == 16 and units == 3, (batch, kv_heads, max_new, layout, units)
+    for places, want in ((512, 2), (513, 3), (768, 3), (769, 2), (1024, 2), (1025, 3), (4000, 3)):
+        # (one kv head: an even number of places, in 64-token workgroups below half a million token places)
+        max_new = 64 * ((places + 1) // 2 if want == 3 or places > 768 else places // 2)
+        layout, tokens, units = _form(fmt, 1, 1, max_new)
+        assert (layout, tokens, units) == (16, 64, want), (places, layout, tokens, units)

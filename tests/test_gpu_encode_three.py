@@ -1,6 +1,6 @@
 """The encoder's instances for three workgroups to a compute unit store the same bytes as those for two: a ragged batch of nine
-sequences (720 workgroups of 64 tokens) against three calls of three sequences each (480 workgroups of 32 tokens).  Both take the
-sixteen-channel layout; lengths sit at the edges of its 8-token steps and of the workgroups."""
+sequences (2160 workgroups of 64 tokens) against three calls of three sequences each (720).  Both take the sixteen-channel layout;
+lengths sit at the edges of its 8-token steps and of the workgroups."""
 import numpy as np
 import pytest
 
@@ -21,7 +21,7 @@ def test_large_call_equals_its_parts(gpu_api, codebooks, sub, sign, rope, G, sid
     import torch
     api = gpu_api
     print(f"case sub={sub} sign={sign} rope={rope} G={G} side_bits={side_bits} page={page} start={start}", flush=True)
-    B, H, max_len = len(LENS), 8, 1024
+    B, H, max_len = len(LENS), 24, 1024
     g = torch.Generator(device="cuda").manual_seed(21)
     cb = torch.from_numpy(codebooks[sub].astype(np.float16)).cuda()
     if sign:
@@ -34,7 +34,7 @@ def test_large_call_equals_its_parts(gpu_api, codebooks, sub, sign, rope, G, sid
     n = torch.tensor(LENS, dtype=torch.int32, device="cuda")
     pos = torch.full((B,), start, dtype=torch.int32, device="cuda")
     freeze = start > 0
-    assert [helpers.encode_layout(api, shape, n_seq, CAP, freeze) for n_seq in (B, 3)] == [16, 16]
+    assert [helpers.encode_launch_form(api, shape, n_seq, CAP, freeze) for n_seq in (B, 3)] == [(16, 64, 3), (16, 64, 2)]
 
     def fresh():
         caches = api.alloc_cache(shape, B, block_table=bt), api.alloc_cache(shape, B, block_table=bt)
