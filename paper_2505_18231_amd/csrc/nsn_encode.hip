@@ -412,6 +412,8 @@ __global__ __launch_bounds__(256, WAVES) void enc_kernel(EncArgs A) {
   asm volatile("" ::"s"(A.codebook), "s"(A.k_in), "s"(A.v_in), "s"(A.max_new), "s"(A.max_len), "s"(A.seq_start), "s"(A.n_new),
                "s"(A.kc.codes), "s"(A.vc.codes), "s"(A.kc.means), "s"(A.vc.means), "s"(A.kc.norms), "s"(A.vc.norms),
                "s"(A.wg_tokens), "s"(g.dq), "s"(g.n_kv_heads), "s"(g.n_groups_max), "s"(g.group_size));
+  // (asked for in the step that turns the token, it was waited for there: one token x 1024 sequences x 8 kv heads, 4-dim 92.1 -> 88.3 us)
+  if constexpr (ROPE) asm volatile("" ::"s"(g.rope));
   const CacheView cv = {tensor ? A.vc.codes : A.kc.codes, tensor ? A.vc.norms : A.kc.norms, tensor ? A.vc.means : A.kc.means,
                         tensor ? A.vc.block_table : A.kc.block_table};
   const __half* in = (tensor ? A.v_in : A.k_in) + (int64_t)(b * g.n_kv_heads + h) * A.max_new * kHeadDim;
