@@ -11,7 +11,7 @@ from tests import helpers
 
 pytestmark = pytest.mark.gpu
 
-# copies (of row, at rows): two in one group of eight (rows 0..3 and 8..11 of a tile half), in neighbouring groups, in other tiles
+# copies (of row, at rows): two in one group of eight (codewords lie in order), in neighbouring groups, in other tiles
 PAIRS = [(0, [1]), (2, [11]), (4, [17]), (5, [21]), (33, [250]), (64, [70]), (255, [100]), (130, [131])]
 MANY = [(0, [1, 2]), (8, [40, 200]), (77, [78, 79]), (99, [100])]
 # 32 and 33 equal rows: the most that the lists settle, and one more
