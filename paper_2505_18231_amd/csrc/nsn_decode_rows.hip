@@ -1,7 +1,7 @@
 // Kernel instances of the legacy code layout: the sign + index format, and every format with keys normalised before the rotary
 // embedding.  (Group and page indices by reciprocals for all sizes, powers of two among them: half as many instances.)
-// All but six rotary instances fit in 256 registers; those spill 1 to 9 of them (persistent, sign codes and 4-bit side information
-// most).
+// All but six rotary instances, all of them paged, fit in 256 registers; those spill 2 to 9 of them (persistent, sign codes and
+// 4-bit side information most).
 #include "nsn_decode_tile.h"
 
 namespace nsn {

@@ -32,14 +32,22 @@ def test_sign_codes_with_4bit_side_information_spill_no_vector_registers(tmp_pat
     assert spilled == [0] * len(SIGN_4BIT), spilled
 
 
+def test_rotary_instances_spill_what_their_comment_says(tmp_path):
+    """(The other 26 instances of the legacy layout spill none: too many to build here.)"""
+    paged = ["8,8,false,true,true,true,true,true", "4,8,false,true,true,true,false,true", "8,8,false,true,true,false,true,true"]
+    text = _listing(paged + ["8,8,false,false,true,true,true,true", "8,8,false,false,false,true,true,true"], tmp_path)
+    spilled = [int(n) for n in re.findall(r"\.vgpr_spill_count:\s+(\d+)", text)]
+    assert len(spilled) == 5 and sorted(spilled)[:2] == [0, 0] and max(spilled) <= 9, spilled
+
+
 def _loop_loads(kernel):
-    """4-byte load targets of the main loop (Shift vectors, read only where the Shift group changes) with the number of vector
-    and LDS instructions of the loop that write the same register."""
+    """Targets of the main loop's loads of four bytes and less (Shift vectors, read only where the Shift group changes, and 4-bit
+    side information) with the number of vector and LDS instructions of the loop that write the same register."""
     code = [line.split(";")[0].strip() for line in kernel]
     code = [line for line in code if line]
     first = next(i for i, line in enumerate(code) if line.startswith("v_mfma_f32_16x16x32"))
     last = max(i for i, line in enumerate(code) if line.startswith("v_mfma_f32_4x4x4"))
-    targets = {line.split()[1].rstrip(",") for line in code[first:last] if line.startswith("global_load_dword ")}
+    targets = {line.split()[1].rstrip(",") for line in code[first:last] if re.match(r"(global|buffer)_load_(dword|ushort|ubyte) ", line)}
     writes = dict.fromkeys(targets, 0)
     for line in code[first:last]:
         if line.startswith(("v_", "ds_read")):
@@ -76,7 +84,7 @@ def test_the_codebook_row_is_requested_ahead_of_the_other_loads(tmp_path):
     for kernel in re.split(r"^_Z\S*dec_tile_kernel\S*:", _listing(ONE_SPLIT[:2], tmp_path), flags=re.M)[1:]:
         code = [line.split(";")[0].strip() for line in kernel.splitlines()]
         code = [line for line in code if line and not line.startswith(".")]
-        first, second = [i for i, line in enumerate(code) if line.startswith("global_load")][:2]
+        first, second = [i for i, line in enumerate(code) if line.startswith(("global_load", "buffer_load"))][:2]
         assert second - first >= 20, (first, second)
 
 
