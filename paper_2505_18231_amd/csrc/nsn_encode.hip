@@ -384,9 +384,9 @@ __device__ __forceinline__ void rotate_token(double (&v)[CPL], int lane) {
 
 // WAVES: workgroups on a compute unit, i.e. waves per SIMD.  Three (CPL = 16) leave 168 registers and 53 KB of LDS to each: the
 // search has its LEAN form, the Shift vector is unpacked in every step instead of held in 32 registers, and the sums of pass 1 lie
-// where the tokens come later.  8-dim instances spill 8 to 20 registers, none in the loop over the search's tiles.  8 x 8192
-// tokens, 8 kv heads, 4-dim: 542 -> 518 us; 4 ragged sequences of up to 4096 tokens, 8-dim signs with the rotary embedding:
-// 104.5 -> 92.6 us.
+// where the tokens come later.  8-dim instances spill 8 to 20 registers, none in the loop over the search's tiles.  Calls back
+// to back, 8 x 8192 tokens, 8 kv heads, 4-dim: 543 -> 517 us; 4 ragged sequences of up to 4096 tokens, 8-dim signs with the
+// rotary embedding: 105 -> 93 us.
 template <int SUB, int CPL, bool SIGN, bool ROPE, bool PASS1, int WAVES = 2>
 __global__ __launch_bounds__(256, WAVES) void enc_kernel(EncArgs A) {
   static_assert(CPL == 16 || CPL == 8 || CPL == SUB, "lane layouts");

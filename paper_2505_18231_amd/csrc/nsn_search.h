@@ -385,7 +385,9 @@ __device__ __forceinline__ int search_nearest(const SearchTables<SUB, EXACT16, L
   // Error bound of either form of a distance, relative to M >= (|c| + |y|)^2, in units of 2^-24: the fp16 splits of
   // y and c leave 4 each (two roundings of 2^-11), the dropped low x low product 4, low parts below the normal fp16
   // range 2 (M >= 16), fp32 rounding of the inputs and of the threshold 3, the sum of at most 32 terms 24 (matrix cores)
-  // or SUB + 3 (fp32).  Anything that can be nearest lies within twice the bound of the computed minimum.
+  // or SUB + 3 (fp32).  (fp16 rows of step 3 are exact but for elements below the fp16 subnormal unit once scaled: at most
+  // 2^-25 |y|_1, less than one unit of the bound.)  Anything that can be nearest lies within twice the bound of the computed
+  // minimum.
   const float reach = R.cm + 1.0001f * __builtin_amdgcn_sqrtf(yn);
   // (beyond the fp16 range - ||y||^2 above 58000 -, a codebook that is not finite, or not a number: nothing is listed)
   const bool in_range = reach < 245.f;
